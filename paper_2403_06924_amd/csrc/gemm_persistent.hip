@@ -1,10 +1,15 @@
-// Persistent variant of the INT8 GEMM for full, aligned problems (M, N multiples of 256, K a
-// multiple of 128, 16-byte aligned operands): the shape of every large workload.
+// Persistent variant of the INT8 GEMM for large problems with K-contiguous, 16-byte aligned
+// operands: the products of every large workload.
 //
-// Same output tile as gemm_i8_kernel (256 x 256 per 4-wave workgroup, 128 x 128 per wave,
-// v_mfma_i32_32x32x32_i8) with three differences made for gfx950:
+// One 256 x 256 output tile per 4-wave workgroup at a time (128 x 128 per wave), one workgroup per
+// compute unit:
 //
-//  * operand tiles go from global memory straight into LDS (global_load_lds_dwordx4): no
+//  * v_mfma_i32_16x16x64_i8, not 32x32x32: at the same rate per clock it moves 8 KiB instead of
+//    10 KiB through the registers per 65536 operations (the accumulators of a 32 x 32 block are
+//    read and written twice as often per operation as its operands are saved), and the launch runs
+//    at the chip's power limit.  A register-resident loop on random operand bytes: 4.27 POP/s at
+//    2.07 GHz against 3.54 POP/s at 1.72 GHz.
+//  * operand tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds): no
 //    staging registers and no ds_write instructions.  The hardware writes the 64 lanes of one
 //    load to 1 KiB of consecutive LDS bytes, so the tile rows are unpadded (128 B) and bank
 //    conflicts of the 16-byte fragment reads are avoided by an XOR swizzle instead: the 16-byte
@@ -13,17 +18,30 @@
 //  * a workgroup walks over several output tiles and the stream of staged K-tiles never drains
 //    between them: while one tile's epilogue runs, the first K-tiles of the next are already
 //    landing in LDS (they need no registers), and the epilogue's stores retire while the next
-//    tile is multiplied.  A one-tile-per-workgroup launch pays launch, prologue latency and
-//    drain once per tile - four times per CU at 8192^3, since only one workgroup fits a CU;
+//    tile is multiplied;
 //  * LDS holds three buffers for the tiles of A and two for the tiles of B (5 x 32 KiB, all of a
-//    CU's LDS).  The sixteen loads that a wave issues per K-tile are spread evenly over its four
-//    steps: the CU's vector-memory path takes a 1 KiB load about every 20 clocks, and a wave
-//    whose load cannot be accepted yet also holds back the MFMAs behind it (with all sixteen in
-//    the one step that follows the hand-over of a buffer, that step took 2.3 times as long as
-//    the others).  The third A buffer is what makes room for that: the A tile of K-tile g+2 is
-//    fetched during the middle steps of K-tile g, one K-tile earlier than a two-buffer scheme
-//    could, so those loads also have twice as long to land, which matters when the operands
-//    come from HBM rather than from the caches.
+//    CU's LDS).  The fragments of a step are read a whole step (64 MFMAs) ahead, so both buffers
+//    of a K-tile are free at its one barrier, half-way through it; the sixteen loads a wave issues
+//    per K-tile go out one after every eighth MFMA: in the first half of K-tile g the A tile of
+//    K-tile g+2 (into the buffer that K-tile g-1 left), in the second half its B tile.  (The CU's
+//    vector-memory path takes a 1 KiB load about every 20 clocks, and a wave whose load cannot be
+//    accepted yet also holds back the MFMAs behind it.)
+//  * the first operand of an MFMA is the B fragment, so that a lane ends up with four consecutive
+//    columns of one row of C, in 16-row x 16-column blocks; two neighbouring blocks are exchanged
+//    between the half rows of 8 lanes (one DPP move per element), so that every access to C is
+//    16 bytes per lane and whole 128-byte lines per row.  (All compute units store at once: with
+//    64-byte pieces a round of 64 MiB leaves at 3.0 TB/s, with whole lines at 5.9 TB/s.)
+//
+// What bounds it: on operands that toggle, the power limit (the K loop runs at 1.6-1.8 GHz on random
+// bytes); on zeros about 2300 clocks per K-tile against 2048 of matrix-core time, and 12-15 us per
+// round of tiles for the epilogue, most of it the 64 MiB of C that all compute units write at once
+// (starting them staggered was tried: it costs the tiles of an XCD their common panels in L2).
+// 8192^3, first product / both corrections in one launch, us: random codes 466 / 1018 before (32x32x32,
+// 64 dwords per row block), 425 / 930 now; 95 % zeros in one operand 877 -> 804.
+//
+// M and N need not be multiples of the tile: rows past the end are cut off by the range check of the
+// buffer descriptor (whatever lands in LDS for them feeds elements that are never stored), and the
+// epilogue of a tile on the edge checks every access.
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -36,21 +54,46 @@ namespace srq {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+// four consecutive floats at any 4-byte aligned address (rows of C may start anywhere)
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef v4f v4fu __attribute__((aligned(4)));
 
-constexpr int BM = 256, BN = 256, BK = 128, KS = BK / 32;
+constexpr int BM = 256, BN = 256, BK = 128;
 constexpr int kOperand = BM * BK;                   // 32 KiB per operand tile
-constexpr int TM = 4, TN = 4;                       // 32x32 MFMA tiles per wave
+constexpr int TM = 8, TN = 8;                       // 16 x 16 MFMA tiles per wave
 constexpr int kABufs = 3, kBBufs = 2;               // LDS buffers of the A tiles and of the B tiles
 constexpr int kLdsB = kABufs * kOperand;            // the B buffers follow the A buffers
 constexpr int kLdsBytes = kLdsB + kBBufs * kOperand;   // 160 KiB; the epilogue's scales borrow a free A buffer
 constexpr int kLoads = 8;                           // loads per wave, operand and K-tile
+constexpr int kAhead = 4;                           // rows of blocks of C (of TM) fetched inside the K loop
+enum { kFirst, kMiddle, kPastC, kLast };            // K-tiles of an output tile
 
-template <int MODE, bool SUMS, bool SCALE>
+// sum over the 16 lanes that hold the 16 rows of a block (every lane gets it), four DPP adds
+__device__ __forceinline__ float row16_sum(float x) {
+  auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += dpp(x, std::integral_constant<int, 0x140>());   // row_mirror: lane ^ 15
+  x += dpp(x, std::integral_constant<int, 0x141>());   // row_half_mirror: lane ^ 7
+  x += dpp(x, std::integral_constant<int, 0x1b>());    // quad_perm 3 2 1 0: lane ^ 3
+  x += dpp(x, std::integral_constant<int, 0xb1>());    // quad_perm 1 0 3 2: lane ^ 1
+  return x;
+}
+
+// the lane's number, computed where it is wanted: nothing derived from it can be computed ahead of the
+// K loop and kept (or spilled) through it
+__device__ __forceinline__ int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+// EDGE: M or N is no multiple of 256
+template <int MODE, bool SUMS, bool SCALE, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int64_t N, int64_t K,
                                                                  const int8_t* __restrict__ Qa, int64_t lda,
                                                                  const int8_t* __restrict__ Qb, int64_t ldb,
-                                                                 int64_t tiles_m, int64_t tiles_n,
+                                                                 int tiles_m, int tiles_n,
                                                                  GemmEpilogue ep, GemmSecond sec) {
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   if (MODE == kGemmAccum && guard_tripped(ep)) return;   // the whole grid leaves together
@@ -59,8 +102,11 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));                     // keeps per-thread offsets from being hoisted out of the tile loop
-  const int lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
-  const int64_t total = tiles_m * tiles_n, G = gridDim.x, nk = K / BK;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
+  const int total = tiles_m * tiles_n, G = gridDim.x;
+  const int nk = (int)((K + BK - 1) / BK);
+  // (K is a multiple of 64: the second half of the last K-tile may not exist)
+  const int tail = (K & 64) ? 0 : -1;
   // accumulate mode may carry a second product over the same tiles (sec.Qa != null): a workgroup
   // then runs product 0 and product 1 of a tile back to back, so that the tile of C written by
   // the first is still in the caches when the second adds to it
@@ -72,242 +118,242 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
   // Lane l of load j covers row 64w + 8j + l/8 and LDS piece l%8, which holds the logical piece
   // (l%8) ^ ((row >> 1) & 7); (row >> 1) & 7 = ((l >> 4) + 4j) & 7 depends on j only through
   // its parity.
-  const int lrow = lane >> 3;
-  int64_t vba = blockIdx.x;                         // cursor of the K-tile being fetched: output tile,
-  int kta = 0;                                      // ... K-tile within it
-  int proda = p_lo;                                 // ... and the product it belongs to
-  const int nk32 = (int)nk;
-  const int8_t *pa, *pb;                            // row 64w of that K-tile in A and in B
-  int64_t cur_lda = lda, cur_ldb = ldb;
-  int64_t goff_a0 = 0, goff_a1 = 0, goff_b0 = 0, goff_b1 = 0;
+  const uint32_t la32 = (uint32_t)lda, lb32 = (uint32_t)ldb;
+  uint32_t voff_a[2], voff_b[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const uint32_t piece = 16 * ((lane & 7) ^ (((lane >> 4) + 4 * e) & 7));
+    voff_a[e] = (64 * w + (lane >> 3)) * la32 + piece;
+    voff_b[e] = (64 * w + (lane >> 3)) * lb32 + piece;
+  }
+  // Cursor over the stream of K-tiles: output tile, K-tile within it, product; base address and
+  // remaining bytes of the rows of that K-tile in A and B (uniform: all of it in scalar registers)
+  int cur_vb = blockIdx.x, cur_kt = 0, cur_prod = p_lo, cur_step = 1;
+  uint64_t base_a = 0, base_b = 0;
+  uint32_t bytes_a = 0, bytes_b = 0;
   auto point = [&]() {
-    int64_t tm, tn;
-    tile_of(vba, tiles_m, tiles_n, tm, tn);
-    const int8_t* A0 = proda ? sec.Qa : Qa;
-    const int8_t* B0 = proda ? sec.Qb : Qb;
-    cur_lda = proda ? sec.lda : lda;
-    cur_ldb = proda ? sec.ldb : ldb;
-    goff_a0 = (int64_t)lrow * cur_lda + 16 * ((lane & 7) ^ ((lane >> 4) & 7));
-    goff_a1 = (int64_t)lrow * cur_lda + 16 * ((lane & 7) ^ (((lane >> 4) + 4) & 7));
-    goff_b0 = (int64_t)lrow * cur_ldb + 16 * ((lane & 7) ^ ((lane >> 4) & 7));
-    goff_b1 = (int64_t)lrow * cur_ldb + 16 * ((lane & 7) ^ (((lane >> 4) + 4) & 7));
-    pa = A0 + (tm * BM + 64 * w) * cur_lda + (int64_t)kta * BK;
-    pb = B0 + (tn * BN + 64 * w) * cur_ldb + (int64_t)kta * BK;
+    int tm, tn;
+    tile_of(cur_vb, tiles_m, tiles_n, tm, tn);
+    const int64_t ra = (int64_t)tm * BM, rb = (int64_t)tn * BN;
+    const int64_t left_a = M - ra < BM ? M - ra : BM, left_b = N - rb < BN ? N - rb : BN;
+    base_a = (uint64_t)(uintptr_t)((cur_prod ? sec.Qa : Qa) + ra * lda);
+    base_b = (uint64_t)(uintptr_t)((cur_prod ? sec.Qb : Qb) + rb * ldb);
+    bytes_a = (uint32_t)((left_a - 1) * lda + K);
+    bytes_b = (uint32_t)((left_b - 1) * ldb + K);
   };
-  int kstep = BK;                                   // 0 once the cursor has reached the end of the launch
   auto advance = [&]() {
-    if (kta + 1 < nk32) {
-      kta += kstep ? 1 : 0;
-      pa += kstep;
-      pb += kstep;
-    } else if (proda < p_hi) {
-      ++proda;
-      kta = 0;
+    if (cur_kt + 1 < nk) {
+      cur_kt += cur_step;
+      base_a += BK * cur_step;
+      base_b += BK * cur_step;
+      bytes_a -= BK * cur_step;
+      bytes_b -= BK * cur_step;
+    } else if (cur_prod < p_hi) {
+      ++cur_prod;
+      cur_kt = 0;
       point();
-    } else if (vba + G < total) {
-      vba += G;
-      proda = p_lo;
-      kta = 0;
+    } else if (cur_vb + G < total) {
+      cur_vb += G;
+      cur_prod = p_lo;
+      cur_kt = 0;
       point();
     } else {
-      kstep = 0;                                    // stay on the last K-tile (harmless re-fetch)
+      cur_step = 0;                                 // stay on the last K-tile (harmless re-fetch)
     }
   };
-  // The same where the caller knows that the cursor stays inside its output tile (or has reached
-  // the end): no branch, and so no point where the compiler, having seen the reloads of spilled
-  // registers on the other path, would wait for every load in flight.
-  auto advance_within = [&]() {
-    kta += kstep ? 1 : 0;
-    pa += kstep;
-    pb += kstep;
+  // One load in as few issue slots as possible (an MFMA leaves three until the next one): where it goes
+  // (M0) is set one MFMA ahead, which also keeps the one instruction between the two that the
+  // hardware asks for (nothing the compiler puts there uses M0); the row offset 8 j ld is the scalar
+  // offset, which needs no vector instruction but is not part of the range check, so on the edges it
+  // is added to the lane's offset instead (inside the assembly: as ordinary code the sixteen sums
+  // would be hoisted out of the loops, into registers that are not there).
+  auto target = [&](uint32_t lds_addr, int j) __attribute__((always_inline)) {
+    asm volatile("s_add_i32 m0, %0, %1" : : "s"(lds_addr), "i"(j * 8 * BK) : "m0", "scc");
   };
-  // load j (0..7) of the A resp. B tile at the cursor into buffer `buf` of that operand
-  auto issue_a = [&](int buf, int j) {
-    // wave-uniform by construction; readfirstlane tells the compiler so (it feeds M0)
-    const uint32_t la = __builtin_amdgcn_readfirstlane(lds0 + buf * kOperand + (64 * w) * BK);
-    load_to_lds(pa + (int64_t)(8 * j) * cur_lda + ((j & 1) ? goff_a1 : goff_a0), la + j * 8 * BK);
+  auto issue = [&](uint64_t base, uint32_t bytes, uint32_t voff, uint32_t rows) __attribute__((always_inline)) {
+    const v4i rsrc = {(int)(uint32_t)base, (int)(uint32_t)(base >> 32), (int)bytes, 0x00020000};
+    if (EDGE) {
+      uint32_t tmp;
+      asm volatile("v_add_u32 %0, %1, %3\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds"
+                   : "=&v"(tmp) : "v"(voff), "s"(rsrc), "s"(rows) : "memory");
+    } else {
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(voff), "s"(rsrc), "s"(rows) : "memory");
+    }
   };
-  auto issue_b = [&](int buf, int j) {
-    const uint32_t la = __builtin_amdgcn_readfirstlane(lds0 + kLdsB + buf * kOperand + (64 * w) * BK);
-    load_to_lds(pb + (int64_t)(8 * j) * cur_ldb + ((j & 1) ? goff_b1 : goff_b0), la + j * 8 * BK);
+  const uint32_t lds_a = lds0 + (64 * w) * BK, lds_b = lds_a + kLdsB;
+  auto target_a = [&](int buf, int j) __attribute__((always_inline)) { target(lds_a + buf * kOperand, j); };
+  auto target_b = [&](int buf, int j) __attribute__((always_inline)) { target(lds_b + buf * kOperand, j); };
+  auto issue_a = [&](int j) __attribute__((always_inline)) { issue(base_a, bytes_a, voff_a[j & 1], 8 * j * la32); };
+  auto issue_b = [&](int j) __attribute__((always_inline)) { issue(base_b, bytes_b, voff_b[j & 1], 8 * j * lb32); };
+  auto issue_ktile = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      target_a(buf, j);
+      asm volatile("s_nop 0");
+      issue_a(j);
+    }
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      target_b(buf, j);
+      asm volatile("s_nop 0");
+      issue_b(j);
+    }
   };
 
-  // ---- fragment reads: lane (frow, kh) reads logical piece 2*step + kh of its rows
-  const int frow = lane & 31, kh = lane >> 5, key = (frow >> 1) & 7;
+  // ---- fragment reads: lane (frow, kq) reads logical piece 4*step + kq of its rows; read r of a
+  // step's sixteen: 0..7 -> B blocks, 8..15 -> A blocks
+  const int frow = lane & 15, kq = lane >> 4, key = (frow >> 1) & 7;
   const int a_row = (wm * (BM / 2) + frow) * BK;
   const int b_row = kLdsB + (wn * (BN / 2) + frow) * BK;
-  int xoff[KS];
-#pragma unroll
-  for (int s = 0; s < KS; ++s) xoff[s] = 16 * ((2 * s + kh) ^ key);
+  const int xoff[2] = {16 * (kq ^ key), 16 * ((4 + kq) ^ key)};
   v4i fa[2][TM], fb[2][TN];
-  auto fread = [&](int abuf, int bbuf, int step, int slot) {
-    const int8_t* As = lds + abuf * kOperand + a_row + xoff[step];
-    const int8_t* Bs = lds + bbuf * kOperand + b_row + xoff[step];
-#pragma unroll
-    for (int t = 0; t < TM; ++t) fa[slot][t] = *reinterpret_cast<const v4i*>(As + t * 32 * BK);
-#pragma unroll
-    for (int t = 0; t < TN; ++t) fb[slot][t] = *reinterpret_cast<const v4i*>(Bs + t * 32 * BK);
-  };
-
-  // read r of a step's eight fragment reads: 0..3 -> A tiles, 4..7 -> B tiles
-  auto fread1 = [&](int abuf, int bbuf, int step, int slot, int r) {
-    if (r < TM)
-      fa[slot][r] = *reinterpret_cast<const v4i*>(lds + abuf * kOperand + a_row + xoff[step] + r * 32 * BK);
+  auto fread = [&](int abuf, int bbuf, int step, int r) {
+    if (r < TN)
+      fb[step][r] = *reinterpret_cast<const v4i*>(lds + bbuf * kOperand + b_row + xoff[step] + r * 16 * BK);
     else
-      fb[slot][r - TM] = *reinterpret_cast<const v4i*>(lds + bbuf * kOperand + b_row + xoff[step] + (r - TM) * 32 * BK);
+      fa[step][r - TN] = *reinterpret_cast<const v4i*>(lds + abuf * kOperand + a_row + xoff[step] + (r - TN) * 16 * BK);
   };
 
   // ---- the output tile being multiplied
-  int64_t vb = blockIdx.x, tile_m, tile_n;
+  int vb = blockIdx.x, tile_m, tile_n;
   tile_of(vb, tiles_m, tiles_n, tile_m, tile_n);
-  float sreg_row = (p_lo ? sec.s_row : ep.s_row)[tile_m * BM + tid];
-  float sreg_col = (p_lo ? sec.s_col : ep.s_col)[tile_n * BN + tid];
 
-  // K-tile 0, the A tile of K-tile 1 and the first half of its B tile
+  // K-tiles 0 and 1
   point();
-#pragma unroll
-  for (int j = 0; j < kLoads; ++j) issue_a(0, j);
-#pragma unroll
-  for (int j = 0; j < kLoads; ++j) issue_b(0, j);
+  issue_ktile(0);
   advance();
-#pragma unroll
-  for (int j = 0; j < kLoads; ++j) issue_a(1, j);
-#pragma unroll
-  for (int j = 0; j < kLoads / 2; ++j) issue_b(1, j);
-  wait_loads_but<kLoads + kLoads / 2>();            // K-tile 0 has landed
+  issue_ktile(1);
+  advance();
+  wait_loads();                                     // both have landed
   __syncthreads();
-  fread(0, 0, 0, 0);
 
-  v16i acc[TM][TN];
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int b = 0; b < TN; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
-
-  // Accumulate mode reads the tile of C it adds to.  Every compute unit reaches its epilogue at
-  // about the same time, so loads issued there arrive as one burst per round while the memory
-  // system idles in between: the first band of the tile (the lane's 16 rows x TN columns of the
-  // first 32 rows of its wave tile) is therefore fetched during the K loop instead, a few K-tiles
-  // before the last one, and waits in registers.  All its loads go out in one K-tile and straight
-  // into their registers: nothing in the K loop reads a register that a load is still to fill
-  // (the compiler, which does not see the operand loads, would wait there for all of them).
-  constexpr int kPfBands = 1;                       // bands fetched ahead (of TM); two cost more in spills than they hide
-  const bool pf_on = MODE == kGemmAccum && !SCALE && nk >= 8;   // (alpha / beta need the registers)
-  const int64_t pf0 = nk - 4;                       // K-tile that issues the loads
-  float pre[kPfBands][TN][16];
-#pragma unroll
-  for (int a = 0; a < kPfBands; ++a)
-#pragma unroll
-    for (int b = 0; b < TN; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pre[a][b][v] = 0.f;
-  const int half = lane >> 5, cl = lane & 31;
-  const int cbase = wn * (BN / 2) + cl;
-
-  const int64_t my_tiles = (total - blockIdx.x + G - 1) / G;
+  v4i acc[TM][TN];
+  const int my_tiles = (total - (int)blockIdx.x + G - 1) / G;
   int g = 0;                                        // position in the K-tile stream across tiles
   int abuf = 0;                                     // A buffer of K-tile g (g mod 3)
   int prod = p_lo;                                  // product being multiplied (pairs: 0, 1, 0, 1, ...)
   const bool two = p_lo != p_hi;
-  for (int64_t tile = 0; tile < my_tiles * (p_hi - p_lo + 1); ++tile) {
-  auto ktile = [&](int64_t kt, auto crossing) {
-    // Loads of this K-tile's four steps, four in each:
-    //   step 0: second half of the B tile of K-tile g+1 (its buffer was handed over by the
-    //           barrier of the step before); then the cursor moves on to K-tile g+2;
-    //   steps 1, 2: the A tile of K-tile g+2, into the buffer that K-tile g-1 left;
-    //   step 3, after the barrier: first half of the B tile of K-tile g+2, into this K-tile's.
-    const int bbuf = g & 1;
-    const int anext = abuf == kABufs - 1 ? 0 : abuf + 1, aload = anext == kABufs - 1 ? 0 : anext + 1;
+  for (int tile = 0; tile < my_tiles * (p_hi - p_lo + 1); ++tile) {
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const bool full = !EDGE || (m0 + BM <= M && n0 + BN <= N);
+    const float* srow_g = prod ? sec.s_row : ep.s_row;
+    const float* scol_g = prod ? sec.s_col : ep.s_col;
+    // where the scales of this tile go: the A buffer of its last K-tile, free from that K-tile's
+    // barrier until the second K-tile of the next tile
+    int sbuf = 0;
+    // KIND: first K-tile of the tile (the accumulators start at zero), one in the middle, one with the
+    // first accesses to C in flight, the last one
+    auto ktile = [&](auto kind_tag) {
+      constexpr int KIND = decltype(kind_tag)::value;
+      constexpr bool FIRST = KIND == kFirst, LAST = KIND == kLast;
+      const int bbuf = g & 1;
+      const int anext = abuf == kABufs - 1 ? 0 : abuf + 1;
+      const int aprev = abuf == 0 ? kABufs - 1 : abuf - 1;
+      // first half: the A tile of K-tile g+2 follows (into the buffer that K-tile g-1 left), and the
+      // fragments of the second half are read
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s == KS - 1) {
-        // K-tile g+1 must have landed: everything but the eight loads of the A tile of K-tile
-        // g+2.  After the barrier everybody is also done reading this K-tile's buffers.
-        wait_loads_but<kLoads>();
-        __syncthreads();
-        fread(anext, bbuf ^ 1, 0, (s + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b) {
-            acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s & 1][a], fb[s & 1][b], acc[a][b], 0, 0, 0);
-            if (b == TN - 1) issue_b(bbuf, a);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        if (MODE == kGemmAccum && pf_on && kt == pf0) {
-          // the first band of C: rows 8 (v >> 2) + (v & 3) of the lane's 32-row band
-          const float* cband0 = ep.C + (tile_m * BM + wm * (BM / 2) + 4 * half) * ep.ldc + tile_n * BN + cbase;
-          if (p_lo != p_hi && prod == 1) {            // the first product of the pair left the tile in the caches
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-              for (int b = 0; b < TN; ++b) pre[0][b][v] = cband0[(int64_t)(8 * (v >> 2) + (v & 3)) * ep.ldc + b * 32];
-          } else {
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-              for (int b = 0; b < TN; ++b)
-                pre[0][b][v] = __builtin_nontemporal_load(&cband0[(int64_t)(8 * (v >> 2) + (v & 3)) * ep.ldc + b * 32]);
-          }
+        for (int b = 0; b < TN; ++b) {
+          const v4i zero = {0, 0, 0, 0};
+          acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[0][b], fa[0][a], FIRST ? zero : acc[a][b], 0, 0, 0);
+          const int n = a * TN + b;
+          if (n < 48 && n % 3 == 0) fread(abuf, bbuf, 1, n / 3);
+          if (n % 8 == 5) target_a(aprev, n / 8);
+          if (n % 8 == 6) issue_a(n / 8);
+          __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
-        // the fragments of the next step: one read after each of the first eight MFMAs
-        __builtin_amdgcn_sched_barrier(0);
+      if (LAST) {
 #pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b) {
-            acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s & 1][a], fb[s & 1][b], acc[a][b], 0, 0, 0);
-            if (a * TN + b < 8) fread1(abuf, bbuf, s + 1, (s + 1) & 1, a * TN + b);
-            // ... and one load after every second MFMA of the other eight
-            if (a * TN + b >= 8 && !(b & 1)) {
-              const int n = (a * TN + b - 8) >> 1;
-              if (s == 0) issue_b(bbuf ^ 1, kLoads / 2 + n);
-              if (s == 1) issue_a(aload, n);
-              if (s == 2) issue_a(aload, kLoads / 2 + n);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        if (s == 0) {
-          if (decltype(crossing)::value) advance();
-          else advance_within();
-        }
+        for (int a = 0; a < TM; ++a) fa[1][a] &= tail;
+      }
+      // K-tile g+1 must have landed: everything but the eight loads just issued and the
+      // accesses to C before them.  After the barrier everybody has the fragments of this K-tile in
+      // registers: its buffers are free.  (In the first K-tile of a tile nothing is left to wait for:
+      // the prologue resp. the epilogue before it has waited for every load before its first store,
+      // so that the stores, which the counter counts as well, may still be on their way.)
+      if (KIND == kPastC && full) wait_loads_but<kLoads + 2 * kAhead>();
+      else if (!FIRST) wait_loads_but<kLoads>();
+      __syncthreads();
+      if (LAST) {
+        sbuf = abuf;
+        const int64_t rb = (M - m0 < BM ? M - m0 : BM) * 4, cbytes = (N - n0 < BN ? N - n0 : BN) * 4;
+        const uint64_t pr = (uint64_t)(uintptr_t)(srow_g + m0), pc = (uint64_t)(uintptr_t)(scol_g + n0);
+        const v4i rr = {(int)(uint32_t)pr, (int)(uint32_t)(pr >> 32), (int)rb, 0x00020000};
+        const v4i rc = {(int)(uint32_t)pc, (int)(uint32_t)(pc >> 32), (int)cbytes, 0x00020000};
+        const uint32_t dst = lds0 + sbuf * kOperand + 256 * w, off = 256 * w + 4 * fresh_lane();
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                     : : "s"(dst), "v"(off), "s"(rr) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                     : : "s"(dst + 4 * BM), "v"(off), "s"(rc) : "memory", "m0");
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
-    abuf = anext;
-    ++g;
-  };
-  // The cursor is two K-tiles ahead and moves on in the first step of a K-tile: it leaves its
-  // output tile (or product) in K-tile nk - 2 and nowhere else.
-  if (nk >= 3) {
-    for (int64_t kt = 0; kt < nk - 2; ++kt) ktile(kt, std::false_type());
-    ktile(nk - 2, std::true_type());
-    ktile(nk - 1, std::false_type());
-  } else {
-    for (int64_t kt = 0; kt < nk; ++kt) ktile(kt, std::true_type());
-  }
-
-    // ================= epilogue of tile (tile_m, tile_n); no bounds checks: tiles are full
-    // The scales are staged in the A buffer that the last K-tile has just left (everybody passed
-    // that K-tile's barrier after its last read); the next loads into it go out in the second
-    // step of the next K-tile, which the barrier at the end of the epilogue holds back.
-    float* sc_row = reinterpret_cast<float*>(lds + (abuf == 0 ? kABufs - 1 : abuf - 1) * kOperand);
-    float* sc_col = sc_row + BM;
-    sc_row[tid] = sreg_row;
-    sc_col[tid] = sreg_col;
-    __syncthreads();
-    const int64_t m0 = tile_m * BM, n0 = tile_n * BN;
-    double colsum[TN];
-    float scol[TN];
 #pragma unroll
-    for (int b = 0; b < TN; ++b) {
-      colsum[b] = 0.0;
-      scol[b] = sc_col[cbase + b * 32];
+      for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+          acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[1][b], fa[1][a], acc[a][b], 0, 0, 0);
+          const int n = a * TN + b;
+          if (!LAST && n < 48 && n % 3 == 0) fread(anext, bbuf ^ 1, 0, n / 3);
+          if (n % 8 == 5) target_b(bbuf, n / 8);
+          if (n % 8 == 6) issue_b(n / 8);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      advance();
+      abuf = anext;
+      ++g;
+    };
+    // ---- C in the layout it is stored in: access (j, a, h) of a lane covers four columns of row
+    // 16 a + 8 h + (rl & 7), in the 32 columns of the blocks 2j and 2j + 1
+    auto load4 = [&](auto full_tag, const float* base, int64_t ld, int64_t mw, int64_t nw, int j, int a, int h) -> v4f {
+      const float* p = base + (mw + 16 * a + 8 * h) * ld + nw + 32 * j;
+      if (decltype(full_tag)::value || (mw + 16 * a + 8 * h < M && nw + 32 * j + 3 < N))
+        return *reinterpret_cast<const v4fu*>(p);
+      v4f x = {0.f, 0.f, 0.f, 0.f};
+      if (mw + 16 * a + 8 * h < M) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (nw + 32 * j + v < N) x[v] = p[v];
+      }
+      return x;
+    };
+    // Accumulate mode: the first eighth of the lane's elements of C is fetched before the last two
+    // K-tiles (more of them do not fit the registers), the rest while the epilogue runs, sixteen
+    // accesses ahead.
+    v4f cx[MODE == kGemmAccum ? TM : 1][2];
+    // (read here and not ahead of the last epilogue, which needs the registers)
+#pragma unroll
+    for (int r = 0; r < TM + TN; ++r) fread(abuf, g & 1, 0, r);
+    ktile(std::integral_constant<int, kFirst>());
+    for (int kt = 1; kt < nk - (MODE == kGemmAccum ? 2 : 1); ++kt) ktile(std::integral_constant<int, kMiddle>());
+    if (MODE == kGemmAccum) {
+      const int ln = fresh_lane();
+      const int64_t mw = m0 + wm * (BM / 2) + (ln & 7), nw = n0 + wn * (BN / 2) + 16 * ((ln >> 3) & 1) + 4 * (ln >> 4);
+      if (full) {
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(std::true_type(), ep.C, ep.ldc, mw, nw, 0, a, h);
+      } else {
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(std::false_type(), ep.C, ep.ldc, mw, nw, 0, a, h);
+      }
+      if (nk > 2) ktile(std::integral_constant<int, kPastC>());
     }
+    ktile(std::integral_constant<int, kLast>());
+
+    // ================= epilogue of tile (tile_m, tile_n): acc[a][b][v] is element
+    // (16 a + rl, 16 b + 4 quad + v) of the wave's 128 x 128 block
+    wait_loads_but<kLoads>();                       // the scales (older than the last eight loads)
+    __syncthreads();
+    const int ln = fresh_lane();
+    const int quad = ln >> 4, rl = ln & 15;         // the lane's columns 4*quad.. and its row of a 16 x 16 block
+    const int64_t mw = m0 + wm * (BM / 2) + (rl & 7), nw = n0 + wn * (BN / 2) + 16 * (rl >> 3) + 4 * quad;
+    const float* sc_row = reinterpret_cast<const float*>(lds + sbuf * kOperand) + wm * (BM / 2) + rl;
+    const float* sc_col = reinterpret_cast<const float*>(lds + sbuf * kOperand) + BM + wn * (BN / 2) + 4 * quad;
     // C goes around the caches (it would evict the FP32 operands the next stages stream), except
     // between the two products of a pair: the first leaves its tile cached for the second
     const bool do_scale = SCALE && prod == nprod - 1;
@@ -315,117 +361,132 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
     const float alpha = SCALE ? ep.alpha : 1.f, beta = SCALE ? ep.beta : 0.f;
     const bool has_beta = SCALE && do_scale && beta != 0.f;
     const int64_t ldcin = SCALE ? ep.ldcin : 0;
-    auto bands = [&](auto cached_load_tag, auto cached_store_tag) {
-    constexpr bool CLOAD = decltype(cached_load_tag)::value, CSTORE = decltype(cached_store_tag)::value;
-#pragma unroll
-    for (int a = 0; a < TM; ++a) {
-      const int rbase = wm * (BM / 2) + a * 32 + 4 * half;
-      float* cband = ep.C + (m0 + rbase) * ep.ldc + n0 + cbase;
-      float x[TN][16];
-      float cin[TN][16];                              // the band of Cin, all loads in flight at once
-      if (SCALE && has_beta) {
-        const float* cinband = ep.Cin + (m0 + rbase) * ldcin + n0 + cbase;
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-#pragma unroll
-          for (int b = 0; b < TN; ++b)
-            cin[b][v] = __builtin_nontemporal_load(&cinband[(int64_t)(8 * (v >> 2) + (v & 3)) * ldcin + b * 32]);
-      }
+    auto bands = [&](auto full_tag, auto cached_store_tag) {
+      constexpr bool FULL = decltype(full_tag)::value, CSTORE = decltype(cached_store_tag)::value;
       if (MODE == kGemmAccum) {
-        if (a < kPfBands && pf_on) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
+        for (int a = kAhead; a < TM; ++a)
 #pragma unroll
-            for (int b = 0; b < TN; ++b) x[b][v] = pre[a < kPfBands ? a : 0][b][v];
-        } else {
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-              const float* src = &cband[(int64_t)(8 * (v >> 2) + (v & 3)) * ep.ldc + b * 32];
-              x[b][v] = CLOAD ? *src : __builtin_nontemporal_load(src);
-            }
-        }
+          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(full_tag, ep.C, ep.ldc, mw, nw, 0, a, h);
       }
+      float srow[TM], r1[TM], r2[TM];                // row scales; row sums of the columns 0-63 and 64-127
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int ro = 8 * (v >> 2) + (v & 3);
-        const float srow = sc_row[rbase + ro];
+      for (int a = 0; a < TM; ++a) srow[a] = sc_row[16 * a];
+      // element (row of the 16 x 16 block, column) exists
+      const int64_t me = m0 + wm * (BM / 2) + rl, ne = n0 + wn * (BN / 2) + 4 * quad;
 #pragma unroll
-        for (int b = 0; b < TN; ++b) {
-          const float d = (float)acc[a][b][v] * (srow * scol[b]);
-          float out = MODE == kGemmFirst ? d : x[b][v] + d;
-          if (SCALE && do_scale) {
-            out = alpha * out;
-            if (has_beta) out = out + beta * cin[b][v];
+      for (int j = 0; j < TN / 2; ++j) {
+        v4f sc[2], q1[2], q2[2], q3[2];              // column scales; column sums of 2, 4 and 64 rows
+#pragma unroll
+        for (int e = 0; e < 2; ++e) sc[e] = *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16 * e);
+#pragma unroll
+        for (int a = 0; a < TM; ++a) {
+          v4f cin[2];
+          if (SCALE && has_beta) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) cin[h] = load4(full_tag, ep.Cin, ldcin, mw, nw, j, a, h);
           }
-          if (CSTORE) cband[(int64_t)ro * ep.ldc + b * 32] = out;
-          else __builtin_nontemporal_store(out, &cband[(int64_t)ro * ep.ldc + b * 32]);
-          if (SUMS) x[b][v] = fabsf(d);
-          acc[a][b][v] = 0;
+          v4f d[2];
+          float rs[2];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              d[e][v] = (float)acc[a][2 * j + e][v] * (srow[a] * sc[e][v]);
+              if (!FULL && SUMS && !(me + 16 * a < M && ne + 32 * j + 16 * e + v < N)) d[e][v] = 0.f;
+            }
+            if (SUMS) {
+              rs[e] = (fabsf(d[e][0]) + fabsf(d[e][1])) + (fabsf(d[e][2]) + fabsf(d[e][3]));
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                // pairs of rows, then quads, then the 16 lanes: six levels of additions for 64 rows
+                q1[e][v] = (a & 1) == 0 ? fabsf(d[e][v]) : q1[e][v] + fabsf(d[e][v]);
+                if ((a & 3) == 1) q2[e][v] = q1[e][v];
+                if ((a & 3) == 3) {
+                  q2[e][v] = row16_sum(q2[e][v] + q1[e][v]);
+                  if (a == 3) q3[e][v] = q2[e][v];
+                }
+              }
+            }
+          }
+          if (SUMS) {
+            const float r = rs[0] + rs[1];
+            if (j == 0) r1[a] = r;
+            if (j == 1) r1[a] += r;
+            if (j == 2) r2[a] = r;
+            if (j == 3) r2[a] += r;
+          }
+          // lanes 8-15 of a row of sixteen trade their block 2j for the block 2j + 1 of lanes 0-7
+          v4f t[2];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int d0 = __float_as_int(d[0][v]), d1 = __float_as_int(d[1][v]);
+            t[0][v] = __int_as_float(__builtin_amdgcn_update_dpp(d0, d1, 0x128, 0xf, 0xc, false));
+            t[1][v] = __int_as_float(__builtin_amdgcn_update_dpp(d1, d0, 0x128, 0xf, 0x3, false));
+          }
+          if (j == 0 && a == 0) wait_loads();        // the K-tiles in flight, before the first store
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            v4f out;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              out[v] = MODE == kGemmFirst ? t[h][v] : cx[MODE == kGemmAccum ? a : 0][h][v] + t[h][v];
+              if (SCALE && do_scale) {
+                out[v] = alpha * out[v];
+                if (has_beta) out[v] = out[v] + beta * cin[h][v];
+              }
+            }
+            float* p = ep.C + (mw + 16 * a + 8 * h) * ep.ldc + nw + 32 * j;
+            if (FULL || (mw + 16 * a + 8 * h < M && nw + 32 * j + 3 < N)) {
+              if (CSTORE) *reinterpret_cast<v4fu*>(p) = out;
+              else __builtin_nontemporal_store(out, reinterpret_cast<v4fu*>(p));
+            } else if (mw + 16 * a + 8 * h < M) {
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                if (nw + 32 * j + v < N) p[v] = out[v];
+            }
+          }
+          if (MODE == kGemmAccum && j + 1 < TN / 2) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(full_tag, ep.C, ep.ldc, mw, nw, j + 1, a, h);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (SUMS && rl < 2 && (FULL || m0 + wm * (BM / 2) < M)) {
+          // (every lane has the sums: lane 0 of a row of sixteen writes block 2j, lane 1 block 2j + 1)
+          double* cp = ep.col_part + (int64_t)(2 * tile_m + wm) * (ep.part_ld_n ? ep.part_ld_n : N) + ne + 32 * j + 16 * rl;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float lo = rl ? q3[1][v] : q3[0][v], hi = rl ? q2[1][v] : q2[0][v];
+            if (FULL || ne + 32 * j + 16 * rl + v < N) cp[v] = (double)lo + (double)hi;
+          }
         }
       }
       if (SUMS) {
-        // row sums by a reduce-scatter butterfly over the 32 lanes that share a row
-        float r[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) r[v] = (x[0][v] + x[1][v]) + (x[2][v] + x[3][v]);
-#pragma unroll
-        for (int n = 8, o = 16; n >= 1; n >>= 1, o >>= 1) {
-          const bool up = (cl & o) != 0;
-#pragma unroll
-          for (int i = 0; i < n; ++i) {
-            float send = up ? r[i] : r[i + n];
-            float keep = up ? r[i + n] : r[i];
-            r[i] = keep + __shfl_xor(send, o, 64);
-          }
-        }
-        r[0] += __shfl_xor(r[0], 1, 64);
-        const int v = cl >> 1;
-        // each wave leaves its own partial (its 128 columns of the tile): no exchange through LDS
-        // and no barrier, so a wave that is done starts on the next tile
-        if (!(cl & 1)) ep.row_part[(2 * tile_n + wn) * (ep.part_ld_m ? ep.part_ld_m : M) + m0 + rbase + 8 * (v >> 2) + (v & 3)] =
-              (double)r[0];
-#pragma unroll
-        for (int b = 0; b < TN; ++b) {
-          float t8[8], t4[4];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) t8[i] = x[b][2 * i] + x[b][2 * i + 1];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) t4[i] = t8[2 * i] + t8[2 * i + 1];
-          colsum[b] += (double)((t4[0] + t4[1]) + (t4[2] + t4[3]));
+        for (int a = 0; a < TM; ++a) {
+          // 32 values of the lane and four lanes: seven levels of additions for 128 columns
+          float r = r1[a] + r2[a];
+          r += __shfl_xor(r, 16, 64);
+          r += __shfl_xor(r, 32, 64);
+          if (quad == 0 && (FULL || (me + 16 * a < M && n0 + wn * (BN / 2) < N)))
+            ep.row_part[(int64_t)(2 * tile_n + wn) * (ep.part_ld_m ? ep.part_ld_m : M) + me + 16 * a] = (double)r;
         }
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
     };
-    if (two && prod == 0) bands(std::false_type(), std::true_type());
-    else if (two) bands(std::true_type(), std::false_type());
-    else bands(std::false_type(), std::false_type());
-    if (SUMS) {
-#pragma unroll
-      for (int b = 0; b < TN; ++b) {
-        double c = colsum[b];
-        c += __shfl_xor(c, 32, 64);
-        if (half == 0) ep.col_part[(2 * tile_m + wm) * (ep.part_ld_n ? ep.part_ld_n : N) + n0 + cbase + b * 32] = c;
-      }
-    }
+    if (EDGE && !full) bands(std::integral_constant<bool, !EDGE>(), std::true_type());
+    else if (MODE == kGemmAccum && two && prod == 0) bands(std::true_type(), std::true_type());
+    else bands(std::true_type(), std::false_type());
     // everybody has read its scales: the A buffer that held them may be loaded again (a bare
     // barrier: the stores of C stay in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
     // next product of this tile, or the next output tile of this workgroup
     if (prod < p_hi) {
       prod = 1;
-      sreg_row = sec.s_row[tile_m * BM + tid];
-      sreg_col = sec.s_col[tile_n * BN + tid];
     } else {
       prod = p_lo;
       vb += G;
-      if (vb < total) {
-        tile_of(vb, tiles_m, tiles_n, tile_m, tile_n);
-        sreg_row = (p_lo ? sec.s_row : ep.s_row)[tile_m * BM + tid];
-        sreg_col = (p_lo ? sec.s_col : ep.s_col)[tile_n * BN + tid];
-      }
+      if (vb < total) tile_of(vb, tiles_m, tiles_n, tile_m, tile_n);
     }
   }
   wait_loads();                                     // nothing may still be writing LDS when the wave ends
@@ -436,10 +497,12 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
 bool gemm_persistent_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                         int64_t ldb, const GemmEpilogue& ep) {
   if (ep.D_int || ep.D_F_copy) return false;                 // parity-check outputs use the plain kernel
-  if (M <= 0 || N <= 0 || K <= 0 || (M % BM) || (N % BN) || (K % BK)) return false;
+  if (M <= 0 || N <= 0 || K <= 0 || K <= BK || (K % 64)) return false;   // (two K-tiles at least)
+  if (lda >= (1 << 23) || ldb >= (1 << 23)) return false;    // byte offsets within a tile are 32-bit
   if (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) || (lda % 16) || (ldb % 16))
     return false;
-  return (M / BM) * (N / BN) >= 256;                        // at least one tile per compute unit
+  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+  return tiles >= 256 && tiles < (1 << 30);                 // at least one tile per compute unit
 }
 
 // Compute units of the current device, looked up once per device (srq_create primes it, so
@@ -481,29 +544,25 @@ hipError_t launch_gemm_i8_persistent(int64_t M, int64_t N, int64_t K, const int8
   int num_cu = 0;
   hipError_t e = gemm_device_cus(&num_cu);
   if (e != hipSuccess) return e;
-  const int64_t tm = M / BM, tn = N / BN;
+  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
   int64_t wgs = num_cu / 8 * 8;                              // one workgroup per CU, a multiple of the 8 XCDs
   if (wgs < 8) wgs = 8;
   if (wgs > tm * tn) wgs = tm * tn;
   const bool sums = ep.mode == kGemmFirst && ep.row_part != nullptr;
-  const bool scale = ep.final_scale != 0;
-  void (*kern)(int64_t, int64_t, int64_t, const int8_t*, int64_t, const int8_t*, int64_t, int64_t, int64_t,
-               GemmEpilogue, GemmSecond);
+  const bool scale = ep.final_scale != 0, edge = (M % BM) || (N % BN);
+  void (*kern)(int64_t, int64_t, int64_t, const int8_t*, int64_t, const int8_t*, int64_t, int, int, GemmEpilogue,
+               GemmSecond);
   GemmSecond sec = {nullptr, nullptr, 0, 0, nullptr, nullptr};
   if (second && ep.mode == kGemmAccum) sec = *second;
-  if (ep.mode == kGemmFirst) {
-    kern = sums ? (scale ? gemm_i8_persistent_kernel<kGemmFirst, true, true>
-                         : gemm_i8_persistent_kernel<kGemmFirst, true, false>)
-                : (scale ? gemm_i8_persistent_kernel<kGemmFirst, false, true>
-                         : gemm_i8_persistent_kernel<kGemmFirst, false, false>);
-  } else {
-    kern = scale ? gemm_i8_persistent_kernel<kGemmAccum, false, true>
-                 : gemm_i8_persistent_kernel<kGemmAccum, false, false>;
-  }
+#define SRQ_KERN(MODE, SUMS)                                                                          \
+  (scale ? (edge ? gemm_i8_persistent_kernel<MODE, SUMS, true, true> : gemm_i8_persistent_kernel<MODE, SUMS, true, false>) \
+         : (edge ? gemm_i8_persistent_kernel<MODE, SUMS, false, true> : gemm_i8_persistent_kernel<MODE, SUMS, false, false>))
+  kern = ep.mode != kGemmFirst ? SRQ_KERN(kGemmAccum, false) : sums ? SRQ_KERN(kGemmFirst, true) : SRQ_KERN(kGemmFirst, false);
+#undef SRQ_KERN
   e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kLdsBytes, st, M, N, K, Qa, lda, Qb, ldb, tm, tn, ep,
-                     sec);
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kLdsBytes, st, M, N, K, Qa, lda, Qb, ldb, (int)tm,
+                     (int)tn, ep, sec);
   return hipGetLastError();
 }
 

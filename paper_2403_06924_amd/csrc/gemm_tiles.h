@@ -19,6 +19,17 @@ static __device__ __forceinline__ void tile_of(int64_t vb, int64_t tiles_m, int6
   tn = in / rows_in;
 }
 
+static __device__ __forceinline__ void tile_of(int vb, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const uint32_t total = (uint32_t)tiles_m * (uint32_t)tiles_n, per = total / 8;
+  uint32_t bid = (uint32_t)vb;
+  if (per > 0 && bid < per * 8) bid = (bid & 7) * per + (bid >> 3);
+  const uint32_t wide = 8u * (uint32_t)tiles_n, grp = bid / wide, first = grp * 8u;
+  const uint32_t rows_in = (uint32_t)tiles_m - first < 8u ? (uint32_t)tiles_m - first : 8u;
+  const uint32_t in = bid - grp * wide;
+  tm = (int)(first + in % rows_in);
+  tn = (int)(in / rows_in);
+}
+
 // One wave-wide 16-byte-per-lane load from global memory into LDS: lane l's bytes land at
 // lds_base + 16*l.  Issued as inline assembly so that its completion is waited for explicitly
 // (wait_loads) right before the barrier that publishes the tile, not before every LDS read.
