@@ -142,8 +142,8 @@ size_t plan_fixed(char* base, int64_t M, int64_t N, int64_t K, Plan* p) {
   p->s_b = c.take<float>(N); p->lam_b = c.take<float>(N); p->s_rb = c.take<float>(N);
   p->lam_rb = c.take<float>(N); p->dcol = c.take<float>(N); p->t_b = c.take<float>(N);
   p->amax_b = c.take<uint32_t>(N); p->ramax_b = c.take<uint32_t>(N);
-  p->row_part = c.take<double>((size_t)tiles(N, gemm_tile_n()) * M);
-  p->col_part = c.take<double>((size_t)tiles(M, gemm_tile_m()) * N);
+  p->row_part = c.take<double>((size_t)tiles(N, kGemmPart) * M);
+  p->col_part = c.take<double>((size_t)tiles(M, kGemmPart) * N);
   int64_t chk = select_chunks(K);
   p->cnt_a = c.take<int32_t>((size_t)chk * M); p->tot_a = c.take<int32_t>(M);
   p->a_ptr = c.take<int32_t>(M + 1);
@@ -202,7 +202,7 @@ size_t stage_bytes(int64_t M, int64_t N, int64_t K) {
   size_t b = 0;
   b += align_up(mx * 4) * 4;                                            // lambdas, totals, ptr
   b += align_up(((size_t)select_chunks(K) * big + (size_t)select_chunks(big) * K) * 4);  // counts
-  b += align_up(((size_t)tiles(N, gemm_tile_n()) * M + (size_t)tiles(M, gemm_tile_m()) * N) * 8);
+  b += align_up(((size_t)tiles(N, kGemmPart) * M + (size_t)tiles(M, kGemmPart) * N) * 8) + kAlign;
   b += align_up(big * K);                                               // expanded operand
   // srq_build_sparse_residual's streaming path on an operand of up to max(M,N) x K or K x max(M,N):
   // three vectors of per-vector values, the keep-mask and the codes (rows padded to 16)
@@ -580,10 +580,15 @@ static srq_status_t gemm_i8_impl(srq_handle_t h, int64_t M, int64_t N, int64_t K
     if (K > 0 && (!Qa || !Qb || lda < K || ldb < K)) return SRQ_STATUS_INVALID_ARG;
   }
   if ((drow == nullptr) != (dcol == nullptr)) return SRQ_STATUS_INVALID_ARG;
-  size_t need = align_up((size_t)tiles(N, gemm_tile_n()) * M * 8) + align_up((size_t)tiles(M, gemm_tile_m()) * N * 8);
+  // Partial sums per 64 rows / columns where there is room for them, else (static scratch, larger
+  // problems) the kernels that leave one per 128; a problem for which that is too little as well is
+  // refused before anything is launched.
+  int part = kGemmPart;
   if (drow && M > 0 && N > 0) {
-    // (a problem whose partial sums do not fit is refused before anything is launched)
-    if (use_static ? need > kStaticScratchBytes : (!h->ws || h->ws_bytes < need)) return SRQ_STATUS_WORKSPACE;
+    const size_t room = use_static ? kStaticScratchBytes : h->ws ? h->ws_bytes : 0;
+    auto need = [&](int t) { return align_up((size_t)tiles(N, t) * M * 8) + align_up((size_t)tiles(M, t) * N * 8); };
+    if (room < need(part)) part = kGemmPartLarge;
+    if (room < need(part)) return SRQ_STATUS_WORKSPACE;
   }
   srq_status_t s = bind_device(h);
   if (s) return s;
@@ -602,8 +607,9 @@ static srq_status_t gemm_i8_impl(srq_handle_t h, int64_t M, int64_t N, int64_t K
       if (!base) return hip_fail(h, g_scratch_error != hipSuccess ? g_scratch_error : hipErrorInvalidDevice);
     }
     Carver c{base, 0};
-    ep.row_part = c.take<double>((size_t)tiles(N, gemm_tile_n()) * M);
-    ep.col_part = c.take<double>((size_t)tiles(M, gemm_tile_m()) * N);
+    ep.row_part = c.take<double>((size_t)tiles(N, part) * M);
+    ep.col_part = c.take<double>((size_t)tiles(M, part) * N);
+    ep.no_tile64 = part != kGemmPart;
   }
   SRQ_HIP(h, launch_gemm_i8(M, N, K, Qa, lda, Qb, ldb, ep, st));
   if (drow) {
@@ -730,7 +736,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     GemmEpilogue probe;
     memset(&probe, 0, sizeof(probe));
     probe.mode = kGemmAccum;
-    if (gemm_small_ok(M, N, Kc, p.A_int, Kc, p.B_int, Kc, probe)) strategy = SRQ_STRATEGY_CSR_MFMA;
+    probe.ldc = ldc;
+    const bool tiled = gemm_small_ok(M, N, Kc, p.A_int, Kc, p.B_int, Kc, probe);
+    // (debug outputs are there to compare the executions: decided for them outside whole small tiles)
+    if (dbg ? tiled && M % 128 == 0 && N % 128 == 0
+            : tiled || gemm_tile64_ok(M, N, Kc, p.A_int, Kc, p.B_int, Kc, probe))
+      strategy = SRQ_STRATEGY_CSR_MFMA;
   }
 
   srq_intermediates_t& im = h->last;

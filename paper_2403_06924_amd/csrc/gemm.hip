@@ -221,9 +221,8 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(int64_t M, int64_t N, int6
 
   // ---- epilogue.  acc[a][b][v] is element (row, col) of the wave's block with
   //      row = a*32 + 8*(v/4) + 4*(lane/32) + v%4,  col = b*32 + lane%32.
-  // Partial sums of |D_F| are taken in float over at most 7 additions of non-negative terms
-  // (pairwise over the lane's values, then a fixed shuffle tree over the 32 lanes of a row),
-  // and in double from there on, in a fixed order: the result is reproducible run to run.
+  // Partial sums of |D_F| are taken in double, in a fixed order: the result is reproducible run to
+  // run, and the means are those of any other kernel that sums as precisely.
   double* red = reinterpret_cast<double*>(lds);            // [2][max(BM,BN)], operand tiles are dead
   constexpr int RED = BM > BN ? BM : BN;
   const bool first = ep.mode == kGemmFirst;
@@ -295,34 +294,29 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(int64_t M, int64_t N, int6
       // Row sums: r[v] is this lane's share of row v of the band.  A reduce-scatter butterfly
       // over the 32 lanes of the half-wave (halving the live values at each exchange) leaves
       // the total of row v = cl >> 1 in lanes cl and cl ^ 1: 16 shuffles instead of 80.
-      float r[16];
+      double r[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        if (C::TN == 4) r[v] = (ad[0][v] + ad[1][v]) + (ad[2][v] + ad[3][v]);
-        else r[v] = ad[0][v] + ad[C::TN - 1][v];
+        r[v] = (double)ad[0][v] + (double)ad[1][v];
+        if (C::TN == 4) r[v] += (double)ad[C::TN - 2][v] + (double)ad[C::TN - 1][v];
       }
 #pragma unroll
       for (int n = 8, o = 16; n >= 1; n >>= 1, o >>= 1) {
         const bool up = (cl & o) != 0;
 #pragma unroll
         for (int i = 0; i < n; ++i) {
-          float send = up ? r[i] : r[i + n];
-          float keep = up ? r[i + n] : r[i];
+          double send = up ? r[i] : r[i + n];
+          double keep = up ? r[i + n] : r[i];
           r[i] = keep + __shfl_xor(send, o, 64);
         }
       }
       r[0] += __shfl_xor(r[0], 1, 64);
       const int v = cl >> 1;
-      if (!(cl & 1)) red[wn * RED + rbase + 8 * (v >> 2) + (v & 3)] = (double)r[0];
+      if (!(cl & 1)) red[wn * RED + rbase + 8 * (v >> 2) + (v & 3)] = r[0];
 #pragma unroll
-      for (int b = 0; b < C::TN; ++b) {
-        float t8[8], t4[4];
+      for (int b = 0; b < C::TN; ++b)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t8[i] = ad[b][2 * i] + ad[b][2 * i + 1];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t4[i] = t8[2 * i] + t8[2 * i + 1];
-        colsum[b] += (double)((t4[0] + t4[1]) + (t4[2] + t4[3]));
-      }
+        for (int i = 0; i < 16; ++i) colsum[b] += (double)ad[b][i];
     }
   }
   if (sums) {
@@ -382,13 +376,44 @@ inline bool use_big_tiles(int64_t M, int64_t N) {
 
 }  // namespace
 
-int gemm_tile_m() { return 128; }   // smallest tile: the partial-sum buffers are sized for it
-int gemm_tile_n() { return 128; }
+// 16-byte aligned, K-contiguous operands with whole steps of 64 along K, no debug outputs, offsets within
+// a tile of 128 rows below 2^31
+static bool aligned_operands(int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb, const GemmEpilogue& ep) {
+  if (ep.D_int || ep.D_F_copy || K <= 0 || (K % 64)) return false;
+  if (lda >= (1 << 23) || ldb >= (1 << 23) || ep.ldc >= (1 << 22)) return false;
+  if (ep.final_scale && ep.beta != 0.f && ep.ldcin >= (1 << 22)) return false;
+  return (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) | (lda % 16) | (ldb % 16)) == 0;
+}
+
+bool gemm_tile64_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
+                    const GemmEpilogue& ep) {
+  if (M <= 0 || N <= 0 || ep.no_tile64 || !aligned_operands(K, Qa, lda, Qb, ldb, ep)) return false;
+  const int64_t t = ((M + 63) / 64) * ((N + 63) / 64);
+  return t < (1 << 30) && (K <= 384 || t <= 640);
+}
+
+// 128 x 128 tiles, at most one per compute unit (beyond that the halves of 256 x 256 tiles fill the chip)
+bool gemm_small_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
+                   const GemmEpilogue& ep) {
+  if (M <= 0 || N <= 0 || !aligned_operands(K, Qa, lda, Qb, ldb, ep)) return false;
+  return ((M + 127) / 128) * ((N + 127) / 128) < (1 << 30) && !use_big_tiles(M, N);
+}
+
+static bool gemm_skinny_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
+                           const GemmEpilogue& ep) {
+  return M > 0 && (M <= 32 || (M <= 64 && N <= 8192)) && N > 0 && N < ((int64_t)1 << 31) && K >= 256 && !ep.row_part && aligned_operands(K, Qa, lda, Qb, ldb, ep);
+}
+
 int64_t gemm_tiles_m(int64_t M, int64_t N) { int t = use_big_tiles(M, N) ? 256 : 128; return (M + t - 1) / t; }
 int64_t gemm_tiles_n(int64_t M, int64_t N) { int t = use_big_tiles(M, N) ? 256 : 128; return (N + t - 1) / t; }
 
 void gemm_sum_parts(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
                     const GemmEpilogue& ep, int64_t* parts_n, int64_t* parts_m) {
+  if (gemm_tile64_ok(M, N, K, Qa, lda, Qb, ldb, ep)) {
+    *parts_n = (N + 63) / 64;
+    *parts_m = (M + 63) / 64;
+    return;
+  }
   // (the persistent and the small-tile kernel leave one partial per 128 columns resp. rows)
   const bool per128 = gemm_persistent_ok(M, N, K, Qa, lda, Qb, ldb, ep) || gemm_small_ok(M, N, K, Qa, lda, Qb, ldb, ep);
   *parts_n = per128 ? (N + 127) / 128 : gemm_tiles_n(M, N);
@@ -398,6 +423,11 @@ void gemm_sum_parts(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t l
 hipError_t launch_gemm_i8(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda,
                           const int8_t* Qb, int64_t ldb, const GemmEpilogue& ep, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (gemm_skinny_ok(M, N, K, Qa, lda, Qb, ldb, ep)) return launch_gemm_i8_skinny(M, N, K, Qa, lda, Qb, ldb, ep, st);
+  if (gemm_tile64_ok(M, N, K, Qa, lda, Qb, ldb, ep)) {
+    DirectProducts pr = {{{Qa, Qb, ep.s_row, ep.s_col}}, 1};
+    return launch_gemm_i8_tile64(M, N, K, lda, ldb, pr, ep, st);
+  }
   if (gemm_persistent_ok(M, N, K, Qa, lda, Qb, ldb, ep))
     return launch_gemm_i8_persistent(M, N, K, Qa, lda, Qb, ldb, ep, st);
   if (gemm_small_ok(M, N, K, Qa, lda, Qb, ldb, ep)) return launch_gemm_i8_small(M, N, K, Qa, lda, Qb, ldb, ep, st);
@@ -414,6 +444,8 @@ hipError_t launch_gemm_i8(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int
 bool gemm_pair_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
                   const GemmSecond& sec, const GemmEpilogue& ep) {
   if (ep.mode != kGemmAccum || !sec.Qa || !sec.Qb) return false;
+  if (gemm_tile64_ok(M, N, K, Qa, lda, Qb, ldb, ep))   // (it runs both products or none)
+    return !ep.each_product && sec.lda == lda && sec.ldb == ldb && gemm_tile64_ok(M, N, K, sec.Qa, lda, sec.Qb, ldb, ep);
   if (gemm_persistent_ok(M, N, K, Qa, lda, Qb, ldb, ep))
     return sec.lda == lda && sec.ldb == ldb && gemm_persistent_ok(M, N, K, sec.Qa, sec.lda, sec.Qb, sec.ldb, ep);
   return gemm_small_ok(M, N, K, Qa, lda, Qb, ldb, ep) && gemm_small_ok(M, N, K, sec.Qa, sec.lda, sec.Qb, sec.ldb, ep);
@@ -421,6 +453,10 @@ bool gemm_pair_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda
 
 hipError_t launch_gemm_i8_pair(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                                int64_t ldb, const GemmSecond& sec, const GemmEpilogue& ep, hipStream_t st) {
+  if (gemm_tile64_ok(M, N, K, Qa, lda, Qb, ldb, ep)) {
+    DirectProducts pr = {{{Qa, Qb, ep.s_row, ep.s_col}, {sec.Qa, sec.Qb, sec.s_row, sec.s_col}}, 2};
+    return launch_gemm_i8_tile64(M, N, K, lda, ldb, pr, ep, st);
+  }
   if (gemm_persistent_ok(M, N, K, Qa, lda, Qb, ldb, ep))
     return launch_gemm_i8_persistent(M, N, K, Qa, lda, Qb, ldb, ep, st, &sec);
   return launch_gemm_i8_small(M, N, K, Qa, lda, Qb, ldb, ep, st, &sec);

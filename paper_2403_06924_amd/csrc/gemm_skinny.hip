@@ -1,0 +1,159 @@
+// INT8 GEMM for at most 64 rows (a linear layer applied to a few tokens; K-contiguous, 16-byte aligned
+// operands, K a multiple of 64, any N; no sums of |D_F|): bound by reading the wide operand once.
+//
+// A workgroup of four waves owns all rows x 32 columns and the waves divide K between them, each summing
+// the whole tile over its quarter.  A wave stages its K-tiles of 128 bytes in LDS of its own (straight
+// from global memory, unpadded rows, XOR swizzle as in the other kernels), NST deep, with counted waits
+// and no barrier before the integer sums meet (exact in any order).  So a compute unit keeps about
+// 100 KiB of loads in flight whatever K is, every load is whole 128-byte lines, and 32 columns per
+// workgroup give every compute unit work from N = 8192 on.
+//
+// (Fragments read straight into registers touch sixteen rows per load, for which the vector-memory path
+// takes 64 clocks instead of 16: 16 x 14336 x 4096 in 15.6 us; 128 x 128 tiles: 30.7 us.)
+#include "srq_internal.h"
+#include "gemm_tiles.h"
+#include "gemm_lanes.h"
+
+namespace srq {
+namespace {
+
+constexpr int BN = 32, BK = 128, TNB = BN / 16;
+
+template <int TMB, int NST>                          // 16-row blocks; stages per wave
+__global__ __launch_bounds__(256) void gemm_i8_skinny_kernel(int64_t M, int64_t N, int K, const int8_t* __restrict__ Qa,
+                                                             int64_t lda, const int8_t* __restrict__ Qb, int64_t ldb,
+                                                             GemmEpilogue ep) {
+  constexpr int kB = BN * BK, kA = 16 * TMB * BK, kStage = kA + kB;   // bytes of a wave's stage: B tile, then A tile
+  constexpr int LB = BN / 8, LA = 2 * TMB, kLoads = LA + LB;          // loads of eight rows
+  constexpr int NB = TMB * TNB;                                       // 16 x 16 blocks of the tile
+  extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
+  if (guard_tripped(ep)) return;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) int8_t*)lds);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int quad = lane >> 4, rl = lane & 15;
+  const int64_t n0 = (int64_t)blockIdx.x * BN;
+  const uint32_t rows_a = (uint32_t)M, rows_b = (uint32_t)(N - n0 < BN ? N - n0 : BN);
+
+  // ---- loader: lane l of load j covers row 8j + l/8 and LDS piece l%8, which holds the logical piece
+  // (l%8) ^ ((row >> 1) & 7).  Rows past the operand's last one read as zero.
+  const int nk = (K + BK - 1) / BK, k_lo = nk * w / 4, k_hi = nk * (w + 1) / 4;
+  const uint64_t pa = (uint64_t)(uintptr_t)Qa, pb = (uint64_t)(uintptr_t)(Qb + n0 * ldb);
+  const v4i ra = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)((rows_a - 1) * (uint32_t)lda + (uint32_t)K), 0x00020000};
+  const v4i rb = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)((rows_b - 1) * (uint32_t)ldb + (uint32_t)K), 0x00020000};
+  uint32_t voff_a[LA], voff_b[LB];
+#pragma unroll
+  for (int j = 0; j < LA; ++j) {
+    const uint32_t row = 8 * j + (lane >> 3);
+    voff_a[j] = row * (uint32_t)lda + 16 * ((lane & 7) ^ ((row >> 1) & 7));
+  }
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+    const uint32_t row = 8 * j + (lane >> 3);
+    voff_b[j] = row * (uint32_t)ldb + 16 * ((lane & 7) ^ ((row >> 1) & 7));
+  }
+  auto issue = [&](uint32_t dst, v4i rsrc, uint32_t voff, uint32_t soff) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+  };
+  const int wbase = w * NST * kStage;
+  auto fetch = [&](int stage, int kt) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + wbase + stage * kStage, soff = (uint32_t)kt * BK;
+#pragma unroll
+    for (int j = 0; j < LB; ++j) issue(dst + 8 * j * BK, rb, voff_b[j], soff);
+#pragma unroll
+    for (int j = 0; j < LA; ++j) issue(dst + kB + 8 * j * BK, ra, voff_a[j], soff);
+  };
+#pragma unroll
+  for (int g = 0; g < NST; ++g)
+    if (k_lo + g < k_hi) fetch(g, k_lo + g);
+
+  const int key = (rl >> 1) & 7;
+  const int xoff[2] = {16 * (quad ^ key), 16 * ((4 + quad) ^ key)};
+  v4i acc[TMB][TNB];
+#pragma unroll
+  for (int a = 0; a < TMB; ++a)
+#pragma unroll
+    for (int b = 0; b < TNB; ++b) acc[a][b] = v4i{0, 0, 0, 0};
+  int stage = 0;
+  for (int kt = k_lo; kt < k_hi; ++kt) {
+    // this K-tile has landed: everything but the NST - 1 after it (near the end: everything)
+    if (kt + NST - 1 < k_hi) wait_loads_but<(NST - 1) * kLoads>();
+    else wait_loads();
+    const int8_t* base = lds + wbase + stage * kStage + rl * BK;
+    const int tail = (K & 64) && kt == nk - 1 ? 0 : -1;   // the second half of the last K-tile may not exist
+    v4i fa[2][TMB], fb[2][TNB];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int b = 0; b < TNB; ++b) fb[s][b] = *reinterpret_cast<const v4i*>(base + xoff[s] + b * 16 * BK);
+#pragma unroll
+      for (int a = 0; a < TMB; ++a) fa[s][a] = *reinterpret_cast<const v4i*>(base + kB + xoff[s] + a * 16 * BK);
+    }
+#pragma unroll
+    for (int a = 0; a < TMB; ++a) fa[1][a] &= tail;
+    // (the fragments are in registers before the stage is loaded again)
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    if (kt + NST < k_hi) fetch(stage, kt + NST);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int a = 0; a < TMB; ++a)
+#pragma unroll
+        for (int b = 0; b < TNB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[s][b], fa[s][a], acc[a][b], 0, 0, 0);
+    stage = stage == NST - 1 ? 0 : stage + 1;
+  }
+  // ---- the waves' sums meet in LDS; wave w finishes blocks w, w + 4, ...
+  v4i* part = reinterpret_cast<v4i*>(lds);            // [wave][block][lane]
+  __syncthreads();                                    // (every stage has been read)
+#pragma unroll
+  for (int i = 0; i < NB; ++i) part[(w * NB + i) * 64 + lane] = acc[i / TNB][i % TNB];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NB; i += 4) {
+    const int blk = i + w;
+    if (blk >= NB) break;
+    const int a = blk / TNB, b = blk % TNB;
+    v4i sum = part[blk * 64 + lane];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) sum += part[(s * NB + blk) * 64 + lane];
+    // lane (rl, quad): row rl of the block, columns 4 quad .. 4 quad + 3
+    const uint32_t m = (uint32_t)(16 * a + rl), n = (uint32_t)(16 * b + 4 * quad);
+    const float srow = buf_load_f32(buf_rsrc(ep.s_row, 4 * rows_a), 4u * m);
+    const v4f scol = buf_load_4(buf_rsrc(ep.s_col + n0, 4 * rows_b), 4u * n, rows_b == BN);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (m >= rows_a || n + v >= rows_b) continue;
+      float* c = ep.C + (int64_t)m * ep.ldc + n0 + n + v;
+      const float d = (float)sum[v] * (srow * scol[v]);
+      float out = ep.mode == kGemmFirst ? d : *c + d;
+      if (ep.final_scale) {
+        out = ep.alpha * out;
+        if (ep.beta != 0.f) out = out + ep.beta * ep.Cin[(int64_t)m * ep.ldcin + n0 + n + v];
+      }
+      *c = out;
+    }
+  }
+}
+
+template <int TMB, int NST>
+hipError_t launch(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
+                  const GemmEpilogue& ep, hipStream_t st) {
+  constexpr int bytes = 4 * NST * (BN + 16 * TMB) * BK;
+  auto kern = gemm_i8_skinny_kernel<TMB, NST>;
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((N + BN - 1) / BN)), dim3(256), bytes, st, M, N, (int)K, Qa, lda, Qb, ldb, ep);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm_i8_skinny(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
+                                 int64_t ldb, const GemmEpilogue& ep, hipStream_t st) {
+  if (M <= 16) return launch<1, 3>(M, N, K, Qa, lda, Qb, ldb, ep, st);
+  if (M <= 32) return launch<2, 2>(M, N, K, Qa, lda, Qb, ldb, ep, st);
+  return launch<4, 3>(M, N, K, Qa, lda, Qb, ldb, ep, st);
+}
+
+}  // namespace srq

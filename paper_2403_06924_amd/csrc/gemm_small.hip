@@ -1,7 +1,7 @@
-// INT8 GEMM for aligned problems too small to give every compute unit a 256 x 256 tile (M, N
-// multiples of 128, K a multiple of 128, 16-byte aligned operands): the products of Algorithm 1
-// lines 2, 12 and 14 at sizes like 1024^3 .. 3072^3, where the time of a product is a chain of
-// memory latencies rather than matrix-core throughput.
+// INT8 GEMM for problems too small to give every compute unit half a 256 x 256 tile and too large for
+// 64 x 64 tiles (any M and N, K a multiple of 64, 16-byte aligned operands): the products of Algorithm 1
+// lines 2, 12 and 14 at sizes like 2048^3, where the time of a product is a chain of memory latencies
+// rather than matrix-core throughput.
 //
 // One 128 x 128 output tile per 4-wave workgroup (64 x 64 per wave, v_mfma_i32_32x32x32_i8), K
 // staged 128 bytes at a time as in the persistent kernel - global memory straight into LDS,
@@ -32,7 +32,9 @@ constexpr int kLdsColX = kLdsRowX + 2 * BM * 4;        // double[2][BN]: column 
 constexpr int kLdsBytes = kLdsColX + 2 * BN * 8;
 constexpr int kLoadsPerTile = 8;                    // per wave and K-tile: 4 for A, 4 for B
 
-template <int MODE, bool SUMS, bool SCALE>
+// EDGE: M or N is no multiple of 128 (rows of the operands past the end are cut off by the descriptors,
+// accesses to C and the sums are checked)
+template <int MODE, bool SUMS, bool SCALE, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N, int64_t K,
                                                             const int8_t* __restrict__ Qa, int64_t lda,
                                                             const int8_t* __restrict__ Qb, int64_t ldb,
@@ -48,7 +50,8 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
-  const int64_t nk = K / BK;
+  const int nk = (int)((K + BK - 1) / BK);
+  const int tail = (K & 64) ? 0 : -1;               // the second half of the last K-tile may not exist
   const int nprod = (MODE == kGemmAccum && sec.Qa) ? 2 : 1;
   int p_lo, p_hi;                                   // the products this launch runs (device-side decision)
   pair_range(ep, nprod, p_lo, p_hi);
@@ -61,29 +64,26 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
   // Lane l of load j covers row 32w + 8j + l/8 and LDS piece l%8, which holds the logical piece
   // (l%8) ^ ((row >> 1) & 7); (row >> 1) & 7 = ((l >> 4) + 4j) & 7 depends on j only through
   // its parity.
-  const int lrow = lane >> 3;
-  int64_t kta = 0;                                  // cursor of the K-tile being fetched
+  const uint32_t rows_a = (uint32_t)(M - m0 < BM ? M - m0 : BM), rows_b = (uint32_t)(N - n0 < BN ? N - n0 : BN);
+  int kta = 0;                                      // cursor of the K-tile being fetched
   int proda = p_lo;                                 // ... and the product it belongs to
-  const int8_t *pa, *pb;                            // row 32w of that K-tile in A and in B
-  int64_t cur_lda = lda, cur_ldb = ldb;
-  int64_t goff_a0 = 0, goff_a1 = 0, goff_b0 = 0, goff_b1 = 0;
+  uint32_t voff_a[4], voff_b[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t row = 32 * w + 8 * j + (lane >> 3), piece = 16 * ((lane & 7) ^ ((row >> 1) & 7));
+    voff_a[j] = row * (uint32_t)lda + piece;
+    voff_b[j] = row * (uint32_t)ldb + piece;
+  }
+  v4i ra, rb;                                       // descriptors of the tile's rows of A and of B
   auto point = [&]() {
-    const int8_t* A0 = proda ? sec.Qa : Qa;
-    const int8_t* B0 = proda ? sec.Qb : Qb;
-    cur_lda = proda ? sec.lda : lda;
-    cur_ldb = proda ? sec.ldb : ldb;
-    goff_a0 = (int64_t)lrow * cur_lda + 16 * ((lane & 7) ^ ((lane >> 4) & 7));
-    goff_a1 = (int64_t)lrow * cur_lda + 16 * ((lane & 7) ^ (((lane >> 4) + 4) & 7));
-    goff_b0 = (int64_t)lrow * cur_ldb + 16 * ((lane & 7) ^ ((lane >> 4) & 7));
-    goff_b1 = (int64_t)lrow * cur_ldb + 16 * ((lane & 7) ^ (((lane >> 4) + 4) & 7));
-    pa = A0 + (m0 + 32 * w) * cur_lda + kta * BK;
-    pb = B0 + (n0 + 32 * w) * cur_ldb + kta * BK;
+    const uint64_t pa = (uint64_t)(uintptr_t)((proda ? sec.Qa : Qa) + m0 * lda);
+    const uint64_t pb = (uint64_t)(uintptr_t)((proda ? sec.Qb : Qb) + n0 * ldb);
+    ra = v4i{(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)((rows_a - 1) * (uint32_t)lda + (uint32_t)K), 0x00020000};
+    rb = v4i{(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)((rows_b - 1) * (uint32_t)ldb + (uint32_t)K), 0x00020000};
   };
   auto advance = [&]() {
     if (kta + 1 < nk) {
       ++kta;
-      pa += BK;
-      pb += BK;
     } else if (proda < p_hi) {
       ++proda;
       kta = 0;
@@ -92,12 +92,15 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
   };
   // load i (0..7) of the K-tile at the cursor into LDS buffer `stage`: even i -> A, odd i -> B
   auto issue_load = [&](int stage, int i) {
-    const uint32_t la = __builtin_amdgcn_readfirstlane(lds0 + stage * kStage + (32 * w) * BK);
+    const uint32_t la = lds0 + stage * kStage + (32 * w) * BK;
     const int j = i >> 1;
+    const uint32_t soff = (uint32_t)kta * BK;
     if (i & 1)
-      load_to_lds(pb + (int64_t)(8 * j) * cur_ldb + ((j & 1) ? goff_b1 : goff_b0), la + kOperand + j * 8 * BK);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   : : "s"(la + kOperand + j * 8 * BK), "v"(voff_b[j]), "s"(rb), "s"(soff) : "memory", "m0");
     else
-      load_to_lds(pa + (int64_t)(8 * j) * cur_lda + ((j & 1) ? goff_a1 : goff_a0), la + j * 8 * BK);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   : : "s"(la + j * 8 * BK), "v"(voff_a[j]), "s"(ra), "s"(soff) : "memory", "m0");
   };
   auto issue_loads = [&](int stage) {
 #pragma unroll
@@ -130,7 +133,12 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
   };
 
   // scales of the tile: threads 0..127 hold the row scales, 128..255 the column scales
-  float sreg = tid < BM ? (p_lo ? sec.s_row : ep.s_row)[m0 + tid] : (p_lo ? sec.s_col : ep.s_col)[n0 + tid - BM];
+  auto scale_of = [&](const float* s_row, const float* s_col) {
+    const uint32_t t = tid < BM ? tid : tid - BM;
+    if (EDGE && t >= (tid < BM ? rows_a : rows_b)) return 0.f;
+    return tid < BM ? s_row[m0 + t] : s_col[n0 + t];
+  };
+  float sreg = scale_of(p_lo ? sec.s_row : ep.s_row, p_lo ? sec.s_col : ep.s_col);
 
   point();
   issue_loads(0);
@@ -153,7 +161,7 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
 
   int g = 0;                                        // position in the stream of K-tiles (stage = g mod 4)
   for (int prod = p_lo; prod <= p_hi; ++prod) {
-    for (int64_t kt = 0; kt < nk; ++kt, ++g) {
+    for (int kt = 0; kt < nk; ++kt, ++g) {
       const int cur = g & (NST - 1);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
@@ -164,6 +172,10 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
           __syncthreads();
           fread((cur + 1) & (NST - 1), 0, (s + 1) & 1);
           __builtin_amdgcn_sched_barrier(0);
+        }
+        if (s >= KS / 2 && kt == nk - 1) {
+#pragma unroll
+          for (int a = 0; a < TM; ++a) fa[s & 1][a] &= tail;
         }
         // The stage of K-tile g-1 was handed over by the barrier of that K-tile and takes K-tile
         // g+3: two of its eight loads go out in each step (the CU's vector-memory path takes a
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
       advance();
     }
 
-    // ================= epilogue; no bounds checks: tiles are full
+    // ================= epilogue
     __syncthreads();                                // (the exchange areas of a previous product are free)
     sc_row[tid] = sreg;                             // sc_col follows sc_row
     __syncthreads();
@@ -199,6 +211,8 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
     const float alpha = SCALE ? ep.alpha : 1.f, beta = SCALE ? ep.beta : 0.f;
     const bool has_beta = SCALE && do_scale && beta != 0.f;
     const int64_t ldcin = SCALE ? ep.ldcin : 0;
+    // (row of the tile, column block of the lane) exists
+    auto in = [&](int row, int b) { return !EDGE || ((uint32_t)row < rows_a && (uint32_t)(cbase + b * 32) < rows_b); };
     // C goes around the caches, except between the two products of a pair
     auto bands = [&](auto cached_load_tag, auto cached_store_tag) {
       constexpr bool CLOAD = decltype(cached_load_tag)::value, CSTORE = decltype(cached_store_tag)::value;
@@ -214,7 +228,8 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
           for (int v = 0; v < 16; ++v)
 #pragma unroll
             for (int b = 0; b < TN; ++b)
-              cin[b][v] = __builtin_nontemporal_load(&cinband[(int64_t)(8 * (v >> 2) + (v & 3)) * ldcin + b * 32]);
+              cin[b][v] = in(rbase + 8 * (v >> 2) + (v & 3), b)
+                              ? __builtin_nontemporal_load(&cinband[(int64_t)(8 * (v >> 2) + (v & 3)) * ldcin + b * 32]) : 0.f;
         }
         if (MODE == kGemmAccum) {
 #pragma unroll
@@ -222,7 +237,7 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
               const float* src = &cband[(int64_t)(8 * (v >> 2) + (v & 3)) * ep.ldc + b * 32];
-              x[b][v] = CLOAD ? *src : __builtin_nontemporal_load(src);
+              x[b][v] = !in(rbase + 8 * (v >> 2) + (v & 3), b) ? 0.f : CLOAD ? *src : __builtin_nontemporal_load(src);
             }
         }
 #pragma unroll
@@ -237,7 +252,8 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
               out = alpha * out;
               if (has_beta) out = out + beta * cin[b][v];
             }
-            if (CSTORE) cband[(int64_t)ro * ep.ldc + b * 32] = out;
+            if (!in(rbase + ro, b)) {}
+            else if (CSTORE) cband[(int64_t)ro * ep.ldc + b * 32] = out;
             else __builtin_nontemporal_store(out, &cband[(int64_t)ro * ep.ldc + b * 32]);
             if (SUMS) x[b][v] = fabsf(d);
             acc[a][b][v] = 0;
@@ -286,45 +302,34 @@ __global__ __launch_bounds__(256) void gemm_i8_small_kernel(int64_t M, int64_t N
         if (half == 0) xcol[wm * BN + cbase + b * 32] = c;
       }
       __syncthreads();
-      if (tid < BM)
+      if (EDGE && (uint32_t)(tid < BM ? tid : tid - BM) >= (tid < BM ? rows_a : rows_b)) {}
+      else if (tid < BM)
         ep.row_part[tile_n * (ep.part_ld_m ? ep.part_ld_m : M) + m0 + tid] = (double)xrow[tid] + (double)xrow[BM + tid];
       else
         ep.col_part[tile_m * (ep.part_ld_n ? ep.part_ld_n : N) + n0 + tid - BM] = xcol[tid - BM] + xcol[BN + tid - BM];
     }
-    if (prod < p_hi) sreg = tid < BM ? sec.s_row[m0 + tid] : sec.s_col[n0 + tid - BM];
+    if (prod < p_hi) sreg = scale_of(sec.s_row, sec.s_col);
   }
   wait_loads();                                     // nothing may still be writing LDS when the wave ends
 }
 
 }  // namespace
 
-bool gemm_small_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
-                   const GemmEpilogue& ep) {
-  if (ep.D_int || ep.D_F_copy) return false;                 // parity-check outputs use the plain kernel
-  if (M <= 0 || N <= 0 || K <= 0 || (M % BM) || (N % BN) || (K % BK)) return false;
-  if (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) || (lda % 16) || (ldb % 16))
-    return false;
-  // the partial sums of |D_F| are laid out per 128 columns / rows: only where the plain kernel
-  // would use tiles of that size as well (the buffers are sized for it)
-  return gemm_tiles_m(M, N) == M / BM && gemm_tiles_n(M, N) == N / BN;
-}
-
 hipError_t launch_gemm_i8_small(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                                 int64_t ldb, const GemmEpilogue& ep, hipStream_t st, const GemmSecond* second) {
-  const int64_t tm = M / BM, tn = N / BN;
+  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
   const bool sums = ep.mode == kGemmFirst && ep.row_part != nullptr;
   const bool scale = ep.final_scale != 0;
   void (*kern)(int64_t, int64_t, int64_t, const int8_t*, int64_t, const int8_t*, int64_t, int64_t, int64_t,
                GemmEpilogue, GemmSecond);
   GemmSecond sec = {nullptr, nullptr, 0, 0, nullptr, nullptr};
   if (second && ep.mode == kGemmAccum) sec = *second;
-  if (ep.mode == kGemmFirst) {
-    kern = sums ? (scale ? gemm_i8_small_kernel<kGemmFirst, true, true> : gemm_i8_small_kernel<kGemmFirst, true, false>)
-                : (scale ? gemm_i8_small_kernel<kGemmFirst, false, true>
-                         : gemm_i8_small_kernel<kGemmFirst, false, false>);
-  } else {
-    kern = scale ? gemm_i8_small_kernel<kGemmAccum, false, true> : gemm_i8_small_kernel<kGemmAccum, false, false>;
-  }
+  const bool edge = (M % BM) || (N % BN);
+#define SRQ_KERN(MODE, SUMS)                                                                                    \
+  (scale ? (edge ? gemm_i8_small_kernel<MODE, SUMS, true, true> : gemm_i8_small_kernel<MODE, SUMS, true, false>) \
+         : (edge ? gemm_i8_small_kernel<MODE, SUMS, false, true> : gemm_i8_small_kernel<MODE, SUMS, false, false>))
+  kern = ep.mode != kGemmFirst ? SRQ_KERN(kGemmAccum, false) : sums ? SRQ_KERN(kGemmFirst, true) : SRQ_KERN(kGemmFirst, false);
+#undef SRQ_KERN
   hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(256), kLdsBytes, st, M, N, K, Qa, lda, Qb, ldb, tm, tn,

@@ -1,0 +1,245 @@
+// INT8 GEMM for problems whose time is latency or the traffic of C rather than matrix-core work: few
+// output tiles, or a short inner dimension (operands K-contiguous, 16-byte aligned, K a multiple of 64,
+// any M and N).
+//
+// One 64 x 64 output tile per workgroup of four waves (32 x 32 each, v_mfma_i32_16x16x64_i8), K staged
+// 128 bytes at a time from global memory straight into LDS as in the persistent kernel (unpadded rows,
+// XOR swizzle of the 16-byte pieces), through a ring of NST stages of 16 KiB with NST - 1 K-tiles in
+// flight and one barrier per K-tile.  What a stage costs is the CU's vector-memory path, 256 clocks
+// for 16 KiB against 128 of matrix-core time; that is why larger tiles take over where there are
+// enough of them to fill the chip and K is long.
+//
+//  * few tiles (at most one per compute unit): eight stages, so that the round trips of a long K
+//    overlap seven deep;
+//  * more: four or three stages, two or three workgroups per compute unit, whose loads, products and
+//    accesses to C overlap each other's.
+//
+// Up to three products of the same shape go through one launch (DirectProducts) as one stream of
+// K-tiles, each with accumulators of its own: D_F and both corrections are then added up in registers
+// in the order of Algorithm 1 and C is written once instead of written, read and written again.  With a
+// short K the third product costs less than 8 bytes of traffic per element of C.
+//
+// (Fragments read straight from global memory, without LDS, were slower: the 64 lanes of such a load
+// touch sixteen rows and the vector-memory path takes 64 clocks for it instead of 16.  8192 x 8192 x
+// 256: 262 us.)
+#include "srq_internal.h"
+#include "gemm_tiles.h"
+#include "gemm_lanes.h"
+
+namespace srq {
+namespace {
+
+constexpr int BT = 64, BK = 128;
+constexpr int kOperand = BT * BK;                    // 8 KiB
+constexpr int kStage = 2 * kOperand;                 // A tile then B tile
+constexpr int kLoads = 4;                            // per wave and K-tile: 2 for A, 2 for B
+
+template <int NP, int NST, bool SUMS>
+__global__ __launch_bounds__(256, NST >= 8 ? 1 : 12 / NST) void gemm_i8_tile64_kernel(int64_t M, int64_t N, int K, int64_t lda,
+                                                                                    int64_t ldb, int tiles_m, int tiles_n,
+                                                                                    DirectProducts pr, GemmEpilogue ep) {
+  static_assert(!SUMS || NP == 1, "");
+  extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
+  __shared__ double rowx[SUMS ? 2 * BT : 1], colx[SUMS ? 2 * BT : 1];
+  if (guard_tripped(ep)) return;                     // the whole grid leaves together
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) int8_t*)lds);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
+  const int quad = lane >> 4, rl = lane & 15;
+  int tile_m, tile_n;
+  tile_of((int)blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+  const int64_t m0 = (int64_t)tile_m * BT, n0 = (int64_t)tile_n * BT;
+  const uint32_t rows_a = (uint32_t)(M - m0 < BT ? M - m0 : BT), rows_b = (uint32_t)(N - n0 < BT ? N - n0 : BT);
+  const bool full = rows_a == BT && rows_b == BT;
+
+  // ---- loader: wave w fetches rows 16w .. 16w+15 of each operand tile, eight rows per load.  Lane l of
+  // load j covers row 16w + 8j + l/8 and LDS piece l%8, which holds the logical piece (l%8) ^
+  // ((row >> 1) & 7).  The descriptor ends with the operand's last row: rows past it read as zero.
+  const int nk = (K + BK - 1) / BK;
+  uint32_t voff_a[2], voff_b[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t row = 16 * w + 8 * j + (lane >> 3), piece = 16 * ((lane & 7) ^ ((row >> 1) & 7));
+    voff_a[j] = row * (uint32_t)lda + piece;
+    voff_b[j] = row * (uint32_t)ldb + piece;
+  }
+  int cur_kt = 0, cur_p = 0, cur_g = 0;              // cursor of the fetches
+  v4i ra, rb;
+  auto point = [&](int p) __attribute__((always_inline)) {
+    const uint64_t pa = (uint64_t)(uintptr_t)(pr.p[p].Qa + m0 * lda), pb = (uint64_t)(uintptr_t)(pr.p[p].Qb + n0 * ldb);
+    ra = v4i{(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)((rows_a - 1) * (uint32_t)lda + (uint32_t)K), 0x00020000};
+    rb = v4i{(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)((rows_b - 1) * (uint32_t)ldb + (uint32_t)K), 0x00020000};
+  };
+  auto issue = [&](uint32_t dst, v4i rsrc, uint32_t voff, uint32_t soff) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+  };
+  auto fetch = [&](int stage) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + stage * kStage + 16 * w * BK, soff = (uint32_t)cur_kt * BK;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      issue(dst + 8 * j * BK, ra, voff_a[j], soff);
+      issue(dst + kOperand + 8 * j * BK, rb, voff_b[j], soff);
+    }
+    ++cur_g;
+    if (++cur_kt == nk) {
+      cur_kt = 0;
+      if (NP > 1 && cur_p + 1 < NP) ++cur_p;
+      if (NP > 1) point(cur_p);
+    }
+  };
+  // ---- C, fetched ahead of the products (and older than their loads, see the counted wait).  It is
+  // accessed after an exchange of the two blocks of a row block between the half rows of lanes.
+  const TileAccess<4> tile = {32 * wm + (rl & 7), 32 * wn + 16 * (rl >> 3) + 4 * quad, rows_a, rows_b, full};
+  v4f out[4], cin[4];
+  const bool read_c = ep.mode == kGemmAccum, has_beta = ep.C && ep.final_scale && ep.beta != 0.f;
+  if (read_c) tile.load(out, ep.C + m0 * ep.ldc + n0, (uint32_t)ep.ldc);
+  if (has_beta) tile.load(cin, ep.Cin + m0 * ep.ldcin + n0, (uint32_t)ep.ldcin);
+  point(0);
+  const int total = NP * nk;
+#pragma unroll
+  for (int g = 0; g < NST - 1; ++g)
+    if (g < total) fetch(g);
+
+  // ---- fragments: lane (rl, quad) reads logical piece 4 step + quad of its rows
+  const int key = (rl >> 1) & 7;
+  const int a_row = (32 * wm + rl) * BK, b_row = kOperand + (32 * wn + rl) * BK;
+  const int xoff[2] = {16 * (quad ^ key), 16 * ((4 + quad) ^ key)};
+  v4i acc[NP][2][2];
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[p][a][b] = v4i{0, 0, 0, 0};
+  const int tail = (K & 64) ? 0 : -1;                // the second half of the last K-tile may not exist
+  int stage = 0;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    for (int kt = 0; kt < nk; ++kt) {
+      // this K-tile has landed: everything but the NST - 2 K-tiles after it (near the end: everything)
+      if (p * nk + kt + NST - 2 < total) wait_loads_but<(NST - 2) * kLoads>();
+      else wait_loads();
+      __syncthreads();                               // ... for every wave; and the stage before it is free
+      const int8_t* base = lds + stage * kStage;
+      v4i fa[2][2], fb[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          fb[s][i] = *reinterpret_cast<const v4i*>(base + b_row + xoff[s] + i * 16 * BK);
+          fa[s][i] = *reinterpret_cast<const v4i*>(base + a_row + xoff[s] + i * 16 * BK);
+        }
+      if (cur_g < total) fetch(stage == 0 ? NST - 1 : stage - 1);
+      if (kt == nk - 1) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) fa[1][a] &= tail;
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc[p][a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[s][b], fa[s][a], acc[p][a][b], 0, 0, 0);
+      stage = stage == NST - 1 ? 0 : stage + 1;
+    }
+  }
+
+  // ================= epilogue
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const __amdgpu_buffer_rsrc_t rsr = buf_rsrc(pr.p[p].s_row + m0, 4 * rows_a), rsc = buf_rsrc(pr.p[p].s_col + n0, 4 * rows_b);
+    float srow[2];
+    v4f scol[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      srow[i] = buf_load_f32(rsr, 4u * (uint32_t)(32 * wm + 16 * i + rl));
+      scol[i] = buf_load_4(rsc, 4u * (uint32_t)(32 * wn + 16 * i + 4 * quad), full);
+    }
+    double col8[8];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      v4f t[2];
+      double r = 0.0;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          t[b][v] = (float)acc[p][a][b][v] * (srow[a] * scol[b][v]);
+          if (SUMS) {
+            const double d = (double)fabsf(t[b][v]);
+            r += d;
+            col8[4 * b + v] = a == 0 ? d : col8[4 * b + v] + d;
+          }
+        }
+      if (SUMS) {
+        r += __shfl_xor(r, 16, 64);
+        r += __shfl_xor(r, 32, 64);
+        if (quad == 0) rowx[wn * BT + 32 * wm + 16 * a + rl] = r;
+      }
+      exchange_half_rows(t[0], t[1]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[2 * a + h][v] = (p || read_c) ? out[2 * a + h][v] + t[h][v] : t[h][v];
+    }
+    if (SUMS) {
+      // sums of |D_F| over the tile's 64 columns and rows, in double: the thresholds they become are
+      // then the same whatever kernel formed the product.  Columns: the 16 lanes' 8 values each end
+      // up one per pair of lanes (value rl >> 1).
+      const double c = column_sum8(col8, rl);
+      if (!(rl & 1)) colx[wm * BT + 32 * wn + 16 * (rl >> 3) + 4 * quad + ((rl >> 1) & 3)] = c;
+      __syncthreads();
+      if ((uint32_t)tid < rows_a)
+        ep.row_part[(int64_t)tile_n * (ep.part_ld_m ? ep.part_ld_m : M) + m0 + tid] = rowx[tid] + rowx[BT + tid];
+      if (tid >= 64 && (uint32_t)(tid - 64) < rows_b)
+        ep.col_part[(int64_t)tile_m * (ep.part_ld_n ? ep.part_ld_n : N) + n0 + tid - 64] = colx[tid - 64] + colx[tid];
+    }
+  }
+  if (ep.C) {                                        // (else the sums alone are wanted)
+    if (ep.final_scale) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          out[i][v] = ep.alpha * out[i][v];
+          if (has_beta) out[i][v] = out[i][v] + ep.beta * cin[i][v];
+        }
+    }
+    tile.store(out, ep.C + m0 * ep.ldc + n0, (uint32_t)ep.ldc);
+  }
+}
+
+template <int NP, bool SUMS>
+hipError_t launch(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
+                  const GemmEpilogue& ep, hipStream_t st) {
+  const int64_t tm = (M + BT - 1) / BT, tn = (N + BT - 1) / BT;
+  const int64_t ktiles = NP * ((K + BK - 1) / BK);
+  // stages: as many as the stream has K-tiles, at most 8 where a compute unit has one tile, 4 where it has
+  // two, else 3
+  const int cap = tm * tn <= 256 ? 8 : tm * tn <= 512 ? 4 : 3;
+  void (*kern)(int64_t, int64_t, int, int64_t, int64_t, int, int, DirectProducts, GemmEpilogue);
+  int nst;
+  if (cap == 8 && ktiles > 4) { kern = gemm_i8_tile64_kernel<NP, 8, SUMS>; nst = 8; }
+  else if (cap >= 4 && ktiles > 3) { kern = gemm_i8_tile64_kernel<NP, 4, SUMS>; nst = 4; }
+  else { kern = gemm_i8_tile64_kernel<NP, 3, SUMS>; nst = 3; }
+  const int bytes = nst * kStage;
+  if (bytes > 48 * 1024) {
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), bytes);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(256), bytes, st, M, N, (int)K, lda, ldb, (int)tm, (int)tn, pr, ep);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm_i8_tile64(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
+                                 const GemmEpilogue& ep, hipStream_t st) {
+  if (ep.row_part) return launch<1, true>(M, N, K, lda, ldb, pr, ep, st);
+  if (pr.n == 3) return launch<3, false>(M, N, K, lda, ldb, pr, ep, st);
+  if (pr.n == 2) return launch<2, false>(M, N, K, lda, ldb, pr, ep, st);
+  return launch<1, false>(M, N, K, lda, ldb, pr, ep, st);
+}
+
+}  // namespace srq

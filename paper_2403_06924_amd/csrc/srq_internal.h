@@ -81,6 +81,9 @@ struct GemmEpilogue {
   // paired launches only: the two products are decided one by one (product t runs iff the path of
   // term t+1 is acceptable) instead of both or none; alpha / beta go with the second product only
   int each_product;
+  // the kernel that leaves partial sums per 64 columns / rows is not to be used (the buffers are sized
+  // for one per 128)
+  int no_tile64;
 };
 
 // true when the epilogue's overflow guard is set and tripped (wave-uniform: scalar loads)
@@ -241,8 +244,8 @@ hipError_t launch_reduce_means_pair(const double* part0, int64_t nparts0, int64_
                                     hipStream_t st);
 
 // INT8 GEMM, both operands K-contiguous
-int gemm_tile_m();                          // smallest tile extents (upper bound on tile counts)
-int gemm_tile_n();
+constexpr int kGemmPart = 64;                 // fewest rows / columns of C per partial sum of |D_F| (sizes the buffers)
+constexpr int kGemmPartLarge = 128;        // ... of the kernels with larger tiles
 // number of partial sums launch_gemm_i8 leaves per row (parts_n) and per column (parts_m) of D_F
 // for this problem: what the reduction after it has to add up
 void gemm_sum_parts(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
@@ -268,6 +271,24 @@ bool gemm_small_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t ld
 hipError_t launch_gemm_i8_small(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                                 int64_t ldb, const GemmEpilogue& ep, hipStream_t st,
                                 const GemmSecond* second = nullptr);
+// the kernel for few output tiles or a short K (gemm_tile64.hip), partial sums per 64 columns / rows.  Up
+// to three products of one shape and one pair of leading dimensions, added up in this order; in first
+// mode C is not read, and not written either if it is null (only the sums are wanted then).
+struct DirectProduct {
+  const int8_t *Qa, *Qb;
+  const float *s_row, *s_col;
+};
+struct DirectProducts {
+  DirectProduct p[3];
+  int n;
+};
+bool gemm_tile64_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
+                    const GemmEpilogue& ep);
+hipError_t launch_gemm_i8_tile64(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
+                                 const GemmEpilogue& ep, hipStream_t st);
+// at most 32 rows and no sums (gemm_skinny.hip)
+hipError_t launch_gemm_i8_skinny(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
+                                 int64_t ldb, const GemmEpilogue& ep, hipStream_t st);
 // Both correction products in one accumulate-mode launch (first Qa.Qb^T with ep's scales, then sec):
 // possible when both products fit the same one of the two kernels above.
 bool gemm_pair_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
