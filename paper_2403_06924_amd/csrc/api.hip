@@ -739,9 +739,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     probe.ldc = ldc;
     const bool tiled = gemm_small_ok(M, N, Kc, p.A_int, Kc, p.B_int, Kc, probe);
     // (debug outputs are there to compare the executions: decided for them outside whole small tiles)
-    if (dbg ? tiled && M % 128 == 0 && N % 128 == 0
-            : tiled || gemm_tile64_ok(M, N, Kc, p.A_int, Kc, p.B_int, Kc, probe))
-      strategy = SRQ_STRATEGY_CSR_MFMA;
+    if (tiled && (!dbg || (M % 128 == 0 && N % 128 == 0))) strategy = SRQ_STRATEGY_CSR_MFMA;
   }
 
   srq_intermediates_t& im = h->last;
@@ -1128,7 +1126,15 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       e1.final_scale = scale_needed && !term_b;
       e1.paths = e2.paths = p.paths;
       const GemmSecond sec = {p.RA_int, p.Bd, Kc, Kc, p.s_ra, p.s_b};
-      const bool pair_ok = term_a && term_b && !dbg && gemm_pair_ok(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, sec, e1);
+      GemmEpilogue e12 = e1;
+      e12.final_scale = scale_needed;
+      e12.ok_a = kM; e12.ok_b = kM;
+      const bool may_pair = term_a && term_b && !dbg && gemm_pair_ok(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, sec, e12);
+      e12.each_product = 1;
+      const bool pair_ok = may_pair && gemm_pair_ok(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, sec, e12);
+      // (a kernel that pairs both products or none: the pair, and a launch for each of the other outcomes)
+      const bool pair_both = may_pair && !pair_ok;
+      const uint32_t kOther = pair_both ? kAny & ~kM : kAny;
       {
         StageTimer tm(h, st, SRQ_STAGE_TERM1);
         // (order of the additions to C: term 1, then term 2, whoever runs them)
@@ -1136,13 +1142,11 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
           GemmEpilogue ev = e1, em = e1;
           ev.ok_a = kV; ev.ok_b = kAny;
           SRQ_HIP(h, launch_spmm_valu(0, M, N, K, p.a_ptr, nullptr, p.a_idx, p.a_val, p.cap_a, p.RB_em, N, ev, st));
-          em.ok_a = kM; em.ok_b = kAny;
+          em.ok_a = kM; em.ok_b = kOther;
           if (!pair_ok) SRQ_HIP(h, launch_gemm_i8(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, em, st));
         }
-        if (pair_ok) {
-          GemmEpilogue e12 = e1;
-          e12.final_scale = scale_needed;
-          e12.ok_a = kM; e12.ok_b = kM; e12.each_product = 1;
+        if (pair_ok || pair_both) {
+          e12.each_product = pair_ok ? 1 : 0;
           SRQ_HIP(h, launch_gemm_i8_pair(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, sec, e12, st));
         }
       }
@@ -1151,7 +1155,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         GemmEpilogue ev = e2, em = e2;
         ev.ok_b = kV; ev.ok_a = kAny;
         SRQ_HIP(h, launch_spmm_valu(1, N, M, K, p.b_ptr, nullptr, p.b_idx, p.b_val, p.cap_b, p.RA_em, M, ev, st));
-        em.ok_b = kM; em.ok_a = kAny;
+        em.ok_b = kM; em.ok_a = kOther;
         if (!pair_ok) SRQ_HIP(h, launch_gemm_i8(M, N, Kc, p.RA_int, Kc, p.Bd, Kc, em, st));
       }
       if (stats_dev && !decide_in_scan)
