@@ -433,9 +433,9 @@ srq_status_t srq_quantize(srq_handle_t h, const float* X, int64_t rows, int64_t 
   int qmax = qmax_of_bits(bits);
   if (nvec == 0) return SRQ_STATUS_OK;
   const int trunc = round == SRQ_ROUND_TRUNC;
-  // streaming kernels for aligned operands: rows in one pass, columns in two
+  // streaming kernels: rows in one pass, columns in two
   if (rows > 0 && cols > 0 && axis == SRQ_AXIS_ROW && layout == SRQ_LAYOUT_VECTOR_MAJOR &&
-      rows_fused_ok(X, cols, ldx, Q, ldq, nullptr, 0)) {
+      rows_fused_ok(cols)) {
     SRQ_HIP(h, launch_rows_fused(X, rows, cols, ldx, qmax, trunc, Q, ldq, scale, lam, nullptr, 0, nullptr,
                                  nullptr, st));
     return SRQ_STATUS_OK;
@@ -445,12 +445,7 @@ srq_status_t srq_quantize(srq_handle_t h, const float* X, int64_t rows, int64_t 
     if (lambda) SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(lambda), nvec, 0, st));
     return SRQ_STATUS_OK;
   }
-  // (the column kernels store 16 codes of a vector, resp. 4 codes of a row, at a time: the
-  // caller's Q must be aligned for that, otherwise the generic kernels run)
-  const uintptr_t qaddr = reinterpret_cast<uintptr_t>(Q);
-  const bool q_ok = layout == SRQ_LAYOUT_VECTOR_MAJOR ? ((qaddr % 16) == 0 && (ldq % 16) == 0)
-                                                      : ((qaddr % 4) == 0 && (ldq % 4) == 0);
-  if (axis == SRQ_AXIS_COL && cols_pass_ok(X, cols, ldx) && q_ok) {
+  if (axis == SRQ_AXIS_COL) {
     const bool vm = layout == SRQ_LAYOUT_VECTOR_MAJOR;
     SRQ_HIP(h, launch_cols_amax(X, rows, cols, ldx, reinterpret_cast<uint32_t*>(scale), st));
     SRQ_HIP(h, launch_scales(reinterpret_cast<uint32_t*>(scale), lam, nvec, qmax, st));
@@ -496,7 +491,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
   if (s) return s;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   int qmax = qmax_of_bits(bits), trunc = round == SRQ_ROUND_TRUNC;
-  // ---- streaming kernels for aligned operands (the kernels of the whole-path call): codes of X go
+  // ---- streaming kernels (those of the whole-path call): codes of X go
   // to the workspace, the keep-mask is built in one more read of X and compacted from there
   if (rows > 0 && cols > 0) {
     const int64_t ldqw = (veclen + 15) / 16 * 16;
@@ -508,9 +503,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
     int8_t* q_w = f.take<int8_t>((size_t)nvec * ldqw);
     const bool fits = f.off <= h->ws_bytes;
     const bool vm = r_layout == SRQ_LAYOUT_VECTOR_MAJOR;
-    auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (fits && axis == SRQ_AXIS_ROW && (!do_res || vm) &&
-        rows_fused_ok(X, cols, ldx, q_w, ldqw, do_res ? Rq : nullptr, ldr)) {
+    if (fits && axis == SRQ_AXIS_ROW && (!do_res || vm) && rows_fused_ok(cols)) {
       SRQ_HIP(h, launch_rows_fused(X, rows, cols, ldx, qmax, trunc, q_w, ldqw, nullptr, nullptr, do_res ? Rq : nullptr,
                                    ldr, do_res ? rscale : nullptr, do_res ? rlam_w : nullptr, st, scale, lambda));
       if (do_sel) {
@@ -520,10 +513,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
       }
       return SRQ_STATUS_OK;
     }
-    const bool r_ok = !do_res || (al16(rscale) && (vm ? (al16(Rq) && (ldr % 16) == 0)
-                                                    : ((reinterpret_cast<uintptr_t>(Rq) & 3) == 0 && (ldr % 4) == 0)));
-    if (fits && axis == SRQ_AXIS_COL && cols_pass_ok(X, cols, ldx) && al16(scale) && al16(lambda) &&
-        (!do_sel || al16(thresh)) && r_ok) {
+    if (fits && axis == SRQ_AXIS_COL) {
       SRQ_HIP(h, launch_fill3_u32(ramax_w, nvec, reinterpret_cast<uint32_t*>(tot_w), nvec, nullptr, 0, st));
       SRQ_HIP(h, launch_cols_codes(X, rows, cols, ldx, qmax, trunc, scale, lambda, q_w, ldqw, nullptr, 0,
                                    do_res ? ramax_w : nullptr, st));
@@ -755,8 +745,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   // the one-pass kernels derive each vector's scale from the data they hold; a matrix-wide
   // scale needs all maxima first: one more pass, then the same kernels with the scales given
   const bool global_scale = h->scale_mode == SRQ_SCALE_GLOBAL;
-  const bool fastA = K > 0 && rows_fused_ok(A, K, lda, p.A_int, Kc, p.RA_int, Kc);
-  const bool fastB = K > 0 && cols_pass_ok(B, N, ldb);
+  const bool fastA = rows_fused_ok(K);
   bool ra_vm_done = false, ra_em_done = false, rb_vm_done = false, rb_em_done = false;
   bool rb_in_select = false, rb_want_em = false, rb_want_vm = false;   // residual codes of B left to the selection pass
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
@@ -793,7 +782,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // (SRQ_STRATEGY_AUTO goes by the caller's hint, srq_set_auto_hint; a wrong or missing hint only
     // costs the pass that writes the other layout once the decision is known)
     // (this launch also zeroes what B's passes accumulate into, see below)
-    b_cleared = fastB && rows_fused_can_clear(M, b_clear);
+    b_cleared = rows_fused_can_clear(M, b_clear);
     if (global_scale) {
       // one scale for the whole matrix: the maximum first (one more read of A), then the one-pass
       // kernel with the scales given; the residual codes keep a scale per row
@@ -819,7 +808,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (comp) SRQ_HIP(h, launch_scales(reinterpret_cast<uint32_t*>(p.s_ra), p.lam_ra, M, qmax, st));
   }
   // operand B: vectors are the columns of a row-major matrix; codes are stored transposed
-  if (fastB) {
+  if (K > 0) {
     // (cleared by A's pass where that ran, else by a launch of its own); the code and residual
     // passes derive the scales from the maxima themselves
     if (!b_cleared) SRQ_HIP(h, launch_fill3_u32(b_clear.a, b_clear.na, b_clear.b, b_clear.nb, b_clear.c, b_clear.nc, st));
@@ -850,15 +839,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       rb_em_done = want_em;
     }
   } else {
-    SRQ_HIP(h, launch_fill3_u32(reinterpret_cast<uint32_t*>(p.s_b), N,
-                                comp ? reinterpret_cast<uint32_t*>(p.s_rb) : nullptr, N, nullptr, 0, st));
-    SRQ_HIP(h, launch_amax(B, K, N, ldb, SRQ_AXIS_COL, reinterpret_cast<uint32_t*>(p.s_b), st));
-    if (global_scale) SRQ_HIP(h, launch_broadcast_max(reinterpret_cast<uint32_t*>(p.s_b), N, st));
-    SRQ_HIP(h, launch_scales(reinterpret_cast<uint32_t*>(p.s_b), p.lam_b, N, qmax, st));
-    SRQ_HIP(h, launch_quantize_tiles(B, K, N, ldb, SRQ_AXIS_COL, p.s_b, p.lam_b, qmax, trunc,
-                                     SRQ_LAYOUT_VECTOR_MAJOR, p.B_int, Kc,
-                                     comp ? reinterpret_cast<uint32_t*>(p.s_rb) : nullptr, st));
-    if (comp) SRQ_HIP(h, launch_scales(reinterpret_cast<uint32_t*>(p.s_rb), p.lam_rb, N, qmax, st));
+    SRQ_HIP(h, launch_fill3_u32(reinterpret_cast<uint32_t*>(p.s_b), N, reinterpret_cast<uint32_t*>(p.lam_b), N,
+                                nullptr, 0, st));
   }
   if (comp) {
     im.s_ra = p.s_ra; im.s_rb = p.s_rb;
@@ -880,7 +862,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     SRQ_HIP(h, launch_gemm_i8(M, N, Kc, p.A_int, Kc, p.B_int, Kc, ep, st));
   }
   int path_a = 0, path_b = 0;
-  bool decide_in_scan = false;                 // SRQ_STRATEGY_AUTO's decision and the statistics come from the scan kernel
   if (comp) {
     // line 9 and the branch of line 11 need the counts on the host in these modes
     // Only the density switch needs the counts on the host.  SRQ_STRATEGY_AUTO without it decides on
@@ -906,7 +887,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                         theta_b, p.dcol, p.t_b, st));
     im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
     // lines 8-10: Reduce.  Keep-bits and per-vector counts, then the prefix scans
-    int64_t chk = select_chunks(K);
     if (term_a) {
       // if term 2 is expected on the vector ALUs (fixed by the caller, or where SRQ_STRATEGY_AUTO
       // ended up in the previous call), A's selection pass also writes the k-major residual
@@ -924,39 +904,28 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       }
     }
     if (term_b) {
-      if (fastB) {
-        // (tot_b was cleared in the quantize stage)
-        if (rb_in_select)
-          SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,
-                                            rb_want_vm ? p.RB_int : nullptr, Kc, rb_want_em ? p.RB_em : nullptr,
-                                            N, p.t_b, p.mask_b, p.tot_b, st));
-        else
-          SRQ_HIP(h, launch_cols_mask(B, K, N, ldb, p.t_b, p.mask_b, p.tot_b, st));
-      } else {
-        SRQ_HIP(h, launch_select_count(B, K, N, ldb, SRQ_AXIS_COL, p.t_b, p.cnt_b, st));
-        SRQ_HIP(h, launch_select_scan(p.cnt_b, N, chk, p.tot_b, p.b_ptr, p.nnz + 1, st));
-      }
+      // (tot_b was cleared in the quantize stage)
+      if (rb_in_select)
+        SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,
+                                          rb_want_vm ? p.RB_int : nullptr, Kc, rb_want_em ? p.RB_em : nullptr,
+                                          N, p.t_b, p.mask_b, p.tot_b, st));
+      else
+        SRQ_HIP(h, launch_cols_mask(B, K, N, ldb, p.t_b, p.mask_b, p.tot_b, st));
     }
     // line 9 and the branch of line 11: which execution each term takes.  SRQ_STRATEGY_AUTO: decided
-    // on the device, by the scan kernel itself where it scans both operands (it then also writes
-    // the statistics), else by a kernel of its own.
+    // on the device, by the scan kernel itself, which then also writes the statistics.
     // (for K > 8192 the K x 512-byte slab of codes an XCD gathers from outgrows its L2 and the
     // vector-ALU kernel loses earlier: measured crossover 0.62 % at 16384^3)
     const int64_t min_mfma_a =
         (int64_t)ceil((K > 8192 ? kAutoMfmaDensityALongK : kAutoMfmaDensityA) * (double)M * (double)K);
     const int64_t min_mfma_b =
         (int64_t)ceil((K > 8192 ? kAutoMfmaDensityBLongK : kAutoMfmaDensityB) * (double)N * (double)K);
-    decide_in_scan = auto_dev && (!term_b || fastB);
     const ScanDecision dec = {p.paths, const_cast<int32_t*>(seen_paths(h)), min_mfma_a, min_mfma_b, stats_dev,
                               term_a ? p.cap_a : kNoCap, term_b ? p.cap_b : kNoCap};
     SRQ_HIP(h, launch_scan_pair(term_a ? p.tot_a : nullptr, M, p.a_ptr, p.nnz + 0,
-                                (term_b && fastB) ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st,
-                                decide_in_scan ? &dec : nullptr));
+                                term_b ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st, auto_dev ? &dec : nullptr));
     int64_t known_a = -1, known_b = -1;        // kept entries, once the host has read them
     if (auto_dev) {
-      if (!decide_in_scan)
-        SRQ_HIP(h, launch_decide_paths(p.nnz, term_a, term_b, min_mfma_a, min_mfma_b, p.paths,
-                                       const_cast<int32_t*>(seen_paths(h)), st));
       if (term_a) path_a = kPathOnDevice;
       if (term_b) path_b = kPathOnDevice;
     } else if (sync_mode) {
@@ -990,19 +959,17 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     }
     // the 2:4 kernel needs whole 256 x 256 tiles of C and cannot write the raw sums the debug
     // block asks for: such a term takes the plain matrix-core path
-    // (B's 2:4 form is written from the keep-mask, which its generic, unaligned selection does not produce)
     if (path_a == kPath24 && (dbg || !scatter24_ok(M, Kc, p.A_int, Kc) || !gemm_sparse24_ok(M, N, Kc, op24a, false, ep)))
       path_a = kPathMfma;
     if (path_b == kPath24 &&
-        (dbg || !fastB || !scatter24_ok(N, Kc, p.B_int, Kc) || !gemm_sparse24_ok(M, N, Kc, op24b, true, ep)))
+        (dbg || !scatter24_ok(N, Kc, p.B_int, Kc) || !gemm_sparse24_ok(M, N, Kc, op24b, true, ep)))
       path_b = kPathMfma;
     // overflow flags of the 2:4 forms start at zero (one launch clears both)
     if (path_a == kPath24 || path_b == kPath24)
       SRQ_HIP(h, launch_fill3_u32(path_a == kPath24 ? p.a24f : nullptr, sparse24_flag_words(M, Kc),
                                   path_b == kPath24 ? p.b24f : nullptr, sparse24_flag_words(N, Kc), nullptr, 0, st));
-    // the column-block split reads the keep-mask, which B's generic (unaligned) selection does not
-    // produce: such a term runs as plain CSR on the vector ALUs
-    if (path_b == kPathColblock && !fastB) path_b = kPathValu;
+    // (a B whose rows do not start on 16 bytes runs as plain CSR: callers read that execution from the statistics)
+    if (path_b == kPathColblock && (N % 4 || ldb % 4 || reinterpret_cast<uintptr_t>(B) % 16)) path_b = kPathValu;
     if (path_a == kPathColblock)
       SRQ_HIP(h, launch_colblock_pick(p.mask_a, M, K, kColblockKeepRatio, p.kcnt, p.klist_a, p.kflag_a, p.nstrip, st));
     if (path_b == kPathColblock)
@@ -1028,19 +995,13 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (term_b && path_b == 3) {
       im.b_ptr = p.b_ptr; im.capacity_b = p.cap_b;
     } else if (term_b) {
-      if (path_b == kPath24) {                          // (implies fastB)
+      if (path_b == kPath24) {
         SRQ_HIP(h, launch_scatter24(p.mask_b, N, K, Kc, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.b24v1,
                                     p.b24n1, p.b24v2, p.b24n2, p.b24f, st));
-      } else if (fastB) {
+      } else {
         SRQ_HIP(h, launch_scatter_mask(p.mask_b, N, K, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b,
                                        (path_b == kPathMfma || auto_dev) ? p.Bd : nullptr, Kc, known_b, st,
                                        auto_dev ? b_on_mfma : kAlways));
-      } else {
-        SRQ_HIP(h, launch_select_scatter(B, K, N, ldb, SRQ_AXIS_COL, p.t_b, p.lam_b, qmax, trunc, p.b_ptr,
-                                         p.cnt_b, p.b_idx, p.b_val, p.cap_b, st));
-        if (path_b == kPathMfma || auto_dev)
-          SRQ_HIP(h, launch_densify(p.b_ptr, p.b_idx, p.b_val, N, K, p.cap_b, p.Bd, Kc, st,
-                                    auto_dev ? b_on_mfma : kAlways));
       }
       im.b_ptr = p.b_ptr; im.b_idx = p.b_idx; im.b_val = p.b_val; im.capacity_b = p.cap_b;
     }
@@ -1061,11 +1022,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                      vm ? p.RA_int : nullptr, Kc, vm ? nullptr : p.RA_em, M, st, run);
       };
       auto resid_b = [&](bool vm, RunIf run) -> hipError_t {
-        if (fastB)
-          return launch_cols_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.lam_rb, vm ? p.RB_int : nullptr, Kc,
-                                   vm ? nullptr : p.RB_em, N, st, run);
-        return launch_residual_tiles(B, K, N, ldb, SRQ_AXIS_COL, p.s_b, p.lam_b, p.lam_rb, qmax, trunc,
-                                     vm ? p.RB_int : nullptr, Kc, vm ? nullptr : p.RB_em, N, st, run);
+        return launch_cols_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.lam_rb, vm ? p.RB_int : nullptr, Kc,
+                                 vm ? nullptr : p.RB_em, N, st, run);
       };
       if (term_b && !ra_vm_done) SRQ_HIP(h, resid_a(true, b_on_mfma));
       if (term_b && !ra_em_done) SRQ_HIP(h, resid_a(false, b_on_valu));
@@ -1083,15 +1041,9 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       SRQ_HIP(h, launch_residual_tiles(A, M, K, lda, SRQ_AXIS_ROW, p.s_a, p.lam_a, p.lam_ra, qmax, trunc,
                                        need_ra_vm ? p.RA_int : nullptr, Kc, need_ra_em ? p.RA_em : nullptr, M,
                                        st));
-    if (need_rb_vm || need_rb_em) {
-      if (fastB)
-        SRQ_HIP(h, launch_cols_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.lam_rb,
-                                     need_rb_vm ? p.RB_int : nullptr, Kc, need_rb_em ? p.RB_em : nullptr, N, st));
-      else
-        SRQ_HIP(h, launch_residual_tiles(B, K, N, ldb, SRQ_AXIS_COL, p.s_b, p.lam_b, p.lam_rb, qmax, trunc,
-                                         need_rb_vm ? p.RB_int : nullptr, Kc, need_rb_em ? p.RB_em : nullptr, N,
-                                         st));
-    }
+    if (need_rb_vm || need_rb_em)
+      SRQ_HIP(h, launch_cols_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.lam_rb,
+                                   need_rb_vm ? p.RB_int : nullptr, Kc, need_rb_em ? p.RB_em : nullptr, N, st));
     }
     if (ra_vm) im.RA_int = p.RA_int;
     if (ra_em) im.RA_em = p.RA_em;
@@ -1158,9 +1110,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         em.ok_b = kM; em.ok_a = kOther;
         if (!pair_ok) SRQ_HIP(h, launch_gemm_i8(M, N, Kc, p.RA_int, Kc, p.Bd, Kc, em, st));
       }
-      if (stats_dev && !decide_in_scan)
-        SRQ_HIP(h, launch_stats(term_a ? p.nnz : nullptr, term_b ? p.nnz + 1 : nullptr, 0, 0, term_a ? p.cap_a : kNoCap,
-                                term_b ? p.cap_b : kNoCap, stats_dev, st, p.paths));
       return SRQ_STATUS_OK;
     }
     // both terms on the dense matrix-core kernel: one launch, the two products of a tile back to

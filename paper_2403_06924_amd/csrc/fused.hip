@@ -39,12 +39,36 @@ __device__ __forceinline__ float block_max_256(float m, float* sm) {
   return fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
 }
 
+// Four floats or packed codes at any address their element allows: the target takes unaligned vector
+// accesses, so a row of any length and leading dimension is read with the same 16-byte loads as an
+// aligned one (where a piece straddles two lines it costs a second one, which the next lane asks for
+// anyway).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u1u __attribute__((aligned(1)));
+typedef unsigned u4u __attribute__((ext_vector_type(4), aligned(1)));
+
 // 16-byte load that does not displace cached data (used for the last read of an operand before
 // a product runs in between)
-__device__ __forceinline__ float4 load_streaming(const float4* p) {
-  typedef float f4v __attribute__((ext_vector_type(4)));
-  f4v t = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(p));
+__device__ __forceinline__ float4 load_streaming(const float* p) {
+  const f4u t = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(p));
   return make_float4(t.x, t.y, t.z, t.w);
+}
+
+// the first n (1..4) of the four values at p, zero for the others
+__device__ __forceinline__ float4 load_part(const float* p, int n) {
+  if (n >= 4) {
+    const f4u t = *reinterpret_cast<const f4u*>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+  }
+  return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
+}
+
+__device__ __forceinline__ void store_part(float* p, const float (&v)[4], int n) {
+  if (n >= 4) {
+    *reinterpret_cast<f4u*>(p) = f4u{v[0], v[1], v[2], v[3]};
+  } else {
+    for (int c = 0; c < n; ++c) p[c] = v[c];
+  }
 }
 
 __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d) {
@@ -78,14 +102,18 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     if (clr.c && g < clr.nc) clr.c[g] = 0u;
   }
   const int64_t row = blockIdx.x;
-  const float4* src = reinterpret_cast<const float4*>(X + row * ldx);
+  const float* src = X + row * ldx;
   const int64_t n4 = cols >> 2;
+  // (up to three columns past the last whole piece: one each for the first threads)
+  const int64_t ct = n4 * 4 + threadIdx.x;
+  const bool has_tail = ct < cols && threadIdx.x < 3;
+  float xt = has_tail ? src[ct] : 0.f;
   float4 x[NV4];
-  float m = 0.f;
+  float m = fabsf(xt);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
-    x[i] = c4 < n4 ? load_streaming(src + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    x[i] = c4 < n4 ? load_streaming(src + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
     m = fmaxf(m, fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w))));
   }
   float lam = 0.f, s = 0.f;
@@ -96,8 +124,13 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     const float amax = block_max_256(m, sm);
     if (amax > 0.f) { lam = qmax / amax; s = amax / qmax; }
   }
-  unsigned* qdst = reinterpret_cast<unsigned*>(Q + row * ldq);
-  float rm = 0.f;
+  u1u* qdst = reinterpret_cast<u1u*>(Q + row * ldq);
+  const int qt = quant_code(xt, lam, qmax, trunc);
+  if (has_tail) Q[row * ldq + ct] = (int8_t)qt;
+  xt = xt - (float)qt * s;
+  // (places past the end of the row hold 0, but 0 * lam is not 0 where lam overflowed: they stay out of
+  // the maximum of the residual)
+  float rm = has_tail ? fabsf(xt) : 0.f;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
@@ -108,7 +141,8 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
       // residual r = fl(x - fl(float(q) * s)); kept in place of x
       x[i].x = x[i].x - (float)q0 * s; x[i].y = x[i].y - (float)q1 * s;
       x[i].z = x[i].z - (float)q2 * s; x[i].w = x[i].w - (float)q3 * s;
-      rm = fmaxf(rm, fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w))));
+      const float r4 = fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
+      rm = c4 < n4 ? fmaxf(rm, r4) : rm;
     }
   }
   if (threadIdx.x == 0 && !given_scale) { scale[row] = s; lambda[row] = lam; }
@@ -121,7 +155,8 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     if (rlambda) rlambda[row] = rlam;
   }
   if (!Rq) return;                                   // residual scales only: the codes are written elsewhere
-  unsigned* rdst = reinterpret_cast<unsigned*>(Rq + row * ldr);
+  u1u* rdst = reinterpret_cast<u1u*>(Rq + row * ldr);
+  if (has_tail) Rq[row * ldr + ct] = (int8_t)quant_code(xt, rlam, qmax, trunc);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
@@ -165,19 +200,26 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
   const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG;
   const int64_t col0 = (int64_t)blockIdx.x * BC + cg * 4;
   const int64_t row0 = (int64_t)blockIdx.y * BR + rb * 16;
-  const bool colok = col0 < cols;                 // cols is a multiple of 4
+  const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;   // columns of the patch
+  const bool colok = ncol > 0;
   if (MODE != kColsResid) {
     if (threadIdx.x < BC) red[threadIdx.x] = 0;
     __syncthreads();
   }
   float4 v[16];
+  if (ncol == 4 || !colok) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    int64_t r = row0 + i;
-    const float4* src = reinterpret_cast<const float4*>(X + r * ldx + col0);
-    const bool ok = colok && r < rows;
-    if (cols_resid(MODE) || cols_mask(MODE)) v[i] = ok ? load_streaming(src) : make_float4(0.f, 0.f, 0.f, 0.f);
-    else v[i] = ok ? *src : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < 16; ++i) {
+      int64_t r = row0 + i;
+      const float* src = X + r * ldx + col0;
+      const bool ok = colok && r < rows;
+      if (cols_resid(MODE) || cols_mask(MODE)) v[i] = ok ? load_streaming(src) : make_float4(0.f, 0.f, 0.f, 0.f);
+      else v[i] = ok ? load_part(src, 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      v[i] = load_part(X + (row0 + i) * ldx + col0, row0 + i < rows ? ncol : 0);
   }
   if (MODE == kColsAmax) {
     float m[4] = {0.f, 0.f, 0.f, 0.f};
@@ -196,7 +238,7 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
     return;
   }
   if (cols_mask(MODE)) {
-    float4 t = colok ? *reinterpret_cast<const float4*>(thresh + col0) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 t = load_part(thresh + col0, ncol);
     const float tt[4] = {t.x, t.y, t.z, t.w};
     unsigned bits[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -209,7 +251,7 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
     if (colok && row0 < mask_stride * 8) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        *reinterpret_cast<uint16_t*>(mask + (col0 + c) * mask_stride + (row0 >> 3)) = (uint16_t)bits[c];
+        if (c < ncol) *reinterpret_cast<uint16_t*>(mask + (col0 + c) * mask_stride + (row0 >> 3)) = (uint16_t)bits[c];
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -226,36 +268,36 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
   const bool writer = blockIdx.y == 0 && rb == 0 && colok;
   if (MODE == kColsCodes && amax_in) {
     if (colok) {
-      const uint4 a4 = *reinterpret_cast<const uint4*>(amax_in + col0);
-      const float am[4] = {__uint_as_float(a4.x), __uint_as_float(a4.y), __uint_as_float(a4.z), __uint_as_float(a4.w)};
+      const float4 a4 = load_part(reinterpret_cast<const float*>(amax_in) + col0, ncol);
+      const float am[4] = {a4.x, a4.y, a4.z, a4.w};
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (am[c] > 0.f) { lam[c] = qmax / am[c]; sc[c] = am[c] / qmax; }
     }
     if (writer) {
-      *reinterpret_cast<float4*>(scale_out + col0) = make_float4(sc[0], sc[1], sc[2], sc[3]);
-      *reinterpret_cast<float4*>(lambda_out + col0) = make_float4(lam[0], lam[1], lam[2], lam[3]);
+      store_part(scale_out + col0, sc, ncol);
+      store_part(lambda_out + col0, lam, ncol);
     }
   } else if (colok) {
-    float4 l4 = *reinterpret_cast<const float4*>(lambda + col0);
-    float4 s4 = *reinterpret_cast<const float4*>(scale + col0);
+    const float4 l4 = load_part(lambda + col0, ncol);
+    const float4 s4 = load_part(scale + col0, ncol);
     lam[0] = l4.x; lam[1] = l4.y; lam[2] = l4.z; lam[3] = l4.w;
     sc[0] = s4.x; sc[1] = s4.y; sc[2] = s4.z; sc[3] = s4.w;
   }
   if (cols_resid(MODE) && colok) {
     if (amax_in) {
-      const uint4 a4 = *reinterpret_cast<const uint4*>(amax_in + col0);
-      const float am[4] = {__uint_as_float(a4.x), __uint_as_float(a4.y), __uint_as_float(a4.z), __uint_as_float(a4.w)};
+      const float4 a4 = load_part(reinterpret_cast<const float*>(amax_in) + col0, ncol);
+      const float am[4] = {a4.x, a4.y, a4.z, a4.w};
       float rs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (am[c] > 0.f) { rlam[c] = qmax / am[c]; rs[c] = am[c] / qmax; }
       if (writer) {
-        *reinterpret_cast<float4*>(scale_out + col0) = make_float4(rs[0], rs[1], rs[2], rs[3]);
-        *reinterpret_cast<float4*>(lambda_out + col0) = make_float4(rlam[0], rlam[1], rlam[2], rlam[3]);
+        store_part(scale_out + col0, rs, ncol);
+        store_part(lambda_out + col0, rlam, ncol);
       }
     } else {
-      float4 r4 = *reinterpret_cast<const float4*>(rlambda + col0);
+      const float4 r4 = load_part(rlambda + col0, ncol);
       rlam[0] = r4.x; rlam[1] = r4.y; rlam[2] = r4.z; rlam[3] = r4.w;
     }
   }
@@ -275,24 +317,32 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
       float res = xv[c] - (float)q * sc[c];
       if (MODE == kColsCodes) {
         code[c] = q;
-        rm[c] = fmaxf(rm[c], fabsf(res));
+        rm[c] = row0 + i < rows ? fmaxf(rm[c], fabsf(res)) : rm[c];   // (as in rows_fused_kernel)
       } else {
         code[c] = quant_code(res, rlam[c], qmax, trunc);
       }
       packed[c][i >> 2] |= (unsigned)(code[c] & 0xff) << (8 * (i & 3));
     }
-    if (Qem && colok && row0 + i < rows)
-      *reinterpret_cast<unsigned*>(Qem + (row0 + i) * ldem + col0) = pack4(code[0], code[1], code[2], code[3]);
+    if (Qem && colok && row0 + i < rows) {
+      int8_t* dst = Qem + (row0 + i) * ldem + col0;
+      if (ncol == 4) {
+        *reinterpret_cast<u1u*>(dst) = pack4(code[0], code[1], code[2], code[3]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          if (c < ncol) dst[c] = (int8_t)code[c];
+      }
+    }
   }
   if (Qvm && colok && row0 < rows) {
     const bool full = row0 + 16 <= rows;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
+      if (c >= ncol) break;
       int8_t* dst = Qvm + (col0 + c) * ldvm + row0;
       if (full) {
-        typedef unsigned u4v __attribute__((ext_vector_type(4)));
-        u4v pk = {packed[c][0], packed[c][1], packed[c][2], packed[c][3]};
-        __builtin_nontemporal_store(pk, reinterpret_cast<u4v*>(dst));
+        const u4u pk = {packed[c][0], packed[c][1], packed[c][2], packed[c][3]};
+        __builtin_nontemporal_store(pk, reinterpret_cast<u4u*>(dst));
       } else {
         for (int i = 0; i < 16; ++i)
           if (row0 + i < rows) dst[i] = (int8_t)((packed[c][i >> 2] >> (8 * (i & 3))) & 0xff);
@@ -343,7 +393,7 @@ __global__ __launch_bounds__(256) void rows_resid_em_kernel(const float* __restr
   }
   float4 v[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = load_streaming(reinterpret_cast<const float4*>(X + (row0 + i) * ldx + col0));
+  for (int i = 0; i < 16; ++i) v[i] = load_streaming(X + (row0 + i) * ldx + col0);
   if (MASK) {
 #pragma unroll
     for (int i = 0; i < 16; i += 4) {
@@ -423,7 +473,7 @@ __global__ __launch_bounds__(256) void rows_mask_kernel(const float* __restrict_
   if (threadIdx.x == 0) counts[row] = sm[0] + sm[1] + sm[2] + sm[3];
 }
 
-// Streaming version (16-byte aligned rows of at most 1024*NV4 elements): every thread has all
+// Streaming version (rows of at most 1024*NV4 elements): every thread has all
 // of its float4 loads in flight at once; two neighbouring threads make one mask byte.
 template <int NV4>
 __global__ __launch_bounds__(256) void rows_mask_vec_kernel(const float* __restrict__ X, int64_t cols, int64_t ldx,
@@ -433,13 +483,16 @@ __global__ __launch_bounds__(256) void rows_mask_vec_kernel(const float* __restr
   __shared__ int sm[4];
   const int64_t row = blockIdx.x;
   const float t = thresh[row];
-  const float4* src = reinterpret_cast<const float4*>(X + row * ldx);
+  const float* src = X + row * ldx;
   const int64_t n4 = cols >> 2;
+  // bits of the up to three columns past the last whole piece (the same in every thread)
+  const float4 xt = load_part(src + n4 * 4, (int)(cols & 3));
+  const unsigned tail_nib = (fabsf(xt.x) > t ? 1u : 0u) | (fabsf(xt.y) > t ? 2u : 0u) | (fabsf(xt.z) > t ? 4u : 0u);
   float4 x[NV4];
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
-    x[i] = c4 < n4 ? load_streaming(src + c4) : make_float4(0.f, 0.f, 0.f, 0.f);   // |0| > t is false for every t >= 0
+    x[i] = c4 < n4 ? load_streaming(src + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);   // |0| > t is false for every t >= 0
   }
   uint8_t* mrow = mask + row * mask_stride;
   int total = 0;
@@ -448,7 +501,7 @@ __global__ __launch_bounds__(256) void rows_mask_vec_kernel(const float* __restr
     int64_t c4 = threadIdx.x + i * 256;
     unsigned nib = (fabsf(x[i].x) > t ? 1u : 0u) | (fabsf(x[i].y) > t ? 2u : 0u) |
                    (fabsf(x[i].z) > t ? 4u : 0u) | (fabsf(x[i].w) > t ? 8u : 0u);
-    if (c4 >= n4) nib = 0;
+    if (c4 >= n4) nib = c4 == n4 ? tail_nib : 0u;
     total += __popc(nib);
     // eight neighbouring lanes assemble one 32-bit piece of the mask
     unsigned b8 = nib | (__shfl_down(nib, 1, 64) << 4);
@@ -748,11 +801,10 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 }  // namespace
 
-bool rows_fused_ok(const float* X, int64_t cols, int64_t ldx, const int8_t* Q, int64_t ldq, const int8_t* Rq,
-                   int64_t ldr) {
-  return cols > 0 && cols <= 16384 && (cols % 4) == 0 && (ldx % 4) == 0 && aligned16(X) && (ldq % 4) == 0 &&
-         aligned16(Q) && (!Rq || ((ldr % 4) == 0 && aligned16(Rq)));
-}
+// (any alignment and leading dimension; longer rows do not fit a workgroup.  Operands of 2999 x 3001 and 3001 x 4097:
+// rows 15 us, columns 13 + 20 us, selection 9 + 26 us, where the element-wise kernels took four launches
+// more; the compensated call 617 us with those and edge launches in its products, 357 us now)
+bool rows_fused_ok(int64_t cols) { return cols > 0 && cols <= 16384; }
 
 hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
                              int8_t* Q, int64_t ldq, float* scale, float* lambda, int8_t* Rq, int64_t ldr,
@@ -817,10 +869,6 @@ hipError_t launch_rows_mask_resid_em(const float* X, int64_t rows, int64_t cols,
   hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, mask, mask_words(cols),
                      rows, counts);
   return hipGetLastError();
-}
-
-bool cols_pass_ok(const float* X, int64_t cols, int64_t ldx) {
-  return cols > 0 && (cols % 4) == 0 && (ldx % 4) == 0 && aligned16(X);
 }
 
 static dim3 cols_grid(int mode, int64_t rows, int64_t cols) {
@@ -908,20 +956,16 @@ hipError_t launch_rows_mask(const float* X, int64_t rows, int64_t cols, int64_t 
   if (rows <= 0) return hipSuccess;
   const int64_t words = mask_words(cols);
   dim3 grid((unsigned)rows), block(256);
-  if (cols > 0 && cols <= 16384 && (cols % 4) == 0 && (ldx % 4) == 0 && aligned16(X)) {
+  if (cols > 0 && cols <= 16384) {
     uint8_t* mb = reinterpret_cast<uint8_t*>(mask);
 #define SRQ_MASK(NV4)                                                                                     \
   hipLaunchKernelGGL(rows_mask_vec_kernel<NV4>, grid, block, 0, st, X, cols, ldx, thresh, mb, words * 8, counts)
-    // the last word of a row is written in full only when cols is a multiple of 64; otherwise
-    // the generic kernel, which writes whole words, is used
-    if ((cols % 64) == 0) {
-      if (cols <= 1024) SRQ_MASK(1);
-      else if (cols <= 2048) SRQ_MASK(2);
-      else if (cols <= 4096) SRQ_MASK(4);
-      else if (cols <= 8192) SRQ_MASK(8);
-      else SRQ_MASK(16);
-      return hipGetLastError();
-    }
+    if (cols <= 1024) SRQ_MASK(1);
+    else if (cols <= 2048) SRQ_MASK(2);
+    else if (cols <= 4096) SRQ_MASK(4);
+    else if (cols <= 8192) SRQ_MASK(8);
+    else SRQ_MASK(16);
+    return hipGetLastError();
 #undef SRQ_MASK
   }
   hipLaunchKernelGGL(rows_mask_kernel, grid, block, 0, st, X, cols, ldx, thresh, mask, words, counts);

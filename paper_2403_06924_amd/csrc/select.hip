@@ -183,24 +183,9 @@ __global__ __launch_bounds__(256) void densify_kernel(const int32_t* __restrict_
   for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) row[idx[p]] = val[p];
 }
 
-// seen (optional): host-visible words that receive the decision of each term that exists, for
-// the host to read whenever it next cares to
-__global__ void decide_paths_kernel(const int64_t* nnz, int term_a, int term_b, int64_t min_a, int64_t min_b,
-                                    int32_t* paths, int32_t* seen) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const int pa = term_a ? (nnz[0] >= min_a ? 2 : 1) : 0;
-    const int pb = term_b ? (nnz[1] >= min_b ? 2 : 1) : 0;
-    paths[0] = pa;
-    paths[1] = pb;
-    if (seen && pa) seen[0] = pa;
-    if (seen && pb) seen[1] = pb;
-  }
-}
-
 __global__ void stats_kernel(const int64_t* nnz_a, const int64_t* nnz_b, int path_a, int path_b, int64_t cap_a,
-                             int64_t cap_b, srq_stats_t* out, const int32_t* paths_dev) {
+                             int64_t cap_b, srq_stats_t* out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (paths_dev) { path_a = paths_dev[0]; path_b = paths_dev[1]; }
     const int64_t na = nnz_a ? *nnz_a : 0, nb = nnz_b ? *nnz_b : 0;
     out->nnz_a = na;
     out->nnz_b = nb;
@@ -289,17 +274,9 @@ hipError_t launch_densify(const int32_t* ptr, const int32_t* idx, const int8_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_decide_paths(const int64_t* nnz, int term_a, int term_b, int64_t min_mfma_a, int64_t min_mfma_b,
-                               int32_t* paths, int32_t* seen, hipStream_t st) {
-  hipLaunchKernelGGL(decide_paths_kernel, dim3(1), dim3(64), 0, st, nnz, term_a, term_b, min_mfma_a, min_mfma_b,
-                     paths, seen);
-  return hipGetLastError();
-}
-
 hipError_t launch_stats(const int64_t* nnz_a, const int64_t* nnz_b, int path_a, int path_b, int64_t cap_a,
-                        int64_t cap_b, srq_stats_t* out, hipStream_t st, const int32_t* paths_dev) {
-  hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(64), 0, st, nnz_a, nnz_b, path_a, path_b, cap_a, cap_b, out,
-                     paths_dev);
+                        int64_t cap_b, srq_stats_t* out, hipStream_t st) {
+  hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(64), 0, st, nnz_a, nnz_b, path_a, path_b, cap_a, cap_b, out);
   return hipGetLastError();
 }
 

@@ -155,8 +155,7 @@ hipError_t launch_scan_totals(const int32_t* totals, int64_t nvec, int32_t* ptr,
 
 // ---- streaming fast paths (fused.hip); the *_ok predicates say whether shapes/alignment allow them
 inline int64_t mask_words(int64_t veclen) { return (veclen + 63) / 64; }
-bool rows_fused_ok(const float* X, int64_t cols, int64_t ldx, const int8_t* Q, int64_t ldq, const int8_t* Rq,
-                   int64_t ldr);
+bool rows_fused_ok(int64_t cols);
 // (rscale == null: no residual at all; Rq == null with rscale given: residual scales only;
 //  given_scale / given_lambda: use these per-row values instead of deriving them from the row's
 //  maximum, and leave scale / lambda unwritten; rlambda may be null)
@@ -185,7 +184,6 @@ hipError_t launch_rows_mask_resid_em(const float* X, int64_t rows, int64_t cols,
                                      const float* scale, const float* lambda, const float* rlambda, int8_t* Rem,
                                      int64_t ldem, const float* thresh, uint64_t* mask, int32_t* counts,
                                      hipStream_t st);
-bool cols_pass_ok(const float* X, int64_t cols, int64_t ldx);
 hipError_t launch_cols_amax(const float* X, int64_t rows, int64_t cols, int64_t ldx, uint32_t* amax_bits,
                             hipStream_t st);
 hipError_t launch_cols_codes(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
@@ -224,8 +222,9 @@ hipError_t launch_scatter_mask(const uint64_t* mask, int64_t nvec, int64_t vecle
                                int64_t ldd, int64_t nnz_hint, hipStream_t st, RunIf dense_if = kAlways);
 // two exclusive scans in one launch; a null totals pointer skips that half
 // decide != null (paths set): one block scans both vectors, then writes SRQ_STRATEGY_AUTO's choice per
-// term (as launch_decide_paths would from the totals z0 / z1: a term whose totals pointer is null
-// does not exist) and, if stats != null, the call's statistics
+// term (paths[t] = 0 if its totals pointer is null, i.e. the term does not exist, else the matrix cores (2) if the
+// total z0 / z1 reaches min_mfma, else the vector ALUs (1); seen, optional: host-visible words that
+// receive the decision of each term that exists) and, if stats != null, the call's statistics
 struct ScanDecision {
   int32_t* paths;             // device int32[2]
   int32_t* seen;              // host-visible int32[2] or null
@@ -354,13 +353,8 @@ bool gemm_sparse24_ok(int64_t M, int64_t N, int64_t K, const Sparse24Operand& op
 hipError_t launch_gemm_i8_sparse24(int64_t M, int64_t N, int64_t K, const Sparse24Operand& op, bool trans,
                                    const Sparse24Operand* second, const GemmEpilogue& ep, hipStream_t st);
 
-// (paths_dev != null: the executions are read from the device, path_a / path_b ignored)
 hipError_t launch_stats(const int64_t* nnz_a, const int64_t* nnz_b, int path_a, int path_b, int64_t cap_a,
-                        int64_t cap_b, srq_stats_t* out, hipStream_t st, const int32_t* paths_dev = nullptr);
-// SRQ_STRATEGY_AUTO's choice on the device: paths[t] = 0 if term t does not exist, else the matrix
-// cores (2) if the operand keeps at least min_mfma[t] entries, else the vector ALUs (1)
-hipError_t launch_decide_paths(const int64_t* nnz, int term_a, int term_b, int64_t min_mfma_a, int64_t min_mfma_b,
-                               int32_t* paths, int32_t* seen, hipStream_t st);
+                        int64_t cap_b, srq_stats_t* out, hipStream_t st);
 hipError_t launch_scale_only(int64_t M, int64_t N, const GemmEpilogue& ep, hipStream_t st);
 
 }  // namespace srq
