@@ -746,18 +746,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   // scale needs all maxima first: one more pass, then the same kernels with the scales given
   const bool global_scale = h->scale_mode == SRQ_SCALE_GLOBAL;
   const bool fastA = rows_fused_ok(K);
-  bool ra_vm_done = false, ra_em_done = false, rb_vm_done = false, rb_em_done = false;
-  bool rb_in_select = false, rb_want_em = false, rb_want_vm = false;   // residual codes of B left to the selection pass
-  // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
-  {
-  StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
-  if (Kc != K) {
-    // the padding columns of every matrix a product may read (nothing else ever writes them)
-    int8_t* mats[6] = {p.A_int, p.B_int, comp ? p.RA_int : nullptr, comp ? p.RB_int : nullptr,
-                       comp ? p.Ad : nullptr, comp ? p.Bd : nullptr};
-    const int64_t nrows[6] = {M, N, M, N, M, N};
-    SRQ_HIP(h, launch_zero_pad(mats, nrows, 6, K, Kc, st));
-  }
   if (strategy == SRQ_STRATEGY_AUTO && dense_fallback_density > 1.f) {
     // where the device-side decision of the previous calls went (or the caller's hint)
     if (volatile int32_t* seen = seen_paths(h)) {
@@ -766,13 +754,40 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       if (sb == kPathValu || sb == kPathMfma) h->last_path_b = sb;
     }
   }
+  // Short inner dimension and both terms expected where they read K-contiguous residual codes: both
+  // operands in one launch per pass
+  auto reads_em = [&](int hint_path) {
+    return dense_fallback_density > 1.f && path_reads_em(strategy == SRQ_STRATEGY_AUTO ? hint_path : strategy_path(strategy));
+  };
+  const bool strips = strips_ok(M, N, K) && !global_scale &&
+                      !(comp && ((term_a && reads_em(h->last_path_a)) || (term_b && reads_em(h->last_path_b))));
+  bool ra_vm_done = false, ra_em_done = false, rb_vm_done = false, rb_em_done = false;
+  bool rb_in_select = false, rb_want_em = false, rb_want_vm = false;   // residual codes of B left to the selection pass
+  // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
+  {
+  StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
+  if (strips) {
+    const StripOperand oa = {A, lda, p.A_int, p.s_a, p.lam_a, comp ? p.RA_int : nullptr, p.s_ra, p.lam_ra, p.Ad};
+    const StripOperand ob = {B, ldb, p.B_int, p.s_b, p.lam_b, comp ? p.RB_int : nullptr, p.s_rb, p.lam_rb, p.Bd};
+    SRQ_HIP(h, launch_quant_pair(oa, ob, M, N, K, Kc, qmax, trunc, st));
+    ra_vm_done = rb_vm_done = comp;
+  }
+  if (Kc != K && !strips) {
+    // the padding columns of every matrix a product may read (nothing else ever writes them)
+    int8_t* mats[6] = {p.A_int, p.B_int, comp ? p.RA_int : nullptr, comp ? p.RB_int : nullptr,
+                       comp ? p.Ad : nullptr, comp ? p.Bd : nullptr};
+    const int64_t nrows[6] = {M, N, M, N, M, N};
+    SRQ_HIP(h, launch_zero_pad(mats, nrows, 6, K, Kc, st));
+  }
   // the two vectors of column maxima and the per-column counts of the selection that B's passes
   // accumulate into start at zero
   const ClearList b_clear = {p.amax_b, N, comp ? p.ramax_b : nullptr, N,
                              (comp && term_b) ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N};
   bool b_cleared = false;
   // operand A: vectors are contiguous rows
-  if (fastA) {
+  if (strips) {
+    // (done)
+  } else if (fastA) {
     // the K-contiguous residual codes of A feed the matrix-core executions of term 2; when that
     // term is expected on the vector ALUs (same prediction as for B's layouts below) only the
     // residual scales are produced here and A's selection pass writes the k-major codes
@@ -808,7 +823,9 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (comp) SRQ_HIP(h, launch_scales(reinterpret_cast<uint32_t*>(p.s_ra), p.lam_ra, M, qmax, st));
   }
   // operand B: vectors are the columns of a row-major matrix; codes are stored transposed
-  if (K > 0) {
+  if (strips) {
+    // (done)
+  } else if (K > 0) {
     // (cleared by A's pass where that ran, else by a launch of its own); the code and residual
     // passes derive the scales from the maxima themselves
     if (!b_cleared) SRQ_HIP(h, launch_fill3_u32(b_clear.a, b_clear.na, b_clear.b, b_clear.nb, b_clear.c, b_clear.nc, st));
@@ -883,11 +900,18 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // (the persistent kernel leaves one partial per wave, two per 256-wide tile)
     int64_t parts_n, parts_m;
     gemm_sum_parts(M, N, Kc, p.A_int, Kc, p.B_int, Kc, ep, &parts_n, &parts_m);
-    SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
-                                        theta_b, p.dcol, p.t_b, st));
+    if (strips) {
+      // (means, thresholds and lines 8-10 of both operands at once)
+      const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, term_a ? p.mask_a : nullptr, p.tot_a};
+      const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, term_b ? p.mask_b : nullptr, p.tot_b};
+      SRQ_HIP(h, launch_select_pair(sa, sb, M, N, K, st));
+    } else {
+      SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
+                                          theta_b, p.dcol, p.t_b, st));
+    }
     im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
     // lines 8-10: Reduce.  Keep-bits and per-vector counts, then the prefix scans
-    if (term_a) {
+    if (term_a && !strips) {
       // if term 2 is expected on the vector ALUs (fixed by the caller, or where SRQ_STRATEGY_AUTO
       // ended up in the previous call), A's selection pass also writes the k-major residual
       // codes that execution reads: one read of A less
@@ -903,7 +927,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         SRQ_HIP(h, launch_rows_mask(A, M, K, lda, p.t_a, p.mask_a, p.tot_a, st));
       }
     }
-    if (term_b) {
+    if (term_b && !strips) {
       // (tot_b was cleared in the quantize stage)
       if (rb_in_select)
         SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,
@@ -922,8 +946,16 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         (int64_t)ceil((K > 8192 ? kAutoMfmaDensityBLongK : kAutoMfmaDensityB) * (double)N * (double)K);
     const ScanDecision dec = {p.paths, const_cast<int32_t*>(seen_paths(h)), min_mfma_a, min_mfma_b, stats_dev,
                               term_a ? p.cap_a : kNoCap, term_b ? p.cap_b : kNoCap};
-    SRQ_HIP(h, launch_scan_pair(term_a ? p.tot_a : nullptr, M, p.a_ptr, p.nnz + 0,
-                                term_b ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st, auto_dev ? &dec : nullptr));
+    // (few vectors, both executions known: the compaction adds the counts up itself)
+    const bool compact_pair = strips && strategy == SRQ_STRATEGY_CSR_MFMA && !sync_mode && !always_dense && strips_compact_ok(M, N);
+    if (compact_pair) {
+      const StripCompact ca = {term_a ? (int)M : 0, p.mask_a, p.tot_a, p.A_int, p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.Ad, p.nnz + 0};
+      const StripCompact cb = {term_b ? (int)N : 0, p.mask_b, p.tot_b, p.B_int, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.Bd, p.nnz + 1};
+      SRQ_HIP(h, launch_compact_pair(ca, cb, K, Kc, st));
+    } else {
+      SRQ_HIP(h, launch_scan_pair(term_a ? p.tot_a : nullptr, M, p.a_ptr, p.nnz + 0,
+                                  term_b ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st, auto_dev ? &dec : nullptr));
+    }
     int64_t known_a = -1, known_b = -1;        // kept entries, once the host has read them
     if (auto_dev) {
       if (term_a) path_a = kPathOnDevice;
@@ -986,9 +1018,10 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                     p.a24n1, p.a24v2, p.a24n2, p.a24f, st));
         im.a_idx = p.a_idx; im.a_val = p.a_val;
       } else if (path_a != 3) {
-        SRQ_HIP(h, launch_scatter_mask(p.mask_a, M, K, p.A_int, Kc, p.a_ptr, p.a_idx, p.a_val, p.cap_a,
-                                       (path_a == kPathMfma || auto_dev) ? p.Ad : nullptr, Kc, known_a, st,
-                                       auto_dev ? a_on_mfma : kAlways));
+        if (!compact_pair)
+          SRQ_HIP(h, launch_scatter_mask(p.mask_a, M, K, p.A_int, Kc, p.a_ptr, p.a_idx, p.a_val, p.cap_a,
+                                         (path_a == kPathMfma || auto_dev) ? p.Ad : nullptr, Kc, known_a, st,
+                                         auto_dev ? a_on_mfma : kAlways));
         im.a_idx = p.a_idx; im.a_val = p.a_val;
       }
     }
@@ -998,7 +1031,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       if (path_b == kPath24) {
         SRQ_HIP(h, launch_scatter24(p.mask_b, N, K, Kc, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.b24v1,
                                     p.b24n1, p.b24v2, p.b24n2, p.b24f, st));
-      } else {
+      } else if (!compact_pair) {
         SRQ_HIP(h, launch_scatter_mask(p.mask_b, N, K, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b,
                                        (path_b == kPathMfma || auto_dev) ? p.Bd : nullptr, Kc, known_b, st,
                                        auto_dev ? b_on_mfma : kAlways));

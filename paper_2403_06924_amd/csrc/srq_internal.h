@@ -236,6 +236,48 @@ hipError_t launch_scan_pair(const int32_t* t0, int64_t n0, int32_t* p0, int64_t*
                             int64_t n1, int32_t* p1, int64_t* z1, hipStream_t st,
                             const ScanDecision* decide = nullptr);
 
+// ---- both operands of a call with a short inner dimension at once (strips.hip).  Code matrices have rows
+// of Kc bytes (K rounded up to a multiple of 128) and come out with zeros past K.
+constexpr int64_t kStripsMaxK = 2048;        // columns of B that a workgroup can hold
+constexpr int64_t kStripsMaxScan = 4096;     // vectors whose counts every workgroup of the compaction adds up
+struct StripOperand {
+  const float* X;
+  int64_t ldx;
+  int8_t* Q;
+  float *scale, *lambda;
+  int8_t* Rq;                  // residual codes; null: no residual (and no D)
+  float *rscale, *rlambda;
+  int8_t* D;                   // zero-filled codes: only the places past K are written here
+};
+struct StripSelect {
+  const float* X;
+  int64_t ldx;
+  const double* part;          // partial sums of |D_F|: nparts for each vector
+  int64_t nparts;
+  double count;
+  float theta;
+  float *mean, *thresh;
+  uint64_t* mask;              // null: the mean and the threshold only
+  int32_t* counts;
+};
+struct StripCompact {
+  int nvec;
+  const uint64_t* mask;
+  const int32_t* counts;
+  const int8_t* Q;
+  int32_t *ptr, *idx;
+  int8_t* val;
+  int64_t capacity;
+  int8_t* dense;
+  int64_t* nnz;
+};
+bool strips_ok(int64_t M, int64_t N, int64_t K);
+bool strips_compact_ok(int64_t M, int64_t N);
+hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
+                             int trunc, hipStream_t st);
+hipError_t launch_select_pair(const StripSelect& a, const StripSelect& b, int64_t M, int64_t N, int64_t K, hipStream_t st);
+hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st);
+
 // thresholds from the partial sums of the GEMM epilogue
 hipError_t launch_reduce_means_pair(const double* part0, int64_t nparts0, int64_t n0, int64_t count0, float theta0,
                                     float* mean0, float* thresh0, const double* part1, int64_t nparts1,

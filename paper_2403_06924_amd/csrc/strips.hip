@@ -1,0 +1,420 @@
+// The passes over the operands for a short inner dimension (K <= kStripsMaxK), where one workgroup can
+// hold whole columns of B: what takes ten launches on the kernels of fused.hip and select.hip takes three
+// here.
+//
+//   quant_pair_kernel    both operands in one launch and one read of each: maxima, scales, codes, residual
+//                        scales and residual codes.  A workgroup has either one row of A in registers or a
+//                        strip of 4 * CG columns of B over all of K (256 / CG pieces of RPT rows).
+//   select_pair_kernel   means of |D_F| from the partial sums, thresholds, keep-masks and counts of both
+//                        operands, cut in the same way (no atomics, nothing to clear).
+//   compact_pair_kernel  compaction to CSR / CSC and to zero-filled codes of both operands; every workgroup
+//                        adds up the counts before its vector itself, so that no scan runs in between.
+//
+// What bounds them: at these sizes the latency of a launch and of one trip through a workgroup, not
+// bandwidth; hence few elements per thread for short K (RPT 4 or 8) and as many workgroups as there are.
+// A strip reads 64 or 32 bytes of each row of B; strips that share 128-byte lines are given to the same
+// XCD (strip_of), where the line is found in L2 the second time.
+// Kernel times in a call, us, before (as many launches as listed) and now: 256^3 quantize 3.8 + 2.8 + 6.9 -> 5.0,
+// select 2.6 + 2.9 + 8.2 -> 4.8, scan and compaction 5.2 + 3.8 + 3.9 -> 3.8; 2048^3 21.7 -> 17.0, 20.4 -> 13.0, 20.2 -> 13.1.
+// Whole calls: 256^3 48.0 -> 23.0, 960 x 896 x 64 55 -> 26, 1024^3 60 -> 36, 2048^3 109 -> 95.
+#include "stream.h"
+
+namespace srq {
+namespace {
+
+constexpr int kGroup = 4;                            // neighbouring strips handed to one XCD
+
+__device__ __forceinline__ int strip_of(int b, int strips) {
+  if (b >= strips / (8 * kGroup) * (8 * kGroup)) return b;
+  const int q = b >> 3, x = b & 7;                   // workgroup b runs on XCD b % 8
+  return ((q / kGroup) * 8 + x) * kGroup + q % kGroup;
+}
+
+__device__ __forceinline__ float4 abs4(float4 x) { return make_float4(fabsf(x.x), fabsf(x.y), fabsf(x.z), fabsf(x.w)); }
+__device__ __forceinline__ float max4(float4 x) { return fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)); }
+
+// ---- quantization ----------------------------------------------------------------------------------
+// One row.  Codes go out up to the padded length (zeros past K); places past K stay out of the maxima of
+// the residual (0 * lam is not 0 where lam overflowed).
+template <int NV4>
+__device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, int K, int Kc, float qmax, int trunc, float* sm) {
+  const float* src = s.X + row * s.ldx;
+  float4 x[NV4];
+  int n[NV4];
+  float m = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (threadIdx.x + i * 256);
+    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
+    x[i] = load_part(src + e, n[i]);
+    m = fmaxf(m, max4(abs4(x[i])));
+  }
+  const float amax = block_max_256(m, sm);
+  float lam = 0.f, sc = 0.f;
+  if (amax > 0.f) { lam = qmax / amax; sc = amax / qmax; }
+  float rm = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (threadIdx.x + i * 256);
+    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+    int q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      q[j] = j < n[i] ? quant_code(v[j], lam, qmax, trunc) : 0;
+      v[j] = v[j] - (float)q[j] * sc;
+      rm = fmaxf(rm, fabsf(v[j]));
+    }
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+    x[i] = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  if (threadIdx.x == 0) { s.scale[row] = sc; s.lambda[row] = lam; }
+  if (!s.Rq) return;
+  const float ramax = block_max_256(rm, sm);
+  float rlam = 0.f, rs = 0.f;
+  if (ramax > 0.f) { rlam = qmax / ramax; rs = ramax / qmax; }
+  if (threadIdx.x == 0) { s.rscale[row] = rs; s.rlambda[row] = rlam; }
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (threadIdx.x + i * 256);
+    const float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+    int q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = j < n[i] ? quant_code(v[j], rlam, qmax, trunc) : 0;
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Rq + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+  }
+  for (int e = K + threadIdx.x; e < Kc; e += 256) s.D[row * Kc + e] = 0;
+}
+
+// maxima of the CG * 4 columns of a strip from every thread's own four; red: [4][4 * CG]
+template <int CG>
+__device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cg = threadIdx.x & (CG - 1);
+#pragma unroll
+  for (int off = CG; off < 64; off <<= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) m[c] = fmaxf(m[c], __shfl_xor(m[c], off, 64));
+  if (lane < CG)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[w * 4 * CG + cg * 4 + c] = m[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    m[c] = fmaxf(fmaxf(red[cg * 4 + c], red[4 * CG + cg * 4 + c]), fmaxf(red[8 * CG + cg * 4 + c], red[12 * CG + cg * 4 + c]));
+}
+
+// RPT codes of each of the patch's columns: dst[col * Kc + row0 ..]
+template <int RPT>
+__device__ __forceinline__ void store_codes(int8_t* Q, int64_t col0, int ncol, int Kc, int row0, const unsigned (&pk)[4][RPT / 4]) {
+  if (row0 >= Kc) return;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if (c >= ncol) break;
+    int8_t* dst = Q + (col0 + c) * Kc + row0;        // (Kc and row0 are multiples of RPT)
+    if constexpr (RPT == 16) *reinterpret_cast<uint4*>(dst) = make_uint4(pk[c][0], pk[c][1], pk[c][2], pk[c][3]);
+    else if constexpr (RPT == 8) *reinterpret_cast<uint2*>(dst) = make_uint2(pk[c][0], pk[c][1]);
+    else *reinterpret_cast<unsigned*>(dst) = pk[c][0];
+  }
+}
+
+template <int CG, int RPT>
+__device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, float qmax, int trunc,
+                                            float* red) {
+  const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG, row0 = rb * RPT;
+  const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
+  const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
+  float4 v[RPT];
+  float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, row0 + i < K ? ncol : 0);
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const float4 a = abs4(v[i]);
+    m[0] = fmaxf(m[0], a.x); m[1] = fmaxf(m[1], a.y); m[2] = fmaxf(m[2], a.z); m[3] = fmaxf(m[3], a.w);
+  }
+  strip_max<CG>(m, red);
+  float lam[4], sc[4], rm[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    lam[c] = m[c] > 0.f ? qmax / m[c] : 0.f;
+    sc[c] = m[c] > 0.f ? m[c] / qmax : 0.f;
+  }
+  if (rb == 0) { store_part(s.scale + col0, sc, ncol); store_part(s.lambda + col0, lam, ncol); }
+  unsigned pk[4][RPT / 4];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int q = row0 + i < K ? quant_code(x[c], lam[c], qmax, trunc) : 0;
+      x[c] = x[c] - (float)q * sc[c];
+      rm[c] = fmaxf(rm[c], fabsf(x[c]));
+      if ((i & 3) == 0) pk[c][i >> 2] = 0;
+      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
+    }
+    v[i] = make_float4(x[0], x[1], x[2], x[3]);
+  }
+  store_codes<RPT>(s.Q, col0, ncol, Kc, row0, pk);
+  if (!s.Rq) return;
+  strip_max<CG>(rm, red + 16 * CG);
+  float rlam[4], rs[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    rlam[c] = rm[c] > 0.f ? qmax / rm[c] : 0.f;
+    rs[c] = rm[c] > 0.f ? rm[c] / qmax : 0.f;
+  }
+  if (rb == 0) { store_part(s.rscale + col0, rs, ncol); store_part(s.rlambda + col0, rlam, ncol); }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int q = row0 + i < K ? quant_code(x[c], rlam[c], qmax, trunc) : 0;
+      if ((i & 3) == 0) pk[c][i >> 2] = 0;
+      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
+    }
+  }
+  store_codes<RPT>(s.Rq, col0, ncol, Kc, row0, pk);
+  for (int i = threadIdx.x; i < 4 * CG * (Kc - K); i += 256) {
+    const int64_t col = (int64_t)strip * 4 * CG + i / (Kc - K);
+    if (col < cols) s.D[col * Kc + K + i % (Kc - K)] = 0;
+  }
+}
+
+template <int NV4, int CG, int RPT>
+__global__ __launch_bounds__(256) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t N, int K, int Kc, int strips,
+                                                         float qmax, int trunc) {
+  __shared__ float sm[32 * CG];
+  if ((int)blockIdx.x < strips) quant_strip<CG, RPT>(b, strip_of(blockIdx.x, strips), N, K, Kc, qmax, trunc, sm);
+  else quant_row<NV4>(a, (int64_t)blockIdx.x - strips, K, Kc, qmax, trunc, sm);
+}
+
+// ---- selection -------------------------------------------------------------------------------------
+__device__ __forceinline__ void mean_of(const StripSelect& s, int64_t v, double sum, bool writer, float& t) {
+  const float mean = (float)(sum / s.count);
+  t = s.theta * mean;
+  if (writer) { s.mean[v] = mean; s.thresh[v] = t; }
+}
+
+template <int NV4>
+__device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, double* dsm, int* ism) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int words = (K + 63) / 64;
+  const float* src = s.X + row * s.ldx;
+  float4 x[NV4];
+  int n[NV4];
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {                    // (on their way while the threshold is formed)
+    const int e = 4 * (tid + i * 256);
+    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
+    x[i] = load_part(src + e, s.mask ? n[i] : 0);
+  }
+  double sum = 0.0;
+  for (int64_t p = tid; p < s.nparts; p += 256) sum += s.part[p * rows + row];
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0) dsm[w] = sum;
+  __syncthreads();
+  float t;
+  mean_of(s, row, (dsm[0] + dsm[1]) + (dsm[2] + dsm[3]), tid == 0, t);
+  if (!s.mask) return;
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int c4 = tid + i * 256;
+    unsigned nib = (fabsf(x[i].x) > t ? 1u : 0u) | (fabsf(x[i].y) > t ? 2u : 0u) | (fabsf(x[i].z) > t ? 4u : 0u) |
+                   (fabsf(x[i].w) > t ? 8u : 0u);
+    nib &= (1u << n[i]) - 1u;
+    total += __popc(nib);
+    // eight neighbouring lanes assemble one 32-bit piece of the mask
+    const unsigned b8 = nib | (__shfl_down(nib, 1, 64) << 4);
+    const unsigned b16 = b8 | (__shfl_down(b8, 2, 64) << 8);
+    const unsigned b32 = b16 | (__shfl_down(b16, 4, 64) << 16);
+    if (!(tid & 7) && (c4 >> 3) < 2 * words) reinterpret_cast<uint32_t*>(s.mask + row * words)[c4 >> 3] = b32;
+  }
+  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+  if (lane == 0) ism[w] = total;
+  __syncthreads();
+  if (tid == 0) s.counts[row] = ism[0] + ism[1] + ism[2] + ism[3];
+}
+
+template <int CG, int RPT>
+__device__ __forceinline__ void select_strip(const StripSelect& s, int strip, int64_t cols, int K, double* dsm, int* ism) {
+  constexpr int BC = 4 * CG;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cg = tid & (CG - 1), rb = tid / CG, row0 = rb * RPT;
+  const int words = (K + 63) / 64;
+  const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
+  const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
+  float4 v[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, s.mask && row0 + i < K ? ncol : 0);
+  // partial sums: BC neighbouring columns by BC neighbouring threads
+  const int64_t pc = (int64_t)strip * BC + (tid & (BC - 1));
+  double sum = 0.0;
+  if (pc < cols)
+    for (int64_t p = tid / BC; p < s.nparts; p += 256 / BC) sum += s.part[p * cols + pc];
+#pragma unroll
+  for (int off = BC; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane < BC) dsm[w * BC + lane] = sum;
+  __syncthreads();
+  float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int j = cg * 4 + c;
+    if (c < ncol) mean_of(s, col0 + c, (dsm[j] + dsm[BC + j]) + (dsm[2 * BC + j] + dsm[3 * BC + j]), rb == 0, t[c]);
+  }
+  if (!s.mask) return;
+  unsigned bits[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const float4 a = abs4(v[i]);
+    const bool ok = row0 + i < K;
+    bits[0] |= ok && a.x > t[0] ? 1u << i : 0u;
+    bits[1] |= ok && a.y > t[1] ? 1u << i : 0u;
+    bits[2] |= ok && a.z > t[2] ? 1u << i : 0u;
+    bits[3] |= ok && a.w > t[3] ? 1u << i : 0u;
+  }
+  int cnt[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    cnt[c] = c < ncol ? __popc(bits[c]) : 0;
+    unsigned piece = bits[c];
+    if constexpr (RPT == 4) piece |= __shfl_down(piece, CG, 64) << 4;     // two threads' rows make one byte
+    if (c < ncol && row0 < words * 64) {
+      uint8_t* dst = reinterpret_cast<uint8_t*>(s.mask + (col0 + c) * words) + (row0 >> 3);
+      if constexpr (RPT == 16) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)piece;
+      else if constexpr (RPT == 8) *dst = (uint8_t)piece;
+      else if (!(rb & 1)) *dst = (uint8_t)piece;
+    }
+  }
+#pragma unroll
+  for (int off = CG; off < 64; off <<= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cnt[c] += __shfl_xor(cnt[c], off, 64);
+  if (lane < CG)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ism[w * BC + cg * 4 + c] = cnt[c];
+  __syncthreads();
+  if (tid < BC && (int64_t)strip * BC + tid < cols)
+    s.counts[(int64_t)strip * BC + tid] = ism[tid] + ism[BC + tid] + ism[2 * BC + tid] + ism[3 * BC + tid];
+}
+
+template <int NV4, int CG, int RPT>
+__global__ __launch_bounds__(256) void select_pair_kernel(StripSelect a, StripSelect b, int64_t M, int64_t N, int K, int strips) {
+  __shared__ double dsm[16 * CG];
+  __shared__ int ism[16 * CG];
+  if ((int)blockIdx.x < strips) select_strip<CG, RPT>(b, strip_of(blockIdx.x, strips), N, K, dsm, ism);
+  else select_row<NV4>(a, (int64_t)blockIdx.x - strips, M, K, dsm, ism);
+}
+
+// ---- compaction ------------------------------------------------------------------------------------
+// One workgroup per vector, four elements per thread and round: the place of a thread's first kept entry
+// is the number of entries of earlier vectors, rounds, waves and lanes (the last from three ballots of its
+// own count, 0..4).  Codes and zero-filled copy have rows of Kc bytes with zeros past K.
+template <int NV4>
+__global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int K, int Kc) {
+  __shared__ int64_t before[4];
+  __shared__ int kept[NV4][4];
+  const bool second = blockIdx.x >= (unsigned)a.nvec;
+  const StripCompact& s = second ? b : a;
+  const int v = (int)blockIdx.x - (second ? a.nvec : 0);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int words = (K + 63) / 64;
+  const uint32_t* mv = reinterpret_cast<const uint32_t*>(s.mask + (int64_t)v * words);
+  unsigned nib[NV4], code[NV4];
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (tid + i * 256);
+    nib[i] = e < K ? (mv[e >> 5] >> (e & 31)) & 0xfu : 0u;   // (bits past K are zero)
+    code[i] = e < Kc ? *reinterpret_cast<const unsigned*>(s.Q + (int64_t)v * Kc + e) : 0u;
+  }
+  int64_t sum = 0;
+  for (int i = tid; i < v; i += 256) sum += s.counts[i];
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0) before[w] = sum;
+  const uint64_t lower = (1ull << lane) - 1ull;
+  int at[NV4];
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (tid + i * 256);
+    const unsigned keep = ((nib[i] & 1u) ? 0xffu : 0u) | ((nib[i] & 2u) ? 0xff00u : 0u) | ((nib[i] & 4u) ? 0xff0000u : 0u) |
+                          ((nib[i] & 8u) ? 0xff000000u : 0u);
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
+    const int cnt = __popc(nib[i]);
+    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
+    at[i] = __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower);
+    if (lane == 0) kept[i][w] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+  }
+  __syncthreads();
+  const int64_t first = before[0] + before[1] + before[2] + before[3];
+  int64_t base = first;
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    int64_t p = base + at[i];
+    for (int j = 0; j < w; ++j) p += kept[i][j];
+    base += kept[i][0] + kept[i][1] + kept[i][2] + kept[i][3];
+    const int e = 4 * (tid + i * 256);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (nib[i] >> j & 1u) {
+        if (p < s.capacity) {
+          s.idx[p] = e + j;
+          s.val[p] = (int8_t)(code[i] >> (8 * j));
+        }
+        ++p;
+      }
+    }
+  }
+  if (tid == 0) {
+    s.ptr[v] = (int32_t)first;
+    if (v == s.nvec - 1) {
+      s.ptr[s.nvec] = (int32_t)base;
+      *s.nnz = base;
+    }
+  }
+}
+
+// strips of B and rows per thread: CG * 4 columns, 256 / CG * RPT rows
+struct StripShape { int nv4, cg, rpt; };
+StripShape strip_shape(int64_t K) {
+  if (K <= 256) return {1, 4, 4};
+  if (K <= 512) return {1, 4, 8};
+  if (K <= 1024) return {1, 2, 8};
+  return {2, 2, 16};
+}
+
+}  // namespace
+
+bool strips_ok(int64_t M, int64_t N, int64_t K) { return K > 0 && K <= kStripsMaxK && M + N < (1 << 24); }
+bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
+
+#define SRQ_STRIPS(KERN, ...)                                                                                  \
+  do {                                                                                                         \
+    const StripShape sh = strip_shape(K);                                                                      \
+    const int strips = (int)((N + 4 * sh.cg - 1) / (4 * sh.cg));                                               \
+    const dim3 grid((unsigned)(strips + M));                                                                   \
+    if (sh.nv4 == 2) hipLaunchKernelGGL((KERN<2, 2, 16>), grid, dim3(256), 0, st, __VA_ARGS__);                \
+    else if (sh.cg == 2) hipLaunchKernelGGL((KERN<1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);             \
+    else if (sh.rpt == 8) hipLaunchKernelGGL((KERN<1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);            \
+    else hipLaunchKernelGGL((KERN<1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                             \
+  } while (0)
+
+hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
+                             int trunc, hipStream_t st) {
+  SRQ_STRIPS(quant_pair_kernel, a, b, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
+  return hipGetLastError();
+}
+
+hipError_t launch_select_pair(const StripSelect& a, const StripSelect& b, int64_t M, int64_t N, int64_t K, hipStream_t st) {
+  SRQ_STRIPS(select_pair_kernel, a, b, M, N, (int)K, strips);
+  return hipGetLastError();
+}
+#undef SRQ_STRIPS
+
+hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st) {
+  const dim3 grid((unsigned)(a.nvec + b.nvec));
+  if (grid.x == 0) return hipSuccess;
+  if (Kc <= 1024) hipLaunchKernelGGL(compact_pair_kernel<1>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  else hipLaunchKernelGGL(compact_pair_kernel<2>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  return hipGetLastError();
+}
+
+}  // namespace srq

@@ -1,0 +1,116 @@
+"""The streaming kernels at widths, leading dimensions and base addresses that are multiples of nothing, and
+the kernels that hold whole columns of B for a short inner dimension: every integer stage against the
+oracle, bit for bit, at the edges of their shapes."""
+import numpy as np
+import pytest
+
+from oracle import srq_oracle as o
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+F32 = np.float32
+
+
+@pytest.fixture(scope="module")
+def srq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2403_06924_amd import binding as b
+    h = b.Srq(device=0)
+    yield h
+    h.close()
+
+
+@pytest.fixture(scope="module")
+def b():
+    from paper_2403_06924_amd import binding
+    return binding
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+@pytest.mark.parametrize("cols", [1, 3, 6, 61, 1025, 2050])
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_windows_that_start_anywhere(srq, b, cols, axis, layout):
+    """X as a window one element into rows of odd length: codes and scales against the oracle, residual codes
+    and selection against the same call on a contiguous copy."""
+    rng = np.random.default_rng(cols + axis)
+    big = (rng.standard_normal((77, cols + 4 + cols % 2)) * np.exp(rng.standard_normal((77, 1)))).astype(F32)
+    big[3] = 0
+    big[5, :] = F32(1e-38)                                   # qmax / amax overflows there (rows), or nearly so
+    W = dev(big)[:, 1:cols + 1]
+    assert W.stride(0) % 2 == 1 and W.data_ptr() % 16 == 4
+    X = big[:, 1:cols + 1]
+    name = "row" if axis == 0 else "col"
+    with np.errstate(all="ignore"):
+        q_ref, s_ref, lam_ref = o.quantize_vectors(np.delete(X, 5, axis=0), name)
+    keep = [i for i in range(77) if i != 5]
+    Q, s, lam = srq.quantize(dev(big[keep])[:, 1:cols + 1], axis, layout=layout)
+    vm = q_ref if axis == 0 else q_ref.T
+    assert (host(s) == s_ref).all() and (host(lam) == lam_ref).all()
+    assert (host(Q) == (vm if layout == 0 else vm.T)).all()
+    Q, s, lam = srq.quantize(W, axis, layout=layout)
+    Y = W.contiguous()
+    Q2, s2, lam2 = srq.quantize(Y, axis, layout=layout)
+    assert torch.equal(Q, Q2) and torch.equal(s, s2) and torch.equal(lam, lam2)
+    thresh = Y.abs().mean(dim=1 - axis).contiguous()
+    r = srq.build_sparse_residual(W, axis, s, lam, thresh, r_layout=layout)
+    r2 = srq.build_sparse_residual(Y, axis, s, lam, thresh, r_layout=layout)
+    n = int(r["nnz"].item())
+    mask = Y.abs() > (thresh.view(-1, 1) if axis == 0 else thresh.view(1, -1))
+    assert n == int(mask.sum())
+    for key in ("Rq", "rscale", "ptr", "nnz"):
+        assert torch.equal(r[key], r2[key]), key
+    assert torch.equal(r["idx"][:n], r2["idx"][:n]) and torch.equal(r["val"][:n], r2["val"][:n])
+
+
+# K at the edges of the strip shapes (256, 512, 1024, 2048) and of the padded length, M and N around strips of
+# 8 and 16 columns, the compaction's own limit on vectors (4096)
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 17, 2), (33, 9, 63), (130, 15, 255), (65, 33, 256), (64, 70, 257), (31, 129, 512),
+                                   (40, 24, 513), (129, 65, 1023), (24, 40, 1024), (33, 31, 1025), (50, 63, 2047), (16, 8, 2048),
+                                   (20, 12, 2049), (4097, 40, 100), (40, 4097, 100), (4096, 24, 130)])
+@pytest.mark.parametrize("terms", ["both", "a", "b", "dense"])
+def test_short_inner_dimension(srq, b, shape, terms):
+    M, N, K = shape
+    rng = np.random.default_rng(M + 3 * N + 5 * K)
+    A = (rng.standard_normal((M, K)) * np.exp(rng.standard_normal((M, 1)))).astype(F32)
+    B = (rng.standard_normal((K, N)) * np.exp(rng.standard_normal((1, N)))).astype(F32)
+    if M > 2:
+        A[1] = 0
+    if N > 2:
+        B[:, 2] = 0
+    theta = 1.5 / K ** 0.5
+    ta, tb = (theta if terms != "b" else np.inf), (theta if terms != "a" else np.inf)
+    Cin = rng.standard_normal((M, N)).astype(F32)
+    stats = b.stats_tensor()
+    s = 0.0 if terms == "dense" else 2.0
+    C, _, _ = srq.compensated_gemm(dev(A), dev(B), ta, tb, strategy=b.STRATEGY_CSR_MFMA, dense_fallback_density=s, stats=stats,
+                                   alpha=0.5, beta=-0.75, C_in=dev(Cin))
+    torch.cuda.synchronize()
+    im, st = srq.intermediates(M, N, K), b.read_stats(stats)
+    ref = o.compensated_gemm(A, B, ta, tb, alpha=0.5, beta=-0.75, C_in=Cin, dense_fallback_density=s,
+                             thresh_a=host(im["t_a"]) if terms != "b" else None,
+                             thresh_b=host(im["t_b"]) if terms != "a" else None)
+    assert (host(im["A_int"]) == ref.A_int).all() and (host(im["B_int"]) == ref.B_int.T).all()
+    for key in ("s_a", "s_b", "lam_a", "lam_b", "s_ra", "s_rb"):
+        assert (host(im[key]) == getattr(ref, key)).all(), key
+    np.testing.assert_allclose(host(im["drow"]), ref.drow, rtol=1e-6)
+    np.testing.assert_allclose(host(im["dcol"]), ref.dcol, rtol=1e-6)
+    if terms != "a":
+        assert (host(im["RA_int"]) == ref.RA_int).all()
+        assert st["nnz_b"] == ref.csc_b.nnz and (host(im["b_ptr"]) == ref.csc_b.ptr).all()
+    if terms != "b":
+        assert (host(im["RB_int"]) == ref.RB_int.T).all()
+        assert st["nnz_a"] == ref.csr_a.nnz and (host(im["a_ptr"]) == ref.csr_a.ptr).all()
+    if terms in ("both", "a"):
+        assert (host(im["a_idx"]) == ref.csr_a.idx).all() and (host(im["a_val"]) == ref.csr_a.val).all()
+    if terms in ("both", "b"):
+        assert (host(im["b_idx"]) == ref.csc_b.idx).all() and (host(im["b_val"]) == ref.csc_b.val).all()
+    assert o.error_rel(ref.C, host(C)) <= 1e-5              # the FP32 output's tolerance everywhere
