@@ -649,55 +649,78 @@ __global__ __launch_bounds__(256) void scatter_mask16_kernel(const uint64_t* __r
 // Exclusive scan of one count vector by a group of NT threads of a block (tid = index in the group,
 // wave_sum = NT / 64 words of LDS of the group's own); the block-wide barrier between the two
 // phases is the caller's, so that two groups can scan two vectors side by side.  totals == null:
-// nothing to do in either phase.
+// nothing to do in either phase.  (No sum passes 2^31: callers refuse operands that could keep as many.)
+//
+// Every wave owns a run of whole pieces of 256 counts, four per lane: what bounds the launch is the one
+// compute unit's vector-memory path, which takes a clock per line touched.  (Threads that own sixteen
+// consecutive counts each touch 64 lines with every load and store: 20 us for two vectors of 8192.)
 template <int NT>
 struct ScanGroup {
-  static constexpr int kHeld = 32;                    // spans of up to 32 vectors are held in registers:
-  int32_t held[kHeld];                                // their loads are independent and all in flight at once
-  int64_t x, inc, per, v0, v1;
+  static constexpr int kHeld = 8;                     // pieces a wave keeps in registers between the phases
+  typedef int32_t i4u __attribute__((ext_vector_type(4), aligned(4)));
+  i4u held[kHeld];
+  int64_t first, pieces;
+  int wave_total;
+  static __device__ __forceinline__ i4u piece(const int32_t* totals, int64_t nvec, int64_t at) {
+    if (at + 4 <= nvec) return *reinterpret_cast<const i4u*>(totals + at);
+    return i4u{at < nvec ? totals[at] : 0, at + 1 < nvec ? totals[at + 1] : 0, at + 2 < nvec ? totals[at + 2] : 0, 0};
+  }
   __device__ __forceinline__ void sums(const int32_t* totals, int64_t nvec, int tid, int64_t* wave_sum) {
     if (!totals) return;
-    // thread t owns the `per` consecutive vectors from t * per on
-    per = (nvec + NT - 1) / NT;
-    v0 = tid * per;
-    v1 = v0 + per < nvec ? v0 + per : nvec;
-    x = 0;
-    if (per <= kHeld) {
-#pragma unroll
-      for (int i = 0; i < kHeld; ++i) held[i] = v0 + i < v1 ? totals[v0 + i] : 0;
-#pragma unroll
-      for (int i = 0; i < kHeld; ++i) x += held[i];
-    } else {
-      for (int64_t v = v0; v < v1; ++v) x += totals[v];
-    }
     const int lane = tid & 63;
-    inc = x;
-    for (int d = 1; d < 64; d <<= 1) {
-      int64_t y = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += y;
+    pieces = ((nvec + 255) / 256 + NT / 64 - 1) / (NT / 64);
+    first = (tid >> 6) * pieces * 256 + 4 * lane;
+    int x = 0;
+    if (pieces <= kHeld) {
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i) held[i] = i < pieces ? piece(totals, nvec, first + i * 256) : i4u{0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i) x += held[i].x + held[i].y + held[i].z + held[i].w;
+    } else {
+      for (int64_t i = 0; i < pieces; ++i) {
+        const i4u v = piece(totals, nvec, first + i * 256);
+        x += v.x + v.y + v.z + v.w;
+      }
     }
-    if (lane == 63) wave_sum[tid >> 6] = inc;
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+    if (lane == 0) wave_sum[tid >> 6] = x;
+    wave_total = x;
   }
   __device__ __forceinline__ void offsets(const int32_t* totals, int64_t nvec, int32_t* ptr, int64_t* nnz_dev,
                                           int tid, const int64_t* wave_sum) {
     if (!totals) return;
-    int64_t run = inc - x;                            // exclusive prefix of this thread's span
-    for (int i = 0; i < (tid >> 6); ++i) run += wave_sum[i];
-    if (per <= kHeld) {
+    const int lane = tid & 63;
+    int run = 0;                                      // entries before the current piece
+    for (int i = 0; i < (tid >> 6); ++i) run += (int)wave_sum[i];
+    const int end = run + wave_total;
+    auto put = [&](int64_t at, i4u v) {
+      const int mine = v.x + v.y + v.z + v.w;
+      int inc = mine;
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+      }
+      const int p0 = run + inc - mine;
+      const i4u out = {p0, p0 + v.x, p0 + v.x + v.y, p0 + v.x + v.y + v.z};
+      if (at + 4 <= nvec) {
+        *reinterpret_cast<i4u*>(ptr + at) = out;
+      } else {
+        if (at < nvec) ptr[at] = out.x;
+        if (at + 1 < nvec) ptr[at + 1] = out.y;
+        if (at + 2 < nvec) ptr[at + 2] = out.z;
+      }
+      run += __shfl(inc, 63, 64);
+    };
+    if (pieces <= kHeld) {
 #pragma unroll
-      for (int i = 0; i < kHeld; ++i) {
-        if (v0 + i < v1) ptr[v0 + i] = (int32_t)run;
-        run += held[i];
-      }
+      for (int i = 0; i < kHeld; ++i)
+        if (i < pieces) put(first + i * 256, held[i]);
     } else {
-      for (int64_t v = v0; v < v1; ++v) {
-        ptr[v] = (int32_t)run;
-        run += totals[v];
-      }
+      for (int64_t i = 0; i < pieces; ++i) put(first + i * 256, piece(totals, nvec, first + i * 256));
     }
     if (tid == NT - 1) {
-      ptr[nvec] = (int32_t)run;
-      if (nnz_dev) *nnz_dev = run;
+      ptr[nvec] = end;
+      if (nnz_dev) *nnz_dev = end;
     }
   }
 };

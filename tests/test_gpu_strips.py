@@ -42,11 +42,11 @@ def test_windows_that_start_anywhere(srq, b, cols, axis, layout):
     """X as a window one element into rows of odd length: codes and scales against the oracle, residual codes
     and selection against the same call on a contiguous copy."""
     rng = np.random.default_rng(cols + axis)
-    big = (rng.standard_normal((77, cols + 4 + cols % 2)) * np.exp(rng.standard_normal((77, 1)))).astype(F32)
+    big = (rng.standard_normal((77, cols + 4 - (cols + 1) % 2)) * np.exp(rng.standard_normal((77, 1)))).astype(F32)
     big[3] = 0
     big[5, :] = F32(1e-38)                                   # qmax / amax overflows there (rows), or nearly so
     W = dev(big)[:, 1:cols + 1]
-    assert W.stride(0) % 2 == 1 and W.data_ptr() % 16 == 4
+    assert W.stride(0) % 2 == 1 and W.data_ptr() % 16 == 4    # (rows start at every multiple of 4 bytes)
     X = big[:, 1:cols + 1]
     name = "row" if axis == 0 else "col"
     with np.errstate(all="ignore"):
@@ -114,3 +114,15 @@ def test_short_inner_dimension(srq, b, shape, terms):
     if terms in ("both", "b"):
         assert (host(im["b_idx"]) == ref.csc_b.idx).all() and (host(im["b_val"]) == ref.csc_b.val).all()
     assert o.error_rel(ref.C, host(C)) <= 1e-5              # the FP32 output's tolerance everywhere
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 4095, 8192, 16385, 20001])
+def test_scan_of_many_counts(srq, b, n):
+    """Row pointers over piece, wave and block boundaries of the scan (one and two vectors a launch)."""
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 5)).astype(F32)
+    Q, s, lam = srq.quantize(dev(X), 0)
+    t = rng.random(n).astype(F32)
+    r = srq.build_sparse_residual(dev(X), 0, s, lam, dev(t))
+    counts = (np.abs(X) > t[:, None]).sum(axis=1)
+    assert (host(r["ptr"]) == np.concatenate([[0], np.cumsum(counts)])).all() and int(r["nnz"].item()) == counts.sum()
