@@ -305,16 +305,20 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
       ++g;
     };
     // ---- C in the layout it is stored in: access (j, a, h) of a lane covers four columns of row
-    // 16 a + 8 h + (rl & 7), in the 32 columns of the blocks 2j and 2j + 1
+    // 16 a + 8 h + (rl & 7), in the 32 columns of the blocks 2j and 2j + 1.  (On the edge every access is
+    // compared with the rows and columns left from the lane's first one, 32-bit numbers: with 64-bit
+    // coordinates the comparisons took the registers of 116 accumulators.)
+    auto left = [](int64_t n) { return (int)(n < BM ? n : BM); };
     auto load4 = [&](auto full_tag, const float* base, int64_t ld, int64_t mw, int64_t nw, int j, int a, int h) -> v4f {
       const float* p = base + (mw + 16 * a + 8 * h) * ld + nw + 32 * j;
-      if (decltype(full_tag)::value || (mw + 16 * a + 8 * h < M && nw + 32 * j + 3 < N))
-        return *reinterpret_cast<const v4fu*>(p);
+      if (decltype(full_tag)::value) return *reinterpret_cast<const v4fu*>(p);
+      const int rows = left(M - mw), cols = left(N - nw);
+      if (16 * a + 8 * h < rows && 32 * j + 3 < cols) return *reinterpret_cast<const v4fu*>(p);
       v4f x = {0.f, 0.f, 0.f, 0.f};
-      if (mw + 16 * a + 8 * h < M) {
+      if (16 * a + 8 * h < rows) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (nw + 32 * j + v < N) x[v] = p[v];
+        for (int v = 0; v < 3; ++v)
+          if (32 * j + v < cols) x[v] = p[v];
       }
       return x;
     };
@@ -374,6 +378,8 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
       for (int a = 0; a < TM; ++a) srow[a] = sc_row[16 * a];
       // element (row of the 16 x 16 block, column) exists
       const int64_t me = m0 + wm * (BM / 2) + rl, ne = n0 + wn * (BN / 2) + 4 * quad;
+      int rows_e = FULL ? 0 : left(M - me), cols_e = FULL ? 0 : left(N - ne);
+      int rows_w = FULL ? 0 : left(M - mw), cols_w = FULL ? 0 : left(N - nw);
 #pragma unroll
       for (int j = 0; j < TN / 2; ++j) {
         v4f sc[2], q1[2], q2[2], q3[2];              // column scales; column sums of 2, 4 and 64 rows
@@ -381,6 +387,8 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
         for (int e = 0; e < 2; ++e) sc[e] = *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16 * e);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
+          // (the comparisons are made afresh in every step: kept, their masks push accumulators out)
+          if (!FULL) asm volatile("" : "+v"(rows_e), "+v"(cols_e), "+v"(rows_w), "+v"(cols_w));
           v4f cin[2];
           if (SCALE && has_beta) {
 #pragma unroll
@@ -393,7 +401,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               d[e][v] = (float)acc[a][2 * j + e][v] * (srow[a] * sc[e][v]);
-              if (!FULL && SUMS && !(me + 16 * a < M && ne + 32 * j + 16 * e + v < N)) d[e][v] = 0.f;
+              if (!FULL && SUMS && !(16 * a < rows_e && 32 * j + 16 * e + v < cols_e)) d[e][v] = 0.f;
             }
             if (SUMS) {
               rs[e] = (fabsf(d[e][0]) + fabsf(d[e][1])) + (fabsf(d[e][2]) + fabsf(d[e][3]));
@@ -437,13 +445,13 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
               }
             }
             float* p = ep.C + (mw + 16 * a + 8 * h) * ep.ldc + nw + 32 * j;
-            if (FULL || (mw + 16 * a + 8 * h < M && nw + 32 * j + 3 < N)) {
+            if (FULL || (16 * a + 8 * h < rows_w && 32 * j + 3 < cols_w)) {
               if (CSTORE) *reinterpret_cast<v4fu*>(p) = out;
               else __builtin_nontemporal_store(out, reinterpret_cast<v4fu*>(p));
-            } else if (mw + 16 * a + 8 * h < M) {
+            } else if (16 * a + 8 * h < rows_w) {
 #pragma unroll
-              for (int v = 0; v < 4; ++v)
-                if (nw + 32 * j + v < N) p[v] = out[v];
+              for (int v = 0; v < 3; ++v)
+                if (32 * j + v < cols_w) p[v] = out[v];
             }
           }
           if (MODE == kGemmAccum && j + 1 < TN / 2) {
@@ -458,7 +466,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const float lo = rl ? q3[1][v] : q3[0][v], hi = rl ? q2[1][v] : q2[0][v];
-            if (FULL || ne + 32 * j + 16 * rl + v < N) cp[v] = (double)lo + (double)hi;
+            if (FULL || 32 * j + 16 * rl + v < cols_e) cp[v] = (double)lo + (double)hi;
           }
         }
       }
@@ -469,7 +477,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
           float r = r1[a] + r2[a];
           r += __shfl_xor(r, 16, 64);
           r += __shfl_xor(r, 32, 64);
-          if (quad == 0 && (FULL || (me + 16 * a < M && n0 + wn * (BN / 2) < N)))
+          if (quad == 0 && (FULL || (16 * a < rows_e && n0 + wn * (BN / 2) < N)))
             ep.row_part[(int64_t)(2 * tile_n + wn) * (ep.part_ld_m ? ep.part_ld_m : M) + me + 16 * a] = (double)r;
         }
       }
@@ -502,7 +510,12 @@ bool gemm_persistent_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64
   if (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) || (lda % 16) || (ldb % 16))
     return false;
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  return tiles >= 256 && tiles < (1 << 30);                 // at least one tile per compute unit
+  // One tile per compute unit, or a little more than half of that where the K loop is long against the
+  // epilogue (longer still for tiles on the edge, whose epilogue is slow): 128 x 128 tiles reach half the
+  // rate per compute unit.  Random codes without sums, us, 128 against 256: 132 tiles, K 3072 45 / 38,
+  // K 1024 23 / 22; 240 tiles 64 / 46, 31 / 25; 108 tiles 32 / 38; with edges 204 tiles, K 3072 68 / 62, K 1024 35 / 44.
+  const bool edge = (M % BM) || (N % BN);
+  return (tiles >= 256 || (tiles >= 132 && K >= (edge ? 2560 : 1024))) && tiles < (1 << 30);
 }
 
 // Compute units of the current device, looked up once per device (srq_create primes it, so
