@@ -383,7 +383,12 @@ StripShape strip_shape(int64_t K) {
 
 }  // namespace
 
-bool strips_ok(int64_t M, int64_t N, int64_t K) { return K > 0 && K <= kStripsMaxK && M + N < (1 << 24); }
+// Calls at 5 % kept, us, streaming kernels against these: 8192 x 8192 x 1024 540 / 521, x 1500 637 / 643, x 2048
+// 697 / 713; 10000 x 1024 x 2048 238 / 236, 1024 x 10000 x 2048 279 / 241, 4096 x 4096 x 2048 228 / 215.  (Columns of
+// 4096 in 512 threads: 4096^3 125 us in these passes against 94, so the line is drawn at 2048.)
+bool strips_ok(int64_t M, int64_t N, int64_t K) {
+  return K > 0 && K <= kStripsMaxK && (K <= 1024 || M + N <= 12288) && M + N < (1 << 24);
+}
 bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
 
 #define SRQ_STRIPS(KERN, ...)                                                                                  \
