@@ -754,7 +754,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       if (sb == kPathValu || sb == kPathMfma) h->last_path_b = sb;
     }
   }
-  // Short inner dimension and both terms expected where they read K-contiguous residual codes: both
+  // Short inner dimension or few vectors, and both terms expected where they read K-contiguous residual codes: both
   // operands in one launch per pass
   auto reads_em = [&](int hint_path) {
     return dense_fallback_density > 1.f && path_reads_em(strategy == SRQ_STRATEGY_AUTO ? hint_path : strategy_path(strategy));

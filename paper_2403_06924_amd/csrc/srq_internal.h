@@ -236,9 +236,9 @@ hipError_t launch_scan_pair(const int32_t* t0, int64_t n0, int32_t* p0, int64_t*
                             int64_t n1, int32_t* p1, int64_t* z1, hipStream_t st,
                             const ScanDecision* decide = nullptr);
 
-// ---- both operands of a call with a short inner dimension at once (strips.hip).  Code matrices have rows
+// ---- both operands of a small call, or one with a short inner dimension, at once (strips.hip).  Code matrices have rows
 // of Kc bytes (K rounded up to a multiple of 128) and come out with zeros past K.
-constexpr int64_t kStripsMaxK = 2048;        // columns of B that a workgroup can hold
+constexpr int64_t kStripsMaxK = 8192;        // columns of B that a workgroup can hold
 constexpr int64_t kStripsMaxScan = 4096;     // vectors whose counts every workgroup of the compaction adds up
 struct StripOperand {
   const float* X;

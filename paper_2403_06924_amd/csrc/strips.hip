@@ -1,10 +1,10 @@
-// The passes over the operands for a short inner dimension (K <= kStripsMaxK), where one workgroup can
-// hold whole columns of B: what takes ten launches on the kernels of fused.hip and select.hip takes three
-// here.
+// The passes over the operands for a short inner dimension, or few rows and columns (strips_ok), where one
+// workgroup can hold whole columns of B: what takes ten launches on the kernels of fused.hip and
+// select.hip takes three here.
 //
 //   quant_pair_kernel    both operands in one launch and one read of each: maxima, scales, codes, residual
 //                        scales and residual codes.  A workgroup has either one row of A in registers or a
-//                        strip of 4 * CG columns of B over all of K (256 / CG pieces of RPT rows).
+//                        strip of 4 * CG columns of B over all of K (TH / CG pieces of RPT rows).
 //   select_pair_kernel   means of |D_F| from the partial sums, thresholds, keep-masks and counts of both
 //                        operands, cut in the same way (no atomics, nothing to clear).
 //   compact_pair_kernel  compaction to CSR / CSC and to zero-filled codes of both operands; every workgroup
@@ -12,7 +12,7 @@
 //
 // What bounds them: at these sizes the latency of a launch and of one trip through a workgroup, not
 // bandwidth; hence few elements per thread for short K (RPT 4 or 8) and as many workgroups as there are.
-// A strip reads 64 or 32 bytes of each row of B; strips that share 128-byte lines are given to the same
+// A strip reads 64, 32 or 16 bytes of each row of B; strips that share 128-byte lines are given to the same
 // XCD (strip_of), where the line is found in L2 the second time.
 // Kernel times in a call, us, before (as many launches as listed) and now: 256^3 quantize 3.8 + 2.8 + 6.9 -> 5.0,
 // select 2.6 + 2.9 + 8.2 -> 4.8, scan and compaction 5.2 + 3.8 + 3.9 -> 3.8; 2048^3 21.7 -> 17.0, 20.4 -> 13.0, 20.2 -> 13.1.
@@ -22,8 +22,8 @@
 namespace srq {
 namespace {
 
-constexpr int kGroup = 4;                            // neighbouring strips handed to one XCD
-
+// (kGroup: neighbouring strips handed to one XCD)
+template <int kGroup>
 __device__ __forceinline__ int strip_of(int b, int strips) {
   if (b >= strips / (8 * kGroup) * (8 * kGroup)) return b;
   const int q = b >> 3, x = b & 7;                   // workgroup b runs on XCD b % 8
@@ -33,10 +33,23 @@ __device__ __forceinline__ int strip_of(int b, int strips) {
 __device__ __forceinline__ float4 abs4(float4 x) { return make_float4(fabsf(x.x), fabsf(x.y), fabsf(x.z), fabsf(x.w)); }
 __device__ __forceinline__ float max4(float4 x) { return fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)); }
 
+// TH threads, sm: TH / 64 words
+template <int TH>
+__device__ __forceinline__ float block_max(float m, float* sm) {
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  __syncthreads();                                   // sm may still be read from a previous use
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = sm[0];
+#pragma unroll
+  for (int i = 1; i < TH / 64; ++i) m = fmaxf(m, sm[i]);
+  return m;
+}
+
 // ---- quantization ----------------------------------------------------------------------------------
 // One row.  Codes go out up to the padded length (zeros past K); places past K stay out of the maxima of
 // the residual (0 * lam is not 0 where lam overflowed).
-template <int NV4>
+template <int TH, int NV4>
 __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, int K, int Kc, float qmax, int trunc, float* sm) {
   const float* src = s.X + row * s.ldx;
   float4 x[NV4];
@@ -44,18 +57,18 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   float m = 0.f;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * 256);
+    const int e = 4 * (threadIdx.x + i * TH);
     n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
     x[i] = load_part(src + e, n[i]);
     m = fmaxf(m, max4(abs4(x[i])));
   }
-  const float amax = block_max_256(m, sm);
+  const float amax = block_max<TH>(m, sm);
   float lam = 0.f, sc = 0.f;
   if (amax > 0.f) { lam = qmax / amax; sc = amax / qmax; }
   float rm = 0.f;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * 256);
+    const int e = 4 * (threadIdx.x + i * TH);
     float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
     int q[4];
 #pragma unroll
@@ -69,24 +82,24 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   }
   if (threadIdx.x == 0) { s.scale[row] = sc; s.lambda[row] = lam; }
   if (!s.Rq) return;
-  const float ramax = block_max_256(rm, sm);
+  const float ramax = block_max<TH>(rm, sm);
   float rlam = 0.f, rs = 0.f;
   if (ramax > 0.f) { rlam = qmax / ramax; rs = ramax / qmax; }
   if (threadIdx.x == 0) { s.rscale[row] = rs; s.rlambda[row] = rlam; }
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * 256);
+    const int e = 4 * (threadIdx.x + i * TH);
     const float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
     int q[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) q[j] = j < n[i] ? quant_code(v[j], rlam, qmax, trunc) : 0;
     if (e < Kc) *reinterpret_cast<unsigned*>(s.Rq + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
   }
-  for (int e = K + threadIdx.x; e < Kc; e += 256) s.D[row * Kc + e] = 0;
+  for (int e = K + threadIdx.x; e < Kc; e += TH) s.D[row * Kc + e] = 0;
 }
 
-// maxima of the CG * 4 columns of a strip from every thread's own four; red: [4][4 * CG]
-template <int CG>
+// maxima of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
+template <int TH, int CG>
 __device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cg = threadIdx.x & (CG - 1);
 #pragma unroll
@@ -99,7 +112,7 @@ __device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < 4; ++c)
-    m[c] = fmaxf(fmaxf(red[cg * 4 + c], red[4 * CG + cg * 4 + c]), fmaxf(red[8 * CG + cg * 4 + c], red[12 * CG + cg * 4 + c]));
+    for (int i = 0; i < TH / 64; ++i) m[c] = fmaxf(m[c], red[(i * CG + cg) * 4 + c]);
 }
 
 // RPT codes of each of the patch's columns: dst[col * Kc + row0 ..]
@@ -116,7 +129,7 @@ __device__ __forceinline__ void store_codes(int8_t* Q, int64_t col0, int ncol, i
   }
 }
 
-template <int CG, int RPT>
+template <int TH, int CG, int RPT>
 __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, float qmax, int trunc,
                                             float* red) {
   const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG, row0 = rb * RPT;
@@ -131,7 +144,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     const float4 a = abs4(v[i]);
     m[0] = fmaxf(m[0], a.x); m[1] = fmaxf(m[1], a.y); m[2] = fmaxf(m[2], a.z); m[3] = fmaxf(m[3], a.w);
   }
-  strip_max<CG>(m, red);
+  strip_max<TH, CG>(m, red);
   float lam[4], sc[4], rm[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -155,7 +168,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   }
   store_codes<RPT>(s.Q, col0, ncol, Kc, row0, pk);
   if (!s.Rq) return;
-  strip_max<CG>(rm, red + 16 * CG);
+  strip_max<TH, CG>(rm, red + TH / 16 * CG);
   float rlam[4], rs[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -174,18 +187,18 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     }
   }
   store_codes<RPT>(s.Rq, col0, ncol, Kc, row0, pk);
-  for (int i = threadIdx.x; i < 4 * CG * (Kc - K); i += 256) {
+  for (int i = threadIdx.x; i < 4 * CG * (Kc - K); i += TH) {
     const int64_t col = (int64_t)strip * 4 * CG + i / (Kc - K);
     if (col < cols) s.D[col * Kc + K + i % (Kc - K)] = 0;
   }
 }
 
-template <int NV4, int CG, int RPT>
-__global__ __launch_bounds__(256) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t N, int K, int Kc, int strips,
+template <int TH, int NV4, int CG, int RPT>
+__global__ __launch_bounds__(TH) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t N, int K, int Kc, int strips,
                                                          float qmax, int trunc) {
-  __shared__ float sm[32 * CG];
-  if ((int)blockIdx.x < strips) quant_strip<CG, RPT>(b, strip_of(blockIdx.x, strips), N, K, Kc, qmax, trunc, sm);
-  else quant_row<NV4>(a, (int64_t)blockIdx.x - strips, K, Kc, qmax, trunc, sm);
+  __shared__ float sm[TH / 8 * CG];
+  if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, qmax, trunc, sm);
+  else quant_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, K, Kc, qmax, trunc, sm);
 }
 
 // ---- selection -------------------------------------------------------------------------------------
@@ -195,7 +208,7 @@ __device__ __forceinline__ void mean_of(const StripSelect& s, int64_t v, double 
   if (writer) { s.mean[v] = mean; s.thresh[v] = t; }
 }
 
-template <int NV4>
+template <int TH, int NV4>
 __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, double* dsm, int* ism) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int words = (K + 63) / 64;
@@ -204,22 +217,25 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
   int n[NV4];
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {                    // (on their way while the threshold is formed)
-    const int e = 4 * (tid + i * 256);
+    const int e = 4 * (tid + i * TH);
     n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
     x[i] = load_part(src + e, s.mask ? n[i] : 0);
   }
   double sum = 0.0;
-  for (int64_t p = tid; p < s.nparts; p += 256) sum += s.part[p * rows + row];
+  for (int64_t p = tid; p < s.nparts; p += TH) sum += s.part[p * rows + row];
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
   if (lane == 0) dsm[w] = sum;
   __syncthreads();
   float t;
-  mean_of(s, row, (dsm[0] + dsm[1]) + (dsm[2] + dsm[3]), tid == 0, t);
+  sum = dsm[0];
+#pragma unroll
+  for (int i = 1; i < TH / 64; ++i) sum += dsm[i];
+  mean_of(s, row, sum, tid == 0, t);
   if (!s.mask) return;
   int total = 0;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int c4 = tid + i * 256;
+    const int c4 = tid + i * TH;
     unsigned nib = (fabsf(x[i].x) > t ? 1u : 0u) | (fabsf(x[i].y) > t ? 2u : 0u) | (fabsf(x[i].z) > t ? 4u : 0u) |
                    (fabsf(x[i].w) > t ? 8u : 0u);
     nib &= (1u << n[i]) - 1u;
@@ -233,10 +249,15 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
   if (lane == 0) ism[w] = total;
   __syncthreads();
-  if (tid == 0) s.counts[row] = ism[0] + ism[1] + ism[2] + ism[3];
+  if (tid == 0) {
+    total = ism[0];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) total += ism[i];
+    s.counts[row] = total;
+  }
 }
 
-template <int CG, int RPT>
+template <int TH, int CG, int RPT>
 __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, int64_t cols, int K, double* dsm, int* ism) {
   constexpr int BC = 4 * CG;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cg = tid & (CG - 1), rb = tid / CG, row0 = rb * RPT;
@@ -250,7 +271,7 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
   const int64_t pc = (int64_t)strip * BC + (tid & (BC - 1));
   double sum = 0.0;
   if (pc < cols)
-    for (int64_t p = tid / BC; p < s.nparts; p += 256 / BC) sum += s.part[p * cols + pc];
+    for (int64_t p = tid / BC; p < s.nparts; p += TH / BC) sum += s.part[p * cols + pc];
 #pragma unroll
   for (int off = BC; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
   if (lane < BC) dsm[w * BC + lane] = sum;
@@ -258,8 +279,10 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
   float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int j = cg * 4 + c;
-    if (c < ncol) mean_of(s, col0 + c, (dsm[j] + dsm[BC + j]) + (dsm[2 * BC + j] + dsm[3 * BC + j]), rb == 0, t[c]);
+    double all = dsm[cg * 4 + c];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) all += dsm[i * BC + cg * 4 + c];
+    if (c < ncol) mean_of(s, col0 + c, all, rb == 0, t[c]);
   }
   if (!s.mask) return;
   unsigned bits[4] = {0, 0, 0, 0};
@@ -293,16 +316,20 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
 #pragma unroll
     for (int c = 0; c < 4; ++c) ism[w * BC + cg * 4 + c] = cnt[c];
   __syncthreads();
-  if (tid < BC && (int64_t)strip * BC + tid < cols)
-    s.counts[(int64_t)strip * BC + tid] = ism[tid] + ism[BC + tid] + ism[2 * BC + tid] + ism[3 * BC + tid];
+  if (tid < BC && (int64_t)strip * BC + tid < cols) {
+    int total = ism[tid];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) total += ism[i * BC + tid];
+    s.counts[(int64_t)strip * BC + tid] = total;
+  }
 }
 
-template <int NV4, int CG, int RPT>
-__global__ __launch_bounds__(256) void select_pair_kernel(StripSelect a, StripSelect b, int64_t M, int64_t N, int K, int strips) {
-  __shared__ double dsm[16 * CG];
-  __shared__ int ism[16 * CG];
-  if ((int)blockIdx.x < strips) select_strip<CG, RPT>(b, strip_of(blockIdx.x, strips), N, K, dsm, ism);
-  else select_row<NV4>(a, (int64_t)blockIdx.x - strips, M, K, dsm, ism);
+template <int TH, int NV4, int CG, int RPT>
+__global__ __launch_bounds__(TH) void select_pair_kernel(StripSelect a, StripSelect b, int64_t M, int64_t N, int K, int strips) {
+  __shared__ double dsm[TH / 16 * CG];
+  __shared__ int ism[TH / 16 * CG];
+  if ((int)blockIdx.x < strips) select_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, dsm, ism);
+  else select_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, M, K, dsm, ism);
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
@@ -372,34 +399,35 @@ __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, Strip
   }
 }
 
-// strips of B and rows per thread: CG * 4 columns, 256 / CG * RPT rows
-struct StripShape { int nv4, cg, rpt; };
-StripShape strip_shape(int64_t K) {
-  if (K <= 256) return {1, 4, 4};
-  if (K <= 512) return {1, 4, 8};
-  if (K <= 1024) return {1, 2, 8};
-  return {2, 2, 16};
-}
+// a strip of B is 4 * CG columns wide
+int strip_cg(int64_t K) { return K <= 512 ? 4 : K <= 4096 ? 2 : 1; }
 
 }  // namespace
 
-// Calls at 5 % kept, us, streaming kernels against these: 8192 x 8192 x 1024 540 / 521, x 1500 637 / 643, x 2048
-// 697 / 713; 10000 x 1024 x 2048 238 / 236, 1024 x 10000 x 2048 279 / 241, 4096 x 4096 x 2048 228 / 215.  (Columns of
-// 4096 in 512 threads: 4096^3 125 us in these passes against 94, so the line is drawn at 2048.)
+// Where the lines lie (calls at 5 % kept, us, streaming kernels / these).  Wider strips of a longer K hold
+// more of a compute unit and read narrower pieces of each row, so what launches cost has to be a larger
+// share of the call:
+//   K <= 1024, any size    512^2 x 256 49 / 26, 8192^2 x 1024 540 / 521
+//   K <= 2048              4096^2 x 2048 228 / 215, 10000 x 1024 x 2048 238 / 236, 8192^2 x 2048 697 / 713
+//   K <= 4096              512^2 x 4096 84 / 67, 2048^2 x 4096 148 / 138, 1000 x 5000 x 4000 283 / 251, 3000^2 x 3000
+//                          277 / 277, 4096^3 323 / 370; M > 4096 has no joint compaction: 6000 x 600 x 2100 150 / 178
+//   K <= 8192              512^2 x 8192 120 / 106, 1024^2 x 8192 139 / 137, 2048^2 x 8192 241 / 261
 bool strips_ok(int64_t M, int64_t N, int64_t K) {
-  return K > 0 && K <= kStripsMaxK && (K <= 1024 || M + N <= 12288) && M + N < (1 << 24);
+  if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
+  return K <= 1024 || (K <= 2048 && M + N <= 12288) || (K <= 4096 && M <= 4096 && M + N <= 6000) || M + N <= 2048;
 }
 bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
 
-#define SRQ_STRIPS(KERN, ...)                                                                                  \
-  do {                                                                                                         \
-    const StripShape sh = strip_shape(K);                                                                      \
-    const int strips = (int)((N + 4 * sh.cg - 1) / (4 * sh.cg));                                               \
-    const dim3 grid((unsigned)(strips + M));                                                                   \
-    if (sh.nv4 == 2) hipLaunchKernelGGL((KERN<2, 2, 16>), grid, dim3(256), 0, st, __VA_ARGS__);                \
-    else if (sh.cg == 2) hipLaunchKernelGGL((KERN<1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);             \
-    else if (sh.rpt == 8) hipLaunchKernelGGL((KERN<1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);            \
-    else hipLaunchKernelGGL((KERN<1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                             \
+#define SRQ_STRIPS(KERN, ...)                                                                                       \
+  do {                                                                                                              \
+    const int strips = (int)((N + 4 * strip_cg(K) - 1) / (4 * strip_cg(K)));                                        \
+    const dim3 grid((unsigned)(strips + M));                                                                        \
+    if (K <= 256) hipLaunchKernelGGL((KERN<256, 1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                    \
+    else if (K <= 512) hipLaunchKernelGGL((KERN<256, 1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);               \
+    else if (K <= 1024) hipLaunchKernelGGL((KERN<256, 1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);              \
+    else if (K <= 2048) hipLaunchKernelGGL((KERN<256, 2, 2, 16>), grid, dim3(256), 0, st, __VA_ARGS__);             \
+    else if (K <= 4096) hipLaunchKernelGGL((KERN<512, 2, 2, 16>), grid, dim3(512), 0, st, __VA_ARGS__);             \
+    else hipLaunchKernelGGL((KERN<512, 4, 1, 16>), grid, dim3(512), 0, st, __VA_ARGS__);                            \
   } while (0)
 
 hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
@@ -418,7 +446,9 @@ hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int
   const dim3 grid((unsigned)(a.nvec + b.nvec));
   if (grid.x == 0) return hipSuccess;
   if (Kc <= 1024) hipLaunchKernelGGL(compact_pair_kernel<1>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
-  else hipLaunchKernelGGL(compact_pair_kernel<2>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  else if (Kc <= 2048) hipLaunchKernelGGL(compact_pair_kernel<2>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  else if (Kc <= 4096) hipLaunchKernelGGL(compact_pair_kernel<4>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  else hipLaunchKernelGGL(compact_pair_kernel<8>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
   return hipGetLastError();
 }
 
