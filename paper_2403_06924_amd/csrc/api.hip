@@ -440,6 +440,11 @@ srq_status_t srq_quantize(srq_handle_t h, const float* X, int64_t rows, int64_t 
                                  nullptr, st));
     return SRQ_STATUS_OK;
   }
+  if (axis == SRQ_AXIS_COL && layout == SRQ_LAYOUT_VECTOR_MAJOR && cols > 0 && strips_one_ok(axis, cols, rows)) {
+    const StripOperand op = {X, ldx, Q, scale, lam, nullptr, nullptr, nullptr, nullptr};
+    SRQ_HIP(h, launch_quant_strips(op, cols, rows, ldq, qmax, trunc, st));
+    return SRQ_STATUS_OK;
+  }
   SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(scale), nvec, 0, st));
   if (rows == 0 || cols == 0) {
     if (lambda) SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(lambda), nvec, 0, st));
@@ -503,6 +508,22 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
     int8_t* q_w = f.take<int8_t>((size_t)nvec * ldqw);
     const bool fits = f.off <= h->ws_bytes;
     const bool vm = r_layout == SRQ_LAYOUT_VECTOR_MAJOR;
+    if (fits && do_res && do_sel && vm && strips_one_ok(axis, nvec, veclen)) {
+      // one read of X, then the compaction (with its own sums of the counts for few vectors)
+      const StripReduce r = {X, ldx, scale, lambda, thresh, q_w, Rq, ldr, rscale, mask_w, tot_w};
+      if (axis == SRQ_AXIS_ROW) SRQ_HIP(h, launch_reduce_rows(r, nvec, veclen, ldqw, qmax, trunc, st));
+      else SRQ_HIP(h, launch_reduce_cols(r, nvec, veclen, ldqw, qmax, trunc, st));
+      if (strips_compact_ok(nvec, 0)) {
+        const StripCompact one = {(int)nvec, mask_w, tot_w, q_w, ptr, idx, val, capacity, nullptr, nnz_dev};
+        StripCompact none;
+        memset(&none, 0, sizeof(none));
+        SRQ_HIP(h, launch_compact_pair(one, none, veclen, ldqw, st));
+      } else {
+        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
+        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
+      }
+      return SRQ_STATUS_OK;
+    }
     if (fits && axis == SRQ_AXIS_ROW && (!do_res || vm) && rows_fused_ok(cols)) {
       SRQ_HIP(h, launch_rows_fused(X, rows, cols, ldx, qmax, trunc, q_w, ldqw, nullptr, nullptr, do_res ? Rq : nullptr,
                                    ldr, do_res ? rscale : nullptr, do_res ? rlam_w : nullptr, st, scale, lambda));

@@ -268,14 +268,31 @@ struct StripCompact {
   int32_t *ptr, *idx;
   int8_t* val;
   int64_t capacity;
-  int8_t* dense;
-  int64_t* nnz;
+  int8_t* dense;               // null: not wanted
+  int64_t* nnz;                // null: not wanted
+};
+struct StripReduce {
+  const float* X;
+  int64_t ldx;
+  const float *scale, *lambda, *thresh;
+  int8_t* Q;                   // codes, rows of Kc bytes
+  int8_t* Rq;
+  int64_t ldr;
+  float* rscale;
+  uint64_t* mask;
+  int32_t* counts;
 };
 bool strips_ok(int64_t M, int64_t N, int64_t K);
+bool strips_one_ok(int axis, int64_t nvec, int64_t veclen);      // the staged entry points, one operand
 bool strips_compact_ok(int64_t M, int64_t N);
 hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
                              int trunc, hipStream_t st);
 hipError_t launch_select_pair(const StripSelect& a, const StripSelect& b, int64_t M, int64_t N, int64_t K, hipStream_t st);
+// one operand: N columns of K codes into Q (leading dimension ldq, any alignment); its reduction (Kc: K rounded up
+// to a multiple of 16)
+hipError_t launch_quant_strips(const StripOperand& s, int64_t N, int64_t K, int64_t ldq, int qmax, int trunc, hipStream_t st);
+hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st);
+hipError_t launch_reduce_cols(const StripReduce& s, int64_t N, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st);
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st);
 
 // thresholds from the partial sums of the GEMM epilogue

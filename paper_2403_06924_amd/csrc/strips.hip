@@ -7,6 +7,7 @@
 //                        strip of 4 * CG columns of B over all of K (TH / CG pieces of RPT rows).
 //   select_pair_kernel   means of |D_F| from the partial sums, thresholds, keep-masks and counts of both
 //                        operands, cut in the same way (no atomics, nothing to clear).
+//   quant_cols_kernel, reduce_rows_kernel, reduce_cols_kernel   the staged entry points on one operand
 //   compact_pair_kernel  compaction to CSR / CSC and to zero-filled codes of both operands; every workgroup
 //                        adds up the counts before its vector itself, so that no scan runs in between.
 //
@@ -29,6 +30,8 @@ __device__ __forceinline__ int strip_of(int b, int strips) {
   const int q = b >> 3, x = b & 7;                   // workgroup b runs on XCD b % 8
   return ((q / kGroup) * 8 + x) * kGroup + q % kGroup;
 }
+
+typedef unsigned u2u __attribute__((ext_vector_type(2), aligned(1)));
 
 __device__ __forceinline__ float4 abs4(float4 x) { return make_float4(fabsf(x.x), fabsf(x.y), fabsf(x.z), fabsf(x.w)); }
 __device__ __forceinline__ float max4(float4 x) { return fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)); }
@@ -115,23 +118,30 @@ __device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
     for (int i = 0; i < TH / 64; ++i) m[c] = fmaxf(m[c], red[(i * CG + cg) * 4 + c]);
 }
 
-// RPT codes of each of the patch's columns: dst[col * Kc + row0 ..]
+// RPT codes of each of the patch's columns: Q[col * ld + row0 ..], places from `lim` on left alone
 template <int RPT>
-__device__ __forceinline__ void store_codes(int8_t* Q, int64_t col0, int ncol, int Kc, int row0, const unsigned (&pk)[4][RPT / 4]) {
-  if (row0 >= Kc) return;
+__device__ __forceinline__ void store_codes(int8_t* Q, int64_t ld, int lim, int64_t col0, int ncol, int row0,
+                                            const unsigned (&pk)[4][RPT / 4]) {
+  if (row0 >= lim) return;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     if (c >= ncol) break;
-    int8_t* dst = Q + (col0 + c) * Kc + row0;        // (Kc and row0 are multiples of RPT)
-    if constexpr (RPT == 16) *reinterpret_cast<uint4*>(dst) = make_uint4(pk[c][0], pk[c][1], pk[c][2], pk[c][3]);
-    else if constexpr (RPT == 8) *reinterpret_cast<uint2*>(dst) = make_uint2(pk[c][0], pk[c][1]);
-    else *reinterpret_cast<unsigned*>(dst) = pk[c][0];
+    int8_t* dst = Q + (col0 + c) * ld + row0;
+    if (row0 + RPT <= lim) {
+      if constexpr (RPT == 16) *reinterpret_cast<u4u*>(dst) = u4u{pk[c][0], pk[c][1], pk[c][2], pk[c][3]};
+      else if constexpr (RPT == 8) *reinterpret_cast<u2u*>(dst) = u2u{pk[c][0], pk[c][1]};
+      else *reinterpret_cast<u1u*>(dst) = pk[c][0];
+    } else {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i)
+        if (row0 + i < lim) dst[i] = (int8_t)(pk[c][i >> 2] >> (8 * (i & 3)));
+    }
   }
 }
 
 template <int TH, int CG, int RPT>
-__device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, float qmax, int trunc,
-                                            float* red) {
+__device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, int64_t ldq, float qmax,
+                                            int trunc, float* red) {
   const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG, row0 = rb * RPT;
   const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
@@ -166,7 +176,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     }
     v[i] = make_float4(x[0], x[1], x[2], x[3]);
   }
-  store_codes<RPT>(s.Q, col0, ncol, Kc, row0, pk);
+  store_codes<RPT>(s.Q, ldq, Kc, col0, ncol, row0, pk);
   if (!s.Rq) return;
   strip_max<TH, CG>(rm, red + TH / 16 * CG);
   float rlam[4], rs[4];
@@ -186,7 +196,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
       pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
     }
   }
-  store_codes<RPT>(s.Rq, col0, ncol, Kc, row0, pk);
+  store_codes<RPT>(s.Rq, ldq, Kc, col0, ncol, row0, pk);
   for (int i = threadIdx.x; i < 4 * CG * (Kc - K); i += TH) {
     const int64_t col = (int64_t)strip * 4 * CG + i / (Kc - K);
     if (col < cols) s.D[col * Kc + K + i % (Kc - K)] = 0;
@@ -197,8 +207,16 @@ template <int TH, int NV4, int CG, int RPT>
 __global__ __launch_bounds__(TH) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t N, int K, int Kc, int strips,
                                                          float qmax, int trunc) {
   __shared__ float sm[TH / 8 * CG];
-  if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, qmax, trunc, sm);
+  if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, Kc, qmax, trunc, sm);
   else quant_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, K, Kc, qmax, trunc, sm);
+}
+
+// columns alone, into a caller's matrix of any leading dimension
+template <int TH, int NV4, int CG, int RPT>
+__global__ __launch_bounds__(TH) void quant_cols_kernel(StripOperand s, int64_t N, int K, int64_t ldq, int strips, float qmax,
+                                                        int trunc) {
+  __shared__ float sm[TH / 8 * CG];
+  quant_strip<TH, CG, RPT>(s, strip_of<8 / CG>(blockIdx.x, strips), N, K, K, ldq, qmax, trunc, sm);
 }
 
 // ---- selection -------------------------------------------------------------------------------------
@@ -206,6 +224,14 @@ __device__ __forceinline__ void mean_of(const StripSelect& s, int64_t v, double 
   const float mean = (float)(sum / s.count);
   t = s.theta * mean;
   if (writer) { s.mean[v] = mean; s.thresh[v] = t; }
+}
+
+// eight neighbouring lanes assemble one 32-bit piece of a row's mask
+__device__ __forceinline__ void store_nibble(uint64_t* mrow, int words, int c4, unsigned nib) {
+  const unsigned b8 = nib | (__shfl_down(nib, 1, 64) << 4);
+  const unsigned b16 = b8 | (__shfl_down(b8, 2, 64) << 8);
+  const unsigned b32 = b16 | (__shfl_down(b16, 4, 64) << 16);
+  if (!(c4 & 7) && (c4 >> 3) < 2 * words) reinterpret_cast<uint32_t*>(mrow)[c4 >> 3] = b32;
 }
 
 template <int TH, int NV4>
@@ -240,11 +266,7 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
                    (fabsf(x[i].w) > t ? 8u : 0u);
     nib &= (1u << n[i]) - 1u;
     total += __popc(nib);
-    // eight neighbouring lanes assemble one 32-bit piece of the mask
-    const unsigned b8 = nib | (__shfl_down(nib, 1, 64) << 4);
-    const unsigned b16 = b8 | (__shfl_down(b8, 2, 64) << 8);
-    const unsigned b32 = b16 | (__shfl_down(b16, 4, 64) << 16);
-    if (!(tid & 7) && (c4 >> 3) < 2 * words) reinterpret_cast<uint32_t*>(s.mask + row * words)[c4 >> 3] = b32;
+    store_nibble(s.mask + row * words, words, c4, nib);
   }
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
   if (lane == 0) ism[w] = total;
@@ -254,6 +276,42 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
 #pragma unroll
     for (int i = 1; i < TH / 64; ++i) total += ism[i];
     s.counts[row] = total;
+  }
+}
+
+// keep-bits of a patch (bit i of bits[c]: row row0 + i of column c) into the mask, and the counts of the strip's columns
+template <int TH, int CG, int RPT>
+__device__ __forceinline__ void store_bits(uint64_t* mask, int32_t* counts, int strip, int64_t cols, int K, int64_t col0, int ncol,
+                                           const unsigned (&bits)[4], int* ism) {
+  constexpr int BC = 4 * CG;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cg = tid & (CG - 1), rb = tid / CG, row0 = rb * RPT;
+  const int words = (K + 63) / 64;
+  int cnt[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    cnt[c] = c < ncol ? __popc(bits[c]) : 0;
+    unsigned piece = bits[c];
+    if constexpr (RPT == 4) piece |= __shfl_down(piece, CG, 64) << 4;     // two threads' rows make one byte
+    if (c < ncol && row0 < words * 64) {
+      uint8_t* dst = reinterpret_cast<uint8_t*>(mask + (col0 + c) * words) + (row0 >> 3);
+      if constexpr (RPT == 16) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)piece;
+      else if constexpr (RPT == 8) *dst = (uint8_t)piece;
+      else if (!(rb & 1)) *dst = (uint8_t)piece;
+    }
+  }
+#pragma unroll
+  for (int off = CG; off < 64; off <<= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cnt[c] += __shfl_xor(cnt[c], off, 64);
+  if (lane < CG)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ism[w * BC + cg * 4 + c] = cnt[c];
+  __syncthreads();
+  if (tid < BC && (int64_t)strip * BC + tid < cols) {
+    int total = ism[tid];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) total += ism[i * BC + tid];
+    counts[(int64_t)strip * BC + tid] = total;
   }
 }
 
@@ -295,33 +353,7 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
     bits[2] |= ok && a.z > t[2] ? 1u << i : 0u;
     bits[3] |= ok && a.w > t[3] ? 1u << i : 0u;
   }
-  int cnt[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    cnt[c] = c < ncol ? __popc(bits[c]) : 0;
-    unsigned piece = bits[c];
-    if constexpr (RPT == 4) piece |= __shfl_down(piece, CG, 64) << 4;     // two threads' rows make one byte
-    if (c < ncol && row0 < words * 64) {
-      uint8_t* dst = reinterpret_cast<uint8_t*>(s.mask + (col0 + c) * words) + (row0 >> 3);
-      if constexpr (RPT == 16) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)piece;
-      else if constexpr (RPT == 8) *dst = (uint8_t)piece;
-      else if (!(rb & 1)) *dst = (uint8_t)piece;
-    }
-  }
-#pragma unroll
-  for (int off = CG; off < 64; off <<= 1)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cnt[c] += __shfl_xor(cnt[c], off, 64);
-  if (lane < CG)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ism[w * BC + cg * 4 + c] = cnt[c];
-  __syncthreads();
-  if (tid < BC && (int64_t)strip * BC + tid < cols) {
-    int total = ism[tid];
-#pragma unroll
-    for (int i = 1; i < TH / 64; ++i) total += ism[i * BC + tid];
-    s.counts[(int64_t)strip * BC + tid] = total;
-  }
+  store_bits<TH, CG, RPT>(s.mask, s.counts, strip, cols, K, col0, ncol, bits, ism);
 }
 
 template <int TH, int NV4, int CG, int RPT>
@@ -330,6 +362,125 @@ __global__ __launch_bounds__(TH) void select_pair_kernel(StripSelect a, StripSel
   __shared__ int ism[TH / 16 * CG];
   if ((int)blockIdx.x < strips) select_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, dsm, ism);
   else select_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, M, K, dsm, ism);
+}
+
+// ---- reduction of one operand (scales and thresholds given): codes, residual codes, keep-mask and counts in
+// one read.  Codes go to rows of Kc bytes with zeros past K, residual codes to the caller's matrix.
+template <int TH, int NV4>
+__global__ __launch_bounds__(TH) void reduce_rows_kernel(StripReduce s, int K, int Kc, float qmax, int trunc) {
+  __shared__ float sm[TH / 64];
+  __shared__ int ism[TH / 64];
+  const int64_t row = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, words = (K + 63) / 64;
+  const float* src = s.X + row * s.ldx;
+  const float lam = s.lambda[row], sc = s.scale[row], t = s.thresh[row];
+  float4 x[NV4];
+  int n[NV4], total = 0;
+  float rm = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (tid + i * TH);
+    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
+    x[i] = load_part(src + e, n[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (tid + i * TH);
+    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+    int q[4];
+    unsigned nib = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      nib |= j < n[i] && fabsf(v[j]) > t ? 1u << j : 0u;
+      q[j] = j < n[i] ? quant_code(v[j], lam, qmax, trunc) : 0;
+      v[j] = v[j] - (float)q[j] * sc;
+      rm = j < n[i] ? fmaxf(rm, fabsf(v[j])) : rm;
+    }
+    total += __popc(nib);
+    store_nibble(s.mask + row * words, words, e >> 2, nib);
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+    x[i] = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+  if (lane == 0) ism[w] = total;
+  const float ramax = block_max<TH>(rm, sm);         // (its barriers publish ism as well)
+  float rlam = 0.f, rs = 0.f;
+  if (ramax > 0.f) { rlam = qmax / ramax; rs = ramax / qmax; }
+  if (tid == 0) {
+    total = ism[0];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) total += ism[i];
+    s.counts[row] = total;
+    s.rscale[row] = rs;
+  }
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (tid + i * TH);
+    const int q[4] = {quant_code(x[i].x, rlam, qmax, trunc), quant_code(x[i].y, rlam, qmax, trunc),
+                      quant_code(x[i].z, rlam, qmax, trunc), quant_code(x[i].w, rlam, qmax, trunc)};
+    int8_t* dst = s.Rq + row * s.ldr + e;
+    if (n[i] == 4) {
+      *reinterpret_cast<u1u*>(dst) = pack4(q[0], q[1], q[2], q[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (j < n[i]) dst[j] = (int8_t)q[j];
+    }
+  }
+}
+
+template <int TH, int NV4, int CG, int RPT>
+__global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t cols, int K, int Kc, int strips, float qmax,
+                                                         int trunc) {
+  __shared__ float red[TH / 16 * CG];
+  __shared__ int ism[TH / 16 * CG];
+  const int strip = strip_of<8 / CG>(blockIdx.x, strips);
+  const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG, row0 = rb * RPT;
+  const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
+  const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
+  float4 v[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, row0 + i < K ? ncol : 0);
+  const float4 l4 = load_part(s.lambda + col0, ncol), s4 = load_part(s.scale + col0, ncol), t4 = load_part(s.thresh + col0, ncol);
+  const float lam[4] = {l4.x, l4.y, l4.z, l4.w}, sc[4] = {s4.x, s4.y, s4.z, s4.w}, t[4] = {t4.x, t4.y, t4.z, t4.w};
+  float rm[4] = {0.f, 0.f, 0.f, 0.f};
+  unsigned bits[4] = {0, 0, 0, 0}, pk[4][RPT / 4];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+    const bool ok = row0 + i < K;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bits[c] |= ok && fabsf(x[c]) > t[c] ? 1u << i : 0u;
+      const int q = ok ? quant_code(x[c], lam[c], qmax, trunc) : 0;
+      x[c] = x[c] - (float)q * sc[c];
+      rm[c] = ok ? fmaxf(rm[c], fabsf(x[c])) : rm[c];
+      if ((i & 3) == 0) pk[c][i >> 2] = 0;
+      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
+    }
+    v[i] = make_float4(x[0], x[1], x[2], x[3]);
+  }
+  store_codes<RPT>(s.Q, Kc, Kc, col0, ncol, row0, pk);
+  store_bits<TH, CG, RPT>(s.mask, s.counts, strip, cols, K, col0, ncol, bits, ism);
+  strip_max<TH, CG>(rm, red);
+  float rlam[4], rs[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    rlam[c] = rm[c] > 0.f ? qmax / rm[c] : 0.f;
+    rs[c] = rm[c] > 0.f ? rm[c] / qmax : 0.f;
+  }
+  if (rb == 0) store_part(s.rscale + col0, rs, ncol);
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int q = quant_code(x[c], rlam[c], qmax, trunc);
+      if ((i & 3) == 0) pk[c][i >> 2] = 0;
+      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
+    }
+  }
+  store_codes<RPT>(s.Rq, s.ldr, K, col0, ncol, row0, pk);
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
@@ -364,7 +515,7 @@ __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, Strip
     const int e = 4 * (tid + i * 256);
     const unsigned keep = ((nib[i] & 1u) ? 0xffu : 0u) | ((nib[i] & 2u) ? 0xff00u : 0u) | ((nib[i] & 4u) ? 0xff0000u : 0u) |
                           ((nib[i] & 8u) ? 0xff000000u : 0u);
-    if (e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
+    if (s.dense && e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
     const int cnt = __popc(nib[i]);
     const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
     at[i] = __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower);
@@ -394,7 +545,7 @@ __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, Strip
     s.ptr[v] = (int32_t)first;
     if (v == s.nvec - 1) {
       s.ptr[s.nvec] = (int32_t)base;
-      *s.nnz = base;
+      if (s.nnz) *s.nnz = base;
     }
   }
 }
@@ -416,12 +567,18 @@ bool strips_ok(int64_t M, int64_t N, int64_t K) {
   if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
   return K <= 1024 || (K <= 2048 && M + N <= 12288) || (K <= 4096 && M <= 4096 && M + N <= 6000) || M + N <= 2048;
 }
+// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, before / now; about 36 us of the small
+// ones is the host): columns 1000 x 1000 51 / 36, 2000 x 10000 130 / 95, 4000 x 5900 157 / 124, but 5000 x 1500 68 / 75, so
+// columns longer than 4096 stay in passes; rows 10000 x 1000 62 / 53, 3000 x 3000 45 / 39, 4000 x 5900 87 / 87.
+bool strips_one_ok(int axis, int64_t nvec, int64_t veclen) {
+  return axis == SRQ_AXIS_ROW ? strips_ok(nvec, 0, veclen) : veclen <= 4096 && strips_ok(0, nvec, veclen);
+}
 bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
 
-#define SRQ_STRIPS(KERN, ...)                                                                                       \
+#define SRQ_STRIPS(KERN, ROWS, ...)                                                                                       \
   do {                                                                                                              \
     const int strips = (int)((N + 4 * strip_cg(K) - 1) / (4 * strip_cg(K)));                                        \
-    const dim3 grid((unsigned)(strips + M));                                                                        \
+    const dim3 grid((unsigned)(strips + (ROWS)));                                                                        \
     if (K <= 256) hipLaunchKernelGGL((KERN<256, 1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                    \
     else if (K <= 512) hipLaunchKernelGGL((KERN<256, 1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);               \
     else if (K <= 1024) hipLaunchKernelGGL((KERN<256, 1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);              \
@@ -432,15 +589,35 @@ bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <
 
 hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
                              int trunc, hipStream_t st) {
-  SRQ_STRIPS(quant_pair_kernel, a, b, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
+  SRQ_STRIPS(quant_pair_kernel, M, a, b, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
   return hipGetLastError();
 }
 
 hipError_t launch_select_pair(const StripSelect& a, const StripSelect& b, int64_t M, int64_t N, int64_t K, hipStream_t st) {
-  SRQ_STRIPS(select_pair_kernel, a, b, M, N, (int)K, strips);
+  SRQ_STRIPS(select_pair_kernel, M, a, b, M, N, (int)K, strips);
+  return hipGetLastError();
+}
+
+hipError_t launch_quant_strips(const StripOperand& s, int64_t N, int64_t K, int64_t ldq, int qmax, int trunc, hipStream_t st) {
+  SRQ_STRIPS(quant_cols_kernel, 0, s, N, (int)K, ldq, strips, (float)qmax, trunc);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_cols(const StripReduce& s, int64_t N, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st) {
+  SRQ_STRIPS(reduce_cols_kernel, 0, s, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
   return hipGetLastError();
 }
 #undef SRQ_STRIPS
+
+hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st) {
+  const dim3 grid((unsigned)M);
+  const float qm = (float)qmax;
+  if (K <= 1024) hipLaunchKernelGGL((reduce_rows_kernel<256, 1>), grid, dim3(256), 0, st, s, (int)K, (int)Kc, qm, trunc);
+  else if (K <= 2048) hipLaunchKernelGGL((reduce_rows_kernel<256, 2>), grid, dim3(256), 0, st, s, (int)K, (int)Kc, qm, trunc);
+  else if (K <= 4096) hipLaunchKernelGGL((reduce_rows_kernel<256, 4>), grid, dim3(256), 0, st, s, (int)K, (int)Kc, qm, trunc);
+  else hipLaunchKernelGGL((reduce_rows_kernel<512, 4>), grid, dim3(512), 0, st, s, (int)K, (int)Kc, qm, trunc);
+  return hipGetLastError();
+}
 
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st) {
   const dim3 grid((unsigned)(a.nvec + b.nvec));

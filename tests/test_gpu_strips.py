@@ -117,6 +117,40 @@ def test_short_inner_dimension(srq, b, shape, terms):
     assert o.error_rel(ref.C, host(C)) <= 1e-5              # the FP32 output's tolerance everywhere
 
 
+@pytest.mark.parametrize("shape", [(1, 1), (77, 61), (9, 255), (256, 33), (257, 7), (512, 40), (1023, 9), (1025, 18), (2049, 5),
+                                   (4095, 11), (4097, 10), (8192, 6), (8193, 6), (100, 4100)])
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_reduction_of_one_operand(srq, b, shape, axis, bits):
+    """Codes, residual codes and compressed form against the definitions, one FP32 rounding per step; shape is
+    (vector length, vectors), the operand a window of odd leading dimension."""
+    K, nvec = shape
+    rng = np.random.default_rng(K + nvec + axis)
+    big = (rng.standard_normal((nvec, K) if axis == 0 else (K, nvec))).astype(F32)
+    width = big.shape[1]
+    W = dev(np.pad(big, ((0, 0), (1, 2 + width % 2))))[:, 1:width + 1]
+    V = host(W) if axis == 0 else host(W).T                   # one vector per row
+    assert V.shape == (nvec, K)
+    Q, s, lam = srq.quantize(W, axis, bits=bits)
+    qmax = F32(2 ** (bits - 1) - 1)
+    amax = np.abs(V).max(axis=1)
+    assert (host(s) == amax / qmax).all() and (host(lam) == qmax / amax).all()
+    q = np.clip(np.rint(V * host(lam)[:, None]), -qmax, qmax)
+    assert (host(Q) == q).all()
+    t = (amax * rng.random(nvec).astype(F32)).astype(F32)
+    r = srq.build_sparse_residual(W, axis, s, lam, dev(t), bits=bits)
+    res = V - q.astype(F32) * host(s)[:, None]
+    ramax = np.abs(res).max(axis=1)
+    with np.errstate(all="ignore"):                       # (a residual of zeros)
+        rlam = np.where(ramax > 0, qmax / ramax, F32(0)).astype(F32)
+    assert (host(r["rscale"]) == ramax / qmax).all()
+    assert (host(r["Rq"]) == np.clip(np.rint(res * rlam[:, None]), -qmax, qmax)).all()
+    vec, k = np.nonzero(np.abs(V) > t[:, None])
+    n = int(r["nnz"].item())
+    assert n == len(k) and (host(r["ptr"]) == np.searchsorted(vec, np.arange(nvec + 1))).all()
+    assert (host(r["idx"][:n]) == k).all() and (host(r["val"][:n]) == q[vec, k]).all()
+
+
 @pytest.mark.parametrize("n", [1, 255, 257, 4095, 8192, 16385, 20001])
 def test_scan_of_many_counts(srq, b, n):
     """Row pointers over piece, wave and block boundaries of the scan (one and two vectors a launch)."""
