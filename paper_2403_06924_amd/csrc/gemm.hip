@@ -392,7 +392,8 @@ bool gemm_tile64_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t l
   return t < (1 << 30) && (K <= 384 || t <= 640);
 }
 
-// 128 x 128 tiles, at most one per compute unit (beyond that the halves of 256 x 256 tiles fill the chip)
+// 128 x 128 tiles: what is left below 256 large tiles (launch_gemm_i8 asks the kernels with 64 x 64 and with
+// 256 x 256 tiles first, which take the shortest and the longest K)
 bool gemm_small_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb, int64_t ldb,
                    const GemmEpilogue& ep) {
   if (M <= 0 || N <= 0 || !aligned_operands(K, Qa, lda, Qb, ldb, ep)) return false;

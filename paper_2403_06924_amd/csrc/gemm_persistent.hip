@@ -306,8 +306,8 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
     };
     // ---- C in the layout it is stored in: access (j, a, h) of a lane covers four columns of row
     // 16 a + 8 h + (rl & 7), in the 32 columns of the blocks 2j and 2j + 1.  (On the edge every access is
-    // compared with the rows and columns left from the lane's first one, 32-bit numbers: with 64-bit
-    // coordinates the comparisons took the registers of 116 accumulators.)
+    // compared with the rows and columns left from the lane's first one, 32-bit numbers: 110 and 86 vector
+    // registers of the edge kernels with sums spill, against 116 and 99 with 64-bit coordinates.)
     auto left = [](int64_t n) { return (int)(n < BM ? n : BM); };
     auto load4 = [&](auto full_tag, const float* base, int64_t ld, int64_t mw, int64_t nw, int j, int a, int h) -> v4f {
       const float* p = base + (mw + 16 * a + 8 * h) * ld + nw + 32 * j;
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
         for (int e = 0; e < 2; ++e) sc[e] = *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16 * e);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
-          // (the comparisons are made afresh in every step: kept, their masks push accumulators out)
+          // (the comparisons are made afresh in every step: kept, their masks spill 94 scalar registers, not 17)
           if (!FULL) asm volatile("" : "+v"(rows_e), "+v"(cols_e), "+v"(rows_w), "+v"(cols_w));
           v4f cin[2];
           if (SCALE && has_beta) {

@@ -344,7 +344,7 @@ bool gemm_tile64_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t l
                     const GemmEpilogue& ep);
 hipError_t launch_gemm_i8_tile64(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
                                  const GemmEpilogue& ep, hipStream_t st);
-// at most 32 rows and no sums (gemm_skinny.hip)
+// at most 32 rows, 64 of a narrower product, and no sums (gemm_skinny.hip)
 hipError_t launch_gemm_i8_skinny(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                                  int64_t ldb, const GemmEpilogue& ep, hipStream_t st);
 // Both correction products in one accumulate-mode launch (first Qa.Qb^T with ep's scales, then sec):
