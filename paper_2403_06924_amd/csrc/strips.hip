@@ -575,6 +575,9 @@ bool strips_one_ok(int axis, int64_t nvec, int64_t veclen) {
 }
 bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
 
+// (Rows per thread, calls at 5 % kept, us, 16 in 256 threads / 8 in 512: 512 x 512 x 1100 42 / 38, 1024 x 1024 x 2048 52 / 49,
+// 300 x 3000 x 2048 67 / 65, 4096 x 4096 x 2048 228 / 234, 10000 x 1024 x 2048 249 / 256.  One step further either way loses:
+// 4 in 512 threads at 2048 x 2048 x 1000 73 against 68, 8 in 1024 threads at 2048 x 2048 x 3000 143 against 134.)
 #define SRQ_STRIPS(KERN, ROWS, ...)                                                                                       \
   do {                                                                                                              \
     const int strips = (int)((N + 4 * strip_cg(K) - 1) / (4 * strip_cg(K)));                                        \
@@ -582,6 +585,8 @@ bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <
     if (K <= 256) hipLaunchKernelGGL((KERN<256, 1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                    \
     else if (K <= 512) hipLaunchKernelGGL((KERN<256, 1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);               \
     else if (K <= 1024) hipLaunchKernelGGL((KERN<256, 1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);              \
+    else if (K <= 2048 && N + (ROWS) <= 6000)                                                                       \
+      hipLaunchKernelGGL((KERN<512, 1, 2, 8>), grid, dim3(512), 0, st, __VA_ARGS__);                                \
     else if (K <= 2048) hipLaunchKernelGGL((KERN<256, 2, 2, 16>), grid, dim3(256), 0, st, __VA_ARGS__);             \
     else if (K <= 4096) hipLaunchKernelGGL((KERN<512, 2, 2, 16>), grid, dim3(512), 0, st, __VA_ARGS__);             \
     else hipLaunchKernelGGL((KERN<512, 4, 1, 16>), grid, dim3(512), 0, st, __VA_ARGS__);                            \

@@ -76,7 +76,7 @@ def test_windows_that_start_anywhere(srq, b, cols, axis, layout):
 @pytest.mark.parametrize("shape", [(1, 1, 1), (3, 17, 2), (33, 9, 63), (130, 15, 255), (65, 33, 256), (64, 70, 257), (31, 129, 512),
                                    (40, 24, 513), (129, 65, 1023), (24, 40, 1024), (33, 31, 1025), (50, 63, 2047), (16, 8, 2048),
                                    (20, 12, 2049), (35, 50, 4095), (17, 9, 4097),
-                                   (9, 17, 8192), (5, 6, 8193), (4097, 40, 100), (40, 4097, 100), (4096, 24, 130)])
+                                   (9, 17, 8192), (5, 6, 8193), (6001, 8, 1100), (10, 6001, 2047), (4097, 40, 100), (40, 4097, 100), (4096, 24, 130)])
 @pytest.mark.parametrize("terms", ["both", "a", "b", "dense"])
 def test_short_inner_dimension(srq, b, shape, terms):
     M, N, K = shape
