@@ -33,12 +33,24 @@
 //    64-byte pieces a round of 64 MiB leaves at 3.0 TB/s, with whole lines at 5.9 TB/s.)
 //
 // What bounds it: on operands that toggle, the power limit (1.86 GHz in a loop of products on random
-// bytes); on zeros about 2300 clocks per K-tile against 2048 of matrix-core time, and 12-15 us per
-// round of tiles for the epilogue, most of it the 64 MiB of C that all compute units write at once
-// (starting them staggered was tried: it costs the tiles of an XCD their common panels in L2).
+// bytes); on zeros about 2300 clocks per K-tile against 2048 of matrix-core time; and the epilogue, in which all compute
+// units access C at once: 64 MiB a round written in first mode, read and written in accumulate mode.
 // 8192^3, us, with 32x32x32 and 64 dwords per row block / now: product without sums, random codes 472 / 389-404,
-// zeros 322 / 309; normal operands with outliers, 5 % kept, in a call: first product 443 / 375, both corrections in
-// one launch 968 / 806.
+// zeros 322 / 309; normal operands with outliers, 5 % kept, in a call: first product 443 / 367, both corrections in
+// one launch 968 / 781, of which 592 are the K loops and 190 eight epilogues: 14 us each for loading C, converting and
+// adding, 10 for the stores, together 5.5 TB/s.
+//
+// The epilogues spill nothing, inside and outside the K loop, because (a) the accumulators are read one by one through
+// assembly: otherwise the conversions that the copies of an epilogue have in common are all computed ahead of the
+// branch between them; (b) C is accessed through buffer descriptors with running scalar row pointers and one lane
+// offset, not 64-bit addresses per access; (c) accesses on the edge are cut off by the descriptor's range, not
+// branched around; (d) sums are pinned where they are formed.  Before / after, calls at 5 % kept, us: 2999 x 4097 x
+// 3001 319 / 294 (first product 67 / 60, corrections 135 / 106), 5000^2 x 2000 with beta 475 / 424, 4096 x 14336 x 4096
+// 972 / 938, 8192^3 1576 / 1535, 4096 x 8192 x 1024 with beta 327 / 295.
+// The order in which the accumulating epilogue visits its blocks (JN): down the 128 rows of 32 columns, then the next
+// 32; on the edge, where rows of C seldom start on the same channels of memory, along the row unless the pitch is a
+// multiple of 4 KiB (corrections, us, down / along: pitch 32 KiB 781 / 858, 56 KiB 456 / 456, 16388 bytes 122 / 106,
+// 20000 bytes 236 / 222; edge with 32 KiB 191 / 208).  8, 12, 16 or 20 blocks ahead are the same time.
 //
 // M and N need not be multiples of the tile: rows past the end are cut off by the range check of the
 // buffer descriptor (whatever lands in LDS for them feeds elements that are never stored), and the
@@ -65,8 +77,7 @@ constexpr int kABufs = 3, kBBufs = 2;               // LDS buffers of the A tile
 constexpr int kLdsB = kABufs * kOperand;            // the B buffers follow the A buffers
 constexpr int kLdsBytes = kLdsB + kBBufs * kOperand;   // 160 KiB; the epilogue's scales borrow a free A buffer
 constexpr int kLoads = 8;                           // loads per wave, operand and K-tile
-constexpr int kAhead = 4;                           // rows of blocks of C (of TM) fetched inside the K loop
-enum { kFirst, kMiddle, kPastC, kLast };            // K-tiles of an output tile
+enum { kFirst, kMiddle, kLast };                    // K-tiles of an output tile
 
 // the lane's number, computed where it is wanted: nothing derived from it can be computed ahead of the
 // K loop and kept (or spilled) through it
@@ -76,8 +87,59 @@ __device__ __forceinline__ int fresh_lane() {
   return l;
 }
 
-// EDGE: M or N is no multiple of 256
-template <int MODE, bool SUMS, bool SCALE, bool EDGE>
+// an accumulator as a number, read where it is wanted (several copies of an epilogue follow the K loop: what they
+// have in common the compiler computes before it branches to one of them, all 256 conversions at once)
+__device__ __forceinline__ float acc_value(int x) {
+  int y;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(x));
+  return (float)y;
+}
+
+// 16 bytes of a row of C (at any 4-byte aligned address): uniform base and offset, the lane's offset
+__device__ __forceinline__ v4f row_load(uint64_t base, uint32_t lane, uint32_t off) {
+  const v4i t = buf_load16(buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off);
+  return v4f{__int_as_float(t.x), __int_as_float(t.y), __int_as_float(t.z), __int_as_float(t.w)};
+}
+template <bool CACHED>
+__device__ __forceinline__ void row_store(v4f x, uint64_t base, uint32_t lane, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(
+      v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)},
+      buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off, CACHED ? 0 : 2 /* non-temporal */);
+}
+
+// the same on the edge, without branches: row `row`, columns col .. col + 3 of the rows that start at `base`, of which
+// rows x cols exist; an access outside gets an offset past the end of its descriptor (its load brings zero, its
+// store is dropped).  ELEMS: the last columns are not a whole access.
+constexpr uint32_t kOutside = 0xfffffff0u, kRecords = 0x7fffffffu;
+__device__ __forceinline__ uint32_t edge_offset(int64_t ld4, int row, int col, int rows, int cols) {
+  return row < rows && col < cols ? (uint32_t)row * (uint32_t)ld4 + 4u * (uint32_t)col : kOutside;
+}
+template <bool ELEMS>
+__device__ __forceinline__ v4f edge_load(uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
+  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
+  if (!ELEMS) return buf_load_4(rs, edge_offset(ld4, row, col, rows, cols), true);
+  v4f x;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) x[v] = buf_load_f32(rs, edge_offset(ld4, row, col + v, rows, cols));
+  return x;
+}
+template <bool ELEMS>
+__device__ __forceinline__ void edge_store(v4f x, uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
+  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
+  if (!ELEMS) {
+    __builtin_amdgcn_raw_buffer_store_b128(
+        v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)}, rs,
+        edge_offset(ld4, row, col, rows, cols), 0, 0);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[v]), rs, edge_offset(ld4, row, col + v, rows, cols), 0, 0);
+  }
+}
+
+// EDGE: M or N is no multiple of 256.  JN: neighbouring blocks of a row of C that an accumulating epilogue visits before
+// the next row.
+template <int MODE, bool SUMS, bool SCALE, bool EDGE, int JN>
 __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int64_t N, int64_t K,
                                                                  const int8_t* __restrict__ Qa, int64_t lda,
                                                                  const int8_t* __restrict__ Qb, int64_t ldb,
@@ -230,8 +292,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
     // where the scales of this tile go: the A buffer of its last K-tile, free from that K-tile's
     // barrier until the second K-tile of the next tile
     int sbuf = 0;
-    // KIND: first K-tile of the tile (the accumulators start at zero), one in the middle, one with the
-    // first accesses to C in flight, the last one
+    // KIND: first K-tile of the tile (the accumulators start at zero), one in the middle, the last one
     auto ktile = [&](auto kind_tag) {
       constexpr int KIND = decltype(kind_tag)::value;
       constexpr bool FIRST = KIND == kFirst, LAST = KIND == kLast;
@@ -257,13 +318,11 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
 #pragma unroll
         for (int a = 0; a < TM; ++a) fa[1][a] &= half;
       }
-      // K-tile g+1 must have landed: everything but the eight loads just issued and the
-      // accesses to C before them.  After the barrier everybody has the fragments of this K-tile in
+      // K-tile g+1 must have landed: everything but the eight loads just issued.  After the barrier everybody has the fragments of this K-tile in
       // registers: its buffers are free.  (In the first K-tile of a tile nothing is left to wait for:
       // the prologue resp. the epilogue before it has waited for every load before its first store,
       // so that the stores, which the counter counts as well, may still be on their way.)
-      if (KIND == kPastC && full) wait_loads_but<kLoads + 2 * kAhead>();
-      else if (!FIRST) wait_loads_but<kLoads>();
+      if (!FIRST) wait_loads_but<kLoads>();
       __syncthreads();
       if (LAST) {
         sbuf = abuf;
@@ -293,83 +352,163 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
       abuf = anext;
       ++g;
     };
-    // ---- C in the layout it is stored in: access (j, a, h) of a lane covers four columns of row
-    // 16 a + 8 h + (rl & 7), in the 32 columns of the blocks 2j and 2j + 1.  (On the edge every access is
-    // compared with the rows and columns left from the lane's first one, 32-bit numbers: 110 and 86 vector
-    // registers of the edge kernels with sums spill, against 116 and 99 with 64-bit coordinates.)
-    auto left = [](int64_t n) { return (int)(n < BM ? n : BM); };
-    auto load4 = [&](auto full_tag, const float* base, int64_t ld, int64_t mw, int64_t nw, int j, int a, int h) -> v4f {
-      const float* p = base + (mw + 16 * a + 8 * h) * ld + nw + 32 * j;
-      if (decltype(full_tag)::value) return *reinterpret_cast<const v4fu*>(p);
-      const int rows = left(M - mw), cols = left(N - nw);
-      if (16 * a + 8 * h < rows && 32 * j + 3 < cols) return *reinterpret_cast<const v4fu*>(p);
-      v4f x = {0.f, 0.f, 0.f, 0.f};
-      if (16 * a + 8 * h < rows) {
-#pragma unroll
-        for (int v = 0; v < 3; ++v)
-          if (32 * j + v < cols) x[v] = p[v];
-      }
-      return x;
-    };
-    // Accumulate mode: the first eighth of the lane's elements of C is fetched before the last two
-    // K-tiles (more of them do not fit the registers), the rest while the epilogue runs, sixteen
-    // accesses ahead.
-    v4f cx[MODE == kGemmAccum ? TM : 1][2];
     // (read here and not ahead of the last epilogue, which needs the registers)
 #pragma unroll
     for (int r = 0; r < TM + TN; ++r) fread(abuf, g & 1, 0, r);
     ktile(std::integral_constant<int, kFirst>());
-    for (int kt = 1; kt < nk - (MODE == kGemmAccum ? 2 : 1); ++kt) ktile(std::integral_constant<int, kMiddle>());
-    if (MODE == kGemmAccum) {
-      const int ln = fresh_lane();
-      const int64_t mw = m0 + wm * (BM / 2) + (ln & 7), nw = n0 + wn * (BN / 2) + 16 * ((ln >> 3) & 1) + 4 * (ln >> 4);
-      if (full) {
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(std::true_type(), ep.C, ep.ldc, mw, nw, 0, a, h);
-      } else {
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(std::false_type(), ep.C, ep.ldc, mw, nw, 0, a, h);
-      }
-      if (nk > 2) ktile(std::integral_constant<int, kPastC>());
-    }
+    for (int kt = 1; kt < nk - 1; ++kt) ktile(std::integral_constant<int, kMiddle>());
     ktile(std::integral_constant<int, kLast>());
 
     // ================= epilogue of tile (tile_m, tile_n): acc[a][b][v] is element
     // (16 a + rl, 16 b + 4 quad + v) of the wave's 128 x 128 block
     wait_loads_but<kLoads>();                       // the scales (older than the last eight loads)
     __syncthreads();
+    // (the accumulators are read through assembly, where the compiler does not see to the distance from the last MFMA)
+    asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");
     const int ln = fresh_lane();
     const int quad = ln >> 4, rl = ln & 15;         // the lane's columns 4*quad.. and its row of a 16 x 16 block
-    const int64_t mw = m0 + wm * (BM / 2) + (rl & 7), nw = n0 + wn * (BN / 2) + 16 * (rl >> 3) + 4 * quad;
     const float* sc_row = reinterpret_cast<const float*>(lds + sbuf * kOperand) + wm * (BM / 2) + rl;
     const float* sc_col = reinterpret_cast<const float*>(lds + sbuf * kOperand) + BM + wn * (BN / 2) + 4 * quad;
-    // C goes around the caches (it would evict the FP32 operands the next stages stream), except
-    // between the two products of a pair: the first leaves its tile cached for the second
     const bool do_scale = SCALE && prod == nprod - 1;
-    // (alpha, beta and the stride of Cin are read here, not kept in registers through the K loop)
+    // (alpha, beta and the strides are read here, not kept in registers through the K loop)
     const float alpha = SCALE ? ep.alpha : 1.f, beta = SCALE ? ep.beta : 0.f;
     const bool has_beta = SCALE && do_scale && beta != 0.f;
     const int64_t ldcin = SCALE ? ep.ldcin : 0;
-    auto bands = [&](auto full_tag, auto cached_store_tag) {
-      constexpr bool FULL = decltype(full_tag)::value, CSTORE = decltype(cached_store_tag)::value;
-      if (MODE == kGemmAccum) {
+    auto left = [](int64_t n) { return (int)(n < BM ? n : BM); };
+    // elements of block (a, j), scaled, in the layout C is stored in
+    auto block_of = [&](int a, int j, float sr, v4f c0, v4f c1, v4f (&t)[2]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int a = kAhead; a < TM; ++a)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(full_tag, ep.C, ep.ldc, mw, nw, 0, a, h);
+      for (int v = 0; v < 4; ++v) {
+        t[0][v] = acc_value(acc[a][2 * j][v]) * (sr * c0[v]);
+        t[1][v] = acc_value(acc[a][2 * j + 1][v]) * (sr * c1[v]);
       }
+      exchange_half_rows(t[0], t[1]);
+    };
+    const int64_t ldc4 = 4 * ep.ldc;
+    auto lane_bytes = [&](int64_t ld4) { return (uint32_t)(ln & 7) * (uint32_t)ld4 + 64u * ((ln >> 3) & 1) + 16u * quad; };
+    auto first_row = [&](const float* base, int64_t ld) { return (uint64_t)(uintptr_t)(base + (m0 + wm * (BM / 2)) * ld + n0 + wn * (BN / 2)); };
+    // ---- accumulate mode, a whole tile: the tile's C goes through a ring of kRing blocks of 16 x 32 (two accesses
+    // of eight rows each), loaded kRing blocks ahead of their turn.  Block i is column j_of(i) of row a_of(i) of
+    // the blocks; row addresses are running (scalar) pointers.  CACHED: the first product of a pair leaves its
+    // tile of C cached for the second; the last one goes around the caches (it would evict the FP32 operands
+    // the next stages stream)
+    auto add_to_c = [&](auto cached_tag, auto scaled_tag, auto beta_tag) {
+      constexpr bool CACHED = decltype(cached_tag)::value, SCALED = decltype(scaled_tag)::value, BETA = decltype(beta_tag)::value;
+      constexpr int kBlocks = TM * TN / 2, kRing = EDGE ? 8 : 12, kIn = 4;   // kIn: blocks of Cin ahead
+      auto a_of = [](int i) constexpr { return i / JN % TM; };
+      auto j_of = [](int i) constexpr { return i / (TM * JN) * JN + i % JN; };
+      // from a block's rows to the next one's
+      auto next = [&](uint64_t& p, int i, int64_t ld4) __attribute__((always_inline)) {
+        if (i % JN != JN - 1) return;
+        p += a_of(i) == TM - 1 ? -(TM - 1) * 16 * ld4 : 16 * ld4;
+        asm volatile("" : "+s"(p));
+      };
+      const uint32_t lane = lane_bytes(ldc4), in_lane = BETA ? lane_bytes(4 * ldcin) : 0;
+      uint64_t c_next = first_row(ep.C, ep.ldc), c_out = c_next, in_next = BETA ? first_row(ep.Cin, ldcin) : 0;
+      v4f cx[kRing][2], cin[BETA ? kIn : 1][2];
+      auto load_c = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) cx[i % kRing][h] = row_load(c_next, lane + 128 * j_of(i), h * 8 * (uint32_t)ldc4);
+        next(c_next, i, ldc4);
+      };
+      auto load_in = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) cin[BETA ? i % kIn : 0][h] = row_load(in_next, in_lane + 128 * j_of(i), h * 32 * (uint32_t)ldcin);
+        next(in_next, i, 4 * ldcin);
+      };
+#pragma unroll
+      for (int i = 0; i < kRing; ++i) load_c(i);
+      if (BETA) {
+#pragma unroll
+        for (int i = 0; i < kIn; ++i) load_in(i);
+      }
+      float srow[TM];
+      v4f sc[2 * JN];
+#pragma unroll
+      for (int a = 0; a < TM; ++a) srow[a] = sc_row[16 * a];
+#pragma unroll
+      for (int i = 0; i < kBlocks; ++i) {
+        const int a = a_of(i), j = j_of(i), jl = i % JN;
+        if (a == 0) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) sc[2 * jl + e] = *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16 * e);
+        }
+        v4f t[2];
+        block_of(a, j, srow[a], sc[2 * jl], sc[2 * jl + 1], t);
+        // (the K-tiles in flight, before the first store: they are older than the loads issued here)
+        if (i == 0) wait_loads_but<2 * kRing + (BETA ? 2 * kIn : 0)>();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          v4f out;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            out[v] = cx[i % kRing][h][v] + t[h][v];
+            if (SCALED) out[v] = alpha * out[v];
+            if (BETA) out[v] = out[v] + beta * cin[BETA ? i % kIn : 0][h][v];
+          }
+          row_store<CACHED>(out, c_out, lane + 128 * j, h * 8 * (uint32_t)ldc4);
+        }
+        next(c_out, i, ldc4);
+        if (i + kRing < kBlocks) load_c(i + kRing);
+        if (BETA && i + kIn < kBlocks) load_in(i + kIn);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // ---- accumulate mode, a tile on the edge: sixteen rows at a time (a ring through the branches spills)
+    auto add_to_edge = [&](auto elems_tag, int rows, int cols) {
+      constexpr bool ELEMS = decltype(elems_tag)::value;
+      const int r8 = ln & 7, c16 = 16 * ((ln >> 3) & 1) + 4 * quad;
+      uint64_t c_row = first_row(ep.C, ep.ldc), in_row = has_beta ? first_row(ep.Cin, ldcin) : 0;
+      wait_loads();                                  // (the K-tiles in flight, before the first store)
+#pragma unroll
+      for (int a = 0; a < TM; ++a) {
+        if (16 * a < rows) {
+          const float sr = sc_row[16 * a];
+          v4f x[TN / 2][2];
+#pragma unroll
+          for (int j = 0; j < TN / 2; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) x[j][h] = edge_load<ELEMS>(c_row, ldc4, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < TN / 2; ++j) {
+            v4f t[2];
+            block_of(a, j, sr, *reinterpret_cast<const v4f*>(sc_col + 32 * j), *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16), t);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              v4f out, cin = {0.f, 0.f, 0.f, 0.f};
+              if (SCALE && has_beta) cin = edge_load<ELEMS>(in_row, 4 * ldcin, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols);
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                out[v] = x[j][h][v] + t[h][v];
+                if (SCALE && do_scale) {
+                  out[v] = alpha * out[v];
+                  if (has_beta) out[v] = out[v] + beta * cin[v];
+                }
+              }
+              edge_store<ELEMS>(out, c_row, ldc4, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        c_row += 16 * ldc4;
+        in_row += 64 * ldcin;
+        asm volatile("" : "+s"(c_row), "+s"(in_row));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // ---- first mode.  EDGES: 0 a whole tile, 1 a tile on the edge, 2 one whose last columns are not a whole access
+    // (rows x cols of the wave's block exist)
+    auto write_c = [&](auto edges_tag, int rows, int cols) {
+      constexpr int EDGES = decltype(edges_tag)::value;
+      const int r8 = ln & 7, c16 = 16 * ((ln >> 3) & 1) + 4 * quad;
+      uint64_t c_row = first_row(ep.C, ep.ldc), in_row = has_beta ? first_row(ep.Cin, ldcin) : 0;
+      const uint32_t lane = lane_bytes(ldc4), in_lane = SCALE ? lane_bytes(4 * ldcin) : 0;
       // |D_F| is added up in FP32 over a lane's 16 columns of 64 resp. 4 rows of 64 and in double from there
       float srow[TM], r1[TM], r2[TM];                // row scales; the lane's sums of the columns 0-63 and 64-127
 #pragma unroll
       for (int a = 0; a < TM; ++a) srow[a] = sc_row[16 * a];
-      // element (row of the 16 x 16 block, column) exists
       const int64_t me = m0 + wm * (BM / 2) + rl, ne = n0 + wn * (BN / 2) + 4 * quad;
-      int rows_e = FULL ? 0 : left(M - me), cols_e = FULL ? 0 : left(N - ne);
-      int rows_w = FULL ? 0 : left(M - mw), cols_w = FULL ? 0 : left(N - nw);
 #pragma unroll
       for (int j = 0; j < TN / 2; ++j) {
         v4f sc[2], q1[2], q2[2], q4[2];              // column scales; column sums of 2, 2 and 4 rows
@@ -378,12 +517,14 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
         for (int e = 0; e < 2; ++e) sc[e] = *reinterpret_cast<const v4f*>(sc_col + 32 * j + 16 * e);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
-          // (the comparisons are made afresh in every step: kept, their masks spill 94 scalar registers, not 17)
-          if (!FULL) asm volatile("" : "+v"(rows_e), "+v"(cols_e), "+v"(rows_w), "+v"(cols_w));
+          // (the comparisons are made afresh in every step: kept, their masks spill scalar registers)
+          if (EDGES) asm volatile("" : "+s"(rows), "+s"(cols));
           v4f cin[2];
           if (SCALE && has_beta) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) cin[h] = load4(full_tag, ep.Cin, ldcin, mw, nw, j, a, h);
+            for (int h = 0; h < 2; ++h)
+              cin[h] = EDGES ? edge_load<EDGES == 2>(in_row, 4 * ldcin, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols)
+                             : row_load(in_row, in_lane + 128 * j, h * 32 * (uint32_t)ldcin);
           }
           v4f d[2];
           float rs[2];
@@ -391,8 +532,8 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
           for (int e = 0; e < 2; ++e) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              d[e][v] = (float)acc[a][2 * j + e][v] * (srow[a] * sc[e][v]);
-              if (!FULL && SUMS && !(16 * a < rows_e && 32 * j + 16 * e + v < cols_e)) d[e][v] = 0.f;
+              d[e][v] = acc_value(acc[a][2 * j + e][v]) * (srow[a] * sc[e][v]);
+              if (EDGES && SUMS && !(16 * a + rl < rows && 32 * j + 16 * e + 4 * quad + v < cols)) d[e][v] = 0.f;
             }
             if (SUMS) {
               rs[e] = (fabsf(d[e][0]) + fabsf(d[e][1])) + (fabsf(d[e][2]) + fabsf(d[e][3]));
@@ -406,53 +547,42 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
             }
           }
           if (SUMS) {
+            // (the sums are formed here: nothing but this keeps the compiler from putting them off, with all they add
+            // up, to the end)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) asm volatile("" : "+v"(rs[e]), "+v"(q1[e][0]), "+v"(q1[e][1]), "+v"(q1[e][2]), "+v"(q1[e][3]));
             const float r = rs[0] + rs[1];
             if (j == 0) r1[a] = r;
             if (j == 1) r1[a] += r;
             if (j == 2) r2[a] = r;
             if (j == 3) r2[a] += r;
           }
-          // lanes 8-15 of a row of sixteen trade their block 2j for the block 2j + 1 of lanes 0-7
-          v4f t[2];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int d0 = __float_as_int(d[0][v]), d1 = __float_as_int(d[1][v]);
-            t[0][v] = __int_as_float(__builtin_amdgcn_update_dpp(d0, d1, 0x128, 0xf, 0xc, false));
-            t[1][v] = __int_as_float(__builtin_amdgcn_update_dpp(d1, d0, 0x128, 0xf, 0x3, false));
-          }
+          exchange_half_rows(d[0], d[1]);
           if (j == 0 && a == 0) wait_loads();        // the K-tiles in flight, before the first store
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             v4f out;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              out[v] = MODE == kGemmFirst ? t[h][v] : cx[MODE == kGemmAccum ? a : 0][h][v] + t[h][v];
+              out[v] = d[h][v];
               if (SCALE && do_scale) {
                 out[v] = alpha * out[v];
                 if (has_beta) out[v] = out[v] + beta * cin[h][v];
               }
             }
-            float* p = ep.C + (mw + 16 * a + 8 * h) * ep.ldc + nw + 32 * j;
-            if (FULL || (16 * a + 8 * h < rows_w && 32 * j + 3 < cols_w)) {
-              if (CSTORE) *reinterpret_cast<v4fu*>(p) = out;
-              else __builtin_nontemporal_store(out, reinterpret_cast<v4fu*>(p));
-            } else if (16 * a + 8 * h < rows_w) {
-#pragma unroll
-              for (int v = 0; v < 3; ++v)
-                if (32 * j + v < cols_w) p[v] = out[v];
-            }
+            if (EDGES) edge_store<EDGES == 2>(out, c_row, ldc4, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols);
+            else row_store<false>(out, c_row, lane + 128 * j, h * 8 * (uint32_t)ldc4);
           }
-          if (MODE == kGemmAccum && j + 1 < TN / 2) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) cx[MODE == kGemmAccum ? a : 0][h] = load4(full_tag, ep.C, ep.ldc, mw, nw, j + 1, a, h);
-          }
+          c_row += a == TM - 1 ? -(TM - 1) * 16 * ldc4 : 16 * ldc4;
+          if (SCALE) in_row += a == TM - 1 ? -(TM - 1) * 64 * ldcin : 64 * ldcin;
+          asm volatile("" : "+s"(c_row), "+s"(in_row));
           __builtin_amdgcn_sched_barrier(0);
         }
         if (SUMS) {
           // the 16 rows of a block: lane rl gets the sum of its value rl >> 1
           const double c = column_sum8(col8, rl);
           const int at = 32 * j + 16 * (rl >> 3) + ((rl >> 1) & 3);
-          if (!(rl & 1) && (FULL || (m0 + wm * (BM / 2) < M && at < cols_e)))
+          if (!(rl & 1) && (!EDGES || at + 4 * quad < cols))
             ep.col_part[(int64_t)(2 * tile_m + wm) * N + ne + at] = c;
         }
       }
@@ -462,14 +592,31 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
           double r = (double)r1[a] + (double)r2[a];
           r += __shfl_xor(r, 16, 64);
           r += __shfl_xor(r, 32, 64);
-          if (quad == 0 && (FULL || (16 * a < rows_e && n0 + wn * (BN / 2) < N)))
+          if (quad == 0 && (!EDGES || 16 * a + rl < rows))
             ep.row_part[(int64_t)(2 * tile_n + wn) * M + me + 16 * a] = r;
         }
       }
     };
-    if (EDGE && !full) bands(std::integral_constant<bool, !EDGE>(), std::true_type());
-    else if (MODE == kGemmAccum && two && prod == 0) bands(std::true_type(), std::true_type());
-    else bands(std::true_type(), std::false_type());
+    if (EDGE && !full) {
+      const int rows = left(M - m0 - wm * (BM / 2)), cols = left(N - n0 - wn * (BN / 2));
+      const bool whole = cols >= BN / 2 || (cols & 3) == 0;
+      if (rows <= 0 || cols <= 0) wait_loads();
+      else if constexpr (MODE == kGemmFirst) {
+        if (whole) write_c(std::integral_constant<int, 1>(), rows, cols);
+        else write_c(std::integral_constant<int, 2>(), rows, cols);
+      } else {
+        if (whole) add_to_edge(std::false_type(), rows, cols);
+        else add_to_edge(std::true_type(), rows, cols);
+      }
+    } else if constexpr (MODE == kGemmFirst) {
+      write_c(std::integral_constant<int, 0>(), BM, BN);
+    } else if (SCALE ? !do_scale : two && prod == 0) {   // (another product or kernel adds to this tile)
+      add_to_c(std::true_type(), std::false_type(), std::false_type());
+    } else if (has_beta) {
+      add_to_c(std::false_type(), std::integral_constant<bool, SCALE>(), std::integral_constant<bool, SCALE>());
+    } else {
+      add_to_c(std::false_type(), std::integral_constant<bool, SCALE>(), std::false_type());
+    }
     // everybody has read its scales: the A buffer that held them may be loaded again (a bare
     // barrier: the stores of C stay in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
@@ -492,6 +639,7 @@ bool gemm_persistent_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64
   if (ep.D_int || ep.D_F_copy) return false;                 // parity-check outputs use the plain kernel
   if (M <= 0 || N <= 0 || K <= 0 || K <= BK || (K % 64)) return false;   // (two K-tiles at least)
   if (lda >= (1 << 23) || ldb >= (1 << 23)) return false;    // byte offsets within a tile are 32-bit
+  if (ep.ldc >= (1 << 25) || (ep.final_scale && ep.beta != 0.f && ep.ldcin >= (1 << 25))) return false;   // ... and within 16 rows of C
   if (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) || (lda % 16) || (ldb % 16))
     return false;
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -558,8 +706,11 @@ hipError_t launch_gemm_i8_persistent(int64_t M, int64_t N, int64_t K, const int8
                GemmSecond);
   GemmSecond sec = {nullptr, nullptr, 0, 0, nullptr, nullptr};
   if (second && ep.mode == kGemmAccum) sec = *second;
-#define SRQ_KERN(MODE, SUMS, SCALE) \
-  (edge ? gemm_i8_persistent_kernel<MODE, SUMS, SCALE, true> : gemm_i8_persistent_kernel<MODE, SUMS, SCALE, false>)
+#define SRQ_KERN(MODE, SUMS, SCALE)                                                  \
+  (!edge                                                                           \
+       ? gemm_i8_persistent_kernel<MODE, SUMS, SCALE, false, 1>                    \
+       : MODE == kGemmAccum && ep.ldc % 1024 ? gemm_i8_persistent_kernel<MODE, SUMS, SCALE, true, MODE == kGemmAccum ? 4 : 1> \
+                                             : gemm_i8_persistent_kernel<MODE, SUMS, SCALE, true, 1>)
   // (sums come with a correction after this product, alpha and beta with the last one)
   if (sums && scale) return hipErrorInvalidValue;
   kern = ep.mode != kGemmFirst ? (scale ? SRQ_KERN(kGemmAccum, false, true) : SRQ_KERN(kGemmAccum, false, false))
