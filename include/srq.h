@@ -173,7 +173,8 @@ srq_status_t srq_set_auto_hint(srq_handle_t handle, int path_a, int path_b);
  * `enable`: 0 = off, SRQ_PROFILE_ALL = every stage, SRQ_PROFILE_PRODUCTS = only the three
  * products (SRQ_STAGE_GEMM, SRQ_STAGE_TERM1, SRQ_STAGE_TERM2; the other entries read 0): an event
  * record costs the call about 3 microseconds, since the kernel after it cannot start under the
- * tail of the kernel before it. */
+ * tail of the kernel before it.  Small calls with K up to 256 run as two launches that hold the other stages too:
+ * SRQ_STAGE_GEMM and SRQ_STAGE_TERM1; with SRQ_PROFILE_ALL their stages are launches of their own. */
 enum { SRQ_PROFILE_ALL = 1, SRQ_PROFILE_PRODUCTS = 2 };
 enum {
   SRQ_STAGE_QUANTIZE = 0,   /* amax, scales, codes of A and B, max |residual|             */

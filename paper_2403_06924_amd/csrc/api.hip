@@ -783,6 +783,47 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   };
   const bool strips = strips_ok(M, N, K) && !global_scale &&
                       !(comp && ((term_a && reads_em(h->last_path_a)) || (term_b && reads_em(h->last_path_b))));
+  GemmEpilogue ep;
+  memset(&ep, 0, sizeof(ep));
+  ep.mode = kGemmFirst;
+  ep.s_row = p.s_a; ep.s_col = p.s_b; ep.C = C; ep.ldc = ldc;
+  ep.alpha = alpha; ep.beta = beta; ep.Cin = Cin; ep.ldcin = ldcin;
+  ep.ldd = N;
+  if (dbg) { ep.D_int = dbg->D_int; ep.D_F_copy = dbg->D_F; }
+  if (comp) { ep.row_part = p.row_part; ep.col_part = p.col_part; }
+  ep.final_scale = !comp && scale_needed;
+  // A short inner dimension and few tiles: two launches, one without compensation (booked as the products; with every
+  // stage timed the stages stay launches of their own).  The compressed arrays have to hold any selection:
+  // nothing counts the kept entries before the corrections.
+  const bool every_stage = h->prof_enabled && ((h->prof_mask >> SRQ_STAGE_QUANTIZE) & 1u);
+  if (!dbg && !global_scale && !every_stage && (!comp || (strategy == SRQ_STRATEGY_CSR_MFMA && dense_fallback_density > 1.f &&
+                                          (!term_a || p.cap_a >= M * K) && (!term_b || p.cap_b >= N * K)))) {
+    GemmEpilogue last = ep;
+    last.final_scale = scale_needed;
+    if (short_ok(M, N, K, lda, ldb, last)) {
+      const ShortCall g = {A, B, lda, ldb, (int)M, (int)N, (int)K, trunc, (float)qmax, theta_a, theta_b, term_a, term_b,
+                           p.A_int, p.B_int, p.RA_int, p.RB_int, p.s_a, p.lam_a, p.s_ra, p.s_b, p.lam_b, p.s_rb,
+                           p.row_part, p.col_part, p.drow, p.dcol, p.t_a, p.t_b, p.tot_a, p.tot_b,
+                           {p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.nnz + 0}, {p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.nnz + 1}};
+      {
+        StageTimer tm(h, st, SRQ_STAGE_GEMM);
+        SRQ_HIP(h, launch_short_first(g, comp, ep, st));
+      }
+      if (comp) {
+        StageTimer tm(h, st, SRQ_STAGE_TERM1);
+        SRQ_HIP(h, launch_short_second(g, last, st));
+        im.s_ra = p.s_ra; im.s_rb = p.s_rb;
+        im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
+        if (term_a) { im.a_ptr = p.a_ptr; im.a_idx = p.a_idx; im.a_val = p.a_val; im.capacity_a = p.cap_a; im.RB_int = p.RB_int; }
+        if (term_b) { im.b_ptr = p.b_ptr; im.b_idx = p.b_idx; im.b_val = p.b_val; im.capacity_b = p.cap_b; im.RA_int = p.RA_int; }
+      }
+      if (stats_dev)
+        SRQ_HIP(h, launch_stats(comp && term_a ? p.nnz : nullptr, comp && term_b ? p.nnz + 1 : nullptr, comp && term_a ? kPathMfma : 0,
+                                comp && term_b ? kPathMfma : 0, comp && term_a ? p.cap_a : kNoCap, comp && term_b ? p.cap_b : kNoCap,
+                                stats_dev, st));
+      return SRQ_STATUS_OK;
+    }
+  }
   bool ra_vm_done = false, ra_em_done = false, rb_vm_done = false, rb_em_done = false;
   bool rb_in_select = false, rb_want_em = false, rb_want_vm = false;   // residual codes of B left to the selection pass
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
@@ -887,15 +928,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   }
 
   // lines 2-3: D_int = A_int.B_int, D_F = dequant; line 7: partial sums of |D_F|
-  GemmEpilogue ep;
-  memset(&ep, 0, sizeof(ep));
-  ep.mode = kGemmFirst;
-  ep.s_row = p.s_a; ep.s_col = p.s_b; ep.C = C; ep.ldc = ldc;
-  ep.alpha = alpha; ep.beta = beta; ep.Cin = Cin; ep.ldcin = ldcin;
-  ep.ldd = N;
-  if (dbg) { ep.D_int = dbg->D_int; ep.D_F_copy = dbg->D_F; }
-  if (comp) { ep.row_part = p.row_part; ep.col_part = p.col_part; }
-  ep.final_scale = !comp && scale_needed;
   {
     StageTimer tm(h, st, SRQ_STAGE_GEMM);
     SRQ_HIP(h, launch_gemm_i8(M, N, Kc, p.A_int, Kc, p.B_int, Kc, ep, st));

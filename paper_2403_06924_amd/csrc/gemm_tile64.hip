@@ -23,7 +23,7 @@
 // 256: 262 us.)
 #include "srq_internal.h"
 #include "gemm_tiles.h"
-#include "gemm_lanes.h"
+#include "gemm_tile64.h"
 
 namespace srq {
 namespace {
@@ -155,55 +155,13 @@ __global__ __launch_bounds__(256, NST >= 8 ? 1 : 12 / NST) void gemm_i8_tile64_k
       srow[i] = buf_load_f32(rsr, 4u * (uint32_t)(32 * wm + 16 * i + rl));
       scol[i] = buf_load_4(rsc, 4u * (uint32_t)(32 * wn + 16 * i + 4 * quad), full);
     }
-    double col8[8];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      v4f t[2];
-      double r = 0.0;
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          t[b][v] = (float)acc[p][a][b][v] * (srow[a] * scol[b][v]);
-          if (SUMS) {
-            const double d = (double)fabsf(t[b][v]);
-            r += d;
-            col8[4 * b + v] = a == 0 ? d : col8[4 * b + v] + d;
-          }
-        }
-      if (SUMS) {
-        r += __shfl_xor(r, 16, 64);
-        r += __shfl_xor(r, 32, 64);
-        if (quad == 0) rowx[wn * BT + 32 * wm + 16 * a + rl] = r;
-      }
-      exchange_half_rows(t[0], t[1]);
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) out[2 * a + h][v] = (p || read_c) ? out[2 * a + h][v] + t[h][v] : t[h][v];
-    }
+    tile64_product<SUMS>(acc[p], srow, scol, p || read_c, out, wm, wn, quad, rl, rowx, colx);
     if (SUMS) {
-      // sums of |D_F| over the tile's 64 columns and rows, in double: the thresholds they become are
-      // then the same whatever kernel formed the product.  Columns: the 16 lanes' 8 values each end
-      // up one per pair of lanes (value rl >> 1).
-      const double c = column_sum8(col8, rl);
-      if (!(rl & 1)) colx[wm * BT + 32 * wn + 16 * (rl >> 3) + 4 * quad + ((rl >> 1) & 3)] = c;
       __syncthreads();
-      if ((uint32_t)tid < rows_a)
-        ep.row_part[(int64_t)tile_n * M + m0 + tid] = rowx[tid] + rowx[BT + tid];
-      if (tid >= 64 && (uint32_t)(tid - 64) < rows_b)
-        ep.col_part[(int64_t)tile_m * N + n0 + tid - 64] = colx[tid - 64] + colx[tid];
+      tile64_store_sums(ep, tid, M, N, tile_m, tile_n, rows_a, rows_b, rowx, colx);
     }
   }
-  if (ep.final_scale) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        out[i][v] = ep.alpha * out[i][v];
-        if (has_beta) out[i][v] = out[i][v] + ep.beta * cin[i][v];
-      }
-  }
+  if (ep.final_scale) tile64_scale(ep, has_beta, out, cin);
   tile.store(out, ep.C + m0 * ep.ldc + n0, (uint32_t)ep.ldc);
 }
 

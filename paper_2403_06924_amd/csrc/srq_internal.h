@@ -289,6 +289,30 @@ hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_
 hipError_t launch_reduce_cols(const StripReduce& s, int64_t N, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st);
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st);
 
+// ---- an inner dimension of at most 256 and few tiles of C: the whole call in two launches (short.hip).  Code matrices
+// have rows of K rounded up to 128.  state_a / state_b: a word per sixteen rows of A / columns of B.
+struct ShortCompact {
+  int32_t *ptr, *idx;
+  int8_t* val;
+  int64_t capacity, *nnz;
+};
+struct ShortCall {
+  const float *A, *B;
+  int64_t lda, ldb;
+  int M, N, K, trunc;
+  float qmax, theta_a, theta_b;
+  bool term_a, term_b;
+  int8_t *Qa, *Qb, *Ra, *Rb;
+  float *s_a, *lam_a, *s_ra, *s_b, *lam_b, *s_rb;
+  double *row_part, *col_part;
+  float *drow, *dcol, *t_a, *t_b;
+  int32_t *state_a, *state_b;
+  ShortCompact ca, cb;
+};
+bool short_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const GemmEpilogue& ep);
+hipError_t launch_short_first(const ShortCall& g, bool comp, const GemmEpilogue& ep, hipStream_t st);
+hipError_t launch_short_second(const ShortCall& g, const GemmEpilogue& ep, hipStream_t st);
+
 // thresholds from the partial sums of the GEMM epilogue
 hipError_t launch_reduce_means_pair(const double* part0, int64_t nparts0, int64_t n0, int64_t count0, float theta0,
                                     float* mean0, float* thresh0, const double* part1, int64_t nparts1,

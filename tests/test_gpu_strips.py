@@ -220,3 +220,35 @@ def test_thresholds_do_not_depend_on_the_execution(srq, b, shape):
                     assert x.tobytes() == y.tobytes()
     finally:
         srq.set_auto_hint(0, 0)
+
+
+# The two launches for K up to 256, at the edges of their 64 x 64 tiles, chunks of sixteen vectors and K-tiles, against the
+# same call with its stages as launches of their own (every stage timed): the same bits everywhere
+@pytest.mark.parametrize("shape", [(1, 16, 1), (15, 17, 3), (16, 64, 64), (63, 65, 127), (64, 1, 128), (129, 48, 129), (960, 896, 64),
+                                   (1000, 1023, 250), (17, 1024, 256), (1024, 33, 192), (1024, 1024, 256)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_two_launches_are_the_separate_ones(srq, b, shape, odd):
+    M, N, K = shape
+    gen = torch.Generator(device="cuda").manual_seed(M + 3 * N + 5 * K)
+    wide = 3 if odd else 0
+    A, B, Cin = (torch.randn((r, c + wide), generator=gen, device="cuda")[:, wide // 2:wide // 2 + c] for r, c in ((M, K), (K, N), (M, N)))
+    A[M // 2] = 0
+    B[:, N // 2] = 0
+    for ta, tb, beta, bits, rounding in ((0.02, 0.02, 0.0, 8, b.ROUND_NEAREST_EVEN), (0.01, np.inf, -0.75, 4, b.ROUND_TRUNC),
+                                         (np.inf, 0.0, 0.5, 8, b.ROUND_NEAREST_EVEN), (np.inf, np.inf, 0.5, 5, b.ROUND_TRUNC)):
+        got = []
+        for separate in (False, True):
+            srq.profile_enable(separate)
+            stats, out = b.stats_tensor(), torch.full((M, N + wide), -5.0, device="cuda")
+            try:
+                srq.compensated_gemm(A, B, ta, tb, bits=bits, rounding=rounding, strategy=b.STRATEGY_CSR_MFMA, alpha=1.5, beta=beta,
+                                     C_in=Cin, out=out[:, :N], stats=stats)
+                torch.cuda.synchronize()
+            finally:
+                srq.profile_enable(False)
+            im = srq.intermediates(M, N, K)
+            got.append((out, stats, {k: v.clone() for k, v in im.items() if torch.is_tensor(v)}))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        assert got[0][2].keys() == got[1][2].keys()
+        for key, value in got[0][2].items():               # (bits: a threshold of an infinite factor and a zero mean is no number)
+            assert torch.equal(value.contiguous().view(torch.uint8), got[1][2][key].contiguous().view(torch.uint8)), key
