@@ -132,23 +132,6 @@ __device__ __forceinline__ void multiply(const int8_t* a, const int8_t* b, int w
 }
 
 // ---- quantization ----------------------------------------------------------------------------------
-// fl(x * lambda) rounded and clamped as quant_code does, plus 1.5 * 2^23: the code in two's complement is the low byte, and
-// code_value the code as a float (the addition rounds to the nearest even integer, exactly for what is one already)
-constexpr float kMagic = 12582912.f;
-template <bool TRUNC>
-__device__ __forceinline__ float biased_code(float x, float lam, float qmax) {
-  float y = x * lam;
-  if (TRUNC) y = truncf(y);
-  return fminf(fmaxf(y, -qmax), qmax) + kMagic;
-}
-__device__ __forceinline__ float code_value(float z) { return z - kMagic; }
-// the low bytes of the first n (at least 4: all) of four, zeros for the others
-__device__ __forceinline__ unsigned pack_codes(float z0, float z1, float z2, float z3, int n) {
-  unsigned p = __builtin_amdgcn_perm(__float_as_uint(z1), __float_as_uint(z0), 0x0c0c0400u);
-  p = __builtin_amdgcn_perm(__float_as_uint(z2), p, 0x0c040100u);
-  p = __builtin_amdgcn_perm(__float_as_uint(z3), p, 0x04020100u);
-  return n >= 4 ? p : p & ((1u << (8 * (n > 0 ? n : 0))) - 1u);
-}
 __device__ __forceinline__ float max_abs4(v4f x, float m) {
   return fmaxf(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))), m);
 }
@@ -189,7 +172,7 @@ __device__ __forceinline__ void quantize_rows(const ShortCall& g, int chunk) {
   for (int i = 0; i < NI; ++i) {
     v4f z;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) z[j] = biased_code<TRUNC>(x[i][j], lam, qmax);
+    for (int j = 0; j < 4; ++j) z[j] = biased_code(x[i][j], lam, qmax, TRUNC);
     const int n = left4(K - 64 * i - 4 * c);
     pk[i] = pack_codes(z[0], z[1], z[2], z[3], n);
     if (COMP) {
@@ -210,7 +193,7 @@ __device__ __forceinline__ void quantize_rows(const ShortCall& g, int chunk) {
   for (int i = 0; i < NI; ++i) {
     v4f z;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) z[j] = biased_code<TRUNC>(x[i][j], rlam, qmax);
+    for (int j = 0; j < 4; ++j) z[j] = biased_code(x[i][j], rlam, qmax, TRUNC);
     *reinterpret_cast<unsigned*>(g.Ra + (int64_t)row * KC + 64 * i + 4 * c) = pack_codes(z[0], z[1], z[2], z[3], left4(K - 64 * i - 4 * c));
   }
 }
@@ -250,7 +233,7 @@ __device__ __forceinline__ void quantize_cols(const ShortCall& g, int chunk, Chu
   auto put = [&](int8_t* Q, const v4f (&z)[R]) __attribute__((always_inline)) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const unsigned p = pack_codes(z[0][c], z[1][c], R == 4 ? z[R - 2][c] : kMagic, R == 4 ? z[R - 1][c] : kMagic, left4(K - row0));
+      const unsigned p = pack_codes(z[0][c], z[1][c], R == 4 ? z[R - 2][c] : kCodeBias, R == 4 ? z[R - 1][c] : kCodeBias, left4(K - row0));
       int8_t* dst = Q + (int64_t)(col + c) * KC + row0;
       if (c < ncol) {
         if (R == 4) *reinterpret_cast<unsigned*>(dst) = p;
@@ -273,7 +256,7 @@ __device__ __forceinline__ void quantize_cols(const ShortCall& g, int chunk, Chu
     sc[c] = quotient(m[c], qmax, m[c] > 0.f);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      z[i][c] = biased_code<TRUNC>(x[i][c], lam[c], qmax);
+      z[i][c] = biased_code(x[i][c], lam[c], qmax, TRUNC);
       if (COMP) {
         x[i][c] = row0 + i < K ? x[i][c] - code_value(z[i][c]) * sc[c] : 0.f;
         rm[c] = fmaxf(rm[c], fabsf(x[i][c]));
@@ -290,7 +273,7 @@ __device__ __forceinline__ void quantize_cols(const ShortCall& g, int chunk, Chu
     const float rlam = quotient(qmax, rm[c], rm[c] > 0.f);
     rs[c] = quotient(rm[c], qmax, rm[c] > 0.f);
 #pragma unroll
-    for (int i = 0; i < R; ++i) z[i][c] = biased_code<TRUNC>(x[i][c], rlam, qmax);
+    for (int i = 0; i < R; ++i) z[i][c] = biased_code(x[i][c], rlam, qmax, TRUNC);
   }
   put(g.Rb, z);
   if (tid < 4) store_part(g.s_rb + col, rs, ncol);
@@ -351,7 +334,7 @@ __global__ __launch_bounds__(256) void short_first_kernel(ShortCall g, int tiles
     for (int i = 0; i < KC / 64; ++i) {
       v4f z;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) z[j] = biased_code<TRUNC>(a.x[gr][i][j], lam, qmax);
+      for (int j = 0; j < 4; ++j) z[j] = biased_code(a.x[gr][i][j], lam, qmax, TRUNC);
       *reinterpret_cast<unsigned*>(ta + lds_at(row, a.elem(i))) = pack_codes(z[0], z[1], z[2], z[3], left4(K - a.elem(i)));
     }
     if (rl == 0) s_row[row] = quotient(amax, qmax, amax > 0.f);
@@ -373,7 +356,7 @@ __global__ __launch_bounds__(256) void short_first_kernel(ShortCall g, int tiles
     for (int i = 0; i < R; i += 4) {
       float z[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) z[j] = biased_code<TRUNC>(b.x[i + j][c], lam, qmax);
+      for (int j = 0; j < 4; ++j) z[j] = biased_code(b.x[i + j][c], lam, qmax, TRUNC);
       pk[i / 4] = pack_codes(z[0], z[1], z[2], z[3], left4(K - k0 - i));
     }
     put_codes<R>(tb + lds_at(col + c, k0), pk);

@@ -44,6 +44,36 @@ static __device__ __forceinline__ float4 load_part(const float* p, int n) {
   return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
 }
 
+// The same without a branch, for rows of `len` (at least 4) values: the values at .. at + 3 of a row, zero from len on, in two
+// steps, so that many loads can be on their way together (a load behind a branch is waited for before the next
+// is issued): a load from a place that exists, and the shift to where it was wanted.
+static __device__ __forceinline__ f4u load_inside(const float* row, int at, int len) {
+  return *reinterpret_cast<const f4u*>(row + (at < len - 4 ? at : len - 4));
+}
+static __device__ __forceinline__ float4 shifted(f4u x, int at, int len) {
+  const int past = at - (len - 4);                   // <= 0: the load was where it was wanted
+  if (past <= 0) return make_float4(x.x, x.y, x.z, x.w);
+  return make_float4(past == 1 ? x.y : past == 2 ? x.z : past == 3 ? x.w : 0.f, past == 1 ? x.z : past == 2 ? x.w : 0.f,
+                     past == 1 ? x.w : 0.f, 0.f);
+}
+
+// fl(x * lambda) rounded and clamped as quant_code does, plus 1.5 * 2^23: the code in two's complement is the low byte, and
+// code_value the code as a float (the addition rounds to the nearest even integer, exactly for what is one already)
+constexpr float kCodeBias = 12582912.f;
+static __device__ __forceinline__ float biased_code(float x, float lam, float qmax, bool trunc) {
+  float y = x * lam;
+  if (trunc) y = truncf(y);
+  return fminf(fmaxf(y, -qmax), qmax) + kCodeBias;
+}
+static __device__ __forceinline__ float code_value(float z) { return z - kCodeBias; }
+// the low bytes of the first n of four, zeros for the others
+static __device__ __forceinline__ unsigned pack_codes(float z0, float z1, float z2, float z3, int n) {
+  unsigned p = __builtin_amdgcn_perm(__float_as_uint(z1), __float_as_uint(z0), 0x0c0c0400u);
+  p = __builtin_amdgcn_perm(__float_as_uint(z2), p, 0x0c040100u);
+  p = __builtin_amdgcn_perm(__float_as_uint(z3), p, 0x04020100u);
+  return n >= 4 ? p : p & ((1u << (8 * (n > 0 ? n : 0))) - 1u);
+}
+
 static __device__ __forceinline__ void store_part(float* p, const float (&v)[4], int n) {
   if (n >= 4) {
     *reinterpret_cast<f4u*>(p) = f4u{v[0], v[1], v[2], v[3]};

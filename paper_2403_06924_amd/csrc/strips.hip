@@ -49,22 +49,66 @@ __device__ __forceinline__ float block_max(float m, float* sm) {
   return m;
 }
 
+// A thread's NV4 pieces of a row (of every TH-th four values), zeros past K
+template <int TH, int NV4>
+__device__ __forceinline__ void load_row(float4 (&x)[NV4], int (&n)[NV4], const float* src, int K) {
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) {
+    const int e = 4 * (threadIdx.x + i * TH);
+    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
+  }
+  if (K < 4) {
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) x[i] = load_part(src + 4 * (threadIdx.x + i * TH), n[i]);
+    return;
+  }
+  f4u t[NV4];
+#pragma unroll
+  for (int i = 0; i < NV4; ++i) t[i] = load_inside(src, 4 * (threadIdx.x + i * TH), K);
+  if (K >= 4 * TH * NV4) {                           // (nobody reaches past K)
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) x[i] = make_float4(t[i].x, t[i].y, t[i].z, t[i].w);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) x[i] = shifted(t[i], 4 * (threadIdx.x + i * TH), K);
+  }
+}
+// A thread's patch of a strip: rows row0 .. row0 + RPT - 1 of four columns from col0 on, zeros outside
+template <int TH, int CG, int RPT>
+__device__ __forceinline__ void load_patch(float4 (&v)[RPT], const float* X, int64_t ldx, int strip, int row0, int64_t col0, int64_t cols,
+                                           int K) {
+  if (cols < 4) {
+    const int n = (int)(cols - col0);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) v[i] = load_part(X + (int64_t)(row0 + i) * ldx + col0, row0 + i < K ? n : 0);
+    return;
+  }
+  f4u t[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) t[i] = load_inside(X + (int64_t)(row0 + i < K ? row0 + i : K - 1) * ldx, (int)col0, (int)cols);
+  if (K >= TH / CG * RPT && (int64_t)(strip + 1) * 4 * CG <= cols) {   // (the whole strip exists)
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) v[i] = make_float4(t[i].x, t[i].y, t[i].z, t[i].w);
+  } else {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      v[i] = shifted(t[i], (int)col0, (int)cols);
+      if (row0 + i >= K) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+}
+
 // ---- quantization ----------------------------------------------------------------------------------
 // One row.  Codes go out up to the padded length (zeros past K); places past K stay out of the maxima of
 // the residual (0 * lam is not 0 where lam overflowed).
 template <int TH, int NV4>
 __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, int K, int Kc, float qmax, int trunc, float* sm) {
-  const float* src = s.X + row * s.ldx;
   float4 x[NV4];
   int n[NV4];
   float m = 0.f;
+  load_row<TH, NV4>(x, n, s.X + row * s.ldx, K);
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * TH);
-    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
-    x[i] = load_part(src + e, n[i]);
-    m = fmaxf(m, max4(abs4(x[i])));
-  }
+  for (int i = 0; i < NV4; ++i) m = fmaxf(m, max4(abs4(x[i])));
   const float amax = block_max<TH>(m, sm);
   float lam = 0.f, sc = 0.f;
   if (amax > 0.f) { lam = qmax / amax; sc = amax / qmax; }
@@ -72,15 +116,14 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     const int e = 4 * (threadIdx.x + i * TH);
-    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-    int q[4];
+    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w}, z[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      q[j] = j < n[i] ? quant_code(v[j], lam, qmax, trunc) : 0;
-      v[j] = v[j] - (float)q[j] * sc;
+      z[j] = biased_code(v[j], lam, qmax, trunc);
+      v[j] = j < n[i] ? v[j] - code_value(z[j]) * sc : 0.f;
       rm = fmaxf(rm, fabsf(v[j]));
     }
-    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack_codes(z[0], z[1], z[2], z[3], n[i]);
     x[i] = make_float4(v[0], v[1], v[2], v[3]);
   }
   if (threadIdx.x == 0) { s.scale[row] = sc; s.lambda[row] = lam; }
@@ -93,10 +136,10 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   for (int i = 0; i < NV4; ++i) {
     const int e = 4 * (threadIdx.x + i * TH);
     const float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-    int q[4];
+    float z[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = j < n[i] ? quant_code(v[j], rlam, qmax, trunc) : 0;
-    if (e < Kc) *reinterpret_cast<unsigned*>(s.Rq + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+    for (int j = 0; j < 4; ++j) z[j] = biased_code(v[j], rlam, qmax, trunc);
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Rq + row * Kc + e) = pack_codes(z[0], z[1], z[2], z[3], n[i]);
   }
   for (int e = K + threadIdx.x; e < Kc; e += TH) s.D[row * Kc + e] = 0;
 }
@@ -139,6 +182,31 @@ __device__ __forceinline__ void store_codes(int8_t* Q, int64_t ld, int lim, int6
   }
 }
 
+// codes of a patch, zeros from row K on; RESID: the patch becomes its residual, rm its columns' maxima
+template <int RPT, bool RESID>
+__device__ __forceinline__ void patch_codes(float4 (&v)[RPT], const float (&lam)[4], const float (&sc)[4], float qmax, bool trunc, int left,
+                                            unsigned (&pk)[4][RPT / 4], float (&rm)[4]) {
+#pragma unroll
+  for (int i = 0; i < RPT; i += 4) {
+    float z[4][4];                                   // [row][column]
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float x[4] = {v[i + r].x, v[i + r].y, v[i + r].z, v[i + r].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        z[r][c] = biased_code(x[c], lam[c], qmax, trunc);
+        if (RESID) {
+          x[c] = i + r < left ? x[c] - code_value(z[r][c]) * sc[c] : 0.f;   // (0 * lam is not 0 where lam overflowed)
+          rm[c] = fmaxf(rm[c], fabsf(x[c]));
+        }
+      }
+      if (RESID) v[i + r] = make_float4(x[0], x[1], x[2], x[3]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pk[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], left - i);
+  }
+}
+
 template <int TH, int CG, int RPT>
 __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, int64_t ldq, float qmax,
                                             int trunc, float* red) {
@@ -147,8 +215,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
   float4 v[RPT];
   float m[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, row0 + i < K ? ncol : 0);
+  load_patch<TH, CG, RPT>(v, s.X, s.ldx, strip, row0, col0, cols, K);
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const float4 a = abs4(v[i]);
@@ -163,19 +230,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   }
   if (rb == 0) { store_part(s.scale + col0, sc, ncol); store_part(s.lambda + col0, lam, ncol); }
   unsigned pk[4][RPT / 4];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int q = row0 + i < K ? quant_code(x[c], lam[c], qmax, trunc) : 0;
-      x[c] = x[c] - (float)q * sc[c];
-      rm[c] = fmaxf(rm[c], fabsf(x[c]));
-      if ((i & 3) == 0) pk[c][i >> 2] = 0;
-      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
-    }
-    v[i] = make_float4(x[0], x[1], x[2], x[3]);
-  }
+  patch_codes<RPT, true>(v, lam, sc, qmax, trunc, K - row0, pk, rm);
   store_codes<RPT>(s.Q, ldq, Kc, col0, ncol, row0, pk);
   if (!s.Rq) return;
   strip_max<TH, CG>(rm, red + TH / 16 * CG);
@@ -186,16 +241,7 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     rs[c] = rm[c] > 0.f ? rm[c] / qmax : 0.f;
   }
   if (rb == 0) { store_part(s.rscale + col0, rs, ncol); store_part(s.rlambda + col0, rlam, ncol); }
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int q = row0 + i < K ? quant_code(x[c], rlam[c], qmax, trunc) : 0;
-      if ((i & 3) == 0) pk[c][i >> 2] = 0;
-      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
-    }
-  }
+  patch_codes<RPT, false>(v, rlam, rs, qmax, trunc, K - row0, pk, rm);
   store_codes<RPT>(s.Rq, ldq, Kc, col0, ncol, row0, pk);
   for (int i = threadIdx.x; i < 4 * CG * (Kc - K); i += TH) {
     const int64_t col = (int64_t)strip * 4 * CG + i / (Kc - K);
@@ -238,15 +284,9 @@ template <int TH, int NV4>
 __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, double* dsm, int* ism) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int words = (K + 63) / 64;
-  const float* src = s.X + row * s.ldx;
   float4 x[NV4];
   int n[NV4];
-#pragma unroll
-  for (int i = 0; i < NV4; ++i) {                    // (on their way while the threshold is formed)
-    const int e = 4 * (tid + i * TH);
-    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
-    x[i] = load_part(src + e, s.mask ? n[i] : 0);
-  }
+  if (s.mask) load_row<TH, NV4>(x, n, s.X + row * s.ldx, K);   // (on their way while the threshold is formed)
   double sum = 0.0;
   for (int64_t p = tid; p < s.nparts; p += TH) sum += s.part[p * rows + row];
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
@@ -323,8 +363,7 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
   const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
   float4 v[RPT];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, s.mask && row0 + i < K ? ncol : 0);
+  if (s.mask) load_patch<TH, CG, RPT>(v, s.X, s.ldx, strip, row0, col0, cols, K);
   // partial sums: BC neighbouring columns by BC neighbouring threads
   const int64_t pc = (int64_t)strip * BC + (tid & (BC - 1));
   double sum = 0.0;
@@ -377,28 +416,22 @@ __global__ __launch_bounds__(TH) void reduce_rows_kernel(StripReduce s, int K, i
   float4 x[NV4];
   int n[NV4], total = 0;
   float rm = 0.f;
+  load_row<TH, NV4>(x, n, src, K);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     const int e = 4 * (tid + i * TH);
-    n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
-    x[i] = load_part(src + e, n[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (tid + i * TH);
-    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-    int q[4];
+    float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w}, z[4];
     unsigned nib = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       nib |= j < n[i] && fabsf(v[j]) > t ? 1u << j : 0u;
-      q[j] = j < n[i] ? quant_code(v[j], lam, qmax, trunc) : 0;
-      v[j] = v[j] - (float)q[j] * sc;
-      rm = j < n[i] ? fmaxf(rm, fabsf(v[j])) : rm;
+      z[j] = biased_code(v[j], lam, qmax, trunc);
+      v[j] = j < n[i] ? v[j] - code_value(z[j]) * sc : 0.f;
+      rm = fmaxf(rm, fabsf(v[j]));
     }
     total += __popc(nib);
     store_nibble(s.mask + row * words, words, e >> 2, nib);
-    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack4(q[0], q[1], q[2], q[3]);
+    if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack_codes(z[0], z[1], z[2], z[3], n[i]);
     x[i] = make_float4(v[0], v[1], v[2], v[3]);
   }
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
@@ -416,15 +449,15 @@ __global__ __launch_bounds__(TH) void reduce_rows_kernel(StripReduce s, int K, i
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     const int e = 4 * (tid + i * TH);
-    const int q[4] = {quant_code(x[i].x, rlam, qmax, trunc), quant_code(x[i].y, rlam, qmax, trunc),
-                      quant_code(x[i].z, rlam, qmax, trunc), quant_code(x[i].w, rlam, qmax, trunc)};
+    const unsigned p = pack_codes(biased_code(x[i].x, rlam, qmax, trunc), biased_code(x[i].y, rlam, qmax, trunc),
+                                  biased_code(x[i].z, rlam, qmax, trunc), biased_code(x[i].w, rlam, qmax, trunc), 4);
     int8_t* dst = s.Rq + row * s.ldr + e;
     if (n[i] == 4) {
-      *reinterpret_cast<u1u*>(dst) = pack4(q[0], q[1], q[2], q[3]);
+      *reinterpret_cast<u1u*>(dst) = p;
     } else {
 #pragma unroll
       for (int j = 0; j < 3; ++j)
-        if (j < n[i]) dst[j] = (int8_t)q[j];
+        if (j < n[i]) dst[j] = (int8_t)(p >> (8 * j));
     }
   }
 }
@@ -439,27 +472,21 @@ __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t 
   const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
   float4 v[RPT];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) v[i] = load_part(s.X + (int64_t)(row0 + i) * s.ldx + col0, row0 + i < K ? ncol : 0);
+  load_patch<TH, CG, RPT>(v, s.X, s.ldx, strip, row0, col0, cols, K);
   const float4 l4 = load_part(s.lambda + col0, ncol), s4 = load_part(s.scale + col0, ncol), t4 = load_part(s.thresh + col0, ncol);
   const float lam[4] = {l4.x, l4.y, l4.z, l4.w}, sc[4] = {s4.x, s4.y, s4.z, s4.w}, t[4] = {t4.x, t4.y, t4.z, t4.w};
   float rm[4] = {0.f, 0.f, 0.f, 0.f};
   unsigned bits[4] = {0, 0, 0, 0}, pk[4][RPT / 4];
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
-    float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+    const float4 a = abs4(v[i]);
     const bool ok = row0 + i < K;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      bits[c] |= ok && fabsf(x[c]) > t[c] ? 1u << i : 0u;
-      const int q = ok ? quant_code(x[c], lam[c], qmax, trunc) : 0;
-      x[c] = x[c] - (float)q * sc[c];
-      rm[c] = ok ? fmaxf(rm[c], fabsf(x[c])) : rm[c];
-      if ((i & 3) == 0) pk[c][i >> 2] = 0;
-      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
-    }
-    v[i] = make_float4(x[0], x[1], x[2], x[3]);
+    bits[0] |= ok && a.x > t[0] ? 1u << i : 0u;
+    bits[1] |= ok && a.y > t[1] ? 1u << i : 0u;
+    bits[2] |= ok && a.z > t[2] ? 1u << i : 0u;
+    bits[3] |= ok && a.w > t[3] ? 1u << i : 0u;
   }
+  patch_codes<RPT, true>(v, lam, sc, qmax, trunc, K - row0, pk, rm);
   store_codes<RPT>(s.Q, Kc, Kc, col0, ncol, row0, pk);
   store_bits<TH, CG, RPT>(s.mask, s.counts, strip, cols, K, col0, ncol, bits, ism);
   strip_max<TH, CG>(rm, red);
@@ -470,16 +497,7 @@ __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t 
     rs[c] = rm[c] > 0.f ? rm[c] / qmax : 0.f;
   }
   if (rb == 0) store_part(s.rscale + col0, rs, ncol);
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int q = quant_code(x[c], rlam[c], qmax, trunc);
-      if ((i & 3) == 0) pk[c][i >> 2] = 0;
-      pk[c][i >> 2] |= (unsigned)(q & 0xff) << (8 * (i & 3));
-    }
-  }
+  patch_codes<RPT, false>(v, rlam, rs, qmax, trunc, RPT, pk, rm);
   store_codes<RPT>(s.Rq, s.ldr, K, col0, ncol, row0, pk);
 }
 
