@@ -25,9 +25,9 @@ namespace srq {
 namespace {
 
 // ---- operand with contiguous vectors (A): one 256-thread block per row --------------------
-template <int NV4>   // float4 pieces per thread; the row has at most 1024*NV4 elements
+template <int NV4, bool TRUNC>   // NV4: float4 pieces per thread; the row has at most 1024*NV4 elements
 __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict__ X, int64_t cols,
-                                                         int64_t ldx, float qmax, int trunc,
+                                                         int64_t ldx, float qmax,
                                                          int8_t* __restrict__ Q, int64_t ldq,
                                                          float* __restrict__ scale, float* __restrict__ lambda,
                                                          int8_t* __restrict__ Rq, int64_t ldr,
@@ -73,22 +73,22 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     if (amax > 0.f) { lam = qmax / amax; s = amax / qmax; }
   }
   u1u* qdst = reinterpret_cast<u1u*>(Q + row * ldq);
-  const int qt = quant_code(xt, lam, qmax, trunc);
-  if (has_tail) Q[row * ldq + ct] = (int8_t)qt;
-  xt = xt - (float)qt * s;
+  const float zt = biased_code(xt, lam, qmax, TRUNC);
+  if (has_tail) Q[row * ldq + ct] = (int8_t)__float_as_int(zt);
+  xt = xt - code_value(zt) * s;
   // (places past the end of the row hold 0, but 0 * lam is not 0 where lam overflowed: they stay out of
   // the maximum of the residual)
   float rm = has_tail ? fabsf(xt) : 0.f;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
-    int q0 = quant_code(x[i].x, lam, qmax, trunc), q1 = quant_code(x[i].y, lam, qmax, trunc);
-    int q2 = quant_code(x[i].z, lam, qmax, trunc), q3 = quant_code(x[i].w, lam, qmax, trunc);
-    if (c4 < n4) __builtin_nontemporal_store(pack4(q0, q1, q2, q3), &qdst[c4]);
+    const float z0 = biased_code(x[i].x, lam, qmax, TRUNC), z1 = biased_code(x[i].y, lam, qmax, TRUNC);
+    const float z2 = biased_code(x[i].z, lam, qmax, TRUNC), z3 = biased_code(x[i].w, lam, qmax, TRUNC);
+    if (c4 < n4) __builtin_nontemporal_store(pack_codes(z0, z1, z2, z3, 4), &qdst[c4]);
     if (rscale) {
       // residual r = fl(x - fl(float(q) * s)); kept in place of x
-      x[i].x = x[i].x - (float)q0 * s; x[i].y = x[i].y - (float)q1 * s;
-      x[i].z = x[i].z - (float)q2 * s; x[i].w = x[i].w - (float)q3 * s;
+      x[i].x = x[i].x - code_value(z0) * s; x[i].y = x[i].y - code_value(z1) * s;
+      x[i].z = x[i].z - code_value(z2) * s; x[i].w = x[i].w - code_value(z3) * s;
       const float r4 = fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
       rm = c4 < n4 ? fmaxf(rm, r4) : rm;
     }
@@ -104,14 +104,14 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
   }
   if (!Rq) return;                                   // residual scales only: the codes are written elsewhere
   u1u* rdst = reinterpret_cast<u1u*>(Rq + row * ldr);
-  if (has_tail) Rq[row * ldr + ct] = (int8_t)quant_code(xt, rlam, qmax, trunc);
+  if (has_tail) Rq[row * ldr + ct] = (int8_t)__float_as_int(biased_code(xt, rlam, qmax, TRUNC));
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t c4 = threadIdx.x + i * 256;
     if (c4 < n4)
       // (residual codes are first read two products later: kept out of the caches)
-      __builtin_nontemporal_store(pack4(quant_code(x[i].x, rlam, qmax, trunc), quant_code(x[i].y, rlam, qmax, trunc),
-                                        quant_code(x[i].z, rlam, qmax, trunc), quant_code(x[i].w, rlam, qmax, trunc)),
+      __builtin_nontemporal_store(pack_codes(biased_code(x[i].x, rlam, qmax, TRUNC), biased_code(x[i].y, rlam, qmax, TRUNC),
+                                             biased_code(x[i].z, rlam, qmax, TRUNC), biased_code(x[i].w, rlam, qmax, TRUNC), 4),
                                   &rdst[c4]);
   }
 }
@@ -130,9 +130,9 @@ constexpr bool cols_mask(int mode) { return mode == kColsMask || mode == kColsMa
 // column groups per block of each pass (powers of two, 16..64)
 constexpr int cols_cg(int mode) { return mode == kColsAmax ? kCgAmax : mode == kColsMask ? kCgMask : kCgCodes; }
 
-template <int MODE>
+template <int MODE, bool TRUNC>
 __global__ __launch_bounds__(256) void cols_pass_kernel(
-    const float* __restrict__ X, int64_t rows, int64_t cols, int64_t ldx, float qmax, int trunc,
+    const float* __restrict__ X, int64_t rows, int64_t cols, int64_t ldx, float qmax,
     const float* __restrict__ scale, const float* __restrict__ lambda, const float* __restrict__ rlambda,
     // when given, the scales are derived here from the maxima of an earlier pass (their bit
     // patterns) and the first row of blocks writes them out: no separate kernel in between
@@ -252,35 +252,32 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
   float rm[4] = {0.f, 0.f, 0.f, 0.f};
   unsigned packed[4][4];                            // [column][word]: 16 codes of one column
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int i = 0; i < 16; i += 4) {
+    float z[4][4];                                  // [row][column]
 #pragma unroll
-    for (int wd = 0; wd < 4; ++wd) packed[c][wd] = 0;
+    for (int r = 0; r < 4; ++r) {
+      const float xv[4] = {v[i + r].x, v[i + r].y, v[i + r].z, v[i + r].w};
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const float xv[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-    int code[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int q = quant_code(xv[c], lam[c], qmax, trunc);
-      float res = xv[c] - (float)q * sc[c];
-      if (MODE == kColsCodes) {
-        code[c] = q;
-        rm[c] = row0 + i < rows ? fmaxf(rm[c], fabsf(res)) : rm[c];   // (as in rows_fused_kernel)
-      } else {
-        code[c] = quant_code(res, rlam[c], qmax, trunc);
+      for (int c = 0; c < 4; ++c) {
+        z[r][c] = biased_code(xv[c], lam[c], qmax, TRUNC);
+        const float res = xv[c] - code_value(z[r][c]) * sc[c];
+        if (MODE == kColsCodes) rm[c] = row0 + i + r < rows ? fmaxf(rm[c], fabsf(res)) : rm[c];   // (as in rows_fused_kernel)
+        else z[r][c] = biased_code(res, rlam[c], qmax, TRUNC);
       }
-      packed[c][i >> 2] |= (unsigned)(code[c] & 0xff) << (8 * (i & 3));
-    }
-    if (Qem && colok && row0 + i < rows) {
-      int8_t* dst = Qem + (row0 + i) * ldem + col0;
-      if (ncol == 4) {
-        *reinterpret_cast<u1u*>(dst) = pack4(code[0], code[1], code[2], code[3]);
-      } else {
+      if (Qem && colok && row0 + i + r < rows) {
+        int8_t* dst = Qem + (row0 + i + r) * ldem + col0;
+        const unsigned p = pack_codes(z[r][0], z[r][1], z[r][2], z[r][3], 4);
+        if (ncol == 4) {
+          *reinterpret_cast<u1u*>(dst) = p;
+        } else {
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-          if (c < ncol) dst[c] = (int8_t)code[c];
+          for (int c = 0; c < 3; ++c)
+            if (c < ncol) dst[c] = (int8_t)(p >> (8 * c));
+        }
       }
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) packed[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], 4);
   }
   if (Qvm && colok && row0 < rows) {
     const bool full = row0 + 16 <= rows;
@@ -314,9 +311,9 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(
 // MASK: the pass is also the selection pass of the operand (threshold compare per row; cols is
 // then a multiple of 64): the sixteen lanes that share a row assemble its 64 keep-bits with
 // shuffles.  The per-row counts are taken from the mask afterwards (mask_count_kernel).
-template <bool MASK>
+template <bool MASK, bool TRUNC>
 __global__ __launch_bounds__(256) void rows_resid_em_kernel(const float* __restrict__ X, int64_t rows,
-                                                            int64_t cols, int64_t ldx, float qmax, int trunc,
+                                                            int64_t cols, int64_t ldx, float qmax,
                                                             const float* __restrict__ scale,
                                                             const float* __restrict__ lambda,
                                                             const float* __restrict__ rlambda,
@@ -363,19 +360,19 @@ __global__ __launch_bounds__(256) void rows_resid_em_kernel(const float* __restr
   }
   unsigned packed[4][4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int i = 0; i < 16; i += 4) {
+    float z[4][4];
 #pragma unroll
-    for (int wd = 0; wd < 4; ++wd) packed[c][wd] = 0;
+    for (int r = 0; r < 4; ++r) {
+      const float xv[4] = {v[i + r].x, v[i + r].y, v[i + r].z, v[i + r].w};
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const float xv[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int q = quant_code(xv[c], lam[i], qmax, trunc);
-      const float res = xv[c] - (float)q * sc[i];
-      const int code = quant_code(res, rlam[i], qmax, trunc);
-      packed[c][i >> 2] |= (unsigned)(code & 0xff) << (8 * (i & 3));
+      for (int c = 0; c < 4; ++c) {
+        const float res = xv[c] - code_value(biased_code(xv[c], lam[i + r], qmax, TRUNC)) * sc[i + r];
+        z[r][c] = biased_code(res, rlam[i + r], qmax, TRUNC);
+      }
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) packed[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], 4);
   }
   typedef unsigned u4v __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -790,7 +787,7 @@ hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t
   dim3 grid((unsigned)rows), block(256);
   const float qm = (float)qmax;
 #define SRQ_ROWS(NV4)                                                                                        \
-  hipLaunchKernelGGL(rows_fused_kernel<NV4>, grid, block, 0, st, X, cols, ldx, qm, trunc, Q, ldq, scale,     \
+  hipLaunchKernelGGL((trunc ? rows_fused_kernel<NV4, true> : rows_fused_kernel<NV4, false>), grid, block, 0, st, X, cols, ldx, qm, Q, ldq, scale, \
                      lambda, Rq, ldr, rscale, rlambda, given_scale, given_lambda, clr)
   if (cols <= 1024) SRQ_ROWS(1);
   else if (cols <= 2048) SRQ_ROWS(2);
@@ -816,7 +813,7 @@ hipError_t launch_rows_resid_em(const float* X, int64_t rows, int64_t cols, int6
                                 const float* scale, const float* lambda, const float* rlambda, int8_t* Rem,
                                 int64_t ldem, hipStream_t st, RunIf run) {
   dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 255) / 256));
-  hipLaunchKernelGGL(rows_resid_em_kernel<false>, grid, dim3(256), 0, st, X, rows, cols, ldx, (float)qmax, trunc,
+  hipLaunchKernelGGL((trunc ? rows_resid_em_kernel<false, true> : rows_resid_em_kernel<false, false>), grid, dim3(256), 0, st, X, rows, cols, ldx, (float)qmax,
                      scale, lambda, rlambda, Rem, ldem, nullptr, nullptr, 0, run);
   return hipGetLastError();
 }
@@ -835,7 +832,7 @@ hipError_t launch_rows_mask_resid_em(const float* X, int64_t rows, int64_t cols,
                                      int64_t ldem, const float* thresh, uint64_t* mask, int32_t* counts,
                                      hipStream_t st) {
   dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 255) / 256));
-  hipLaunchKernelGGL(rows_resid_em_kernel<true>, grid, dim3(256), 0, st, X, rows, cols, ldx, (float)qmax, trunc,
+  hipLaunchKernelGGL((trunc ? rows_resid_em_kernel<true, true> : rows_resid_em_kernel<true, false>), grid, dim3(256), 0, st, X, rows, cols, ldx, (float)qmax,
                      scale, lambda, rlambda, Rem, ldem, thresh, reinterpret_cast<uint8_t*>(mask),
                      mask_words(cols) * 8, kAlways);
   hipError_t e = hipGetLastError();
@@ -853,8 +850,8 @@ static dim3 cols_grid(int mode, int64_t rows, int64_t cols) {
 hipError_t launch_cols_amax(const float* X, int64_t rows, int64_t cols, int64_t ldx, uint32_t* amax_bits,
                             hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsAmax>, cols_grid(kColsAmax, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     0.f, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, amax_bits, nullptr, 0,
+  hipLaunchKernelGGL((cols_pass_kernel<kColsAmax, false>), cols_grid(kColsAmax, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     0.f, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, amax_bits, nullptr, 0,
                      nullptr, 0, nullptr, 0, nullptr, kAlways);
   return hipGetLastError();
 }
@@ -863,8 +860,8 @@ hipError_t launch_cols_codes(const float* X, int64_t rows, int64_t cols, int64_t
                              const float* scale, const float* lambda, int8_t* Qvm, int64_t ldvm, int8_t* Qem,
                              int64_t ldem, uint32_t* ramax_bits, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsCodes>, cols_grid(kColsCodes, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     (float)qmax, trunc, scale, lambda, nullptr, nullptr, nullptr, nullptr, nullptr, ramax_bits,
+  hipLaunchKernelGGL((trunc ? cols_pass_kernel<kColsCodes, true> : cols_pass_kernel<kColsCodes, false>), cols_grid(kColsCodes, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     (float)qmax, scale, lambda, nullptr, nullptr, nullptr, nullptr, nullptr, ramax_bits,
                      Qvm, ldvm, Qem, ldem, nullptr, 0, nullptr, kAlways);
   return hipGetLastError();
 }
@@ -874,8 +871,8 @@ hipError_t launch_cols_codes_from_amax(const float* X, int64_t rows, int64_t col
                                        int trunc, const uint32_t* amax_bits, float* scale, float* lambda,
                                        int8_t* Qvm, int64_t ldvm, uint32_t* ramax_bits, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsCodes>, cols_grid(kColsCodes, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     (float)qmax, trunc, nullptr, nullptr, nullptr, amax_bits, scale, lambda, nullptr,
+  hipLaunchKernelGGL((trunc ? cols_pass_kernel<kColsCodes, true> : cols_pass_kernel<kColsCodes, false>), cols_grid(kColsCodes, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     (float)qmax, nullptr, nullptr, nullptr, amax_bits, scale, lambda, nullptr,
                      ramax_bits, Qvm, ldvm, nullptr, 0, nullptr, 0, nullptr, kAlways);
   return hipGetLastError();
 }
@@ -886,8 +883,8 @@ hipError_t launch_cols_resid_from_amax(const float* X, int64_t rows, int64_t col
                                        const uint32_t* ramax_bits, float* rscale, float* rlambda, int8_t* Rvm,
                                        int64_t ldvm, int8_t* Rem, int64_t ldem, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsResid>, cols_grid(kColsResid, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     (float)qmax, trunc, scale, lambda, nullptr, ramax_bits, rscale, rlambda, nullptr, nullptr,
+  hipLaunchKernelGGL((trunc ? cols_pass_kernel<kColsResid, true> : cols_pass_kernel<kColsResid, false>), cols_grid(kColsResid, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     (float)qmax, scale, lambda, nullptr, ramax_bits, rscale, rlambda, nullptr, nullptr,
                      Rvm, ldvm, Rem, ldem, nullptr, 0, nullptr, kAlways);
   return hipGetLastError();
 }
@@ -896,8 +893,8 @@ hipError_t launch_cols_resid(const float* X, int64_t rows, int64_t cols, int64_t
                              const float* scale, const float* lambda, const float* rlambda, int8_t* Rvm,
                              int64_t ldvm, int8_t* Rem, int64_t ldem, hipStream_t st, RunIf run) {
   if (rows <= 0 || cols <= 0 || (!Rvm && !Rem)) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsResid>, cols_grid(kColsResid, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     (float)qmax, trunc, scale, lambda, rlambda, nullptr, nullptr, nullptr, nullptr, nullptr, Rvm,
+  hipLaunchKernelGGL((trunc ? cols_pass_kernel<kColsResid, true> : cols_pass_kernel<kColsResid, false>), cols_grid(kColsResid, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     (float)qmax, scale, lambda, rlambda, nullptr, nullptr, nullptr, nullptr, nullptr, Rvm,
                      ldvm, Rem, ldem, nullptr, 0, nullptr, run);
   return hipGetLastError();
 }
@@ -906,8 +903,8 @@ hipError_t launch_cols_resid(const float* X, int64_t rows, int64_t cols, int64_t
 hipError_t launch_cols_mask(const float* X, int64_t rows, int64_t cols, int64_t ldx, const float* thresh,
                             uint64_t* mask, int32_t* counts, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsMask>, cols_grid(kColsMask, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
-                     0.f, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, thresh, nullptr, nullptr, 0,
+  hipLaunchKernelGGL((cols_pass_kernel<kColsMask, false>), cols_grid(kColsMask, rows, cols), dim3(256), 0, st, X, rows, cols, ldx,
+                     0.f, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, thresh, nullptr, nullptr, 0,
                      nullptr, 0, reinterpret_cast<uint8_t*>(mask), mask_words(rows) * 8, counts, kAlways);
   return hipGetLastError();
 }
@@ -919,8 +916,8 @@ hipError_t launch_cols_mask_resid(const float* X, int64_t rows, int64_t cols, in
                                   int64_t ldem, const float* thresh, uint64_t* mask, int32_t* counts,
                                   hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(cols_pass_kernel<kColsMaskResid>, cols_grid(kColsMaskResid, rows, cols), dim3(256), 0, st, X, rows, cols,
-                     ldx, (float)qmax, trunc, scale, lambda, nullptr, ramax_bits, rscale, rlambda, thresh, nullptr,
+  hipLaunchKernelGGL((trunc ? cols_pass_kernel<kColsMaskResid, true> : cols_pass_kernel<kColsMaskResid, false>), cols_grid(kColsMaskResid, rows, cols), dim3(256), 0, st, X, rows, cols,
+                     ldx, (float)qmax, scale, lambda, nullptr, ramax_bits, rscale, rlambda, thresh, nullptr,
                      Rvm, ldvm, Rem, ldem, reinterpret_cast<uint8_t*>(mask), mask_words(rows) * 8, counts, kAlways);
   return hipGetLastError();
 }

@@ -63,7 +63,7 @@ constexpr float kCodeBias = 12582912.f;
 static __device__ __forceinline__ float biased_code(float x, float lam, float qmax, bool trunc) {
   float y = x * lam;
   if (trunc) y = truncf(y);
-  return fminf(fmaxf(y, -qmax), qmax) + kCodeBias;
+  return __builtin_amdgcn_fmed3f(y, -qmax, qmax) + kCodeBias;   // (0 * inf becomes -qmax, as with fminf(fmaxf()))
 }
 static __device__ __forceinline__ float code_value(float z) { return z - kCodeBias; }
 // the low bytes of the first n of four, zeros for the others
