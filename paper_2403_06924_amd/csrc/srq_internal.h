@@ -233,7 +233,7 @@ hipError_t launch_scan_pair(const int32_t* t0, int64_t n0, int32_t* p0, int64_t*
 // ---- both operands of a small call, or one with a short inner dimension, at once (strips.hip).  Code matrices have rows
 // of Kc bytes (K rounded up to a multiple of 128) and come out with zeros past K.
 constexpr int64_t kStripsMaxK = 8192;        // columns of B that a workgroup can hold
-constexpr int64_t kStripsMaxScan = 4096;     // vectors whose counts every workgroup of the compaction adds up
+constexpr int64_t kStripsMaxScan = 16384;    // vectors whose counts every workgroup of the compaction adds up
 struct StripOperand {
   const float* X;
   int64_t ldx;

@@ -3,7 +3,7 @@
 // select.hip takes three here.
 //
 //   quant_pair_kernel    both operands in one launch and one read of each: maxima, scales, codes, residual
-//                        scales and residual codes.  A workgroup has either one row of A in registers or a
+//                        scales and residual codes.  A workgroup has either rows of A in registers or a
 //                        strip of 4 * CG columns of B over all of K (TH / CG pieces of RPT rows).
 //   select_pair_kernel   means of |D_F| from the partial sums, thresholds, keep-masks and counts of both
 //                        operands, cut in the same way (no atomics, nothing to clear).
@@ -15,9 +15,12 @@
 // bandwidth; hence few elements per thread for short K (RPT 4 or 8) and as many workgroups as there are.
 // A strip reads 64, 32 or 16 bytes of each row of B; strips that share 128-byte lines are given to the same
 // XCD (strip_of), where the line is found in L2 the second time.
-// Kernel times in a call, us, before (as many launches as listed) and now: 256^3 quantize 3.8 + 2.8 + 6.9 -> 5.0,
-// select 2.6 + 2.9 + 8.2 -> 4.8, scan and compaction 5.2 + 3.8 + 3.9 -> 3.8; 2048^3 21.7 -> 17.0, 20.4 -> 13.0, 20.2 -> 13.1.
-// Whole calls: 256^3 48.0 -> 23.0, 960 x 896 x 64 55 -> 26, 1024^3 60 -> 36, 2048^3 109 -> 95.
+// Up to K = 2048 a wave has a row of A to itself, or a vector of the compaction where there are many: nothing in a row
+// then waits at a barrier, and the workgroups are a quarter to an eighth as many.  With a workgroup per row and
+// vector / a wave: 2048^3 quantize 17.6 / 13.3 us, select 11.6 / 9.8, compact 12.9 / 11.6, calls 83.4 / 77.2;
+// 10000 x 1024 x 2048 234 / 215, 4000 x 100 x 2000 70.6 / 62.0, 2048^2 x 512 46.6 / 42.9, 1024^3 35.3 / 35.1.
+// Kernel times in a call, us, as ten launches and as these three: 1024^3 8.8 + 4.6 + 6.0 now; 2048^3 quantize 21.7 and
+// 13.3, select 20.4 and 9.8, scan and compaction 20.2 and 11.6.
 #include "stream.h"
 
 namespace srq {
@@ -49,28 +52,28 @@ __device__ __forceinline__ float block_max(float m, float* sm) {
   return m;
 }
 
-// A thread's NV4 pieces of a row (of every TH-th four values), zeros past K
-template <int TH, int NV4>
-__device__ __forceinline__ void load_row(float4 (&x)[NV4], int (&n)[NV4], const float* src, int K) {
+// The NV4 pieces of a row that thread t of RT has (every RT-th four values), zeros past K
+template <int RT, int NV4>
+__device__ __forceinline__ void load_row(float4 (&x)[NV4], int (&n)[NV4], const float* src, int K, int t) {
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * TH);
+    const int e = 4 * (t + i * RT);
     n[i] = K - e >= 4 ? 4 : K - e > 0 ? K - e : 0;
   }
   if (K < 4) {
 #pragma unroll
-    for (int i = 0; i < NV4; ++i) x[i] = load_part(src + 4 * (threadIdx.x + i * TH), n[i]);
+    for (int i = 0; i < NV4; ++i) x[i] = load_part(src + 4 * (t + i * RT), n[i]);
     return;
   }
-  f4u t[NV4];
+  f4u y[NV4];
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) t[i] = load_inside(src, 4 * (threadIdx.x + i * TH), K);
-  if (K >= 4 * TH * NV4) {                           // (nobody reaches past K)
+  for (int i = 0; i < NV4; ++i) y[i] = load_inside(src, 4 * (t + i * RT), K);
+  if (K >= 4 * RT * NV4) {                           // (nobody reaches past K)
 #pragma unroll
-    for (int i = 0; i < NV4; ++i) x[i] = make_float4(t[i].x, t[i].y, t[i].z, t[i].w);
+    for (int i = 0; i < NV4; ++i) x[i] = make_float4(y[i].x, y[i].y, y[i].z, y[i].w);
   } else {
 #pragma unroll
-    for (int i = 0; i < NV4; ++i) x[i] = shifted(t[i], 4 * (threadIdx.x + i * TH), K);
+    for (int i = 0; i < NV4; ++i) x[i] = shifted(y[i], 4 * (t + i * RT), K);
   }
 }
 // A thread's patch of a strip: rows row0 .. row0 + RPT - 1 of four columns from col0 on, zeros outside
@@ -98,24 +101,33 @@ __device__ __forceinline__ void load_patch(float4 (&v)[RPT], const float* X, int
   }
 }
 
+// maximum over the RT threads of a row: a wave or the workgroup
+template <int RT>
+__device__ __forceinline__ float row_max(float m, float* sm) {
+  if constexpr (RT > 64) return block_max<RT>(m, sm);
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  return m;
+}
+
 // ---- quantization ----------------------------------------------------------------------------------
-// One row.  Codes go out up to the padded length (zeros past K); places past K stay out of the maxima of
+// One row by RT threads, a wave (no barriers) or the whole workgroup.  Codes go out up to the padded length (zeros past K); places past K stay out of the maxima of
 // the residual (0 * lam is not 0 where lam overflowed).
-template <int TH, int NV4>
+template <int RT, int NV4>
 __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, int K, int Kc, float qmax, int trunc, float* sm) {
+  const int t = threadIdx.x & (RT - 1);
   float4 x[NV4];
   int n[NV4];
   float m = 0.f;
-  load_row<TH, NV4>(x, n, s.X + row * s.ldx, K);
+  load_row<RT, NV4>(x, n, s.X + row * s.ldx, K, t);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) m = fmaxf(m, max4(abs4(x[i])));
-  const float amax = block_max<TH>(m, sm);
+  const float amax = row_max<RT>(m, sm);
   float lam = 0.f, sc = 0.f;
   if (amax > 0.f) { lam = qmax / amax; sc = amax / qmax; }
   float rm = 0.f;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * TH);
+    const int e = 4 * (t + i * RT);
     float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w}, z[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -126,22 +138,22 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
     if (e < Kc) *reinterpret_cast<unsigned*>(s.Q + row * Kc + e) = pack_codes(z[0], z[1], z[2], z[3], n[i]);
     x[i] = make_float4(v[0], v[1], v[2], v[3]);
   }
-  if (threadIdx.x == 0) { s.scale[row] = sc; s.lambda[row] = lam; }
+  if (t == 0) { s.scale[row] = sc; s.lambda[row] = lam; }
   if (!s.Rq) return;
-  const float ramax = block_max<TH>(rm, sm);
+  const float ramax = row_max<RT>(rm, sm);
   float rlam = 0.f, rs = 0.f;
   if (ramax > 0.f) { rlam = qmax / ramax; rs = ramax / qmax; }
-  if (threadIdx.x == 0) { s.rscale[row] = rs; s.rlambda[row] = rlam; }
+  if (t == 0) { s.rscale[row] = rs; s.rlambda[row] = rlam; }
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (threadIdx.x + i * TH);
+    const int e = 4 * (t + i * RT);
     const float v[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
     float z[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) z[j] = biased_code(v[j], rlam, qmax, trunc);
     if (e < Kc) *reinterpret_cast<unsigned*>(s.Rq + row * Kc + e) = pack_codes(z[0], z[1], z[2], z[3], n[i]);
   }
-  for (int e = K + threadIdx.x; e < Kc; e += TH) s.D[row * Kc + e] = 0;
+  for (int e = K + t; e < Kc; e += RT) s.D[row * Kc + e] = 0;
 }
 
 // maxima of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
@@ -249,16 +261,17 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   }
 }
 
-template <int TH, int NV4, int CG, int RPT>
-__global__ __launch_bounds__(TH) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t N, int K, int Kc, int strips,
+template <int TH, int RT, int NV4, int CG, int RPT>
+__global__ __launch_bounds__(TH) void quant_pair_kernel(StripOperand a, StripOperand b, int64_t M, int64_t N, int K, int Kc, int strips,
                                                          float qmax, int trunc) {
   __shared__ float sm[TH / 8 * CG];
+  const int64_t row = ((int64_t)blockIdx.x - strips) * (TH / RT) + (RT == 64 ? threadIdx.x >> 6 : 0);
   if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, Kc, qmax, trunc, sm);
-  else quant_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, K, Kc, qmax, trunc, sm);
+  else if (row < M) quant_row<RT, NV4>(a, row, K, Kc, qmax, trunc, sm);
 }
 
 // columns alone, into a caller's matrix of any leading dimension
-template <int TH, int NV4, int CG, int RPT>
+template <int TH, int RT, int NV4, int CG, int RPT>
 __global__ __launch_bounds__(TH) void quant_cols_kernel(StripOperand s, int64_t N, int K, int64_t ldq, int strips, float qmax,
                                                         int trunc) {
   __shared__ float sm[TH / 8 * CG];
@@ -280,28 +293,31 @@ __device__ __forceinline__ void store_nibble(uint64_t* mrow, int words, int c4, 
   if (!(c4 & 7) && (c4 >> 3) < 2 * words) reinterpret_cast<uint32_t*>(mrow)[c4 >> 3] = b32;
 }
 
-template <int TH, int NV4>
+// (the partial sums of a row: every RT-th by a thread, its wave's lanes as a tree, the waves one after the other)
+template <int RT, int NV4>
 __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, double* dsm, int* ism) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x & (RT - 1), lane = tid & 63, w = tid >> 6;
   const int words = (K + 63) / 64;
   float4 x[NV4];
   int n[NV4];
-  if (s.mask) load_row<TH, NV4>(x, n, s.X + row * s.ldx, K);   // (on their way while the threshold is formed)
+  if (s.mask) load_row<RT, NV4>(x, n, s.X + row * s.ldx, K, tid);   // (on their way while the threshold is formed)
   double sum = 0.0;
-  for (int64_t p = tid; p < s.nparts; p += TH) sum += s.part[p * rows + row];
+  for (int64_t p = tid; p < s.nparts; p += RT) sum += s.part[p * rows + row];
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) dsm[w] = sum;
-  __syncthreads();
-  float t;
-  sum = dsm[0];
+  if constexpr (RT > 64) {
+    if (lane == 0) dsm[w] = sum;
+    __syncthreads();
+    sum = dsm[0];
 #pragma unroll
-  for (int i = 1; i < TH / 64; ++i) sum += dsm[i];
+    for (int i = 1; i < RT / 64; ++i) sum += dsm[i];
+  }
+  float t;
   mean_of(s, row, sum, tid == 0, t);
   if (!s.mask) return;
   int total = 0;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int c4 = tid + i * TH;
+    const int c4 = tid + i * RT;
     unsigned nib = (fabsf(x[i].x) > t ? 1u : 0u) | (fabsf(x[i].y) > t ? 2u : 0u) | (fabsf(x[i].z) > t ? 4u : 0u) |
                    (fabsf(x[i].w) > t ? 8u : 0u);
     nib &= (1u << n[i]) - 1u;
@@ -309,14 +325,14 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
     store_nibble(s.mask + row * words, words, c4, nib);
   }
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
-  if (lane == 0) ism[w] = total;
-  __syncthreads();
-  if (tid == 0) {
+  if constexpr (RT > 64) {
+    if (lane == 0) ism[w] = total;
+    __syncthreads();
     total = ism[0];
 #pragma unroll
-    for (int i = 1; i < TH / 64; ++i) total += ism[i];
-    s.counts[row] = total;
+    for (int i = 1; i < RT / 64; ++i) total += ism[i];
   }
+  if (tid == 0) s.counts[row] = total;
 }
 
 // keep-bits of a patch (bit i of bits[c]: row row0 + i of column c) into the mask, and the counts of the strip's columns
@@ -395,12 +411,13 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
   store_bits<TH, CG, RPT>(s.mask, s.counts, strip, cols, K, col0, ncol, bits, ism);
 }
 
-template <int TH, int NV4, int CG, int RPT>
+template <int TH, int RT, int NV4, int CG, int RPT>
 __global__ __launch_bounds__(TH) void select_pair_kernel(StripSelect a, StripSelect b, int64_t M, int64_t N, int K, int strips) {
   __shared__ double dsm[TH / 16 * CG];
   __shared__ int ism[TH / 16 * CG];
+  const int64_t row = ((int64_t)blockIdx.x - strips) * (TH / RT) + (RT == 64 ? threadIdx.x >> 6 : 0);
   if ((int)blockIdx.x < strips) select_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, dsm, ism);
-  else select_row<TH, NV4>(a, (int64_t)blockIdx.x - strips, M, K, dsm, ism);
+  else if (row < M) select_row<RT, NV4>(a, row, M, K, dsm, ism);
 }
 
 // ---- reduction of one operand (scales and thresholds given): codes, residual codes, keep-mask and counts in
@@ -416,7 +433,7 @@ __global__ __launch_bounds__(TH) void reduce_rows_kernel(StripReduce s, int K, i
   float4 x[NV4];
   int n[NV4], total = 0;
   float rm = 0.f;
-  load_row<TH, NV4>(x, n, src, K);
+  load_row<TH, NV4>(x, n, src, K, tid);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     const int e = 4 * (tid + i * TH);
@@ -462,7 +479,7 @@ __global__ __launch_bounds__(TH) void reduce_rows_kernel(StripReduce s, int K, i
   }
 }
 
-template <int TH, int NV4, int CG, int RPT>
+template <int TH, int RT, int NV4, int CG, int RPT>
 __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t cols, int K, int Kc, int strips, float qmax,
                                                          int trunc) {
   __shared__ float red[TH / 16 * CG];
@@ -502,52 +519,65 @@ __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t 
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
-// One workgroup per vector, four elements per thread and round: the place of a thread's first kept entry
-// is the number of entries of earlier vectors, rounds, waves and lanes (the last from three ballots of its
+// A vector by RT threads, a wave or the workgroup, four elements per thread and round: the place of a thread's first
+// kept entry is the number of entries of earlier vectors, rounds, waves and lanes (the last from three ballots of its
 // own count, 0..4).  Codes and zero-filled copy have rows of Kc bytes with zeros past K.
-template <int NV4>
-__global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int K, int Kc) {
+template <int RT, int NV4>
+__global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int groups_a, int K, int Kc) {
+  constexpr int kVec = 256 / RT, kWaves = RT / 64;   // vectors of a workgroup, waves of a vector
   __shared__ int64_t before[4];
-  __shared__ int kept[NV4][4];
-  const bool second = blockIdx.x >= (unsigned)a.nvec;
+  __shared__ int kept[RT > 64 ? NV4 : 1][4], count[4];
+  const bool second = (int)blockIdx.x >= groups_a;
   const StripCompact& s = second ? b : a;
-  const int v = (int)blockIdx.x - (second ? a.nvec : 0);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, t = tid & (RT - 1);
+  const int v0 = ((int)blockIdx.x - (second ? groups_a : 0)) * kVec, v = v0 + (RT == 64 ? w : 0);
+  const bool ok = v < s.nvec;
   const int words = (K + 63) / 64;
-  const uint32_t* mv = reinterpret_cast<const uint32_t*>(s.mask + (int64_t)v * words);
+  const uint32_t* mv = reinterpret_cast<const uint32_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
+  const int8_t* qv = s.Q + (int64_t)(ok ? v : 0) * Kc;
   unsigned nib[NV4], code[NV4];
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (tid + i * 256);
-    nib[i] = e < K ? (mv[e >> 5] >> (e & 31)) & 0xfu : 0u;   // (bits past K are zero)
-    code[i] = e < Kc ? *reinterpret_cast<const unsigned*>(s.Q + (int64_t)v * Kc + e) : 0u;
+  for (int i = 0; i < NV4; ++i) {                    // (without branches: what is not wanted is read where something is)
+    const int e = 4 * (t + i * RT), last = 2 * words - 1;
+    nib[i] = mv[e >> 5 < last ? e >> 5 : last];
+    code[i] = *reinterpret_cast<const unsigned*>(qv + (e < Kc ? e : Kc - 4));
   }
   int64_t sum = 0;
-  for (int i = tid; i < v; i += 256) sum += s.counts[i];
+  for (int i = tid; i < v0; i += 256) sum += s.counts[i];
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
   if (lane == 0) before[w] = sum;
   const uint64_t lower = (1ull << lane) - 1ull;
-  int at[NV4];
+  int at[NV4], mine = 0;                             // RT = 64: places within the vector, its kept entries
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (tid + i * 256);
+    const int e = 4 * (t + i * RT);
+    nib[i] = ok && e < K ? (nib[i] >> (e & 31)) & 0xfu : 0u;   // (bits past K are zero)
     const unsigned keep = ((nib[i] & 1u) ? 0xffu : 0u) | ((nib[i] & 2u) ? 0xff00u : 0u) | ((nib[i] & 4u) ? 0xff0000u : 0u) |
                           ((nib[i] & 8u) ? 0xff000000u : 0u);
-    if (s.dense && e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
+    if (s.dense && ok && e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
     const int cnt = __popc(nib[i]);
     const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
-    at[i] = __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower);
-    if (lane == 0) kept[i][w] = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+    at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower);
+    const int all = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+    if constexpr (RT == 64) mine += all;
+    else if (lane == 0) kept[i][w] = all;
   }
+  if (RT == 64 && lane == 0) count[w] = mine;
   __syncthreads();
-  const int64_t first = before[0] + before[1] + before[2] + before[3];
+  int64_t first = before[0] + before[1] + before[2] + before[3];
+  if constexpr (RT == 64) {
+    for (int j = 0; j < w; ++j) first += count[j];
+  }
   int64_t base = first;
 #pragma unroll
   for (int i = 0; i < NV4; ++i) {
     int64_t p = base + at[i];
-    for (int j = 0; j < w; ++j) p += kept[i][j];
-    base += kept[i][0] + kept[i][1] + kept[i][2] + kept[i][3];
-    const int e = 4 * (tid + i * 256);
+    if constexpr (RT > 64) {
+      for (int j = 0; j < w; ++j) p += kept[i][j];
+#pragma unroll
+      for (int j = 0; j < kWaves; ++j) base += kept[i][j];
+    }
+    const int e = 4 * (t + i * RT);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (nib[i] >> j & 1u) {
@@ -559,7 +589,8 @@ __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, Strip
       }
     }
   }
-  if (tid == 0) {
+  if (RT == 64) base += mine;
+  if (t == 0 && ok) {
     s.ptr[v] = (int32_t)first;
     if (v == s.nvec - 1) {
       s.ptr[s.nvec] = (int32_t)base;
@@ -577,42 +608,48 @@ int strip_cg(int64_t K) { return K <= 512 ? 4 : K <= 4096 ? 2 : 1; }
 // more of a compute unit and read narrower pieces of each row, so what launches cost has to be a larger
 // share of the call:
 //   K <= 1024, any size    512^2 x 256 49 / 26, 8192^2 x 1024 540 / 521
-//   K <= 2048              4096^2 x 2048 228 / 215, 10000 x 1024 x 2048 238 / 236, 8192^2 x 2048 697 / 713
+//   K <= 2048              4096^2 x 2048 228 / 194, 20000 x 200 x 2000 261 / 234, 8192^2 x 2048 654 / 650, 16384 x 4096 x 2048
+//                          643 / 636, 12288^2 x 2048 1269 / 1280
 //   K <= 4096              512^2 x 4096 84 / 67, 2048^2 x 4096 148 / 138, 1000 x 5000 x 4000 283 / 251, 3000^2 x 3000
-//                          277 / 277, 4096^3 323 / 370; M > 4096 has no joint compaction: 6000 x 600 x 2100 150 / 178
+//                          277 / 277, 4096^3 323 / 370; with M > 4096 the rows lose: 5000 x 500 x 3000 156 / 162,
+//                          5900 x 90 x 2200 117 / 150
 //   K <= 8192              512^2 x 8192 120 / 106, 1024^2 x 8192 139 / 137, 2048^2 x 8192 241 / 261
 bool strips_ok(int64_t M, int64_t N, int64_t K) {
   if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
-  return K <= 1024 || (K <= 2048 && M + N <= 12288) || (K <= 4096 && M <= 4096 && M + N <= 6000) || M + N <= 2048;
+  return K <= 1024 || (K <= 2048 && M + N <= 20480) || (K <= 4096 && M <= 4096 && M + N <= 6000) || M + N <= 2048;
 }
 // One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, before / now; about 36 us of the small
 // ones is the host): columns 1000 x 1000 51 / 36, 2000 x 10000 130 / 95, 4000 x 5900 157 / 124, but 5000 x 1500 68 / 75, so
-// columns longer than 4096 stay in passes; rows 10000 x 1000 62 / 53, 3000 x 3000 45 / 39, 4000 x 5900 87 / 87.
+// columns longer than 4096 stay in passes; 15000 x 2000 197 / 125; rows 10000 x 1000 62 / 53, 3000 x 3000 45 / 39,
+// 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 5900 x 2500 65 / 57, 4000 x 5900 87 / 87.
 bool strips_one_ok(int axis, int64_t nvec, int64_t veclen) {
-  return axis == SRQ_AXIS_ROW ? strips_ok(nvec, 0, veclen) : veclen <= 4096 && strips_ok(0, nvec, veclen);
+  if (axis == SRQ_AXIS_ROW && veclen > 0 && veclen <= 4096 && nvec <= 6000) return true;
+  return (axis == SRQ_AXIS_ROW || veclen <= 4096) && strips_ok(axis == SRQ_AXIS_ROW ? nvec : 0, axis == SRQ_AXIS_ROW ? 0 : nvec, veclen);
 }
+// (Every workgroup adds up the counts before its vectors: scan and scatter in launches of their own / here, us:
+// 8000 x 200 x 2000 94.9 / 82.3, 16000 x 200 x 200 66.2 / 61.8, 40 x 40000 x 1000 202 / 220, 60000 x 60 x 2000 505 / 539.)
 bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <= kStripsMaxScan; }
 
 // (Rows per thread, calls at 5 % kept, us, 16 in 256 threads / 8 in 512: 512 x 512 x 1100 42 / 38, 1024 x 1024 x 2048 52 / 49,
 // 300 x 3000 x 2048 67 / 65, 4096 x 4096 x 2048 228 / 234, 10000 x 1024 x 2048 249 / 256.  One step further either way loses:
 // 4 in 512 threads at 2048 x 2048 x 1000 73 against 68, 8 in 1024 threads at 2048 x 2048 x 3000 143 against 134.)
+#define SRQ_STRIPS_AS(TH, RT, NV4, CG, RPT, KERN, ROWS, ...)                                                                  \
+  hipLaunchKernelGGL((KERN<TH, RT, NV4, CG, RPT>), dim3((unsigned)(strips + ((ROWS) + TH / RT - 1) / (TH / RT))), dim3(TH), 0, st, __VA_ARGS__)
 #define SRQ_STRIPS(KERN, ROWS, ...)                                                                                       \
   do {                                                                                                              \
     const int strips = (int)((N + 4 * strip_cg(K) - 1) / (4 * strip_cg(K)));                                        \
-    const dim3 grid((unsigned)(strips + (ROWS)));                                                                        \
-    if (K <= 256) hipLaunchKernelGGL((KERN<256, 1, 4, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                    \
-    else if (K <= 512) hipLaunchKernelGGL((KERN<256, 1, 4, 8>), grid, dim3(256), 0, st, __VA_ARGS__);               \
-    else if (K <= 1024) hipLaunchKernelGGL((KERN<256, 1, 2, 8>), grid, dim3(256), 0, st, __VA_ARGS__);              \
-    else if (K <= 2048 && N + (ROWS) <= 6000)                                                                       \
-      hipLaunchKernelGGL((KERN<512, 1, 2, 8>), grid, dim3(512), 0, st, __VA_ARGS__);                                \
-    else if (K <= 2048) hipLaunchKernelGGL((KERN<256, 2, 2, 16>), grid, dim3(256), 0, st, __VA_ARGS__);             \
-    else if (K <= 4096) hipLaunchKernelGGL((KERN<512, 2, 2, 16>), grid, dim3(512), 0, st, __VA_ARGS__);             \
-    else hipLaunchKernelGGL((KERN<512, 4, 1, 16>), grid, dim3(512), 0, st, __VA_ARGS__);                            \
+    if (K <= 256) SRQ_STRIPS_AS(256, 64, 1, 4, 4, KERN, ROWS, __VA_ARGS__);                                          \
+    else if (K <= 512) SRQ_STRIPS_AS(256, 64, 2, 4, 8, KERN, ROWS, __VA_ARGS__);                                     \
+    else if (K <= 1024) SRQ_STRIPS_AS(256, 64, 4, 2, 8, KERN, ROWS, __VA_ARGS__);                                    \
+    else if (K <= 2048 && N + (ROWS) <= 6000) SRQ_STRIPS_AS(512, 64, 8, 2, 8, KERN, ROWS, __VA_ARGS__);              \
+    else if (K <= 2048) SRQ_STRIPS_AS(256, 64, 8, 2, 16, KERN, ROWS, __VA_ARGS__);                                   \
+    else if (K <= 4096) SRQ_STRIPS_AS(512, 512, 2, 2, 16, KERN, ROWS, __VA_ARGS__);                                  \
+    else SRQ_STRIPS_AS(512, 512, 4, 1, 16, KERN, ROWS, __VA_ARGS__);                                                 \
   } while (0)
 
 hipError_t launch_quant_pair(const StripOperand& a, const StripOperand& b, int64_t M, int64_t N, int64_t K, int64_t Kc, int qmax,
                              int trunc, hipStream_t st) {
-  SRQ_STRIPS(quant_pair_kernel, M, a, b, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
+  SRQ_STRIPS(quant_pair_kernel, M, a, b, M, N, (int)K, (int)Kc, strips, (float)qmax, trunc);
   return hipGetLastError();
 }
 
@@ -631,6 +668,7 @@ hipError_t launch_reduce_cols(const StripReduce& s, int64_t N, int64_t K, int64_
   return hipGetLastError();
 }
 #undef SRQ_STRIPS
+#undef SRQ_STRIPS_AS
 
 hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_t Kc, int qmax, int trunc, hipStream_t st) {
   const dim3 grid((unsigned)M);
@@ -643,12 +681,26 @@ hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_
 }
 
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st) {
-  const dim3 grid((unsigned)(a.nvec + b.nvec));
-  if (grid.x == 0) return hipSuccess;
-  if (Kc <= 1024) hipLaunchKernelGGL(compact_pair_kernel<1>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
-  else if (Kc <= 2048) hipLaunchKernelGGL(compact_pair_kernel<2>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
-  else if (Kc <= 4096) hipLaunchKernelGGL(compact_pair_kernel<4>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
-  else hipLaunchKernelGGL(compact_pair_kernel<8>, grid, dim3(256), 0, st, a, b, (int)K, (int)Kc);
+  if (a.nvec + b.nvec == 0) return hipSuccess;
+#define SRQ_COMPACT(RT, NV4)                                                                                                \
+  do {                                                                                                                      \
+    const int ga = (a.nvec + 256 / RT - 1) / (256 / RT), gb = (b.nvec + 256 / RT - 1) / (256 / RT);                          \
+    hipLaunchKernelGGL((compact_pair_kernel<RT, NV4>), dim3((unsigned)(ga + gb)), dim3(256), 0, st, a, b, ga, (int)K, (int)Kc); \
+  } while (0)
+  // A wave per vector takes a quarter of the workgroups and prefixes, and longer in each.  Up to 2048 vectors (eight
+  // workgroups on each CU, all at once) that loses: 1024^3 6.2 us with a workgroup per vector, 6.8 with a wave;
+  // 2048^3 12.9 and 11.6.
+  const bool few = a.nvec + b.nvec <= 2048;
+  if (Kc <= 256) SRQ_COMPACT(64, 1);
+  else if (Kc <= 1024) {
+    if (few) SRQ_COMPACT(256, 1);
+    else SRQ_COMPACT(64, 4);
+  } else if (Kc <= 2048) {
+    if (few) SRQ_COMPACT(256, 2);
+    else SRQ_COMPACT(64, 8);
+  } else if (Kc <= 4096) SRQ_COMPACT(256, 4);
+  else SRQ_COMPACT(256, 8);
+#undef SRQ_COMPACT
   return hipGetLastError();
 }
 

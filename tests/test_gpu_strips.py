@@ -72,7 +72,7 @@ def test_windows_that_start_anywhere(srq, b, cols, axis, layout):
 
 
 # K at the edges of the strip shapes (256, 512, 1024, 2048, 4096, 8192) and of the padded length, M and N around strips of
-# 8 and 16 columns, the compaction's own limit on vectors (4096)
+# 8 and 16 columns, many vectors
 @pytest.mark.parametrize("shape", [(1, 1, 1), (3, 17, 2), (33, 9, 63), (130, 15, 255), (65, 33, 256), (64, 70, 257), (31, 129, 512),
                                    (40, 24, 513), (129, 65, 1023), (24, 40, 1024), (33, 31, 1025), (50, 63, 2047), (16, 8, 2048),
                                    (20, 12, 2049), (35, 50, 4095), (17, 9, 4097),
@@ -117,6 +117,14 @@ def test_short_inner_dimension(srq, b, shape, terms):
     assert o.error_rel(ref.C, host(C)) <= 1e-5              # the FP32 output's tolerance everywhere
 
 
+# more than 2048 vectors together: a wave of the compaction has a whole vector; vectors at the edges of its shapes, and
+# counts of vectors that are no multiple of four; the limit on vectors (16384) of a compaction without a scan
+@pytest.mark.parametrize("shape", [(1502, 549, 256), (2043, 6, 257), (7, 2042, 1024), (2041, 9, 1025), (9, 2041, 2048), (2049, 1, 3),
+                                   (16384, 5, 40), (16385, 5, 40), (3, 16385, 130)])
+def test_a_wave_per_vector(srq, b, shape):
+    test_short_inner_dimension(srq, b, shape, "both")
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (77, 61), (9, 255), (256, 33), (257, 7), (512, 40), (1023, 9), (1025, 18), (2049, 5),
                                    (4095, 11), (4097, 10), (8192, 6), (8193, 6), (100, 4100)])
 @pytest.mark.parametrize("axis", [0, 1])
@@ -149,6 +157,12 @@ def test_reduction_of_one_operand(srq, b, shape, axis, bits):
     n = int(r["nnz"].item())
     assert n == len(k) and (host(r["ptr"]) == np.searchsorted(vec, np.arange(nvec + 1))).all()
     assert (host(r["idx"][:n]) == k).all() and (host(r["val"][:n]) == q[vec, k]).all()
+
+
+@pytest.mark.parametrize("shape", [(4096, 4100), (2049, 6000), (1027, 12300), (2048, 4099)])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_reduction_of_many_vectors(srq, b, shape, axis):
+    test_reduction_of_one_operand(srq, b, shape, axis, 8)
 
 
 @pytest.mark.parametrize("n", [1, 255, 257, 4095, 8192, 16385, 20001])
