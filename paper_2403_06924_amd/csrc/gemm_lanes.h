@@ -35,6 +35,58 @@ static __device__ __forceinline__ v4f buf_load_4(__amdgpu_buffer_rsrc_t r, uint3
   return x;
 }
 
+// an accumulator as a number, read where it is wanted (several copies of an epilogue follow the K loop: what they
+// have in common the compiler computes before it branches to one of them, all conversions at once; nor does it keep
+// accumulators in ordinary registers and move them there and back in every K-tile).  Two s_nop 15 stand between the
+// last MFMA and the first of these.
+static __device__ __forceinline__ float acc_value(int x) {
+  int y;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(x));
+  return (float)y;
+}
+
+// 16 bytes of a row of C (at any 4-byte aligned address): uniform base and offset, the lane's offset
+static __device__ __forceinline__ v4f row_load(uint64_t base, uint32_t lane, uint32_t off) {
+  const v4i t = buf_load16(buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off);
+  return v4f{__int_as_float(t.x), __int_as_float(t.y), __int_as_float(t.z), __int_as_float(t.w)};
+}
+template <bool CACHED>
+static __device__ __forceinline__ void row_store(v4f x, uint64_t base, uint32_t lane, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(
+      v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)},
+      buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off, CACHED ? 0 : 2 /* non-temporal */);
+}
+
+// the same on the edge, without branches: row `row`, columns col .. col + 3 of the rows that start at `base`, of which
+// rows x cols exist; an access outside gets an offset past the end of its descriptor (its load brings zero, its
+// store is dropped).  ELEMS: the last columns are not a whole access.
+constexpr uint32_t kOutside = 0xfffffff0u, kRecords = 0x7fffffffu;
+static __device__ __forceinline__ uint32_t edge_offset(int64_t ld4, int row, int col, int rows, int cols) {
+  return row < rows && col < cols ? (uint32_t)row * (uint32_t)ld4 + 4u * (uint32_t)col : kOutside;
+}
+template <bool ELEMS>
+static __device__ __forceinline__ v4f edge_load(uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
+  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
+  if (!ELEMS) return buf_load_4(rs, edge_offset(ld4, row, col, rows, cols), true);
+  v4f x;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) x[v] = buf_load_f32(rs, edge_offset(ld4, row, col + v, rows, cols));
+  return x;
+}
+template <bool ELEMS>
+static __device__ __forceinline__ void edge_store(v4f x, uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
+  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
+  if (!ELEMS) {
+    __builtin_amdgcn_raw_buffer_store_b128(
+        v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)}, rs,
+        edge_offset(ld4, row, col, rows, cols), 0, 0);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[v]), rs, edge_offset(ld4, row, col + v, rows, cols), 0, 0);
+  }
+}
+
 // A lane's N accesses of four consecutive floats of a tile of C: access i covers row row + 8 (i & 1) +
 // 16 (i >> 1), columns col .. col + 3; rows x cols of the tile exist (full: all of it).
 template <int N>

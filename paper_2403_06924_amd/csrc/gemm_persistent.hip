@@ -87,56 +87,6 @@ __device__ __forceinline__ int fresh_lane() {
   return l;
 }
 
-// an accumulator as a number, read where it is wanted (several copies of an epilogue follow the K loop: what they
-// have in common the compiler computes before it branches to one of them, all 256 conversions at once)
-__device__ __forceinline__ float acc_value(int x) {
-  int y;
-  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(y) : "a"(x));
-  return (float)y;
-}
-
-// 16 bytes of a row of C (at any 4-byte aligned address): uniform base and offset, the lane's offset
-__device__ __forceinline__ v4f row_load(uint64_t base, uint32_t lane, uint32_t off) {
-  const v4i t = buf_load16(buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off);
-  return v4f{__int_as_float(t.x), __int_as_float(t.y), __int_as_float(t.z), __int_as_float(t.w)};
-}
-template <bool CACHED>
-__device__ __forceinline__ void row_store(v4f x, uint64_t base, uint32_t lane, uint32_t off) {
-  __builtin_amdgcn_raw_buffer_store_b128(
-      v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)},
-      buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off, CACHED ? 0 : 2 /* non-temporal */);
-}
-
-// the same on the edge, without branches: row `row`, columns col .. col + 3 of the rows that start at `base`, of which
-// rows x cols exist; an access outside gets an offset past the end of its descriptor (its load brings zero, its
-// store is dropped).  ELEMS: the last columns are not a whole access.
-constexpr uint32_t kOutside = 0xfffffff0u, kRecords = 0x7fffffffu;
-__device__ __forceinline__ uint32_t edge_offset(int64_t ld4, int row, int col, int rows, int cols) {
-  return row < rows && col < cols ? (uint32_t)row * (uint32_t)ld4 + 4u * (uint32_t)col : kOutside;
-}
-template <bool ELEMS>
-__device__ __forceinline__ v4f edge_load(uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
-  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
-  if (!ELEMS) return buf_load_4(rs, edge_offset(ld4, row, col, rows, cols), true);
-  v4f x;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) x[v] = buf_load_f32(rs, edge_offset(ld4, row, col + v, rows, cols));
-  return x;
-}
-template <bool ELEMS>
-__device__ __forceinline__ void edge_store(v4f x, uint64_t base, int64_t ld4, int row, int col, int rows, int cols) {
-  const __amdgpu_buffer_rsrc_t rs = buf_rsrc(reinterpret_cast<const void*>(base), kRecords);
-  if (!ELEMS) {
-    __builtin_amdgcn_raw_buffer_store_b128(
-        v4u{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)}, rs,
-        edge_offset(ld4, row, col, rows, cols), 0, 0);
-  } else {
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[v]), rs, edge_offset(ld4, row, col + v, rows, cols), 0, 0);
-  }
-}
-
 // EDGE: M or N is no multiple of 256.  JN: neighbouring blocks of a row of C that an accumulating epilogue visits before
 // the next row.
 template <int MODE, bool SUMS, bool SCALE, bool EDGE, int JN>
@@ -642,19 +592,7 @@ bool gemm_persistent_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64
   if (ep.ldc >= (1 << 25) || (ep.final_scale && ep.beta != 0.f && ep.ldcin >= (1 << 25))) return false;   // ... and within 16 rows of C
   if (((reinterpret_cast<uintptr_t>(Qa) | reinterpret_cast<uintptr_t>(Qb)) & 15) || (lda % 16) || (ldb % 16))
     return false;
-  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  // One tile per compute unit, or part of that where the K loop is long against the epilogue, the longer the fewer
-  // tiles there are (and longer for tiles on the edge, whose epilogue is slow).  128 x 128 tiles reach half
-  // the rate per compute unit but fill more of them.  Whole calls at 5 % kept, us, 128 / 256 (two numbers for
-  // 128: two cards; that kernel's times differ by up to 10 % from card to card, the other's by 1 %):
-  //   whole tiles  132 K 2048 167, 155 / 170   K 2560 218, 212 / 216   168 179, 165 / 177   234, 229 / 221
-  //                192 K 1024 128, 118 / 130   K 2048 192, 174 / 180   K 2560 242, 234 / 223
-  //                210 K 896 140 / 132         K 1024 147, 136 / 135   240 K 1024 152, 140 / 142   K 2048 229, 209 / 195
-  //   edges        156 K 2048 197, 188 / 209   K 2560 253, 246 / 253   169 207 / 220   281 / 271
-  //                204 K 2048 258, 243 / 242   K 2560 312, 303 / 287   240 264, 247 / 251   353, 349 / 298
-  //   121 tiles    K 1024 108 / 133            K 4096 240 / 276
-  const bool edge = (M % BM) || (N % BN);
-  return (tiles >= 256 || (tiles >= 132 && K >= (edge || tiles < 208 ? 2560 : 1024))) && tiles < (1 << 30);
+  return ((M + BM - 1) / BM) * ((N + BN - 1) / BN) < (1 << 30);
 }
 
 // Compute units of the current device, looked up once per device (srq_create primes it, so

@@ -330,11 +330,12 @@ int64_t gemm_tiles_m(int64_t M, int64_t N);  // tile counts of the configuration
 int64_t gemm_tiles_n(int64_t M, int64_t N);
 hipError_t launch_gemm_i8(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda,
                           const int8_t* Qb, int64_t ldb, const GemmEpilogue& ep, hipStream_t st);
-// persistent-workgroup variant for full, aligned, large problems (chosen inside launch_gemm_i8)
+// compute units of the current device
 hipError_t gemm_device_cus(int* cus);
 // raises a kernel's dynamic-LDS limit to `bytes` once per (device, kernel); safe to call from
 // several host threads
 hipError_t ensure_dynamic_lds(const void* kernel, int bytes);
+// persistent-workgroup variant for aligned, large problems: whether it can take one (chosen inside launch_gemm_i8)
 bool gemm_persistent_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                         int64_t ldb, const GemmEpilogue& ep);
 // (second: accumulate mode only; both products must pass gemm_persistent_ok)
