@@ -52,6 +52,10 @@
 // multiple of 4 KiB (corrections, us, down / along: pitch 32 KiB 781 / 858, 56 KiB 456 / 456, 16388 bytes 122 / 106,
 // 20000 bytes 236 / 222; edge with 32 KiB 191 / 208).  8, 12, 16 or 20 blocks ahead are the same time.
 //
+// Where M or N is no multiple of the tile C goes through the caches, also in whole tiles, so that parts of a line which
+// two rows or tiles share leave together (around them / through them, calls, us: 2999 x 4097 x 3001 279 / 266, 5000^2 x 2000
+// 330 / 313, 9000^2 x 3000 1187 / 1147, 4001 x 14001 x 4000 1246 / 1206); whole tiles of a last product go around them.
+//
 // M and N need not be multiples of the tile: rows past the end are cut off by the range check of the
 // buffer descriptor (whatever lands in LDS for them feeds elements that are never stored), and the
 // epilogue of a tile on the edge checks every access.
@@ -396,7 +400,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
             if (SCALED) out[v] = alpha * out[v];
             if (BETA) out[v] = out[v] + beta * cin[BETA ? i % kIn : 0][h][v];
           }
-          row_store<CACHED>(out, c_out, lane + 128 * j, h * 8 * (uint32_t)ldc4);
+          row_store<CACHED || EDGE>(out, c_out, lane + 128 * j, h * 8 * (uint32_t)ldc4);
         }
         next(c_out, i, ldc4);
         if (i + kRing < kBlocks) load_c(i + kRing);
@@ -521,7 +525,7 @@ __global__ __launch_bounds__(256) void gemm_i8_persistent_kernel(int64_t M, int6
               }
             }
             if (EDGES) edge_store<EDGES == 2>(out, c_row, ldc4, 8 * h + r8, 32 * j + c16, rows - 16 * a, cols);
-            else row_store<false>(out, c_row, lane + 128 * j, h * 8 * (uint32_t)ldc4);
+            else row_store<EDGE>(out, c_row, lane + 128 * j, h * 8 * (uint32_t)ldc4);
           }
           c_row += a == TM - 1 ? -(TM - 1) * 16 * ldc4 : 16 * ldc4;
           if (SCALE) in_row += a == TM - 1 ? -(TM - 1) * 64 * ldcin : 64 * ldcin;
