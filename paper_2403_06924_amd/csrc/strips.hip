@@ -16,7 +16,9 @@
 // A strip reads 64, 32 or 16 bytes of each row of B; strips that share 128-byte lines are given to the same
 // XCD (strip_of), where the line is found in L2 the second time.
 // Up to K = 2048 a wave has a row of A to itself, or a vector of the compaction where there are many: nothing in a row
-// then waits at a barrier, and the workgroups are a quarter to an eighth as many.  With a workgroup per row and
+// then waits at a barrier, and the workgroups are a quarter to an eighth as many.  So it is up to K = 4096 with 16
+// pieces per lane (a workgroup per row has a compute unit to itself there, because the strips need 162 registers:
+// 2048^2 x 2112 quantize 30 / 22, select 25 / 16, calls 105 / 89; 3000^3 229 / 206).  With a workgroup per row and
 // vector / a wave: 2048^3 quantize 17.6 / 13.3 us, select 11.6 / 9.8, compact 12.9 / 11.6, calls 83.4 / 77.2;
 // 10000 x 1024 x 2048 234 / 215, 4000 x 100 x 2000 70.6 / 62.0, 2048^2 x 512 46.6 / 42.9, 1024^3 35.3 / 35.1.
 // Kernel times in a call, us, as ten launches and as these three: 1024^3 8.8 + 4.6 + 6.0 now; 2048^3 quantize 21.7 and
@@ -610,21 +612,22 @@ int strip_cg(int64_t K) { return K <= 512 ? 4 : K <= 4096 ? 2 : 1; }
 //   K <= 1024, any size    512^2 x 256 49 / 26, 8192^2 x 1024 540 / 521
 //   K <= 2048              4096^2 x 2048 228 / 194, 20000 x 200 x 2000 261 / 234, 8192^2 x 2048 654 / 650, 16384 x 4096 x 2048
 //                          643 / 636, 12288^2 x 2048 1269 / 1280
-//   K <= 4096              512^2 x 4096 84 / 67, 2048^2 x 4096 148 / 138, 1000 x 5000 x 4000 283 / 251, 3000^2 x 3000
-//                          277 / 277, 4096^3 323 / 370; with M > 4096 the rows lose: 5000 x 500 x 3000 156 / 162,
-//                          5900 x 90 x 2200 117 / 150
+//   K <= 4096              2048^2 x 4096 148 / 121, 2999 x 4097 x 3001 267 / 246, 2000 x 6000 x 3000 279 / 246, 3500^2 x
+//   and (M + N) K <= 24e6  2500 229 / 215, 4500 x 1400 x 4000 208 / 178, 5900 x 90 x 2200 117 / 96; 4096^2 x 2500 244 / 245;
+//                          3500^2 x 4096 306 / 313, 4096^2 x 3072 265 / 274, 6000^2 x 2112 440 / 486, 4096^3 304 / 320
 //   K <= 8192              512^2 x 8192 120 / 106, 1024^2 x 8192 139 / 137, 2048^2 x 8192 241 / 261
 bool strips_ok(int64_t M, int64_t N, int64_t K) {
   if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
-  return K <= 1024 || (K <= 2048 && M + N <= 20480) || (K <= 4096 && M <= 4096 && M + N <= 6000) || M + N <= 2048;
+  return K <= 1024 || (K <= 2048 && M + N <= 20480) || (K <= 4096 && (M + N) * K <= 24000000) || M + N <= 2048;
 }
-// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, before / now; about 36 us of the small
-// ones is the host): columns 1000 x 1000 51 / 36, 2000 x 10000 130 / 95, 4000 x 5900 157 / 124, but 5000 x 1500 68 / 75, so
-// columns longer than 4096 stay in passes; 15000 x 2000 197 / 125; rows 10000 x 1000 62 / 53, 3000 x 3000 45 / 39,
-// 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 5900 x 2500 65 / 57, 4000 x 5900 87 / 87.
+// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, streaming / here; about 36 us of the small
+// ones is the host): columns 1000 x 1000 51 / 36, 15000 x 2000 197 / 125, 25000 x 2048 296 / 219, 10000 x 4096 204 / 171, but
+// 14336 x 4096 233 / 293, 20000 x 2500 238 / 295, and 5000 x 1500 with columns longer than 4096 in strips 68 / 75; rows 10000 x 1000
+// 62 / 46, 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 30000 x 4096 367 / 300, with longer rows 4000 x 5900 87 / 87.
 bool strips_one_ok(int axis, int64_t nvec, int64_t veclen) {
-  if (axis == SRQ_AXIS_ROW && veclen > 0 && veclen <= 4096 && nvec <= 6000) return true;
-  return (axis == SRQ_AXIS_ROW || veclen <= 4096) && strips_ok(axis == SRQ_AXIS_ROW ? nvec : 0, axis == SRQ_AXIS_ROW ? 0 : nvec, veclen);
+  if (veclen <= 0 || nvec >= (1 << 24)) return false;
+  if (axis == SRQ_AXIS_ROW) return veclen <= 4096 || strips_ok(nvec, 0, veclen);
+  return veclen <= 2048 || (veclen <= 4096 && nvec <= 10240);
 }
 // (Every workgroup adds up the counts before its vectors: scan and scatter in launches of their own / here, us:
 // 8000 x 200 x 2000 94.9 / 82.3, 16000 x 200 x 200 66.2 / 61.8, 40 x 40000 x 1000 202 / 220, 60000 x 60 x 2000 505 / 539.)
@@ -643,7 +646,7 @@ bool strips_compact_ok(int64_t M, int64_t N) { return M <= kStripsMaxScan && N <
     else if (K <= 1024) SRQ_STRIPS_AS(256, 64, 4, 2, 8, KERN, ROWS, __VA_ARGS__);                                    \
     else if (K <= 2048 && N + (ROWS) <= 6000) SRQ_STRIPS_AS(512, 64, 8, 2, 8, KERN, ROWS, __VA_ARGS__);              \
     else if (K <= 2048) SRQ_STRIPS_AS(256, 64, 8, 2, 16, KERN, ROWS, __VA_ARGS__);                                   \
-    else if (K <= 4096) SRQ_STRIPS_AS(512, 512, 2, 2, 16, KERN, ROWS, __VA_ARGS__);                                  \
+    else if (K <= 4096) SRQ_STRIPS_AS(512, 64, 16, 2, 16, KERN, ROWS, __VA_ARGS__);                                  \
     else SRQ_STRIPS_AS(512, 512, 4, 1, 16, KERN, ROWS, __VA_ARGS__);                                                 \
   } while (0)
 
@@ -689,7 +692,7 @@ hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int
   } while (0)
   // A wave per vector takes a quarter of the workgroups and prefixes, and longer in each.  Up to 2048 vectors (eight
   // workgroups on each CU, all at once) that loses: 1024^3 6.2 us with a workgroup per vector, 6.8 with a wave;
-  // 2048^3 12.9 and 11.6.
+  // 2048^3 12.9 and 11.6, 3000^3 23.7 and 21.5.
   const bool few = a.nvec + b.nvec <= 2048;
   if (Kc <= 256) SRQ_COMPACT(64, 1);
   else if (Kc <= 1024) {
@@ -698,8 +701,10 @@ hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int
   } else if (Kc <= 2048) {
     if (few) SRQ_COMPACT(256, 2);
     else SRQ_COMPACT(64, 8);
-  } else if (Kc <= 4096) SRQ_COMPACT(256, 4);
-  else SRQ_COMPACT(256, 8);
+  } else if (Kc <= 4096) {
+    if (few) SRQ_COMPACT(256, 4);
+    else SRQ_COMPACT(64, 16);
+  } else SRQ_COMPACT(256, 8);
 #undef SRQ_COMPACT
   return hipGetLastError();
 }

@@ -119,7 +119,7 @@ def test_short_inner_dimension(srq, b, shape, terms):
 
 # more than 2048 vectors together: a wave of the compaction has a whole vector; vectors at the edges of its shapes, and
 # counts of vectors that are no multiple of four; the limit on vectors (16384) of a compaction without a scan
-@pytest.mark.parametrize("shape", [(1502, 549, 256), (2043, 6, 257), (7, 2042, 1024), (2041, 9, 1025), (9, 2041, 2048), (2049, 1, 3),
+@pytest.mark.parametrize("shape", [(1502, 549, 256), (2043, 6, 257), (7, 2042, 1024), (2041, 9, 1025), (9, 2041, 2048), (2049, 1, 3), (2043, 14, 2049), (14, 2043, 3001), (2050, 7, 4095), (5853, 5, 4096),
                                    (16384, 5, 40), (16385, 5, 40), (3, 16385, 130)])
 def test_a_wave_per_vector(srq, b, shape):
     test_short_inner_dimension(srq, b, shape, "both")
@@ -159,7 +159,7 @@ def test_reduction_of_one_operand(srq, b, shape, axis, bits):
     assert (host(r["idx"][:n]) == k).all() and (host(r["val"][:n]) == q[vec, k]).all()
 
 
-@pytest.mark.parametrize("shape", [(4096, 4100), (2049, 6000), (1027, 12300), (2048, 4099)])
+@pytest.mark.parametrize("shape", [(4096, 4100), (2049, 6000), (1027, 12300), (2048, 4099), (4096, 10241)])
 @pytest.mark.parametrize("axis", [0, 1])
 def test_reduction_of_many_vectors(srq, b, shape, axis):
     test_reduction_of_one_operand(srq, b, shape, axis, 8)
