@@ -67,18 +67,19 @@ __device__ __forceinline__ void load_row(float4 (&x)[NV4], int (&n)[NV4], const 
     for (int i = 0; i < NV4; ++i) x[i] = load_part(src + 4 * (t + i * RT), n[i]);
     return;
   }
-  f4u y[NV4];
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) y[i] = load_inside(src, 4 * (t + i * RT), K);
-  if (K >= 4 * RT * NV4) {                           // (nobody reaches past K)
+  for (int i = 0; i < NV4; ++i) {
+    const f4u y = load_inside(src, 4 * (t + i * RT), K);
+    x[i] = make_float4(y.x, y.y, y.z, y.w);
+  }
+  if (K < 4 * RT * NV4) {                            // (somebody reaches past K)
 #pragma unroll
-    for (int i = 0; i < NV4; ++i) x[i] = make_float4(y[i].x, y[i].y, y[i].z, y[i].w);
-  } else {
-#pragma unroll
-    for (int i = 0; i < NV4; ++i) x[i] = shifted(y[i], 4 * (t + i * RT), K);
+    for (int i = 0; i < NV4; ++i) x[i] = shifted(f4u{x[i].x, x[i].y, x[i].z, x[i].w}, 4 * (t + i * RT), K);
   }
 }
-// A thread's patch of a strip: rows row0 .. row0 + RPT - 1 of four columns from col0 on, zeros outside
+// A thread's patch of a strip: rows row0 .. row0 + RPT - 1 of four columns from col0 on, zeros outside.  (Put right in place,
+// under one branch: with both forms behind an if and else the selection takes 147 registers for 116, one workgroup on a
+// compute unit for two; 2999 x 4097 x 3001 245 us / 239.)
 template <int TH, int CG, int RPT>
 __device__ __forceinline__ void load_patch(float4 (&v)[RPT], const float* X, int64_t ldx, int strip, int row0, int64_t col0, int64_t cols,
                                            int K) {
@@ -88,16 +89,15 @@ __device__ __forceinline__ void load_patch(float4 (&v)[RPT], const float* X, int
     for (int i = 0; i < RPT; ++i) v[i] = load_part(X + (int64_t)(row0 + i) * ldx + col0, row0 + i < K ? n : 0);
     return;
   }
-  f4u t[RPT];
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) t[i] = load_inside(X + (int64_t)(row0 + i < K ? row0 + i : K - 1) * ldx, (int)col0, (int)cols);
-  if (K >= TH / CG * RPT && (int64_t)(strip + 1) * 4 * CG <= cols) {   // (the whole strip exists)
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) v[i] = make_float4(t[i].x, t[i].y, t[i].z, t[i].w);
-  } else {
+  for (int i = 0; i < RPT; ++i) {
+    const f4u t = load_inside(X + (int64_t)(row0 + i < K ? row0 + i : K - 1) * ldx, (int)col0, (int)cols);
+    v[i] = make_float4(t.x, t.y, t.z, t.w);
+  }
+  if (K < TH / CG * RPT || (int64_t)(strip + 1) * 4 * CG > cols) {   // (part of the strip does not exist)
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-      v[i] = shifted(t[i], (int)col0, (int)cols);
+      v[i] = shifted(f4u{v[i].x, v[i].y, v[i].z, v[i].w}, (int)col0, (int)cols);
       if (row0 + i >= K) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
@@ -218,6 +218,7 @@ __device__ __forceinline__ void patch_codes(float4 (&v)[RPT], const float (&lam)
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) pk[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], left - i);
+    __builtin_amdgcn_sched_barrier(0);               // (all rows at once would take 60 more registers)
   }
 }
 
