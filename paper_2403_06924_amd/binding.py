@@ -245,11 +245,14 @@ class Srq:
             ptr = torch.empty(nvec + 1, dtype=torch.int32, device=dev)
             idx = torch.empty(max(capacity, 1), dtype=torch.int32, device=dev)
             val = torch.empty(max(capacity, 1), dtype=torch.int8, device=dev)
-            nnz = torch.zeros(1, dtype=torch.int64, device=dev)
+            # (written by every call that has entries to look at: clearing it was a launch and 5 us of the host's time)
+            nnz = (torch.empty if rows and cols else torch.zeros)(1, dtype=torch.int64, device=dev)
         st = self.lib.srq_build_sparse_residual(
             self.h, _ptr(X), rows, cols, X.stride(0) if rows else cols, axis, _ptr(scale), _ptr(lam),
             _ptr(thresh), bits, rounding, _ptr(Rq), shape[1], r_layout, _ptr(rscale), _ptr(ptr), _ptr(idx),
             _ptr(val), capacity or 0, _ptr(nnz), self._stream())
+        if st and nnz is not None:
+            nnz.zero_()
         self._ret(st, "srq_build_sparse_residual")
         out.update(Rq=Rq, rscale=rscale, ptr=ptr, idx=idx, val=val, nnz=nnz)
         return out

@@ -621,7 +621,7 @@ bool strips_ok(int64_t M, int64_t N, int64_t K) {
   if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
   return K <= 1024 || (K <= 2048 && M + N <= 20480) || (K <= 4096 && (M + N) * K <= 24000000) || M + N <= 2048;
 }
-// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, streaming / here; about 36 us of the small
+// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, streaming / here; about 31 us of the small
 // ones is the host): columns 1000 x 1000 51 / 36, 15000 x 2000 197 / 125, 25000 x 2048 296 / 219, 10000 x 4096 204 / 171, but
 // 14336 x 4096 233 / 293, 20000 x 2500 238 / 295, and 5000 x 1500 with columns longer than 4096 in strips 68 / 75; rows 10000 x 1000
 // 62 / 46, 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 30000 x 4096 367 / 300, with longer rows 4000 x 5900 87 / 87.

@@ -266,3 +266,16 @@ def test_two_launches_are_the_separate_ones(srq, b, shape, odd):
         assert got[0][2].keys() == got[1][2].keys()
         for key, value in got[0][2].items():               # (bits: a threshold of an infinite factor and a zero mean is no number)
             assert torch.equal(value.contiguous().view(torch.uint8), got[1][2][key].contiguous().view(torch.uint8)), key
+
+
+@pytest.mark.parametrize("rows,cols", [(0, 5), (5, 0), (3, 7), (900, 33), (70, 5000), (5000, 70)])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_count_of_nothing_kept(srq, b, rows, cols, axis):
+    """The count is written by every call that has entries to look at, and zero where there are none."""
+    X = torch.ones(rows, cols, device="cuda")
+    _, s, lam = srq.quantize(X, axis)
+    t = torch.full((rows if axis == 0 else cols,), float("inf"), device="cuda")
+    stale = [torch.full((1,), 7, dtype=torch.int64, device="cuda") for _ in range(64)]
+    del stale                                                # what a count that nobody writes would hold
+    r = srq.build_sparse_residual(X, axis, s, lam, t)
+    assert int(r["nnz"].item()) == 0 and not host(r["ptr"]).any()
