@@ -32,6 +32,28 @@ static SRQ_HOST_DEVICE int last_ktile_mask(int K, int half) {
 // 8192^3, random codes, 433 us against 388.)
 static SRQ_HOST_DEVICE int first_ktile_step(int K) { return kKTile - (K & 64); }
 
+// Where a kernel is that fetches ahead of the K-tiles it multiplies, of products `prod` .. last, and goes on issuing its
+// loads when none is left: then with descriptors of no bytes and at offset zero.  (The range check may be against the
+// size less the scalar offset, which for no bytes and an offset is a large number.)
+struct KtileCursor {
+  int prod, kt;                                      // kt: from the number of K-tiles on nothing is left
+  SRQ_HOST_DEVICE bool same_rows(int nk) {           // to the next K-tile of the product
+    if (kt + 1 >= nk) return false;
+    ++kt;
+    return true;
+  }
+  SRQ_HOST_DEVICE bool next_product(int nk, int last) {   // ... or of the next one
+    if (prod >= last) {
+      kt = nk;
+      return false;
+    }
+    ++prod;
+    kt = 0;
+    return true;
+  }
+  SRQ_HOST_DEVICE int start(int nk, int K) const { return kt < nk ? ktile_start(kt, K) : 0; }
+};
+
 }  // namespace srq
 
 #undef SRQ_HOST_DEVICE

@@ -39,3 +39,39 @@ def test_every_ktile_stays_in_its_row_and_counts_once(tmp_path):
             counted += [start + 64 * h for h, m in ((0, head), (1, tail)) if m]
             assert head in (0, -1) and tail in (0, -1)
         assert sorted(counted) == list(range(0, K, 64))
+
+
+CURSOR = r"""
+#include <cstdio>
+#include "gemm_ktiles.h"
+int main() {
+  for (int K = 64; K <= 2048; K += 64)
+    for (int first = 0; first < 2; ++first)
+      for (int last = first; last < 2; ++last) {
+        const int nk = (K + srq::kKTile - 1) / srq::kKTile;
+        srq::KtileCursor c = {first, 0};
+        int step = -1;                       // 0: same rows, 1: the next product, 2: nothing is left
+        for (int g = 0; g < nk * (last - first + 1) + 5; ++g) {
+          std::printf("%d %d %d %d %d %d\n", K, first, last, step, c.prod, c.start(nk, K));
+          step = c.same_rows(nk) ? 0 : c.next_product(nk, last) ? 1 : 2;
+        }
+      }
+}
+"""
+
+
+def test_fetches_behind_the_last_ktile_are_at_offset_zero(tmp_path):
+    """The stream of K-tiles of one or two products: each once, in order; then descriptors of no bytes (step 2), and no
+    offset that a range check against their size less the offset would wrap around with."""
+    src, exe = tmp_path / "cursor.cpp", tmp_path / "cursor"
+    src.write_text(CURSOR)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    rows = [tuple(map(int, ln.split())) for ln in subprocess.run([str(exe)], check=True, capture_output=True,
+                                                                 text=True).stdout.splitlines()]
+    for K in range(64, 2049, 64):
+        for first, last in ((0, 0), (0, 1), (1, 1)):
+            got = [r[3:] for r in rows if r[:3] == (K, first, last)]
+            starts = [min(128 * kt, max(K - 128, 0)) for kt in range((K + 127) // 128)]
+            want = [(0 if kt else -1 if p == first else 1, p, at) for p in range(first, last + 1) for kt, at in enumerate(starts)]
+            assert got[:len(want)] == want
+            assert got[len(want):] == [(2, last, 0)] * 5
