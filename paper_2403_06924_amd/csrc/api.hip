@@ -99,7 +99,7 @@ struct Plan {
   double *row_part, *col_part;
   int32_t *tot_a, *a_ptr, *tot_b, *b_ptr;
   int64_t* nnz;   // [2]
-  int32_t* paths; // [2] executions SRQ_STRATEGY_AUTO decided on the device
+  int32_t* paths; // [2] executions SRQ_STRATEGY_AUTO decided on the device; a short call's count of chunks taken
   uint64_t *mask_a, *mask_b;   // keep-bits, one row of words per vector
   int32_t *a_idx, *b_idx;
   int8_t *a_val, *b_val;
@@ -803,7 +803,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (short_ok(M, N, K, lda, ldb, last)) {
       const ShortCall g = {A, B, lda, ldb, (int)M, (int)N, (int)K, trunc, (float)qmax, theta_a, theta_b, term_a, term_b,
                            p.A_int, p.B_int, p.RA_int, p.RB_int, p.s_a, p.lam_a, p.s_ra, p.s_b, p.lam_b, p.s_rb,
-                           p.row_part, p.col_part, p.drow, p.dcol, p.t_a, p.t_b, p.tot_a, p.tot_b,
+                           p.row_part, p.col_part, p.drow, p.dcol, p.t_a, p.t_b, p.tot_a, p.tot_b, p.paths,
                            {p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.nnz + 0}, {p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.nnz + 1}};
       {
         StageTimer tm(h, st, SRQ_STAGE_GEMM);

@@ -143,6 +143,7 @@ struct ChunkShared {
   int count[kChunk];
   uint32_t wave[4][4];
   int64_t before[4];
+  int chunk;
 };
 
 // sixteen rows of A, one sixteen lanes wide: codes, residual codes, scales
@@ -160,7 +161,10 @@ __device__ __forceinline__ void quantize_rows(const ShortCall& g, int chunk) {
   };
   if (K & 3) load(std::false_type());
   else load(std::true_type());
-  if (COMP && tid == 0) g.state_a[chunk] = -1;       // (what the second launch publishes there starts as absent)
+  if (COMP && tid == 0) {                            // (what the second launch publishes there starts as absent)
+    g.state_a[chunk] = -1;
+    if (chunk == 0) *g.ticket = 0;
+  }
   float m = 0.f;
 #pragma unroll
   for (int i = 0; i < NI; ++i) m = max_abs4(x[i], m);
@@ -430,10 +434,17 @@ __device__ __forceinline__ void threshold_b(const ShortCall& g, int col, float& 
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
+// The chunk a compacting workgroup takes: the next one in the order in which they start (one counter, rows of A before
+// columns of B, whatever their indices in the grid are).
+__device__ __forceinline__ int take_chunk(int32_t* ticket, int* sm) {
+  if (threadIdx.x == 0) *sm = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*sm);
+}
 // Kept entries of the chunks before this one: every chunk publishes its own number as soon as it has it, before it waits,
-// and waits for lower chunks only.  Their workgroups have lower indices in the grid, are started first (each XCD starts
-// its own in order) and never wait for a higher one: the lowest chunk that has not published is running, or next on
-// an XCD with nothing of this grid in front of it.
+// and waits for lower chunks only.  Those have been taken before, by workgroups that are running and wait for nothing
+// until they have published: every wait ends, in whatever order and wherever workgroups are started and whatever else,
+// calls on other streams among it, has taken the compute units.
 __device__ __forceinline__ int64_t kept_before(int32_t* state, int chunk, int kept, int64_t* sm) {
   const int tid = threadIdx.x;
   if (tid == 0) __hip_atomic_store(state + chunk, kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -610,8 +621,11 @@ __global__ __launch_bounds__(256) void short_second_kernel(ShortCall g, int tile
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];       // A', RB, RA, B'
   __shared__ ChunkShared sm;
   __shared__ float t_row[BT], t_col[BT];
-  if ((int)blockIdx.x < chunks_a) return compact_rows<KC>(g, blockIdx.x, sm);
-  if ((int)blockIdx.x < chunks_a + chunks_b) return compact_cols<KC>(g, (int)blockIdx.x - chunks_a, sm);
+  if ((int)blockIdx.x < chunks_a + chunks_b) {
+    const int chunk = take_chunk(g.ticket, &sm.chunk);
+    if (chunk < chunks_a) return compact_rows<KC>(g, chunk, sm);
+    return compact_cols<KC>(g, chunk - chunks_a, sm);
+  }
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) int8_t*)lds);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
   const int quad = lane >> 4, rl = lane & 15, M = g.M, N = g.N, K = g.K;

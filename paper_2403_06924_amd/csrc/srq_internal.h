@@ -290,7 +290,7 @@ hipError_t launch_reduce_cols(const StripReduce& s, int64_t N, int64_t K, int64_
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st);
 
 // ---- an inner dimension of at most 256 and few tiles of C: the whole call in two launches (short.hip).  Code matrices
-// have rows of K rounded up to 128.  state_a / state_b: a word per sixteen rows of A / columns of B.
+// have rows of K rounded up to 128.  state_a / state_b: a word per sixteen rows of A / columns of B; ticket: one.
 struct ShortCompact {
   int32_t *ptr, *idx;
   int8_t* val;
@@ -306,7 +306,7 @@ struct ShortCall {
   float *s_a, *lam_a, *s_ra, *s_b, *lam_b, *s_rb;
   double *row_part, *col_part;
   float *drow, *dcol, *t_a, *t_b;
-  int32_t *state_a, *state_b;
+  int32_t *state_a, *state_b, *ticket;
   ShortCompact ca, cb;
 };
 bool short_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const GemmEpilogue& ep);

@@ -277,3 +277,41 @@ def test_count_of_nothing_kept(srq, b, rows, cols, axis):
     del stale                                                # what a count that nobody writes would hold
     r = srq.build_sparse_residual(X, axis, one, one, t, want_residual=rows * cols > 0)
     assert int(r["nnz"].item()) == 0 and not host(r["ptr"]).any()
+
+
+def test_short_calls_on_several_streams(b):
+    """Calls in two launches on six streams at once, a handle each: the workgroups that compact wait for those of their own
+    call alone.  Every call's result, counts and row pointers are those of the same call by itself."""
+    shapes = [(1024, 1024, 256), (1000, 1023, 250), (256, 256, 256), (960, 896, 64), (1024, 33, 192), (513, 1024, 129)]
+    gen = torch.Generator(device="cuda").manual_seed(41)
+    calls = []
+    for M, N, K in shapes:
+        h = b.Srq(device=0)
+        h.ensure_workspace(b.workspace_bytes(M, N, K, 1.0))
+        A, B = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((K, N), generator=gen, device="cuda")
+        outs = [torch.empty((M, N), device="cuda") for _ in range(8)]
+        stats = [b.stats_tensor() for _ in outs]
+        ref, ref_stats = torch.empty((M, N), device="cuda"), b.stats_tensor()
+        kw = dict(strategy=b.STRATEGY_CSR_MFMA, max_density=1.0)
+        h.compensated_gemm(A, B, 0.03, out=ref, stats=ref_stats, **kw)
+        torch.cuda.synchronize()
+        im = h.intermediates(M, N, K)
+        calls.append((h, A, B, outs, stats, ref, ref_stats, {k: im[k].clone() for k in ("a_ptr", "a_idx", "b_ptr", "b_idx")}, kw,
+                      torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    try:
+        for i in range(8):
+            for h, A, B, outs, stats, _, _, _, kw, stream in calls:
+                with torch.cuda.stream(stream):
+                    h.compensated_gemm(A, B, 0.03, out=outs[i], stats=stats[i], **kw)
+        torch.cuda.synchronize()
+        for (M, N, K), (h, _, _, outs, stats, ref, ref_stats, kept, _, _) in zip(shapes, calls):
+            assert b.read_stats(ref_stats)["nnz_a"] > 0
+            for out, st in zip(outs, stats):
+                assert torch.equal(out, ref) and torch.equal(st, ref_stats)
+            im = h.intermediates(M, N, K)
+            for key, value in kept.items():
+                assert torch.equal(im[key], value), key
+    finally:
+        for c in calls:
+            c[0].close()
