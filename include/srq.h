@@ -238,11 +238,11 @@ srq_status_t srq_build_sparse_residual(srq_handle_t handle, const float* X, int6
  * columns of a row and up to four rows of a column meet in FP32 first; both may be NULL.
  * Any shape and alignment is accepted.  The fast kernels need 16-byte aligned Qa and Qb, lda and ldb
  * multiples of 16 and below 2^23, K a multiple of 64 (pad K with zero codes to get there: they add
- * nothing) and no D_int; M and N may be anything.  Among them, by the shape alone: without means 32 rows
- * at most (64 up to N = 8192) from K = 256 on, and 64 x 64 tiles for up to 640 of them (512 where K > 1400) or for K up
- * to 384 where larger tiles leave compute units idle; otherwise the persistent 256 x 256 kernel (K above 128) or tiles of
- * 128 x 128 or 256 x 128, whichever needs the cheaper rounds over the device's compute units.  Nothing behind the last
- * row of Qa or Qb is read.
+ * nothing) and no D_int; M and N may be anything.  Among them, by the shape alone with means, by the shape and the
+ * device's number of compute units without: without means 32 rows at most (64 up to N = 8192) from K = 256 on, and
+ * 64 x 64 tiles for up to 640 of them (512 where K > 1400), for K below 128, and for K up to 384 where larger tiles leave
+ * compute units idle; otherwise the persistent 256 x 256 kernel (K above 128) or tiles of 128 x 128 or 256 x 128, whichever
+ * needs the cheaper rounds over the compute units.  Nothing behind the last row of Qa or Qb is read.
  */
 srq_status_t srq_gemm_i8(srq_handle_t handle, int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda,
                          const float* sa, const int8_t* Qb, int64_t ldb, const float* sb, float* D_F,
