@@ -794,13 +794,19 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   ep.final_scale = !comp && scale_needed;
   // A short inner dimension and few tiles: two launches, one without compensation (booked as the products; with every
   // stage timed the stages stay launches of their own).  The compressed arrays have to hold any selection:
-  // nothing counts the kept entries before the corrections.
+  // nothing counts the kept entries before the corrections.  Some workgroups read the operands while others write
+  // C: a C that shares memory with one of them (without compensation a program may put it there, since every other
+  // execution has quantized both before it writes) is left to the separate launches.
+  auto apart_from_c = [&](const float* X, int64_t rows, int64_t cols, int64_t ldx) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(X), c = reinterpret_cast<uintptr_t>(C);
+    return x + 4 * (uintptr_t)((rows - 1) * ldx + cols) <= c || c + 4 * (uintptr_t)((M - 1) * ldc + N) <= x;
+  };
   const bool every_stage = h->prof_enabled && ((h->prof_mask >> SRQ_STAGE_QUANTIZE) & 1u);
   if (!dbg && !global_scale && !every_stage && (!comp || (strategy == SRQ_STRATEGY_CSR_MFMA && dense_fallback_density > 1.f &&
                                           (!term_a || p.cap_a >= M * K) && (!term_b || p.cap_b >= N * K)))) {
     GemmEpilogue last = ep;
     last.final_scale = scale_needed;
-    if (short_ok(M, N, K, lda, ldb, last)) {
+    if (short_ok(M, N, K, lda, ldb, last) && apart_from_c(A, M, K, lda) && apart_from_c(B, K, N, ldb)) {
       const ShortCall g = {A, B, lda, ldb, (int)M, (int)N, (int)K, trunc, (float)qmax, theta_a, theta_b, term_a, term_b,
                            p.A_int, p.B_int, p.RA_int, p.RB_int, p.s_a, p.lam_a, p.s_ra, p.s_b, p.lam_b, p.s_rb,
                            p.row_part, p.col_part, p.drow, p.dcol, p.t_a, p.t_b, p.tot_a, p.tot_b, p.paths,

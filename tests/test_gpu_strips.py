@@ -315,3 +315,31 @@ def test_short_calls_on_several_streams(b):
     finally:
         for c in calls:
             c[0].close()
+
+
+# without compensation C may take the place of an operand: both are quantized before it is written, also where workgroups
+# start one after the other because another stream keeps the compute units busy
+@pytest.mark.parametrize("n", [64, 250, 256])
+def test_product_in_place_of_an_operand(srq, b, n):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    inf, side, load = float("inf"), torch.cuda.Stream(), torch.ones(1 << 26, device="cuda")
+    for M, N in ((n, n), (1000, n), (n, 1000)):
+        for place in ("a", "b", "rows of b"):
+            A, B = torch.randn((M, n), generator=gen, device="cuda"), torch.randn((n, N), generator=gen, device="cuda")
+            ref = torch.empty((M, N), device="cuda")
+            srq.compensated_gemm(A, B, inf, out=ref)
+            if place == "a" and N == n:
+                out = A
+            elif place == "b" and M == n:
+                out = B
+            else:                                            # B lies within C
+                out = torch.empty(M + n, N, device="cuda")
+                out[M // 2:M // 2 + n] = B
+                out, B = out[:M], out[M // 2:M // 2 + n]
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                for _ in range(4):
+                    load.mul_(1.0)
+            srq.compensated_gemm(A, B, inf, out=out)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref), (M, N, place)
