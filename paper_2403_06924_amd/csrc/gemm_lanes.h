@@ -57,10 +57,11 @@ static __device__ __forceinline__ void row_store(v4f x, uint64_t base, uint32_t 
       buf_rsrc(reinterpret_cast<const void*>(base), 0xffffffffu), lane, off, CACHED ? 0 : 2 /* non-temporal */);
 }
 
-// the same on the edge, without branches: row `row`, columns col .. col + 3 of the rows that start at `base`, of which
-// rows x cols exist; an access outside gets an offset past the end of its descriptor (its load brings zero, its
-// store is dropped).  ELEMS: the last columns are not a whole access.
+// Accesses without branches (a load behind one is waited for before the next is issued): what does not exist gets an
+// offset past the end of its descriptor, where a load brings zero and a store is dropped.
 constexpr uint32_t kOutside = 0xfffffff0u, kRecords = 0x7fffffffu;
+// the same on the edge: row `row`, columns col .. col + 3 of the rows that start at `base`, of which rows x cols
+// exist.  ELEMS: the last columns are not a whole access.
 static __device__ __forceinline__ uint32_t edge_offset(int64_t ld4, int row, int col, int rows, int cols) {
   return row < rows && col < cols ? (uint32_t)row * (uint32_t)ld4 + 4u * (uint32_t)col : kOutside;
 }

@@ -40,7 +40,8 @@
 // one launch 968 / 781, of which 592 are the K loops and 190 eight epilogues: 14 us each for loading C, converting and
 // adding, 10 for the stores, together 5.5 TB/s.
 //
-// The epilogues spill nothing, inside and outside the K loop, because (a) the accumulators are read one by one through
+// The epilogues spill no vector register, inside and outside the K loop (scalar ones go to lanes of vector registers: 10 to 79 in
+// most variants, about 250 in the accumulating edge kernels with alpha and beta), because (a) the accumulators are read one by one through
 // assembly: otherwise the conversions that the copies of an epilogue have in common are all computed ahead of the
 // branch between them; (b) C is accessed through buffer descriptors with running scalar row pointers and one lane
 // offset, not 64-bit addresses per access; (c) accesses on the edge are cut off by the descriptor's range, not
@@ -72,7 +73,6 @@ namespace srq {
 namespace {
 
 // four consecutive floats at any 4-byte aligned address (rows of C may start anywhere)
-typedef v4f v4fu __attribute__((aligned(4)));
 
 constexpr int BM = 256, BN = 256, BK = kKTile;
 constexpr int kOperand = BM * BK;                   // 32 KiB per operand tile

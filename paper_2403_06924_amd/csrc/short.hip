@@ -15,8 +15,8 @@
 // branch is waited for before the next is issued: 15 us instead of 7 for the first launch at 256^3), few vector
 // instructions per element (a wave's instruction takes four clocks: codes are rounded by an addition and packed by
 // byte permutes, residuals are formed by the sixteen-vector workgroups alone), and no separate pass for anything.
-// Calls at 5 % kept, us, separate launches / these: 256^3 23.3 / 14.5, 960 x 896 x 64 with beta 25.9 / 16.2, 100^3 23.3 /
-// 12.8, 1024^2 x 128 25.1 / 16.7, 1024^2 x 256 25.9 / 20.3, 1000^2 x 250 27.7 / 25.8 (rows of A that are no multiple
+// Calls at 5 % kept, us, separate launches / these: 256^3 23.3 / 14.1, 960 x 896 x 64 with beta 25.9 / 15.4, 100^3 23.3 /
+// 12.8, 1024^2 x 128 25.1 / 16.7, 1024^2 x 256 25.9 / 18.4, 1000^2 x 250 27.7 / 25.4 (rows of A that are no multiple
 // of 16 bytes are loaded by the element); 256^3 without compensation 10.9 / 8.0.  Larger ones would lose (2048^2 x
 // 256 40.8 / 69 with 1024 tiles, that many times the quantization).
 // The codes, the sums of |D_F| and the order in which they are added up are those of the other kernels (tile64_product;
@@ -47,9 +47,7 @@ __device__ __forceinline__ float max16(float m) {
 
 __device__ __forceinline__ int left4(int n) { return n >= 4 ? 4 : n > 0 ? n : 0; }
 
-// The first n (0 .. 4) of four values, zero for the others, without branches (a load behind one is waited for before
-// the next is issued): what does not exist is read past the end of the descriptor.  WHOLE: n is 0 or 4.
-constexpr uint32_t kRecords = 0x7fffffffu, kOutside = 0xfffffff0u;
+// The first n (0 .. 4) of four values, zero for the others.  WHOLE: n is 0 or 4.
 template <bool WHOLE>
 __device__ __forceinline__ v4f load4(__amdgpu_buffer_rsrc_t r, uint32_t off, int n) {
   if (WHOLE) return buf_load_4(r, n > 0 ? off : kOutside, true);
@@ -388,7 +386,7 @@ __global__ __launch_bounds__(256) void short_first_kernel(ShortCall g, int tiles
 }
 
 // ---- means ---------------------------------------------------------------------------------------
-// Sums of the partial sums of one row / one column, added up as select_pair_kernel<256, 1, 4, 4> of strips.hip does, which
+// Sums of the partial sums of one row / one column, added up as select_pair_kernel<256, 64, 1, 4, 4> of strips.hip does, which
 // the other executions of such a call run: a row's as a tree over 64 lanes, distances 32, 16, ... 1 (absent ones are
 // zero); a column's, sixteen at most, in pairs, pairs of pairs, and the four sums of four one after the other.
 // (All loads at once, those of absent partials from the last one that exists: a load behind a branch is waited for

@@ -5,13 +5,6 @@
 
 namespace srq {
 
-static __device__ __forceinline__ int quant_code(float x, float lam, float qmax, int trunc) {
-  float y = x * lam;
-  float r = trunc ? truncf(y) : rintf(y);
-  r = fminf(fmaxf(r, -qmax), qmax);
-  return (int)r;
-}
-
 static __device__ __forceinline__ float block_max_256(float m, float* sm) {
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   __syncthreads();                                   // sm may still be read from a previous use
@@ -57,8 +50,9 @@ static __device__ __forceinline__ float4 shifted(f4u x, int at, int len) {
                      past == 1 ? x.w : 0.f, 0.f);
 }
 
-// fl(x * lambda) rounded and clamped as quant_code does, plus 1.5 * 2^23: the code in two's complement is the low byte, and
-// code_value the code as a float (the addition rounds to the nearest even integer, exactly for what is one already)
+// The code of x: fl(x * lambda) rounded to the nearest even integer or towards zero and clamped to [-qmax, qmax], plus 1.5 * 2^23:
+// the code in two's complement is the low byte, and code_value the code as a float (the addition rounds to the nearest
+// even integer, exactly for what is one already)
 constexpr float kCodeBias = 12582912.f;
 static __device__ __forceinline__ float biased_code(float x, float lam, float qmax, bool trunc) {
   float y = x * lam;
@@ -80,11 +74,6 @@ static __device__ __forceinline__ void store_part(float* p, const float (&v)[4],
   } else {
     for (int c = 0; c < n; ++c) p[c] = v[c];
   }
-}
-
-static __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d) {
-  return (unsigned)(a & 0xff) | ((unsigned)(b & 0xff) << 8) | ((unsigned)(c & 0xff) << 16) |
-         ((unsigned)(d & 0xff) << 24);
 }
 
 }  // namespace srq

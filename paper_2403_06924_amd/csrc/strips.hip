@@ -17,7 +17,7 @@
 // XCD (strip_of), where the line is found in L2 the second time.
 // Up to K = 2048 a wave has a row of A to itself, or a vector of the compaction where there are many: nothing in a row
 // then waits at a barrier, and the workgroups are a quarter to an eighth as many.  So it is up to K = 4096 with 16
-// pieces per lane (a workgroup per row has a compute unit to itself there, because the strips need 162 registers:
+// pieces per lane (a workgroup per row has a compute unit to itself there, because the kernel needs 188 registers, its strips 162:
 // 2048^2 x 2112 quantize 30 / 22, select 25 / 16, calls 105 / 89; 3000^3 229 / 206).  With a workgroup per row and
 // vector / a wave: 2048^3 quantize 17.6 / 13.3 us, select 11.6 / 9.8, compact 12.9 / 11.6, calls 83.4 / 77.2;
 // 10000 x 1024 x 2048 234 / 215, 4000 x 100 x 2000 70.6 / 62.0, 2048^2 x 512 46.6 / 42.9, 1024^3 35.3 / 35.1.
