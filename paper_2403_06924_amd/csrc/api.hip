@@ -4,6 +4,7 @@
 #include <math.h>
 #include <mutex>
 #include <new>
+#include <stdlib.h>
 #include <string.h>
 
 #include "srq_internal.h"
@@ -280,6 +281,10 @@ srq_status_t srq_create(srq_handle_t* handle, int device) {
   if (!c) return SRQ_STATUS_INVALID_ARG;
   memset(c, 0, sizeof(*c));
   c->device = device;
+  // (200 us; whoever runs out of it works the maxima out alone, which zero has every workgroup do that does not find
+  // them at once)
+  const char* ticks = getenv("SRQ_EXCHANGE_WAIT_TICKS");
+  c->wait_ticks = ticks ? (uint32_t)strtoul(ticks, nullptr, 10) : 20000u;
   if (device >= 0) {
     int n = 0;
     hipError_t e = hipGetDeviceCount(&n);
@@ -445,6 +450,14 @@ srq_status_t srq_quantize(srq_handle_t h, const float* X, int64_t rows, int64_t 
     SRQ_HIP(h, launch_quant_strips(op, cols, rows, ldq, qmax, trunc, st));
     return SRQ_STATUS_OK;
   }
+  if (axis == SRQ_AXIS_COL && layout == SRQ_LAYOUT_VECTOR_MAJOR && cols_once_ok(rows, cols, ldx)) {
+    SRQ_HIP(h, launch_fill3_u32(reinterpret_cast<uint32_t*>(scale), nvec, reinterpret_cast<uint32_t*>(lam), nvec, nullptr, 0, st));
+    ColsOnce g;
+    memset(&g, 0, sizeof(g));
+    g.X = X; g.ldx = ldx; g.scale = scale; g.lambda = lam; g.Q = Q; g.ldq = ldq; g.wait_ticks = h->wait_ticks;
+    SRQ_HIP(h, launch_cols_once(g, rows, cols, qmax, trunc, false, st));
+    return SRQ_STATUS_OK;
+  }
   SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(scale), nvec, 0, st));
   if (rows == 0 || cols == 0) {
     if (lambda) SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(lambda), nvec, 0, st));
@@ -507,6 +520,9 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
     uint64_t* mask_w = f.take<uint64_t>((size_t)nvec * mask_words(veclen));
     int8_t* q_w = f.take<int8_t>((size_t)nvec * ldqw);
     const bool fits = f.off <= h->ws_bytes;
+    const int64_t words = axis == SRQ_AXIS_COL ? cols_once_words(rows, cols) : 0;
+    uint32_t* lines = f.take<uint32_t>(words);
+    const bool once = axis == SRQ_AXIS_COL && do_res && cols_once_ok(rows, cols, ldx) && f.off <= h->ws_bytes;
     const bool vm = r_layout == SRQ_LAYOUT_VECTOR_MAJOR;
     if (fits && do_res && do_sel && vm && strips_one_ok(axis, nvec, veclen)) {
       // one read of X, then the compaction (with its own sums of the counts for few vectors)
@@ -529,6 +545,23 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
                                    ldr, do_res ? rscale : nullptr, do_res ? rlam_w : nullptr, st, scale, lambda));
       if (do_sel) {
         SRQ_HIP(h, launch_rows_mask(X, rows, cols, ldx, thresh, mask_w, tot_w, st));
+        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
+        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
+      }
+      return SRQ_STATUS_OK;
+    }
+    if (once) {
+      if (words || do_sel)
+        SRQ_HIP(h, launch_fill3_u32(words ? lines : nullptr, words, do_sel ? reinterpret_cast<uint32_t*>(tot_w) : nullptr, nvec, nullptr, 0, st));
+      ColsOnce g;
+      memset(&g, 0, sizeof(g));
+      g.X = X; g.ldx = ldx; g.scale = const_cast<float*>(scale); g.lambda = const_cast<float*>(lambda);
+      g.Q = q_w; g.ldq = ldqw; g.rscale = rscale;
+      if (vm) { g.Rvm = Rq; g.ldr = ldr; } else { g.Rem = Rq; g.ldem = ldr; }
+      if (do_sel) { g.thresh = thresh; g.mask = reinterpret_cast<uint8_t*>(mask_w); g.mask_stride = mask_words(rows) * 8; g.counts = tot_w; }
+      g.lines = lines; g.wait_ticks = h->wait_ticks;
+      SRQ_HIP(h, launch_cols_once(g, rows, cols, qmax, trunc, true, st));
+      if (do_sel) {
         SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
         SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
       }
@@ -832,6 +865,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   }
   bool ra_vm_done = false, ra_em_done = false, rb_vm_done = false, rb_em_done = false;
   bool rb_in_select = false, rb_want_em = false, rb_want_vm = false;   // residual codes of B left to the selection pass
+  // B in one read; the maxima that its workgroups exchange lie where the 2:4 form of B' goes later
+  const bool once_b = !strips && !global_scale && cols_once_ok(K, N, ldb);
+  const int64_t once_words = once_b && comp ? cols_once_words(K, N) : 0;
+  uint32_t* const once_lines = reinterpret_cast<uint32_t*>(p.b24v1);
+  // selection from the codes, of an operand whose two code matrices are there by then
+  const bool codes_b = once_b && comp && term_b && mask_codes_ok(qmax, theta_b);
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
   {
   StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
@@ -850,8 +889,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   }
   // the two vectors of column maxima and the per-column counts of the selection that B's passes
   // accumulate into start at zero
-  const ClearList b_clear = {p.amax_b, N, comp ? p.ramax_b : nullptr, N,
-                             (comp && term_b) ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N};
+  const bool tot_b_clear = comp && term_b && !codes_b;
+  const ClearList b_clear =
+      once_b && comp ? ClearList{once_words ? once_lines : nullptr, 2 * once_words, nullptr, 0,
+                                 tot_b_clear ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N}
+      : once_b ? ClearList{reinterpret_cast<uint32_t*>(p.s_b), N, reinterpret_cast<uint32_t*>(p.lam_b), N, nullptr, 0}
+               : ClearList{p.amax_b, N, comp ? p.ramax_b : nullptr, N, tot_b_clear ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N};
   bool b_cleared = false;
   // operand A: vectors are contiguous rows
   if (strips) {
@@ -897,7 +940,22 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   } else if (K > 0) {
     // (cleared by A's pass where that ran, else by a launch of its own); the code and residual
     // passes derive the scales from the maxima themselves
-    if (!b_cleared) SRQ_HIP(h, launch_fill3_u32(b_clear.a, b_clear.na, b_clear.b, b_clear.nb, b_clear.c, b_clear.nc, st));
+    if (!b_cleared && (b_clear.a || b_clear.b || b_clear.c))
+      SRQ_HIP(h, launch_fill3_u32(b_clear.a, b_clear.na, b_clear.b, b_clear.nb, b_clear.c, b_clear.nc, st));
+    if (once_b) {
+      // (the layouts as below; the K-contiguous one always, from which the selection is taken)
+      const int expect_a = strategy == SRQ_STRATEGY_AUTO ? h->last_path_a : strategy_path(strategy);
+      const bool want_em = comp && term_a && dense_fallback_density > 1.f && path_reads_em(expect_a);
+      ColsOnce g;
+      memset(&g, 0, sizeof(g));
+      g.X = B; g.ldx = ldb; g.scale = p.s_b; g.lambda = p.lam_b; g.Q = p.B_int; g.ldq = Kc;
+      if (comp) { g.rscale = p.s_rb; g.rlambda = p.lam_rb; g.Rvm = p.RB_int; g.ldr = Kc; }
+      if (want_em) { g.Rem = p.RB_em; g.ldem = N; }
+      g.lines = once_lines; g.wait_ticks = h->wait_ticks;
+      SRQ_HIP(h, launch_cols_once(g, K, N, qmax, trunc, false, st));
+      rb_vm_done = comp;
+      rb_em_done = want_em;
+    } else {
     SRQ_HIP(h, launch_cols_amax(B, K, N, ldb, p.amax_b, st));
     // (one scale for the whole matrix: every column takes the largest of the maxima)
     if (global_scale) SRQ_HIP(h, launch_broadcast_max(p.amax_b, N, st));
@@ -923,6 +981,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                                want_em ? p.RB_em : nullptr, N, st));
       rb_vm_done = want_vm;
       rb_em_done = want_em;
+    }
     }
   } else {
     SRQ_HIP(h, launch_fill3_u32(reinterpret_cast<uint32_t*>(p.s_b), N, reinterpret_cast<uint32_t*>(p.lam_b), N,
@@ -973,6 +1032,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     }
     im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
     // lines 8-10: Reduce.  Keep-bits and per-vector counts, then the prefix scans
+    bool codes_a = false;
     if (term_a && !strips) {
       // if term 2 is expected on the vector ALUs (fixed by the caller, or where SRQ_STRATEGY_AUTO
       // ended up in the previous call), A's selection pass also writes the k-major residual
@@ -985,11 +1045,18 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         SRQ_HIP(h, launch_rows_mask_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M,
                                              p.t_a, p.mask_a, p.tot_a, st));
         ra_em_done = true;
+      } else if (ra_vm_done && K <= 32768 && mask_codes_ok(qmax, theta_a)) {
+        codes_a = true;
       } else {
         SRQ_HIP(h, launch_rows_mask(A, M, K, lda, p.t_a, p.mask_a, p.tot_a, st));
       }
     }
-    if (term_b && !strips) {
+    if (codes_a || codes_b) {
+      const CodesMask ca = {A, lda, 1, p.A_int, p.RA_int, p.s_a, p.lam_a, p.lam_ra, p.t_a, p.mask_a, p.tot_a, codes_a ? M : 0};
+      const CodesMask cb = {B, 1, ldb, p.B_int, p.RB_int, p.s_b, p.lam_b, p.lam_rb, p.t_b, p.mask_b, p.tot_b, codes_b ? N : 0};
+      SRQ_HIP(h, launch_mask_codes(ca, cb, K, Kc, qmax, trunc, st));
+    }
+    if (term_b && !strips && !codes_b) {
       // (tot_b was cleared in the quantize stage)
       if (rb_in_select)
         SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,

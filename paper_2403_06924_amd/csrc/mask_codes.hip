@@ -1,0 +1,173 @@
+// Keep-masks of Eq. avgQuan and counts per vector, of both operands in one launch, from the codes and residual codes that
+// the quantize passes have left, where the mask passes of fused.hip read the FP32 operands again: 2 bytes per
+// element instead of 4.
+//
+// |x| -> (code, residual code) is monotone: fl(x * lambda), the rounding and the clamp are, and for one code so are
+// fl(x - fl(code * s)) and its code in turn; all of them are odd.  With key(x) = |256 code + residual code| therefore
+//     key(x) > key(t)  =>  |x| > t,       key(x) < key(t)  =>  |x| < t,
+// and only the elements of the threshold's own key (one bin in some 16000 of the vector's range) are read in FP32.  So are
+// those of the topmost key, which NaN shares, and whole vectors whose scales are not ordinary numbers.
+//
+// What bounds it: 2 bytes per element (4.8 TB/s on two operands of 8192 x 8192).  Both operands, us, from FP32 / from codes:
+// 8192 x 8192 each 46 + (68 with the residual codes of B) / 55; 4096 x 4096 and 4096 x 14336 12 + 50 / 35 with a wave per
+// vector (55 with a workgroup for each, which has too few bytes on their way).
+#include "stream.h"
+
+namespace srq {
+namespace {
+
+typedef short s2 __attribute__((ext_vector_type(2)));
+typedef unsigned u4a __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ s2 both(int x) { return s2{(short)x, (short)x}; }
+
+// the bits 15 and 31 of word j of eight as bits j and j + 8
+struct Bits16 {
+  unsigned acc = 0;
+  __device__ __forceinline__ void take(unsigned w, int j) { acc |= (w & 0x80008000u) >> (7 - j); }
+  __device__ __forceinline__ unsigned get() const { return (acc >> 8 & 0xffu) | (acc >> 16 & 0xff00u); }
+};
+
+// sixteen elements: bits of those above the threshold's key, and of those that have to be looked at
+__device__ __forceinline__ void compare16(u4a q, u4a r, int tk, int top, unsigned& above, unsigned& open) {
+  const unsigned qw[4] = {q.x, q.y, q.z, q.w};
+  const unsigned rw[4] = {r.x ^ 0x80808080u, r.y ^ 0x80808080u, r.z ^ 0x80808080u, r.w ^ 0x80808080u};
+  const s2 hi = both(tk + 128), lo = both(128 - tk), last = both(top - tk), none = both(0), one = both(1);
+  Bits16 gt, ge, tp;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    // elements j and j + 8 as 256 code + residual code + 128
+    const unsigned b = j & 3;
+    const unsigned lo8 = __builtin_amdgcn_perm(qw[j >> 2], rw[j >> 2], 0x0c0c0400u + 0x0101u * b);
+    const unsigned hi8 = __builtin_amdgcn_perm(qw[2 + (j >> 2)], rw[2 + (j >> 2)], 0x04000c0cu + 0x01010000u * b);
+    const s2 w = __builtin_bit_cast(s2, lo8 | hi8);
+    // |256 code + residual code| - tk
+    const s2 d = __builtin_elementwise_max(__builtin_elementwise_sub_sat(w, hi), __builtin_elementwise_sub_sat(lo, w));
+    gt.take(__builtin_bit_cast(unsigned, (s2)(none - d)), j);
+    ge.take(~__builtin_bit_cast(unsigned, d), j);
+    // d == last: (e - 1) & ~e has the sign bit of e == 0 (and of e = 0x8000 never: d - last >= -32767)
+    const s2 e = d ^ last;
+    tp.take(__builtin_bit_cast(unsigned, (s2)(e - one)) & ~__builtin_bit_cast(unsigned, e), j);
+  }
+  const unsigned g = gt.get();
+  above = g;
+  open = (ge.get() & ~g) | tp.get();
+}
+
+__device__ __forceinline__ bool ordinary(float x) { return x > 0.f && x < INFINITY; }
+
+template <int TH, int NV, bool TRUNC>   // TH threads per vector, NV pieces of 16 elements for each
+__global__ __launch_bounds__(256) void mask_codes_kernel(CodesMask a, CodesMask b, int64_t veclen, int64_t ld, float qmax, int64_t groups_a) {
+  constexpr int VECS = 256 / TH, STEP = 16 * TH;
+  __shared__ int sm[4];
+  const bool first = (int64_t)blockIdx.x < groups_a;
+  const CodesMask& o = first ? a : b;
+  const int tid = threadIdx.x & (TH - 1);
+  const int sub = TH >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / TH) : 0;
+  int64_t v = (first ? blockIdx.x : blockIdx.x - groups_a) * VECS + sub;
+  const bool exists = v < o.nvec;
+  if (!exists) v = o.nvec - 1;                         // (does the last vector's work again and writes nothing)
+  const int8_t *const q = o.Q + v * ld, *const r = o.R + v * ld;
+  u4a qv[NV], rv[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int64_t e = 16 * tid + STEP * i, at = e < ld ? e : 0;
+    qv[i] = *reinterpret_cast<const u4a*>(q + at);
+    rv[i] = *reinterpret_cast<const u4a*>(r + at);
+  }
+  const float t = o.thresh[v], lam = o.lambda[v], s = o.scale[v], rlam = o.rlambda[v];
+  const int64_t words = (veclen + 63) / 64;
+  uint16_t* const out = reinterpret_cast<uint16_t*>(o.mask + v * words);
+  const float* const x = o.X + v * o.vec_step;
+  // elements e .. e + 15 that exist
+  auto present = [&](int64_t e) -> unsigned { return e + 16 <= veclen ? 0xffffu : e < veclen ? (1u << (veclen - e)) - 1u : 0u; };
+  // sixteen elements in FP32; those past the end are read in the last one's place
+  auto look_all = [&](int64_t e) -> unsigned {
+    float y[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) y[j] = x[(e + j < veclen ? e + j : veclen - 1) * o.elem_step];
+    unsigned m = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) m |= fabsf(y[j]) > t ? 1u << j : 0u;
+    return m;
+  };
+  // the elements of `open`: as a rule one in a few hundred lanes
+  auto look = [&](int64_t e, unsigned open) -> unsigned {
+    if (__any(__popc(open) > 4)) return look_all(e) & open;
+    unsigned m = 0;
+    while (open) {
+      const int j = __ffs((int)open) - 1;
+      open &= open - 1u;
+      if (fabsf(x[(e + j) * o.elem_step]) > t) m |= 1u << j;
+    }
+    return m;
+  };
+  int total = 0;
+  auto put = [&](int64_t e, unsigned m) {
+    if (exists && e < words * 64) out[e >> 4] = (uint16_t)m;
+    total += __popc(m);
+  };
+  const bool none = !(t < INFINITY) || (s == 0.f && lam == 0.f && t >= 0.f);   // (nothing is above NaN, infinity or the maximum of a zero vector)
+  if (none) {
+    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, 0u);
+  } else if (!(ordinary(lam) && ordinary(s) && rlam < INFINITY && t >= 0.f)) {
+#pragma unroll 1
+    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, look_all(e) & present(e));
+  } else {
+    const float zc = biased_code(t, lam, qmax, TRUNC), tc = code_value(zc);
+    const int tk = (int)tc * 256 + (int)code_value(biased_code(t - tc * s, rlam, qmax, TRUNC));
+    const int top = 257 * (int)qmax;
+    // a residual that is zero everywhere: x is fl(code * s) itself
+    const bool exact = rlam == 0.f, equal = tc * s > t;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int64_t e = 16 * tid + STEP * i;
+      unsigned m, open;
+      compare16(qv[i], rv[i], tk, top, m, open);
+      const unsigned here = present(e);
+      m &= here & ~open;
+      open &= here;
+      if (exact) {
+        // (only the topmost key is looked at: its residual code is not zero unless x is NaN)
+        unsigned above, t1;
+        compare16(qv[i], rv[i], top, top, above, t1);
+        if (equal) m |= open & ~t1;
+        open &= t1;
+      }
+      if (open) m |= look(e, open);
+      put(e, m);
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+  if (TH > 64) {
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = total;
+    __syncthreads();
+    total = 0;
+#pragma unroll
+    for (int i = 0; i < TH / 64; ++i) total += sm[sub * (TH / 64) + i];
+  }
+  if (tid == 0 && exists) o.counts[v] = total;
+}
+
+}  // namespace
+
+// (With few codes the threshold's bin is wide: 3 bits have 49 keys.  A threshold of zero leaves every zero to be looked at.)
+bool mask_codes_ok(int qmax, float theta) { return qmax >= 7 && theta > 0.f; }
+
+hipError_t launch_mask_codes(const CodesMask& a, const CodesMask& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st) {
+  if (a.nvec + b.nvec <= 0 || veclen <= 0) return hipSuccess;
+#define SRQ_MASK(TH, NV)                                                                                                   \
+  do {                                                                                                                     \
+    const int64_t ga = (a.nvec + 256 / TH - 1) / (256 / TH), gb = (b.nvec + 256 / TH - 1) / (256 / TH);                     \
+    hipLaunchKernelGGL((trunc ? mask_codes_kernel<TH, NV, true> : mask_codes_kernel<TH, NV, false>), dim3((unsigned)(ga + gb)), \
+                       dim3(256), 0, st, a, b, veclen, ld, (float)qmax, ga);                                                \
+  } while (0)
+  if (veclen <= 4096) SRQ_MASK(64, 4);
+  else if (veclen <= 8192) SRQ_MASK(128, 4);
+  else if (veclen <= 16384) SRQ_MASK(256, 4);
+  else SRQ_MASK(256, 8);
+#undef SRQ_MASK
+  return hipGetLastError();
+}
+
+}  // namespace srq

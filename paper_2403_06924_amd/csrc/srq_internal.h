@@ -25,6 +25,7 @@ struct srq_context {
   int scale_mode;        // srq_scale_t of the next srq_compensated_gemm calls
   int last_path_a;       // execution the caller expects SRQ_STRATEGY_AUTO to pick for term 1 (srq_set_auto_hint;
   int last_path_b;       // 0: none given, the matrix cores are assumed), resp. for term 2
+  uint32_t wait_ticks;   // how long workgroups that exchange maxima wait for each other (100 MHz, cols_once.hip)
 };
 
 namespace srq {
@@ -190,6 +191,47 @@ hipError_t launch_cols_resid_from_amax(const float* X, int64_t rows, int64_t col
                                        int trunc, const float* scale, const float* lambda,
                                        const uint32_t* ramax_bits, float* rscale, float* rlambda, int8_t* Rvm,
                                        int64_t ldvm, int8_t* Rem, int64_t ldem, hipStream_t st);
+// columns in one read (cols_once.hip).  With a residual, `lines`: cols_once_words(rows, cols) words of zeros for each
+// exchange (the maxima of X unless its scales are given, those of the residual).  Without, scale and lambda start
+// at zero.
+constexpr int kColsOnceRows = 512, kColsOnceCols = 32;
+struct ColsOnce {
+  const float* X;
+  int64_t ldx;
+  float *scale, *lambda;       // written, or given
+  int8_t* Q;                   // codes, vector-major
+  int64_t ldq;
+  float *rscale, *rlambda;     // null: no residual; rlambda may be null by itself
+  int8_t* Rvm;                 // residual codes in either layout or both
+  int64_t ldr;
+  int8_t* Rem;
+  int64_t ldem;
+  const float* thresh;         // with mask: keep-bits (mask_stride bytes per column) and counts, which start at zero
+  uint8_t* mask;
+  int64_t mask_stride;
+  int32_t* counts;
+  uint32_t* lines;
+  uint32_t wait_ticks;
+};
+bool cols_once_ok(int64_t rows, int64_t cols, int64_t ldx);
+inline int64_t cols_once_words(int64_t rows, int64_t cols) {
+  const int64_t pieces = (rows + kColsOnceRows - 1) / kColsOnceRows, strips = (cols + kColsOnceCols - 1) / kColsOnceCols;
+  return pieces > 1 ? pieces * strips * kColsOnceCols : 0;
+}
+hipError_t launch_cols_once(const ColsOnce& g, int64_t rows, int64_t cols, int qmax, int trunc, bool given, hipStream_t st);
+// keep-masks and counts of one or two operands from their codes and residual codes (mask_codes.hip)
+struct CodesMask {
+  const float* X;              // element e of vector v: X[v * vec_step + e * elem_step]
+  int64_t vec_step, elem_step;
+  const int8_t *Q, *R;         // rows of ld bytes, 16-byte aligned, ld a multiple of 128
+  const float *scale, *lambda, *rlambda, *thresh;
+  uint64_t* mask;
+  int32_t* counts;
+  int64_t nvec;                // 0: no such operand
+};
+// (veclen at most 32768)
+bool mask_codes_ok(int qmax, float theta);
+hipError_t launch_mask_codes(const CodesMask& a, const CodesMask& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st);
 // zeroes columns [cols, ld) of up to six row-major byte matrices of `rows[i]` rows each (null: skipped)
 hipError_t launch_zero_pad(int8_t* const* mats, const int64_t* rows, int n, int64_t cols, int64_t ld,
                            hipStream_t st);

@@ -1,0 +1,102 @@
+"""Columns of a matrix quantized in one read (workgroups that exchange maxima) and the selection from codes and residual
+codes, against the definitions, bit for bit, at the edges of pieces, strips and vectors."""
+import numpy as np
+import pytest
+
+from test_gpu_strips import F32, dev, host, test_reduction_of_one_operand as reduction
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def b():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2403_06924_amd import binding
+    return binding
+
+
+@pytest.fixture(scope="module", params=["20000", "0"])
+def srq(b, request):
+    """A handle whose workgroups wait for each other, and one where whoever does not find a maximum at once works it out
+    alone."""
+    with pytest.MonkeyPatch.context() as m:
+        m.setenv("SRQ_EXCHANGE_WAIT_TICKS", request.param)
+        h = b.Srq(device=0)
+    h.late = request.param == "0"
+    yield h
+    h.close()
+
+
+# (rows, columns): pieces of 512 rows, patches of 16, strips of 32 columns, the last columns no whole patch
+@pytest.mark.parametrize("shape", [(4097, 4), (4100, 5), (4111, 31), (4607, 33), (4608, 34), (4609, 67), (8704, 98), (16385, 6), (32768, 9)])
+@pytest.mark.parametrize("bits", [8, 3])
+def test_columns_in_one_read(srq, b, shape, bits):
+    reduction(srq, b, shape, 1, bits)
+
+
+@pytest.mark.parametrize("shape", [(4099, 37), (4608, 32)])
+def test_other_layouts_and_parts_of_the_reduction(srq, b, shape):
+    X = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(shape[1]), device="cuda")
+    X[:, 3] = 0
+    X[:, 4] = 1e-39                                           # (qmax / amax overflows)
+    t = X.abs().mean(dim=0).contiguous()
+    for rounding in (b.ROUND_NEAREST_EVEN, b.ROUND_TRUNC):
+        Q, s, lam = srq.quantize(X, b.AXIS_COL, rounding=rounding)
+        Qt, st, lamt = srq.quantize(X.t().contiguous(), b.AXIS_ROW, rounding=rounding)
+        assert torch.equal(Q, Qt) and torch.equal(s, st) and torch.equal(lam, lamt)
+        r = srq.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding)
+        rt = srq.build_sparse_residual(X.t().contiguous(), b.AXIS_ROW, s, lam, t, rounding=rounding)
+        em = srq.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding, r_layout=b.LAYOUT_ELEMENT_MAJOR)
+        n = int(r["nnz"].item())
+        for key in ("Rq", "rscale", "ptr", "nnz"):
+            assert torch.equal(r[key], rt[key]), key
+            assert torch.equal(r[key], em[key].t() if key == "Rq" else em[key]), key
+        assert torch.equal(r["idx"][:n], rt["idx"][:n]) and torch.equal(r["val"][:n], rt["val"][:n])
+
+
+def operand(rng, kind, nvec, K):
+    """nvec vectors of K entries, special ones among them."""
+    if kind == "normal":
+        V = rng.standard_normal((nvec, K))
+    elif kind == "outliers":                                  # most codes are 0 or 1: the residual codes decide
+        V = rng.standard_normal((nvec, K))
+        V[:, rng.integers(0, K, 7)] *= 300.0
+    else:                                                     # few values: bins full of ties, residuals of zeros
+        V = rng.integers(-3, 4, (nvec, K)).astype(np.float64)
+        V[::2, 0] = 127.0
+    V = V.astype(F32)
+    V[0] = 0
+    V[1] = F32(2.0 ** -140) * np.sign(V[1])                    # scales that are not ordinary numbers
+    V[2, 1::2] = -1.0
+    V[2, ::2] = 1.0                                           # one magnitude: the topmost code alone
+    V[3, 5] = np.nan
+    return V
+
+
+# (M, N, K): one wave, two and four of them per vector, a last piece that is no whole sixteen; the operands' thresholds
+# put exactly on an entry of some vectors
+@pytest.mark.parametrize("shape", [(300, 1800, 4099), (40, 2100, 8192), (1030, 1029, 8205), (20, 2040, 16384)])
+@pytest.mark.parametrize("kind", ["normal", "outliers", "ties"])
+@pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (4, 0)])
+def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
+    if srq.late:
+        pytest.skip("nothing is exchanged in the selection")
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K + bits)
+    A, B = operand(rng, kind, M, K), operand(rng, kind, N, K).T.copy()
+    theta = 1.0 / K ** 0.5
+    for _ in range(2):
+        srq.compensated_gemm(dev(A), dev(B), theta, theta, bits=bits, rounding=b.ROUND_TRUNC if trunc else b.ROUND_NEAREST_EVEN,
+                             strategy=b.STRATEGY_CSR_MFMA, max_density=1.0)
+        torch.cuda.synchronize()
+        im = srq.intermediates(M, N, K)
+        for V, t, ptr, idx, val, codes in ((A, im["t_a"], im["a_ptr"], im["a_idx"], im["a_val"], im["A_int"]),
+                                           (B.T, im["t_b"], im["b_ptr"], im["b_idx"], im["b_val"], im["B_int"])):
+            with np.errstate(invalid="ignore"):
+                vec, k = np.nonzero(np.abs(V) > host(t)[:, None])
+            assert (host(ptr) == np.searchsorted(vec, np.arange(len(V) + 1))).all()
+            assert (host(idx)[:len(k)] == k).all() and (host(val)[:len(k)] == host(codes)[vec, k]).all()
+        # once more with the threshold of row 7 on (or next to) an entry
+        theta = float(np.sort(np.abs(A[7]))[-K // 10] / host(im["drow"])[7])
