@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsrq.so")
 SOURCES = ["api.hip", "quantize.hip", "fused.hip", "select.hip", "gemm.hip", "gemm_persistent.hip", "gemm_small.hip",
            "gemm_tile64.hip", "gemm_skinny.hip",
-           "gemm_sparse24.hip", "sparse24.hip", "spmm.hip", "colblock.hip", "cols_once.hip", "mask_codes.hip", "strips.hip", "short.hip"]
+           "gemm_sparse24.hip", "sparse24.hip", "spmm.hip", "colblock.hip", "codes_em.hip", "cols_once.hip", "select_codes.hip", "strips.hip", "short.hip"]
 
 # -ffp-contract=off: the dequantize / residual steps are defined with one rounding per
 # operation, so no multiply-add may be fused.  Packed FP32 instructions stay off.

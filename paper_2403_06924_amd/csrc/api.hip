@@ -809,13 +809,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       if (sb == kPathValu || sb == kPathMfma) h->last_path_b = sb;
     }
   }
-  // Short inner dimension or few vectors, and both terms expected where they read K-contiguous residual codes: both
-  // operands in one launch per pass
-  auto reads_em = [&](int hint_path) {
-    return dense_fallback_density > 1.f && path_reads_em(strategy == SRQ_STRATEGY_AUTO ? hint_path : strategy_path(strategy));
-  };
-  const bool strips = strips_ok(M, N, K) && !global_scale &&
-                      !(comp && ((term_a && reads_em(h->last_path_a)) || (term_b && reads_em(h->last_path_b))));
+  // Short inner dimension or few vectors: both operands in one launch per pass
+  const bool strips = strips_ok(M, N, K) && !global_scale;
   GemmEpilogue ep;
   memset(&ep, 0, sizeof(ep));
   ep.mode = kGemmFirst;
@@ -870,7 +865,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   const int64_t once_words = once_b && comp ? cols_once_words(K, N) : 0;
   uint32_t* const once_lines = reinterpret_cast<uint32_t*>(p.b24v1);
   // selection from the codes, of an operand whose two code matrices are there by then
-  const bool codes_b = once_b && comp && term_b && mask_codes_ok(qmax, theta_b);
+  const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b);
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
   {
   StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
@@ -903,7 +898,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // the K-contiguous residual codes of A feed the matrix-core executions of term 2; when that
     // term is expected on the vector ALUs (same prediction as for B's layouts below) only the
     // residual scales are produced here and A's selection pass writes the k-major codes
-    const bool skip_ra_vm = comp && term_b && dense_fallback_density > 1.f &&
+    const bool skip_ra_vm = comp && term_b && !once_b && dense_fallback_density > 1.f &&
                             (strategy == SRQ_STRATEGY_CSR_VALU ||
                              (strategy == SRQ_STRATEGY_AUTO && h->last_path_b == kPathValu));
     // (SRQ_STRATEGY_AUTO goes by the caller's hint, srq_set_auto_hint; a wrong or missing hint only
@@ -943,18 +938,14 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (!b_cleared && (b_clear.a || b_clear.b || b_clear.c))
       SRQ_HIP(h, launch_fill3_u32(b_clear.a, b_clear.na, b_clear.b, b_clear.nb, b_clear.c, b_clear.nc, st));
     if (once_b) {
-      // (the layouts as below; the K-contiguous one always, from which the selection is taken)
-      const int expect_a = strategy == SRQ_STRATEGY_AUTO ? h->last_path_a : strategy_path(strategy);
-      const bool want_em = comp && term_a && dense_fallback_density > 1.f && path_reads_em(expect_a);
+      // (the k-major residual codes of either operand, if wanted, are copied from the K-contiguous ones later)
       ColsOnce g;
       memset(&g, 0, sizeof(g));
       g.X = B; g.ldx = ldb; g.scale = p.s_b; g.lambda = p.lam_b; g.Q = p.B_int; g.ldq = Kc;
       if (comp) { g.rscale = p.s_rb; g.rlambda = p.lam_rb; g.Rvm = p.RB_int; g.ldr = Kc; }
-      if (want_em) { g.Rem = p.RB_em; g.ldem = N; }
       g.lines = once_lines; g.wait_ticks = h->wait_ticks;
       SRQ_HIP(h, launch_cols_once(g, K, N, qmax, trunc, false, st));
       rb_vm_done = comp;
-      rb_em_done = want_em;
     } else {
     SRQ_HIP(h, launch_cols_amax(B, K, N, ldb, p.amax_b, st));
     // (one scale for the whole matrix: every column takes the largest of the maxima)
@@ -1019,44 +1010,46 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // (the persistent kernel leaves one partial per wave, two per 256-wide tile)
     int64_t parts_n, parts_m;
     gemm_sum_parts(M, N, Kc, p.A_int, Kc, p.B_int, Kc, ep, &parts_n, &parts_m);
-    if (strips_ok(M, N, K)) {
-      // (means, thresholds and lines 8-10 of both operands at once; the means alone where the passes of the
-      // strips are not taken: the order of the additions depends on the shape, not on what is expected
-      // of the executions)
-      const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, strips && term_a ? p.mask_a : nullptr, p.tot_a};
-      const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, strips && term_b ? p.mask_b : nullptr, p.tot_b};
-      SRQ_HIP(h, launch_select_pair(sa, sb, M, N, K, st));
-    } else {
-      SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
-                                          theta_b, p.dcol, p.t_b, st));
-    }
-    im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
-    // lines 8-10: Reduce.  Keep-bits and per-vector counts, then the prefix scans
-    bool codes_a = false;
-    if (term_a && !strips) {
+    // Selection from the codes where both code matrices of an operand are there, else in FP32; few vectors or a short K in one
+    // launch with the means.
+    const bool want_ra_em = term_a && !ra_vm_done && [&] {
       // if term 2 is expected on the vector ALUs (fixed by the caller, or where SRQ_STRATEGY_AUTO
       // ended up in the previous call), A's selection pass also writes the k-major residual
       // codes that execution reads: one read of A less
       const int expect_b = strategy == SRQ_STRATEGY_AUTO ? h->last_path_b : strategy_path(strategy);
-      const bool want_ra_em = term_b && dense_fallback_density > 1.f &&
-                              path_reads_em(expect_b) &&
-                              rows_mask_resid_em_ok(A, M, K, lda, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, p.t_a);
-      if (want_ra_em) {
-        SRQ_HIP(h, launch_rows_mask_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M,
-                                             p.t_a, p.mask_a, p.tot_a, st));
-        ra_em_done = true;
-      } else if (ra_vm_done && K <= 32768 && mask_codes_ok(qmax, theta_a)) {
-        codes_a = true;
-      } else {
-        SRQ_HIP(h, launch_rows_mask(A, M, K, lda, p.t_a, p.mask_a, p.tot_a, st));
-      }
+      return term_b && dense_fallback_density > 1.f && path_reads_em(expect_b) &&
+             rows_mask_resid_em_ok(A, M, K, lda, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, p.t_a);
+    }();
+    const bool codes_a = term_a && ra_vm_done && K <= 32768 && select_codes_ok(qmax, theta_a);
+    // (calls, us, in FP32 / from the codes: 1024^3 36.4 / 37.4, 2048^2 x 512 40.6 / 42.2, 4096^2 x 512 115 / 118, but 1500^3 61.6 / 58.8,
+    // 2048^3 74.8 / 71.1, 4096^2 x 2048 195 / 192, 3000^3 239 / 229)
+    const bool in_strips = strips && (K <= 1024 || (term_a && !codes_a) || (term_b && !codes_b));
+    if (in_strips || (strips_ok(M, N, K) && !strips)) {
+      // (the means alone where the passes of the strips are not taken: the order of the additions depends on the shape,
+      // not on what is expected of the executions)
+      const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, in_strips && term_a ? p.mask_a : nullptr, p.tot_a};
+      const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, in_strips && term_b ? p.mask_b : nullptr, p.tot_b};
+      SRQ_HIP(h, launch_select_pair(sa, sb, M, N, K, st));
+    } else if (!strips) {
+      SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
+                                          theta_b, p.dcol, p.t_b, st));
     }
-    if (codes_a || codes_b) {
-      const CodesMask ca = {A, lda, 1, p.A_int, p.RA_int, p.s_a, p.lam_a, p.lam_ra, p.t_a, p.mask_a, p.tot_a, codes_a ? M : 0};
-      const CodesMask cb = {B, 1, ldb, p.B_int, p.RB_int, p.s_b, p.lam_b, p.lam_rb, p.t_b, p.mask_b, p.tot_b, codes_b ? N : 0};
-      SRQ_HIP(h, launch_mask_codes(ca, cb, K, Kc, qmax, trunc, st));
+    if (!in_strips && (strips || codes_a || codes_b)) {
+      const CodesSelect ca = {strips ? p.row_part : nullptr, parts_n, (double)N, theta_a, p.drow, p.t_a, A, lda, 1, p.A_int, p.RA_int,
+                              p.s_a, p.lam_a, p.lam_ra, codes_a ? p.mask_a : nullptr, p.tot_a, strips || codes_a ? M : 0};
+      const CodesSelect cb = {strips ? p.col_part : nullptr, parts_m, (double)M, theta_b, p.dcol, p.t_b, B, 1, ldb, p.B_int, p.RB_int,
+                              p.s_b, p.lam_b, p.lam_rb, codes_b ? p.mask_b : nullptr, p.tot_b, strips || codes_b ? N : 0};
+      SRQ_HIP(h, launch_select_codes(ca, cb, K, Kc, qmax, trunc, st));
     }
-    if (term_b && !strips && !codes_b) {
+    im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
+    // lines 8-10: Reduce.  Keep-bits and per-vector counts, then the prefix scans
+    if (want_ra_em) {
+      SRQ_HIP(h, launch_rows_mask_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, p.t_a, p.mask_a, p.tot_a, st));
+      ra_em_done = true;
+    } else if (term_a && !in_strips && !codes_a) {
+      SRQ_HIP(h, launch_rows_mask(A, M, K, lda, p.t_a, p.mask_a, p.tot_a, st));
+    }
+    if (term_b && !in_strips && !codes_b) {
       // (tot_b was cleared in the quantize stage)
       if (rb_in_select)
         SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,
@@ -1076,7 +1069,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     const ScanDecision dec = {p.paths, const_cast<int32_t*>(seen_paths(h)), min_mfma_a, min_mfma_b, stats_dev,
                               term_a ? p.cap_a : kNoCap, term_b ? p.cap_b : kNoCap};
     // (few vectors, both executions known: the compaction adds the counts up itself)
-    const bool compact_pair = strips && strategy == SRQ_STRATEGY_CSR_MFMA && !sync_mode && !always_dense && strips_compact_ok(M, N);
+    const bool compact_pair = K <= kStripsMaxK && strategy == SRQ_STRATEGY_CSR_MFMA && !sync_mode && !always_dense && strips_compact_ok(M, N);
     if (compact_pair) {
       const StripCompact ca = {term_a ? (int)M : 0, p.mask_a, p.tot_a, p.A_int, p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.Ad, p.nnz + 0};
       const StripCompact cb = {term_b ? (int)N : 0, p.mask_b, p.tot_b, p.B_int, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.Bd, p.nnz + 1};
@@ -1177,6 +1170,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       // written (they went by the hint) is written now, by a launch that does nothing unless the
       // decision asks for it.  Only what is certain to exist is exported as an intermediate.
       StageTimer tm(h, st, SRQ_STAGE_RESIDUAL);
+      // (k-major copies of K-contiguous codes that are there; of those the hint asks for in any case)
+      const bool copy_a = term_b && ra_vm_done && !ra_em_done, copy_b = term_a && rb_vm_done && !rb_em_done;
+      const bool hint_a = copy_a && h->last_path_b == kPathValu, hint_b = copy_b && h->last_path_a == kPathValu;
+      if (copy_a || copy_b)
+        SRQ_HIP(h, launch_codes_em({p.RA_int, p.RA_em, copy_a ? M : 0, hint_a ? kAlways : b_on_valu},
+                                   {p.RB_int, p.RB_em, copy_b ? N : 0, hint_b ? kAlways : a_on_valu}, K, Kc, st));
       auto resid_a = [&](bool vm, RunIf run) -> hipError_t {
         if (!vm && rows_resid_em_ok(A, M, K, lda, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M))
           return launch_rows_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, st, run);
@@ -1188,15 +1187,18 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                  vm ? nullptr : p.RB_em, N, st, run);
       };
       if (term_b && !ra_vm_done) SRQ_HIP(h, resid_a(true, b_on_mfma));
-      if (term_b && !ra_em_done) SRQ_HIP(h, resid_a(false, b_on_valu));
+      if (term_b && !ra_em_done && !copy_a) SRQ_HIP(h, resid_a(false, b_on_valu));
       if (term_a && !rb_vm_done) SRQ_HIP(h, resid_b(true, a_on_mfma));
-      if (term_a && !rb_em_done) SRQ_HIP(h, resid_b(false, a_on_valu));
-      ra_vm = ra_vm_done; ra_em = ra_em_done; rb_vm = rb_vm_done; rb_em = rb_em_done;
+      if (term_a && !rb_em_done && !copy_b) SRQ_HIP(h, resid_b(false, a_on_valu));
+      ra_vm = ra_vm_done; ra_em = ra_em_done || hint_a; rb_vm = rb_vm_done; rb_em = rb_em_done || hint_b;
     } else {
     StageTimer tm(h, st, SRQ_STAGE_RESIDUAL);
     // whatever the quantize stage has not already produced
     const bool need_ra_vm = ra_vm && !ra_vm_done, need_rb_vm = rb_vm && !rb_vm_done;
-    const bool need_rb_em = rb_em && !rb_em_done, need_ra_em = ra_em && !ra_em_done;
+    const bool copy_a = ra_em && ra_vm_done && !ra_em_done, copy_b = rb_em && rb_vm_done && !rb_em_done;
+    if (copy_a || copy_b)
+      SRQ_HIP(h, launch_codes_em({p.RA_int, p.RA_em, copy_a ? M : 0, kAlways}, {p.RB_int, p.RB_em, copy_b ? N : 0, kAlways}, K, Kc, st));
+    const bool need_rb_em = rb_em && !rb_em_done && !copy_b, need_ra_em = ra_em && !ra_em_done && !copy_a;
     if (need_ra_em && !need_ra_vm && rows_resid_em_ok(A, M, K, lda, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M))
       SRQ_HIP(h, launch_rows_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, st));
     else if (need_ra_vm || need_ra_em)

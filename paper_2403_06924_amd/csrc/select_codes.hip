@@ -1,6 +1,6 @@
-// Keep-masks of Eq. avgQuan and counts per vector, of both operands in one launch, from the codes and residual codes that
-// the quantize passes have left, where the mask passes of fused.hip read the FP32 operands again: 2 bytes per
-// element instead of 4.
+// Keep-masks of Eq. avgQuan with their counts per vector, of both operands in one launch, from the codes and residual codes
+// that the quantize passes have left, where the mask passes of fused.hip and strips.hip read the FP32 operands again: 2
+// bytes per element instead of 4.  Where strips.hip would take the selection, with the means and thresholds as it does.
 //
 // |x| -> (code, residual code) is monotone: fl(x * lambda), the rounding and the clamp are, and for one code so are
 // fl(x - fl(code * s)) and its code in turn; all of them are odd.  With key(x) = |256 code + residual code| therefore
@@ -57,11 +57,11 @@ __device__ __forceinline__ void compare16(u4a q, u4a r, int tk, int top, unsigne
 __device__ __forceinline__ bool ordinary(float x) { return x > 0.f && x < INFINITY; }
 
 template <int TH, int NV, bool TRUNC>   // TH threads per vector, NV pieces of 16 elements for each
-__global__ __launch_bounds__(256) void mask_codes_kernel(CodesMask a, CodesMask b, int64_t veclen, int64_t ld, float qmax, int64_t groups_a) {
+__global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesSelect b, int64_t veclen, int64_t ld, float qmax, int64_t groups_a) {
   constexpr int VECS = 256 / TH, STEP = 16 * TH;
   __shared__ int sm[4];
   const bool first = (int64_t)blockIdx.x < groups_a;
-  const CodesMask& o = first ? a : b;
+  const CodesSelect& o = first ? a : b;
   const int tid = threadIdx.x & (TH - 1);
   const int sub = TH >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / TH) : 0;
   int64_t v = (first ? blockIdx.x : blockIdx.x - groups_a) * VECS + sub;
@@ -69,13 +69,28 @@ __global__ __launch_bounds__(256) void mask_codes_kernel(CodesMask a, CodesMask 
   if (!exists) v = o.nvec - 1;                         // (does the last vector's work again and writes nothing)
   const int8_t *const q = o.Q + v * ld, *const r = o.R + v * ld;
   u4a qv[NV], rv[NV];
+  if (o.mask) {                                        // (on their way while the threshold is formed)
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int64_t e = 16 * tid + STEP * i, at = e < ld ? e : 0;
-    qv[i] = *reinterpret_cast<const u4a*>(q + at);
-    rv[i] = *reinterpret_cast<const u4a*>(r + at);
+    for (int i = 0; i < NV; ++i) {
+      const int64_t e = 16 * tid + STEP * i, at = e < ld ? e : 0;
+      qv[i] = *reinterpret_cast<const u4a*>(q + at);
+      rv[i] = *reinterpret_cast<const u4a*>(r + at);
+    }
   }
-  const float t = o.thresh[v], lam = o.lambda[v], s = o.scale[v], rlam = o.rlambda[v];
+  float t;
+  if (o.part) {
+    // line 7: the mean.  Every 64th partial sum by a lane, the lanes as a tree: the order in which strips.hip adds them, too
+    double sum = 0.0;
+    for (int64_t p = threadIdx.x & 63; p < o.nparts; p += 64) sum += o.part[p * o.nvec + v];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float mean = (float)(sum / o.count);
+    t = o.theta * mean;
+    if (tid == 0 && exists) { o.mean[v] = mean; o.thresh[v] = t; }
+  } else {
+    t = o.thresh[v];
+  }
+  if (!o.mask) return;
+  const float lam = o.lambda[v], s = o.scale[v], rlam = o.rlambda[v];
   const int64_t words = (veclen + 63) / 64;
   uint16_t* const out = reinterpret_cast<uint16_t*>(o.mask + v * words);
   const float* const x = o.X + v * o.vec_step;
@@ -152,17 +167,19 @@ __global__ __launch_bounds__(256) void mask_codes_kernel(CodesMask a, CodesMask 
 }  // namespace
 
 // (With few codes the threshold's bin is wide: 3 bits have 49 keys.  A threshold of zero leaves every zero to be looked at.)
-bool mask_codes_ok(int qmax, float theta) { return qmax >= 7 && theta > 0.f; }
+bool select_codes_ok(int qmax, float theta) { return qmax >= 7 && theta > 0.f; }
 
-hipError_t launch_mask_codes(const CodesMask& a, const CodesMask& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st) {
+hipError_t launch_select_codes(const CodesSelect& a, const CodesSelect& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st) {
   if (a.nvec + b.nvec <= 0 || veclen <= 0) return hipSuccess;
 #define SRQ_MASK(TH, NV)                                                                                                   \
   do {                                                                                                                     \
     const int64_t ga = (a.nvec + 256 / TH - 1) / (256 / TH), gb = (b.nvec + 256 / TH - 1) / (256 / TH);                     \
-    hipLaunchKernelGGL((trunc ? mask_codes_kernel<TH, NV, true> : mask_codes_kernel<TH, NV, false>), dim3((unsigned)(ga + gb)), \
+    hipLaunchKernelGGL((trunc ? select_codes_kernel<TH, NV, true> : select_codes_kernel<TH, NV, false>), dim3((unsigned)(ga + gb)), \
                        dim3(256), 0, st, a, b, veclen, ld, (float)qmax, ga);                                                \
   } while (0)
-  if (veclen <= 4096) SRQ_MASK(64, 4);
+  if (veclen <= 1024) SRQ_MASK(64, 1);
+  else if (veclen <= 2048) SRQ_MASK(64, 2);
+  else if (veclen <= 4096) SRQ_MASK(64, 4);
   else if (veclen <= 8192) SRQ_MASK(128, 4);
   else if (veclen <= 16384) SRQ_MASK(256, 4);
   else SRQ_MASK(256, 8);

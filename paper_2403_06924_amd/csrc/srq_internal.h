@@ -219,19 +219,34 @@ inline int64_t cols_once_words(int64_t rows, int64_t cols) {
   return pieces > 1 ? pieces * strips * kColsOnceCols : 0;
 }
 hipError_t launch_cols_once(const ColsOnce& g, int64_t rows, int64_t cols, int qmax, int trunc, bool given, hipStream_t st);
-// keep-masks and counts of one or two operands from their codes and residual codes (mask_codes.hip)
-struct CodesMask {
+// Keep-masks and counts of one or two operands from codes and residual codes (select_codes.hip), with the means of |D_F| and
+// the thresholds or after them
+struct CodesSelect {
+  const double* part;          // partial sums of |D_F|: nparts for each vector; null: the thresholds are there
+  int64_t nparts;
+  double count;
+  float theta;
+  float *mean, *thresh;
   const float* X;              // element e of vector v: X[v * vec_step + e * elem_step]
   int64_t vec_step, elem_step;
   const int8_t *Q, *R;         // rows of ld bytes, 16-byte aligned, ld a multiple of 128
-  const float *scale, *lambda, *rlambda, *thresh;
-  uint64_t* mask;
+  const float *scale, *lambda, *rlambda;
+  uint64_t* mask;              // null: the mean and the threshold only
   int32_t* counts;
   int64_t nvec;                // 0: no such operand
 };
 // (veclen at most 32768)
-bool mask_codes_ok(int qmax, float theta);
-hipError_t launch_mask_codes(const CodesMask& a, const CodesMask& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st);
+bool select_codes_ok(int qmax, float theta);
+hipError_t launch_select_codes(const CodesSelect& a, const CodesSelect& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st);
+// k-major copies of one or two residual code matrices (codes_em.hip): nvec rows of ld bytes (16-byte aligned, ld a multiple of
+// 16) to veclen rows of nvec bytes
+struct CodesEm {
+  const int8_t* R;
+  int8_t* Rem;
+  int64_t nvec;                // 0: no such matrix
+  RunIf run;
+};
+hipError_t launch_codes_em(const CodesEm& a, const CodesEm& b, int64_t veclen, int64_t ld, hipStream_t st);
 // zeroes columns [cols, ld) of up to six row-major byte matrices of `rows[i]` rows each (null: skipped)
 hipError_t launch_zero_pad(int8_t* const* mats, const int64_t* rows, int n, int64_t cols, int64_t ld,
                            hipStream_t st);

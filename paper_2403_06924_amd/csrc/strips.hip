@@ -296,24 +296,23 @@ __device__ __forceinline__ void store_nibble(uint64_t* mrow, int words, int c4, 
   if (!(c4 & 7) && (c4 >> 3) < 2 * words) reinterpret_cast<uint32_t*>(mrow)[c4 >> 3] = b32;
 }
 
-// (the partial sums of a row: every RT-th by a thread, its wave's lanes as a tree, the waves one after the other)
+// The partial sums of a vector, K > 1024: every 64th by a lane, the lanes as a tree, in this order wherever such a call forms
+// its means (select_codes.hip), each wave that wants the sum by itself.  (Up to 1024: see select_strip; a wave has a row.)
+__device__ __forceinline__ double sum_of(const StripSelect& s, int64_t v, int64_t nvec) {
+  double sum = 0.0;
+  for (int64_t p = threadIdx.x & 63; p < s.nparts; p += 64) sum += s.part[p * nvec + v];
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  return sum;
+}
+
 template <int RT, int NV4>
-__device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, double* dsm, int* ism) {
+__device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, int64_t rows, int K, int* ism) {
   const int tid = threadIdx.x & (RT - 1), lane = tid & 63, w = tid >> 6;
   const int words = (K + 63) / 64;
   float4 x[NV4];
   int n[NV4];
   if (s.mask) load_row<RT, NV4>(x, n, s.X + row * s.ldx, K, tid);   // (on their way while the threshold is formed)
-  double sum = 0.0;
-  for (int64_t p = tid; p < s.nparts; p += RT) sum += s.part[p * rows + row];
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if constexpr (RT > 64) {
-    if (lane == 0) dsm[w] = sum;
-    __syncthreads();
-    sum = dsm[0];
-#pragma unroll
-    for (int i = 1; i < RT / 64; ++i) sum += dsm[i];
-  }
+  const double sum = sum_of(s, row, rows);
   float t;
   mean_of(s, row, sum, tid == 0, t);
   if (!s.mask) return;
@@ -377,27 +376,38 @@ __device__ __forceinline__ void store_bits(uint64_t* mask, int32_t* counts, int 
 template <int TH, int CG, int RPT>
 __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, int64_t cols, int K, double* dsm, int* ism) {
   constexpr int BC = 4 * CG;
+  constexpr bool kWaveSums = TH / CG * RPT > 1024;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cg = tid & (CG - 1), rb = tid / CG, row0 = rb * RPT;
   const int words = (K + 63) / 64;
   const int64_t col0 = ((int64_t)strip * CG + cg) * 4;
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
   float4 v[RPT];
   if (s.mask) load_patch<TH, CG, RPT>(v, s.X, s.ldx, strip, row0, col0, cols, K);
-  // partial sums: BC neighbouring columns by BC neighbouring threads
-  const int64_t pc = (int64_t)strip * BC + (tid & (BC - 1));
-  double sum = 0.0;
-  if (pc < cols)
-    for (int64_t p = tid / BC; p < s.nparts; p += TH / BC) sum += s.part[p * cols + pc];
+  if constexpr (kWaveSums) {
+    for (int c = w; c < BC; c += TH / 64) {
+      const int64_t pc = (int64_t)strip * BC + c;
+      const double sum = pc < cols ? sum_of(s, pc, cols) : 0.0;
+      if (lane == 0) dsm[c] = sum;
+    }
+  } else {
+    // partial sums: BC neighbouring columns by BC neighbouring threads
+    const int64_t pc = (int64_t)strip * BC + (tid & (BC - 1));
+    double sum = 0.0;
+    if (pc < cols)
+      for (int64_t p = tid / BC; p < s.nparts; p += TH / BC) sum += s.part[p * cols + pc];
 #pragma unroll
-  for (int off = BC; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane < BC) dsm[w * BC + lane] = sum;
+    for (int off = BC; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane < BC) dsm[w * BC + lane] = sum;
+  }
   __syncthreads();
   float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     double all = dsm[cg * 4 + c];
+    if constexpr (!kWaveSums) {
 #pragma unroll
-    for (int i = 1; i < TH / 64; ++i) all += dsm[i * BC + cg * 4 + c];
+      for (int i = 1; i < TH / 64; ++i) all += dsm[i * BC + cg * 4 + c];
+    }
     if (c < ncol) mean_of(s, col0 + c, all, rb == 0, t[c]);
   }
   if (!s.mask) return;
@@ -420,7 +430,7 @@ __global__ __launch_bounds__(TH) void select_pair_kernel(StripSelect a, StripSel
   __shared__ int ism[TH / 16 * CG];
   const int64_t row = ((int64_t)blockIdx.x - strips) * (TH / RT) + (RT == 64 ? threadIdx.x >> 6 : 0);
   if ((int)blockIdx.x < strips) select_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, dsm, ism);
-  else if (row < M) select_row<RT, NV4>(a, row, M, K, dsm, ism);
+  else if (row < M) select_row<RT, NV4>(a, row, M, K, ism);
 }
 
 // ---- reduction of one operand (scales and thresholds given): codes, residual codes, keep-mask and counts in
