@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
       int8_t* dst = Qvm + (col0 + c) * ldvm + row0;
       if (here == 16) {
         const u4u pk = {packed[c][0], packed[c][1], packed[c][2], packed[c][3]};
-        __builtin_nontemporal_store(pk, reinterpret_cast<u4u*>(dst));
+        *reinterpret_cast<u4u*>(dst) = pk;
       } else {
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -246,8 +246,7 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
             xv[c] = xv[c] - code_value(z[r][c]) * sc[c];
             // (one register per element, through the exchange that follows: the maximum is formed here)
             asm volatile("" : "+v"(xv[c]));
-            // (places past the last row hold 0, but 0 * lam is not 0 where lam overflowed)
-            rm[c] = row0 + i + r < rows ? fmaxf(rm[c], fabsf(xv[c])) : rm[c];
+            rm[c] = fmaxf(rm[c], fabsf(xv[c]));
             asm volatile("" : "+v"(rm[c]));
           }
         }
@@ -263,6 +262,17 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
     put(g.Q, g.ldq, packed);
   }
   if (!RESID) return;
+  if (row0 + 16 > rows) {
+    // (places past the last row hold 0, but 0 * lam is not 0 where lam overflowed: they stay out of the maxima)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) rm[c] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (row0 + i >= rows) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      rm[0] = fmaxf(rm[0], fabsf(v[i].x)); rm[1] = fmaxf(rm[1], fabsf(v[i].y));
+      rm[2] = fmaxf(rm[2], fabsf(v[i].z)); rm[3] = fmaxf(rm[3], fabsf(v[i].w));
+    }
+  }
   __syncthreads();                                     // (red has been read)
   if (tid < BC) red[tid] = 0;
   exchange(g.lines + (GIVEN ? 0 : (int64_t)(gridDim.x * BC)), std::true_type(), rm);
