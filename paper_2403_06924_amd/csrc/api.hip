@@ -865,13 +865,20 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   const int64_t once_words = once_b && comp ? cols_once_words(K, N) : 0;
   uint32_t* const once_lines = reinterpret_cast<uint32_t*>(p.b24v1);
   // selection from the codes, of an operand whose two code matrices are there by then
+  // Both terms on the unreduced codes whatever the counts: those of a threshold of zero are of the entries that are not zero, which
+  // the passes that quantize count on the side, and no mask is read by anybody (8192^2: 17 us per operand for one more pass)
+  const bool always_dense = dense_fallback_density <= 0.f;
+  const bool count_a = comp && always_dense && term_a && theta_a == 0.f && (strips || fastA);
+  const bool count_b = comp && always_dense && term_b && theta_b == 0.f && (strips || once_b);
   const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b);
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
   {
   StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
   if (strips) {
-    const StripOperand oa = {A, lda, p.A_int, p.s_a, p.lam_a, comp ? p.RA_int : nullptr, p.s_ra, p.lam_ra, p.Ad};
-    const StripOperand ob = {B, ldb, p.B_int, p.s_b, p.lam_b, comp ? p.RB_int : nullptr, p.s_rb, p.lam_rb, p.Bd};
+    const StripOperand oa = {A, lda, p.A_int, p.s_a, p.lam_a, comp ? p.RA_int : nullptr, p.s_ra, p.lam_ra, p.Ad,
+                             count_a ? p.tot_a : nullptr};
+    const StripOperand ob = {B, ldb, p.B_int, p.s_b, p.lam_b, comp ? p.RB_int : nullptr, p.s_rb, p.lam_rb, p.Bd,
+                             count_b ? p.tot_b : nullptr};
     SRQ_HIP(h, launch_quant_pair(oa, ob, M, N, K, Kc, qmax, trunc, st));
     ra_vm_done = rb_vm_done = comp;
   }
@@ -916,7 +923,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     SRQ_HIP(h, launch_rows_fused(A, M, K, lda, qmax, trunc, p.A_int, Kc, p.s_a, p.lam_a,
                                  (comp && !skip_ra_vm) ? p.RA_int : nullptr, Kc, comp ? p.s_ra : nullptr,
                                  comp ? p.lam_ra : nullptr, st, global_scale ? p.s_a : nullptr,
-                                 global_scale ? p.lam_a : nullptr, b_cleared ? &b_clear : nullptr));
+                                 global_scale ? p.lam_a : nullptr, b_cleared ? &b_clear : nullptr,
+                                 count_a ? p.tot_a : nullptr));
     ra_vm_done = comp && !skip_ra_vm;
   } else {
     SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(p.s_a), M, 0, st));
@@ -943,6 +951,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       memset(&g, 0, sizeof(g));
       g.X = B; g.ldx = ldb; g.scale = p.s_b; g.lambda = p.lam_b; g.Q = p.B_int; g.ldq = Kc;
       if (comp) { g.rscale = p.s_rb; g.rlambda = p.lam_rb; g.Rvm = p.RB_int; g.ldr = Kc; }
+      if (count_b) g.counts = p.tot_b;
       g.lines = once_lines; g.wait_ticks = h->wait_ticks;
       SRQ_HIP(h, launch_cols_once(g, K, N, qmax, trunc, false, st));
       rb_vm_done = comp;
@@ -995,7 +1004,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // the device: a small kernel turns the counts into an execution per term, and every launch
     // that belongs to one outcome only checks that decision itself and does nothing otherwise.
     // (a limit <= 0 is reached by any density, including none kept: the dense branch needs no count)
-    const bool always_dense = dense_fallback_density <= 0.f;
     const bool sync_mode = dense_fallback_density <= 1.f && !always_dense;
     const bool auto_dev = strategy == SRQ_STRATEGY_AUTO && !sync_mode && !always_dense;
     const RunIf a_on_mfma = {p.paths + 0, 1u << kPathMfma}, a_on_valu = {p.paths + 0, 1u << kPathValu};
@@ -1024,15 +1032,18 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // (calls, us, in FP32 / from the codes: 1024^3 36.4 / 37.4, 2048^2 x 512 40.6 / 42.2, 4096^2 x 512 115 / 118, but 1500^3 61.6 / 58.8,
     // 2048^3 74.8 / 71.1, 4096^2 x 2048 195 / 192, 3000^3 239 / 229)
     const bool in_strips = strips && (K <= 1024 || (term_a && !codes_a) || (term_b && !codes_b));
+    const bool mask_in_strips_a = in_strips && term_a && !count_a, mask_in_strips_b = in_strips && term_b && !count_b;
     if (in_strips || (strips_ok(M, N, K) && !strips)) {
       // (the means alone where the passes of the strips are not taken: the order of the additions depends on the shape,
       // not on what is expected of the executions)
-      const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, in_strips && term_a ? p.mask_a : nullptr, p.tot_a};
-      const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, in_strips && term_b ? p.mask_b : nullptr, p.tot_b};
+      const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, mask_in_strips_a ? p.mask_a : nullptr,
+                             mask_in_strips_a || count_a ? p.tot_a : nullptr};
+      const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, mask_in_strips_b ? p.mask_b : nullptr,
+                             mask_in_strips_b || count_b ? p.tot_b : nullptr};
       SRQ_HIP(h, launch_select_pair(sa, sb, M, N, K, st));
     } else if (!strips) {
       SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
-                                          theta_b, p.dcol, p.t_b, st));
+                                          theta_b, p.dcol, p.t_b, st, count_a ? p.tot_a : nullptr, count_b ? p.tot_b : nullptr));
     }
     if (!in_strips && (strips || codes_a || codes_b)) {
       const CodesSelect ca = {strips ? p.row_part : nullptr, parts_n, (double)N, theta_a, p.drow, p.t_a, A, lda, 1, p.A_int, p.RA_int,
@@ -1046,10 +1057,10 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     if (want_ra_em) {
       SRQ_HIP(h, launch_rows_mask_resid_em(A, M, K, lda, qmax, trunc, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, p.t_a, p.mask_a, p.tot_a, st));
       ra_em_done = true;
-    } else if (term_a && !in_strips && !codes_a) {
+    } else if (term_a && !in_strips && !codes_a && !count_a) {
       SRQ_HIP(h, launch_rows_mask(A, M, K, lda, p.t_a, p.mask_a, p.tot_a, st));
     }
-    if (term_b && !in_strips && !codes_b) {
+    if (term_b && !in_strips && !codes_b && !count_b) {
       // (tot_b was cleared in the quantize stage)
       if (rb_in_select)
         SRQ_HIP(h, launch_cols_mask_resid(B, K, N, ldb, qmax, trunc, p.s_b, p.lam_b, p.ramax_b, p.s_rb, p.lam_rb,

@@ -209,6 +209,19 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
     __syncthreads();
     if (tid < BC && strip * BC + tid < cols && kept[tid]) atomicAdd(&g.counts[strip * BC + tid], (int32_t)kept[tid]);
   }
+  if (RESID && !GIVEN && !MASK && g.counts) {
+    // (kept was cleared before the barriers of the exchange)
+    int n[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      n[0] += fabsf(v[i].x) > 0.f; n[1] += fabsf(v[i].y) > 0.f;
+      n[2] += fabsf(v[i].z) > 0.f; n[3] += fabsf(v[i].w) > 0.f;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) atomicAdd(&kept[cg * 4 + c], (uint32_t)n[c]);
+    __syncthreads();
+    if (tid < BC && strip * BC + tid < cols && kept[tid]) atomicAdd(&g.counts[strip * BC + tid], (int32_t)kept[tid]);
+  }
   // sixteen codes of each of the patch's columns
   auto put = [&](int8_t* Qvm, int64_t ldvm, const unsigned (&packed)[4][4]) __attribute__((always_inline)) {
     const int here = (int)(rows - row0 < 16 ? rows - row0 : 16);

@@ -41,8 +41,10 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
                                                          // words this launch zeroes on the side (one per
                                                          // thread and array), so that the kernels after it
                                                          // need no launch to clear their accumulators
-                                                         ClearList clr) {
+                                                         ClearList clr,
+                                                         int32_t* __restrict__ nonzero) {   // entries that are not zero, per row
   __shared__ float sm[4];
+  __shared__ int kept[4];
   {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (clr.a && g < clr.na) clr.a[g] = 0u;
@@ -63,6 +65,15 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     int64_t c4 = threadIdx.x + i * 256;
     x[i] = c4 < n4 ? load_streaming(src + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
     m = fmaxf(m, fmaxf(fmaxf(fabsf(x[i].x), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w))));
+  }
+  if (nonzero) {
+    int n = fabsf(xt) > 0.f;                         // (not by ballots: the compiler counts NaN there)
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) n += (fabsf(x[i].x) > 0.f) + (fabsf(x[i].y) > 0.f) + (fabsf(x[i].z) > 0.f) + (fabsf(x[i].w) > 0.f);
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+    if ((threadIdx.x & 63) == 0) kept[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) nonzero[row] = kept[0] + kept[1] + kept[2] + kept[3];
   }
   float lam = 0.f, s = 0.f;
   if (given_scale) {
@@ -780,7 +791,7 @@ bool rows_fused_ok(int64_t cols) { return cols > 0 && cols <= 16384; }
 hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
                              int8_t* Q, int64_t ldq, float* scale, float* lambda, int8_t* Rq, int64_t ldr,
                              float* rscale, float* rlambda, hipStream_t st, const float* given_scale,
-                             const float* given_lambda, const ClearList* clear) {
+                             const float* given_lambda, const ClearList* clear, int32_t* nonzero) {
   if (rows <= 0) return hipSuccess;
   ClearList clr = {nullptr, 0, nullptr, 0, nullptr, 0};
   if (clear) clr = *clear;                                   // (the caller has checked rows_fused_can_clear)
@@ -788,7 +799,7 @@ hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t
   const float qm = (float)qmax;
 #define SRQ_ROWS(NV4)                                                                                        \
   hipLaunchKernelGGL((trunc ? rows_fused_kernel<NV4, true> : rows_fused_kernel<NV4, false>), grid, block, 0, st, X, cols, ldx, qm, Q, ldq, scale, \
-                     lambda, Rq, ldr, rscale, rlambda, given_scale, given_lambda, clr)
+                     lambda, Rq, ldr, rscale, rlambda, given_scale, given_lambda, clr, nonzero)
   if (cols <= 1024) SRQ_ROWS(1);
   else if (cols <= 2048) SRQ_ROWS(2);
   else if (cols <= 4096) SRQ_ROWS(4);

@@ -20,7 +20,8 @@ __global__ void reduce_means_pair_kernel(const double* __restrict__ part0, int64
                                          double count0, float theta0, float* __restrict__ mean0,
                                          float* __restrict__ thresh0, const double* __restrict__ part1,
                                          int64_t nparts1, int64_t n1, double count1, float theta1,
-                                         float* __restrict__ mean1, float* __restrict__ thresh1) {
+                                         float* __restrict__ mean1, float* __restrict__ thresh1,
+                                         int32_t* __restrict__ counts0, int32_t* __restrict__ counts1) {
   int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n0 + n1) return;
   const bool second = v >= n0;
@@ -33,7 +34,11 @@ __global__ void reduce_means_pair_kernel(const double* __restrict__ part0, int64
   float m = (float)(s / (second ? count1 : count0));
   (second ? mean1 : mean0)[v] = m;
   float* thresh = second ? thresh1 : thresh0;       // (null: the means alone are wanted)
-  if (thresh) thresh[v] = (second ? theta1 : theta0) * m;
+  if (!thresh) return;
+  const float t = (second ? theta1 : theta0) * m;
+  thresh[v] = t;
+  int32_t* counts = second ? counts1 : counts0;
+  if (counts && t != t) counts[v] = 0;
 }
 
 // ---- vectors are rows: one wave per (row, chunk of kSelChunk consecutive elements) ----
@@ -201,11 +206,11 @@ __global__ void stats_kernel(const int64_t* nnz_a, const int64_t* nnz_b, int pat
 hipError_t launch_reduce_means_pair(const double* part0, int64_t nparts0, int64_t n0, int64_t count0, float theta0,
                                     float* mean0, float* thresh0, const double* part1, int64_t nparts1,
                                     int64_t n1, int64_t count1, float theta1, float* mean1, float* thresh1,
-                                    hipStream_t st) {
+                                    hipStream_t st, int32_t* counts0, int32_t* counts1) {
   if (n0 + n1 <= 0) return hipSuccess;
   hipLaunchKernelGGL(reduce_means_pair_kernel, dim3((unsigned)((n0 + n1 + 255) / 256)), dim3(256), 0, st, part0,
                      nparts0, n0, (double)count0, theta0, mean0, thresh0, part1, nparts1, n1, (double)count1,
-                     theta1, mean1, thresh1);
+                     theta1, mean1, thresh1, counts0, counts1);
   return hipGetLastError();
 }
 

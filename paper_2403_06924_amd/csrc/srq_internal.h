@@ -165,7 +165,8 @@ hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t
                              int8_t* Q, int64_t ldq, float* scale, float* lambda, int8_t* Rq, int64_t ldr,
                              float* rscale, float* rlambda, hipStream_t st, const float* given_scale = nullptr,
                              const float* given_lambda = nullptr,
-                             const ClearList* clear = nullptr);
+                             const ClearList* clear = nullptr,
+                             int32_t* nonzero = nullptr);   // entries that are not zero, per row
 bool rows_resid_em_ok(const float* X, int64_t rows, int64_t cols, int64_t ldx, const float* scale,
                       const float* lambda, const float* rlambda, const int8_t* Rem, int64_t ldem);
 hipError_t launch_rows_resid_em(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
@@ -206,7 +207,8 @@ struct ColsOnce {
   int64_t ldr;
   int8_t* Rem;
   int64_t ldem;
-  const float* thresh;         // with mask: keep-bits (mask_stride bytes per column) and counts, which start at zero
+  const float* thresh;         // with mask: keep-bits (mask_stride bytes per column) and counts, which start at zero;
+                               // counts alone (with a residual, scales not given): of the entries that are not zero
   uint8_t* mask;
   int64_t mask_stride;
   int32_t* counts;
@@ -299,6 +301,7 @@ struct StripOperand {
   int8_t* Rq;                  // residual codes; null: no residual (and no D)
   float *rscale, *rlambda;
   int8_t* D;                   // zero-filled codes: only the places past K are written here
+  int32_t* nonzero;            // entries that are not zero, per vector; null: not wanted
 };
 struct StripSelect {
   const float* X;
@@ -308,8 +311,8 @@ struct StripSelect {
   double count;
   float theta;
   float *mean, *thresh;
-  uint64_t* mask;              // null: the mean and the threshold only
-  int32_t* counts;
+  uint64_t* mask;              // null: the mean and the threshold only, and with counts a zero there if no entry is above
+  int32_t* counts;             // the threshold (of zero, unless it is no number)
 };
 struct StripCompact {
   int nvec;
@@ -370,11 +373,11 @@ bool short_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const G
 hipError_t launch_short_first(const ShortCall& g, bool comp, const GemmEpilogue& ep, hipStream_t st);
 hipError_t launch_short_second(const ShortCall& g, const GemmEpilogue& ep, hipStream_t st);
 
-// thresholds from the partial sums of the GEMM epilogue
+// thresholds from the partial sums of the GEMM epilogue; counts0 / counts1: a zero for vectors whose threshold is no number
 hipError_t launch_reduce_means_pair(const double* part0, int64_t nparts0, int64_t n0, int64_t count0, float theta0,
                                     float* mean0, float* thresh0, const double* part1, int64_t nparts1,
                                     int64_t n1, int64_t count1, float theta1, float* mean1, float* thresh1,
-                                    hipStream_t st);
+                                    hipStream_t st, int32_t* counts0 = nullptr, int32_t* counts1 = nullptr);
 
 // INT8 GEMM, both operands K-contiguous
 constexpr int kGemmPart = 64;                 // fewest rows / columns of C per partial sum of |D_F| (sizes the buffers)

@@ -123,6 +123,21 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   load_row<RT, NV4>(x, n, s.X + row * s.ldx, K, t);
 #pragma unroll
   for (int i = 0; i < NV4; ++i) m = fmaxf(m, max4(abs4(x[i])));
+  if (s.nonzero) {                                   // (as a float: no row is longer than 8192)
+    int some = 0;
+#pragma unroll
+    for (int i = 0; i < NV4; ++i)
+      some += (fabsf(x[i].x) > 0.f) + (fabsf(x[i].y) > 0.f) + (fabsf(x[i].z) > 0.f) + (fabsf(x[i].w) > 0.f);
+    for (int off = 32; off > 0; off >>= 1) some += __shfl_xor(some, off, 64);
+    if constexpr (RT > 64) {
+      if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = (float)some;
+      __syncthreads();
+      float all = 0.f;
+      for (int i = 0; i < RT / 64; ++i) all += sm[i];
+      some = (int)all;
+    }
+    if (t == 0) s.nonzero[row] = some;
+  }
   const float amax = row_max<RT>(m, sm);
   float lam = 0.f, sc = 0.f;
   if (amax > 0.f) { lam = qmax / amax; sc = amax / qmax; }
@@ -158,21 +173,31 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   for (int e = K + t; e < Kc; e += RT) s.D[row * Kc + e] = 0;
 }
 
-// maxima of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
-template <int TH, int CG>
-__device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
+// maxima (sums) of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
+template <int TH, int CG, class Op>
+__device__ __forceinline__ void strip_all(float (&m)[4], float* red, Op op) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cg = threadIdx.x & (CG - 1);
 #pragma unroll
   for (int off = CG; off < 64; off <<= 1)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) m[c] = fmaxf(m[c], __shfl_xor(m[c], off, 64));
+    for (int c = 0; c < 4; ++c) m[c] = op(m[c], __shfl_xor(m[c], off, 64));
   if (lane < CG)
 #pragma unroll
     for (int c = 0; c < 4; ++c) red[w * 4 * CG + cg * 4 + c] = m[c];
   __syncthreads();
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    for (int i = 0; i < TH / 64; ++i) m[c] = fmaxf(m[c], red[(i * CG + cg) * 4 + c]);
+  for (int c = 0; c < 4; ++c) {
+    m[c] = red[cg * 4 + c];
+    for (int i = 1; i < TH / 64; ++i) m[c] = op(m[c], red[(i * CG + cg) * 4 + c]);
+  }
+}
+template <int TH, int CG>
+__device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
+  strip_all<TH, CG>(m, red, [](float x, float y) { return fmaxf(x, y); });
+}
+template <int TH, int CG>
+__device__ __forceinline__ void strip_sum(float (&m)[4], float* red) {
+  strip_all<TH, CG>(m, red, [](float x, float y) { return x + y; });
 }
 
 // RPT codes of each of the patch's columns: Q[col * ld + row0 ..], places from `lim` on left alone
@@ -236,6 +261,14 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     const float4 a = abs4(v[i]);
     m[0] = fmaxf(m[0], a.x); m[1] = fmaxf(m[1], a.y); m[2] = fmaxf(m[2], a.z); m[3] = fmaxf(m[3], a.w);
   }
+  float some[4] = {0.f, 0.f, 0.f, 0.f};               // entries that are not zero
+  if (s.nonzero) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      some[0] += fabsf(v[i].x) > 0.f ? 1.f : 0.f; some[1] += fabsf(v[i].y) > 0.f ? 1.f : 0.f;
+      some[2] += fabsf(v[i].z) > 0.f ? 1.f : 0.f; some[3] += fabsf(v[i].w) > 0.f ? 1.f : 0.f;
+    }
+  }
   strip_max<TH, CG>(m, red);
   float lam[4], sc[4], rm[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -249,6 +282,11 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   store_codes<RPT>(s.Q, ldq, Kc, col0, ncol, row0, pk);
   if (!s.Rq) return;
   strip_max<TH, CG>(rm, red + TH / 16 * CG);
+  if (s.nonzero) {                                   // (the first maxima have been read)
+    strip_sum<TH, CG>(some, red);
+    if (rb == 0)
+      for (int c = 0; c < ncol; ++c) s.nonzero[col0 + c] = (int)some[c];
+  }
   float rlam[4], rs[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -285,7 +323,11 @@ __global__ __launch_bounds__(TH) void quant_cols_kernel(StripOperand s, int64_t 
 __device__ __forceinline__ void mean_of(const StripSelect& s, int64_t v, double sum, bool writer, float& t) {
   const float mean = (float)(sum / s.count);
   t = s.theta * mean;
-  if (writer) { s.mean[v] = mean; s.thresh[v] = t; }
+  if (writer) {
+    s.mean[v] = mean;
+    s.thresh[v] = t;
+    if (!s.mask && s.counts && t != t) s.counts[v] = 0;
+  }
 }
 
 // eight neighbouring lanes assemble one 32-bit piece of a row's mask

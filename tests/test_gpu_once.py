@@ -100,3 +100,30 @@ def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
             assert (host(idx)[:len(k)] == k).all() and (host(val)[:len(k)] == host(codes)[vec, k]).all()
         # once more with the threshold of row 7 on (or next to) an entry
         theta = float(np.sort(np.abs(A[7]))[-K // 10] / host(im["drow"])[7])
+
+
+# (the last three: columns in one read; a wave and a workgroup per row)
+@pytest.mark.parametrize("shape", [(5, 9, 3), (65, 70, 250), (100, 1001, 1024), (129, 65, 1500), (40, 30, 4500), (1100, 1000, 4099), (2100, 37, 8192),
+                                   (70, 2100, 16384)])
+def test_counts_of_operands_that_are_not_compacted(srq, b, shape):
+    """The dense branch whatever the counts, thresholds of zero: every entry that is not zero counts, and none where the
+    threshold is no number (0 times a mean that has overflowed)."""
+    if srq.late:
+        pytest.skip("the default wait is enough")
+    M, N, K = shape
+    rng = np.random.default_rng(K)
+    A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
+    A[rng.random((M, K)) < 0.3] = 0
+    B[rng.random((K, N)) < 0.6] = 0
+    A[1], B[:, 2] = 0, 0
+    A[3, 0], B[0, 4] = np.nan, np.nan
+    A[4] = 1e38                                               # |D_F| overflows in this row
+    stats = b.stats_tensor()
+    srq.compensated_gemm(dev(A), dev(B), 0.0, 0.0, dense_fallback_density=0.0, stats=stats)
+    torch.cuda.synchronize()
+    im, st = srq.intermediates(M, N, K), b.read_stats(stats)
+    with np.errstate(invalid="ignore"):
+        counts = [(np.abs(V) > host(t)[:, None]).sum(axis=1) for V, t in ((A, im["t_a"]), (B.T, im["t_b"]))]
+    assert (host(im["a_ptr"]) == np.concatenate([[0], np.cumsum(counts[0])])).all()
+    assert (host(im["b_ptr"]) == np.concatenate([[0], np.cumsum(counts[1])])).all()
+    assert st["nnz_a"] == counts[0].sum() and st["nnz_b"] == counts[1].sum() and counts[0][0] > 0
