@@ -882,12 +882,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     SRQ_HIP(h, launch_quant_pair(oa, ob, M, N, K, Kc, qmax, trunc, st));
     ra_vm_done = rb_vm_done = comp;
   }
-  if (Kc != K && !strips) {
-    // the padding columns of every matrix a product may read (nothing else ever writes them)
-    int8_t* mats[6] = {p.A_int, p.B_int, comp ? p.RA_int : nullptr, comp ? p.RB_int : nullptr,
-                       comp ? p.Ad : nullptr, comp ? p.Bd : nullptr};
-    const int64_t nrows[6] = {M, N, M, N, M, N};
-    SRQ_HIP(h, launch_zero_pad(mats, nrows, 6, K, Kc, st));
+  if (Kc != K && !strips && !(fastA && once_b)) {
+    // the padding columns of every matrix a product may read (the passes over rows and over columns in one read, and the
+    // expansions, write their own)
+    int8_t* mats[4] = {p.A_int, p.B_int, comp ? p.RA_int : nullptr, comp ? p.RB_int : nullptr};
+    const int64_t nrows[4] = {M, N, M, N};
+    SRQ_HIP(h, launch_zero_pad(mats, nrows, 4, K, Kc, st));
   }
   // the two vectors of column maxima and the per-column counts of the selection that B's passes
   // accumulate into start at zero
@@ -924,7 +924,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                  (comp && !skip_ra_vm) ? p.RA_int : nullptr, Kc, comp ? p.s_ra : nullptr,
                                  comp ? p.lam_ra : nullptr, st, global_scale ? p.s_a : nullptr,
                                  global_scale ? p.lam_a : nullptr, b_cleared ? &b_clear : nullptr,
-                                 count_a ? p.tot_a : nullptr));
+                                 count_a ? p.tot_a : nullptr, (int)(Kc - K)));
     ra_vm_done = comp && !skip_ra_vm;
   } else {
     SRQ_HIP(h, launch_fill_u32(reinterpret_cast<uint32_t*>(p.s_a), M, 0, st));
@@ -952,6 +952,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       g.X = B; g.ldx = ldb; g.scale = p.s_b; g.lambda = p.lam_b; g.Q = p.B_int; g.ldq = Kc;
       if (comp) { g.rscale = p.s_rb; g.rlambda = p.lam_rb; g.Rvm = p.RB_int; g.ldr = Kc; }
       if (count_b) g.counts = p.tot_b;
+      if (Kc != K) g.pad_to = Kc;
       g.lines = once_lines; g.wait_ticks = h->wait_ticks;
       SRQ_HIP(h, launch_cols_once(g, K, N, qmax, trunc, false, st));
       rb_vm_done = comp;

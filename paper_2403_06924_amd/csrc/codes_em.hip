@@ -57,9 +57,15 @@ __global__ __launch_bounds__(256) void codes_em_kernel(CodesEm a, CodesEm b, int
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          unsigned four = x[4 * j + r][c];
-#pragma unroll 1
-          for (int i = 4 * j; i < here && i < 4 * j + 4; ++i, four >>= 8) dst[i] = (int8_t)four;
+          const int n = here - 4 * j;
+          const unsigned four = x[4 * j + r][c];
+          if (n >= 4) {
+            *reinterpret_cast<u1u*>(dst + 4 * j) = four;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+              if (i < n) dst[4 * j + i] = (int8_t)(four >> (8 * i));
+          }
         }
       }
     }

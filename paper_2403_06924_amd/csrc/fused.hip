@@ -42,7 +42,8 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
                                                          // thread and array), so that the kernels after it
                                                          // need no launch to clear their accumulators
                                                          ClearList clr,
-                                                         int32_t* __restrict__ nonzero) {   // entries that are not zero, per row
+                                                         int32_t* __restrict__ nonzero,     // entries that are not zero, per row
+                                                         int pad) {   // zeros to be written past the end of a row of codes
   __shared__ float sm[4];
   __shared__ int kept[4];
   {
@@ -84,6 +85,10 @@ __global__ __launch_bounds__(256) void rows_fused_kernel(const float* __restrict
     if (amax > 0.f) { lam = qmax / amax; s = amax / qmax; }
   }
   u1u* qdst = reinterpret_cast<u1u*>(Q + row * ldq);
+  if ((int)threadIdx.x < pad) {
+    Q[row * ldq + cols + threadIdx.x] = 0;
+    if (Rq) Rq[row * ldr + cols + threadIdx.x] = 0;
+  }
   const float zt = biased_code(xt, lam, qmax, TRUNC);
   if (has_tail) Q[row * ldq + ct] = (int8_t)__float_as_int(zt);
   xt = xt - code_value(zt) * s;
@@ -502,6 +507,7 @@ __global__ __launch_bounds__(256) void scatter_mask_kernel(const uint64_t* __res
   const bool qvec = (reinterpret_cast<uintptr_t>(qv) & 3) == 0;
   const bool dvec = dv && (reinterpret_cast<uintptr_t>(dv) & 3) == 0;
   // chunks of 256 elements (four mask words); wave w owns chunks [c0, c1)
+  if (dv && veclen + tid < ldd) dv[veclen + tid] = 0;   // (rows of the expansion are padded by less than 256)
   const int64_t nchunks = (veclen + 255) >> 8;
   const int64_t cpw = (nchunks + 3) >> 2;
   const int64_t c0 = w * cpw < nchunks ? w * cpw : nchunks;
@@ -581,6 +587,7 @@ __global__ __launch_bounds__(256) void scatter_mask16_kernel(const uint64_t* __r
   const uint16_t* mv16 = reinterpret_cast<const uint16_t*>(mv);
   const int8_t* qv = Q + v * ldq;                        // 16-byte aligned (checked by the launcher)
   int8_t* dv = (dense && run_if_ok(dense_if)) ? dense + v * ldd : nullptr;   // likewise
+  if (dv && veclen + tid < ldd) dv[veclen + tid] = 0;   // (rows of the expansion are padded by less than 256)
   const int64_t nchunks = (veclen + 1023) >> 10;
   const int64_t cpw = (nchunks + 3) >> 2;
   const int64_t c0 = w * cpw < nchunks ? w * cpw : nchunks;
@@ -791,7 +798,7 @@ bool rows_fused_ok(int64_t cols) { return cols > 0 && cols <= 16384; }
 hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
                              int8_t* Q, int64_t ldq, float* scale, float* lambda, int8_t* Rq, int64_t ldr,
                              float* rscale, float* rlambda, hipStream_t st, const float* given_scale,
-                             const float* given_lambda, const ClearList* clear, int32_t* nonzero) {
+                             const float* given_lambda, const ClearList* clear, int32_t* nonzero, int pad) {
   if (rows <= 0) return hipSuccess;
   ClearList clr = {nullptr, 0, nullptr, 0, nullptr, 0};
   if (clear) clr = *clear;                                   // (the caller has checked rows_fused_can_clear)
@@ -799,7 +806,7 @@ hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t
   const float qm = (float)qmax;
 #define SRQ_ROWS(NV4)                                                                                        \
   hipLaunchKernelGGL((trunc ? rows_fused_kernel<NV4, true> : rows_fused_kernel<NV4, false>), grid, block, 0, st, X, cols, ldx, qm, Q, ldq, scale, \
-                     lambda, Rq, ldr, rscale, rlambda, given_scale, given_lambda, clr, nonzero)
+                     lambda, Rq, ldr, rscale, rlambda, given_scale, given_lambda, clr, nonzero, pad)
   if (cols <= 1024) SRQ_ROWS(1);
   else if (cols <= 2048) SRQ_ROWS(2);
   else if (cols <= 4096) SRQ_ROWS(4);

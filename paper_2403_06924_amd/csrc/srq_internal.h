@@ -166,7 +166,8 @@ hipError_t launch_rows_fused(const float* X, int64_t rows, int64_t cols, int64_t
                              float* rscale, float* rlambda, hipStream_t st, const float* given_scale = nullptr,
                              const float* given_lambda = nullptr,
                              const ClearList* clear = nullptr,
-                             int32_t* nonzero = nullptr);   // entries that are not zero, per row
+                             int32_t* nonzero = nullptr,    // entries that are not zero, per row
+                             int pad = 0);   // zeros (less than 256) past the end of the rows of both code matrices
 bool rows_resid_em_ok(const float* X, int64_t rows, int64_t cols, int64_t ldx, const float* scale,
                       const float* lambda, const float* rlambda, const int8_t* Rem, int64_t ldem);
 hipError_t launch_rows_resid_em(const float* X, int64_t rows, int64_t cols, int64_t ldx, int qmax, int trunc,
@@ -207,6 +208,7 @@ struct ColsOnce {
   int64_t ldr;
   int8_t* Rem;
   int64_t ldem;
+  int64_t pad_to;              // zeros in Q and Rvm from the last row on up to here (a multiple of 16; 0: none)
   const float* thresh;         // with mask: keep-bits (mask_stride bytes per column) and counts, which start at zero;
                                // counts alone (with a residual, scales not given): of the entries that are not zero
   uint8_t* mask;

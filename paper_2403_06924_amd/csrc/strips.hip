@@ -173,31 +173,21 @@ __device__ __forceinline__ void quant_row(const StripOperand& s, int64_t row, in
   for (int e = K + t; e < Kc; e += RT) s.D[row * Kc + e] = 0;
 }
 
-// maxima (sums) of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
-template <int TH, int CG, class Op>
-__device__ __forceinline__ void strip_all(float (&m)[4], float* red, Op op) {
+// maxima of the CG * 4 columns of a strip from every thread's own four; red: [TH / 64][4 * CG]
+template <int TH, int CG>
+__device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, cg = threadIdx.x & (CG - 1);
 #pragma unroll
   for (int off = CG; off < 64; off <<= 1)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) m[c] = op(m[c], __shfl_xor(m[c], off, 64));
+    for (int c = 0; c < 4; ++c) m[c] = fmaxf(m[c], __shfl_xor(m[c], off, 64));
   if (lane < CG)
 #pragma unroll
     for (int c = 0; c < 4; ++c) red[w * 4 * CG + cg * 4 + c] = m[c];
   __syncthreads();
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    m[c] = red[cg * 4 + c];
-    for (int i = 1; i < TH / 64; ++i) m[c] = op(m[c], red[(i * CG + cg) * 4 + c]);
-  }
-}
-template <int TH, int CG>
-__device__ __forceinline__ void strip_max(float (&m)[4], float* red) {
-  strip_all<TH, CG>(m, red, [](float x, float y) { return fmaxf(x, y); });
-}
-template <int TH, int CG>
-__device__ __forceinline__ void strip_sum(float (&m)[4], float* red) {
-  strip_all<TH, CG>(m, red, [](float x, float y) { return x + y; });
+  for (int c = 0; c < 4; ++c)
+    for (int i = 0; i < TH / 64; ++i) m[c] = fmaxf(m[c], red[(i * CG + cg) * 4 + c]);
 }
 
 // RPT codes of each of the patch's columns: Q[col * ld + row0 ..], places from `lim` on left alone
@@ -247,7 +237,7 @@ __device__ __forceinline__ void patch_codes(float4 (&v)[RPT], const float (&lam)
   }
 }
 
-template <int TH, int CG, int RPT>
+template <int TH, int CG, int RPT, bool COUNT>   // COUNT: entries that are not zero, if wanted
 __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, int64_t cols, int K, int Kc, int64_t ldq, float qmax,
                                             int trunc, float* red) {
   const int cg = threadIdx.x & (CG - 1), rb = threadIdx.x / CG, row0 = rb * RPT;
@@ -261,13 +251,18 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
     const float4 a = abs4(v[i]);
     m[0] = fmaxf(m[0], a.x); m[1] = fmaxf(m[1], a.y); m[2] = fmaxf(m[2], a.z); m[3] = fmaxf(m[3], a.w);
   }
-  float some[4] = {0.f, 0.f, 0.f, 0.f};               // entries that are not zero
-  if (s.nonzero) {
+  __shared__ int some[COUNT ? 4 * CG : 1];
+  if (COUNT && s.nonzero) {                          // (through LDS at once: four registers more cost 1024 x 1024 2 % of a call)
+    if ((int)threadIdx.x < 4 * CG) some[threadIdx.x] = 0;
+    __syncthreads();
+    int n[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-      some[0] += fabsf(v[i].x) > 0.f ? 1.f : 0.f; some[1] += fabsf(v[i].y) > 0.f ? 1.f : 0.f;
-      some[2] += fabsf(v[i].z) > 0.f ? 1.f : 0.f; some[3] += fabsf(v[i].w) > 0.f ? 1.f : 0.f;
+      n[0] += fabsf(v[i].x) > 0.f; n[1] += fabsf(v[i].y) > 0.f;
+      n[2] += fabsf(v[i].z) > 0.f; n[3] += fabsf(v[i].w) > 0.f;
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) atomicAdd(&some[cg * 4 + c], n[c]);
   }
   strip_max<TH, CG>(m, red);
   float lam[4], sc[4], rm[4] = {0.f, 0.f, 0.f, 0.f};
@@ -282,11 +277,8 @@ __device__ __forceinline__ void quant_strip(const StripOperand& s, int strip, in
   store_codes<RPT>(s.Q, ldq, Kc, col0, ncol, row0, pk);
   if (!s.Rq) return;
   strip_max<TH, CG>(rm, red + TH / 16 * CG);
-  if (s.nonzero) {                                   // (the first maxima have been read)
-    strip_sum<TH, CG>(some, red);
-    if (rb == 0)
-      for (int c = 0; c < ncol; ++c) s.nonzero[col0 + c] = (int)some[c];
-  }
+  if (COUNT && s.nonzero && rb == 0)
+    for (int c = 0; c < ncol; ++c) s.nonzero[col0 + c] = some[cg * 4 + c];
   float rlam[4], rs[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -307,7 +299,7 @@ __global__ __launch_bounds__(TH) void quant_pair_kernel(StripOperand a, StripOpe
                                                          float qmax, int trunc) {
   __shared__ float sm[TH / 8 * CG];
   const int64_t row = ((int64_t)blockIdx.x - strips) * (TH / RT) + (RT == 64 ? threadIdx.x >> 6 : 0);
-  if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, Kc, qmax, trunc, sm);
+  if ((int)blockIdx.x < strips) quant_strip<TH, CG, RPT, true>(b, strip_of<8 / CG>(blockIdx.x, strips), N, K, Kc, Kc, qmax, trunc, sm);
   else if (row < M) quant_row<RT, NV4>(a, row, K, Kc, qmax, trunc, sm);
 }
 
@@ -316,7 +308,7 @@ template <int TH, int RT, int NV4, int CG, int RPT>
 __global__ __launch_bounds__(TH) void quant_cols_kernel(StripOperand s, int64_t N, int K, int64_t ldq, int strips, float qmax,
                                                         int trunc) {
   __shared__ float sm[TH / 8 * CG];
-  quant_strip<TH, CG, RPT>(s, strip_of<8 / CG>(blockIdx.x, strips), N, K, K, ldq, qmax, trunc, sm);
+  quant_strip<TH, CG, RPT, false>(s, strip_of<8 / CG>(blockIdx.x, strips), N, K, K, ldq, qmax, trunc, sm);
 }
 
 // ---- selection -------------------------------------------------------------------------------------
@@ -663,24 +655,28 @@ int strip_cg(int64_t K) { return K <= 512 ? 4 : K <= 4096 ? 2 : 1; }
 // more of a compute unit and read narrower pieces of each row, so what launches cost has to be a larger
 // share of the call:
 //   K <= 1024, any size    512^2 x 256 49 / 26, 8192^2 x 1024 540 / 521
-//   K <= 2048              4096^2 x 2048 228 / 194, 20000 x 200 x 2000 261 / 234, 8192^2 x 2048 654 / 650, 16384 x 4096 x 2048
-//                          643 / 636, 12288^2 x 2048 1269 / 1280
-//   K <= 4096              2048^2 x 4096 148 / 121, 2999 x 4097 x 3001 267 / 246, 2000 x 6000 x 3000 279 / 246, 3500^2 x
-//   and (M + N) K <= 24e6  2500 229 / 215, 4500 x 1400 x 4000 208 / 178, 5900 x 90 x 2200 117 / 96; 4096^2 x 2500 244 / 245;
-//                          3500^2 x 4096 306 / 313, 4096^2 x 3072 265 / 274, 6000^2 x 2112 440 / 486, 4096^3 304 / 320
-//   K <= 8192              512^2 x 8192 120 / 106, 1024^2 x 8192 139 / 137, 2048^2 x 8192 241 / 261
+// Against B in one read and the selection from the codes, us, those / these:
+//   K <= 1600              10000^2 x 1500 830 / 813, 6000 x 3000 x 1600 248 / 235
+//   K <= 2048              4096^2 x 2048 200 / 191, 3000^2 x 2000 154 / 140, 20000 x 200 x 2000 206 / 184; 5000^2 x 2000 298 / 303,
+//   and N K <= 8.5e6       8192^2 x 2048 607 / 626
+//   K <= 4096              2500^2 x 2300 127 / 122, 3000^2 x 2700 190 / 187, 4500 x 1400 x 4000 174 / 167; 3500^2 x 2500 200 / 201,
+//   and N K <= 8.5e6       2000 x 6000 x 3000 226 / 229, 2999 x 4097 x 3001 225 / 230
+//   and (M + N) K <= 24e6
+//   M + N <= 2048          300^2 x 8000 99 / 92, 300 x 400 x 6000 86 / 79, 900 x 1000 x 8191 123 / 123
 bool strips_ok(int64_t M, int64_t N, int64_t K) {
   if (K <= 0 || K > kStripsMaxK || M + N >= (1 << 24)) return false;
-  return K <= 1024 || (K <= 2048 && M + N <= 20480) || (K <= 4096 && (M + N) * K <= 24000000) || M + N <= 2048;
+  return K <= 1024 || (K <= 1600 && M + N <= 20480) || (K <= 2048 && M + N <= 20480 && N * K <= 8500000) ||
+         (K <= 4096 && (M + N) * K <= 24000000 && N * K <= 8500000) || M + N <= 2048;
 }
-// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, streaming / here; about 31 us of the small
-// ones is the host): columns 1000 x 1000 51 / 36, 15000 x 2000 197 / 125, 25000 x 2048 296 / 219, 10000 x 4096 204 / 171, but
-// 14336 x 4096 233 / 293, 20000 x 2500 238 / 295, and 5000 x 1500 with columns longer than 4096 in strips 68 / 75; rows 10000 x 1000
-// 62 / 46, 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 30000 x 4096 367 / 300, with longer rows 4000 x 5900 87 / 87.
+// One operand, srq_quantize and srq_build_sparse_residual with 5 % kept (us, the kernels of cols_once.hip resp. fused.hip / here;
+// about 31 us of the small ones is the host): columns 800 x 800 40 / 31, 1000 x 10000 64 / 48, 2000 x 6000 62 / 52, 2000 x 15000 140 /
+// 124, 2048 x 25000 218 / 215, 3000 x 1500 42 / 37, 4096 x 2000 43 / 43, 4096 x 5000 74 / 99, 3000 x 9000 125 / 147, 4096 x 10000
+// 125 / 167; rows 10000 x 1000 62 / 46, 15000 x 2000 115 / 86, 5000 x 4000 80 / 62, 30000 x 4096 367 / 300, with longer rows 4000 x
+// 5900 87 / 87.
 bool strips_one_ok(int axis, int64_t nvec, int64_t veclen) {
   if (veclen <= 0 || nvec >= (1 << 24)) return false;
   if (axis == SRQ_AXIS_ROW) return veclen <= 4096 || strips_ok(nvec, 0, veclen);
-  return veclen <= 2048 || (veclen <= 4096 && nvec <= 10240);
+  return veclen <= 2048 || (veclen <= 4096 && nvec * veclen <= 8200000);
 }
 // (Every workgroup adds up the counts before its vectors: scan and scatter in launches of their own / here, us:
 // 8000 x 200 x 2000 94.9 / 82.3, 16000 x 200 x 200 66.2 / 61.8, 40 x 40000 x 1000 202 / 220, 60000 x 60 x 2000 505 / 539.)
