@@ -524,20 +524,24 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
     uint32_t* lines = f.take<uint32_t>(words);
     const bool once = axis == SRQ_AXIS_COL && do_res && cols_once_ok(rows, cols, ldx) && f.off <= h->ws_bytes;
     const bool vm = r_layout == SRQ_LAYOUT_VECTOR_MAJOR;
+    // CSR / CSC from the mask and the codes, in one launch that adds the counts up itself, or after a scan
+    auto compact = [&]() -> hipError_t {
+      if (veclen <= kStripsMaxK && strips_compact_ok(nvec, 0)) {
+        const StripCompact one = {(int)nvec, mask_w, tot_w, q_w, ptr, idx, val, capacity, nullptr, nnz_dev};
+        StripCompact none;
+        memset(&none, 0, sizeof(none));
+        return launch_compact_pair(one, none, veclen, ldqw, st);
+      }
+      const hipError_t e = launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st);
+      if (e != hipSuccess) return e;
+      return launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st);
+    };
     if (fits && do_res && do_sel && vm && strips_one_ok(axis, nvec, veclen)) {
       // one read of X, then the compaction (with its own sums of the counts for few vectors)
       const StripReduce r = {X, ldx, scale, lambda, thresh, q_w, Rq, ldr, rscale, mask_w, tot_w};
       if (axis == SRQ_AXIS_ROW) SRQ_HIP(h, launch_reduce_rows(r, nvec, veclen, ldqw, qmax, trunc, st));
       else SRQ_HIP(h, launch_reduce_cols(r, nvec, veclen, ldqw, qmax, trunc, st));
-      if (strips_compact_ok(nvec, 0)) {
-        const StripCompact one = {(int)nvec, mask_w, tot_w, q_w, ptr, idx, val, capacity, nullptr, nnz_dev};
-        StripCompact none;
-        memset(&none, 0, sizeof(none));
-        SRQ_HIP(h, launch_compact_pair(one, none, veclen, ldqw, st));
-      } else {
-        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
-        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
-      }
+      SRQ_HIP(h, compact());
       return SRQ_STATUS_OK;
     }
     if (fits && axis == SRQ_AXIS_ROW && (!do_res || vm) && rows_fused_ok(cols)) {
@@ -545,8 +549,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
                                    ldr, do_res ? rscale : nullptr, do_res ? rlam_w : nullptr, st, scale, lambda));
       if (do_sel) {
         SRQ_HIP(h, launch_rows_mask(X, rows, cols, ldx, thresh, mask_w, tot_w, st));
-        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
-        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
+        SRQ_HIP(h, compact());
       }
       return SRQ_STATUS_OK;
     }
@@ -561,10 +564,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
       if (do_sel) { g.thresh = thresh; g.mask = reinterpret_cast<uint8_t*>(mask_w); g.mask_stride = mask_words(rows) * 8; g.counts = tot_w; }
       g.lines = lines; g.wait_ticks = h->wait_ticks;
       SRQ_HIP(h, launch_cols_once(g, rows, cols, qmax, trunc, true, st));
-      if (do_sel) {
-        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
-        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
-      }
+      if (do_sel) SRQ_HIP(h, compact());
       return SRQ_STATUS_OK;
     }
     if (fits && axis == SRQ_AXIS_COL) {
@@ -579,10 +579,7 @@ srq_status_t srq_build_sparse_residual(srq_handle_t h, const float* X, int64_t r
                                                vm ? Rq : nullptr, ldr, vm ? nullptr : Rq, ldr, st));
       else if (do_sel)
         SRQ_HIP(h, launch_cols_mask(X, rows, cols, ldx, thresh, mask_w, tot_w, st));
-      if (do_sel) {
-        SRQ_HIP(h, launch_scan_pair(tot_w, nvec, ptr, nnz_dev, nullptr, 0, nullptr, nullptr, st));
-        SRQ_HIP(h, launch_scatter_mask(mask_w, nvec, veclen, q_w, ldqw, ptr, idx, val, capacity, nullptr, 0, -1, st));
-      }
+      if (do_sel) SRQ_HIP(h, compact());
       return SRQ_STATUS_OK;
     }
   }

@@ -566,82 +566,87 @@ __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t 
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
-// A vector by RT threads, a wave or the workgroup, four elements per thread and round: the place of a thread's first
-// kept entry is the number of entries of earlier vectors, rounds, waves and lanes (the last from three ballots of its
-// own count, 0..4).  Codes and zero-filled copy have rows of Kc bytes with zeros past K.
-template <int RT, int NV4>
+// A vector by a wave, sixteen elements per lane and piece: the place of a lane's first kept entry is the number of entries of
+// earlier vectors, pieces and lanes (the last from five ballots of its own count, 0..16).  Codes and zero-filled copy have rows
+// of Kc bytes (a multiple of 16) with zeros past K.  One 16-byte load and store per 1024 elements, and as many stores of entries
+// as the lane with most of them has: with four elements per lane, us, 2999 x 4097 x 3001 26 / 16, calls 226 / 216, 2048^3 70.6 / 67.5,
+// 2000 x 1500 x 6000 161 / 154, reduction of 2000 x 15000 124 / 112.
+template <int NV>                                      // pieces of 1024 elements
 __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int groups_a, int K, int Kc) {
-  constexpr int kVec = 256 / RT, kWaves = RT / 64;   // vectors of a workgroup, waves of a vector
   __shared__ int64_t before[4];
-  __shared__ int kept[RT > 64 ? NV4 : 1][4], count[4];
+  __shared__ int count[4];
+  typedef unsigned u4a __attribute__((ext_vector_type(4)));
+  typedef int i4a __attribute__((ext_vector_type(4)));
   const bool second = (int)blockIdx.x >= groups_a;
   const StripCompact& s = second ? b : a;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, t = tid & (RT - 1);
-  const int v0 = ((int)blockIdx.x - (second ? groups_a : 0)) * kVec, v = v0 + (RT == 64 ? w : 0);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int v0 = ((int)blockIdx.x - (second ? groups_a : 0)) * 4, v = v0 + w;
   const bool ok = v < s.nvec;
-  const int words = (K + 63) / 64;
-  const uint32_t* mv = reinterpret_cast<const uint32_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
+  const int words = (K + 63) / 64, last = 4 * words - 1;
+  const uint16_t* mv = reinterpret_cast<const uint16_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
   const int8_t* qv = s.Q + (int64_t)(ok ? v : 0) * Kc;
-  unsigned nib[NV4], code[NV4];
+  u4a code[NV];
+  unsigned m[NV];
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) {                    // (without branches: what is not wanted is read where something is)
-    const int e = 4 * (t + i * RT), last = 2 * words - 1;
-    nib[i] = mv[e >> 5 < last ? e >> 5 : last];
-    code[i] = *reinterpret_cast<const unsigned*>(qv + (e < Kc ? e : Kc - 4));
+  for (int i = 0; i < NV; ++i) {                       // (without branches: what is not wanted is read where something is)
+    const int e = 1024 * i + 16 * lane;
+    m[i] = mv[e >> 4 < last ? e >> 4 : last];
+    code[i] = *reinterpret_cast<const u4a*>(qv + (e < Kc ? e : 0));
   }
+  // kept entries of the vectors before the workgroup's (v0 is a multiple of four)
   int64_t sum = 0;
-  for (int i = tid; i < v0; i += 256) sum += s.counts[i];
+  for (int i = 4 * tid; i < v0; i += 1024) {
+    const i4a c = *reinterpret_cast<const i4a*>(s.counts + i);
+    sum += (int64_t)c.x + c.y + c.z + c.w;
+  }
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
   if (lane == 0) before[w] = sum;
   const uint64_t lower = (1ull << lane) - 1ull;
-  int at[NV4], mine = 0;                             // RT = 64: places within the vector, its kept entries
+  int at[NV], mine = 0;
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) {
-    const int e = 4 * (t + i * RT);
-    nib[i] = ok && e < K ? (nib[i] >> (e & 31)) & 0xfu : 0u;   // (bits past K are zero)
-    const unsigned keep = ((nib[i] & 1u) ? 0xffu : 0u) | ((nib[i] & 2u) ? 0xff00u : 0u) | ((nib[i] & 4u) ? 0xff0000u : 0u) |
-                          ((nib[i] & 8u) ? 0xff000000u : 0u);
-    if (s.dense && ok && e < Kc) *reinterpret_cast<unsigned*>(s.dense + (int64_t)v * Kc + e) = code[i] & keep;
-    const int cnt = __popc(nib[i]);
-    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
-    at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower);
-    const int all = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-    if constexpr (RT == 64) mine += all;
-    else if (lane == 0) kept[i][w] = all;
+  for (int i = 0; i < NV; ++i) {
+    const int e = 1024 * i + 16 * lane;
+    if (!ok || e >= K) m[i] = 0;                       // (bits past K are zero)
+    if (s.dense && ok && e < Kc) {
+      u4a o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const unsigned nib = m[i] >> (4 * j);
+        o[j] = code[i][j] & (((nib & 1u) ? 0xffu : 0u) | ((nib & 2u) ? 0xff00u : 0u) | ((nib & 4u) ? 0xff0000u : 0u) |
+                             ((nib & 8u) ? 0xff000000u : 0u));
+      }
+      *reinterpret_cast<u4a*>(s.dense + (int64_t)v * Kc + e) = o;
+    }
+    const int cnt = __popc(m[i]);
+    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4), b3 = __ballot(cnt & 8), b4 = __ballot(cnt & 16);
+    at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower) + 8 * __popcll(b3 & lower) +
+            16 * __popcll(b4 & lower);
+    mine += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2) + 8 * __popcll(b3) + 16 * __popcll(b4);
   }
-  if (RT == 64 && lane == 0) count[w] = mine;
+  if (lane == 0) count[w] = mine;
   __syncthreads();
   int64_t first = before[0] + before[1] + before[2] + before[3];
-  if constexpr (RT == 64) {
-    for (int j = 0; j < w; ++j) first += count[j];
-  }
-  int64_t base = first;
+  for (int j = 0; j < w; ++j) first += count[j];
 #pragma unroll
-  for (int i = 0; i < NV4; ++i) {
-    int64_t p = base + at[i];
-    if constexpr (RT > 64) {
-      for (int j = 0; j < w; ++j) p += kept[i][j];
-#pragma unroll
-      for (int j = 0; j < kWaves; ++j) base += kept[i][j];
-    }
-    const int e = 4 * (t + i * RT);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (nib[i] >> j & 1u) {
-        if (p < s.capacity) {
-          s.idx[p] = e + j;
-          s.val[p] = (int8_t)(code[i] >> (8 * j));
-        }
-        ++p;
+  for (int i = 0; i < NV; ++i) {
+    int64_t p = first + at[i];
+    unsigned left = m[i];
+    while (left) {
+      const int j = __ffs((int)left) - 1;
+      left &= left - 1u;
+      if (p < s.capacity) {
+        const unsigned word = (j & 8) ? ((j & 4) ? code[i][3] : code[i][2]) : ((j & 4) ? code[i][1] : code[i][0]);
+        s.idx[p] = 1024 * i + 16 * lane + j;
+        s.val[p] = (int8_t)(word >> (8 * (j & 3)));
       }
+      ++p;
     }
   }
-  if (RT == 64) base += mine;
-  if (t == 0 && ok) {
+  if (lane == 0 && ok) {
     s.ptr[v] = (int32_t)first;
     if (v == s.nvec - 1) {
-      s.ptr[s.nvec] = (int32_t)base;
-      if (s.nnz) *s.nnz = base;
+      s.ptr[s.nvec] = (int32_t)(first + mine);
+      if (s.nnz) *s.nnz = first + mine;
     }
   }
 }
@@ -734,26 +739,15 @@ hipError_t launch_reduce_rows(const StripReduce& s, int64_t M, int64_t K, int64_
 
 hipError_t launch_compact_pair(const StripCompact& a, const StripCompact& b, int64_t K, int64_t Kc, hipStream_t st) {
   if (a.nvec + b.nvec == 0) return hipSuccess;
-#define SRQ_COMPACT(RT, NV4)                                                                                                \
+#define SRQ_COMPACT(NV)                                                                                                    \
   do {                                                                                                                      \
-    const int ga = (a.nvec + 256 / RT - 1) / (256 / RT), gb = (b.nvec + 256 / RT - 1) / (256 / RT);                          \
-    hipLaunchKernelGGL((compact_pair_kernel<RT, NV4>), dim3((unsigned)(ga + gb)), dim3(256), 0, st, a, b, ga, (int)K, (int)Kc); \
+    const int ga = (a.nvec + 3) / 4, gb = (b.nvec + 3) / 4;                                                                  \
+    hipLaunchKernelGGL(compact_pair_kernel<NV>, dim3((unsigned)(ga + gb)), dim3(256), 0, st, a, b, ga, (int)K, (int)Kc);     \
   } while (0)
-  // A wave per vector takes a quarter of the workgroups and prefixes, and longer in each.  Up to 2048 vectors (eight
-  // workgroups on each CU, all at once) that loses: 1024^3 6.2 us with a workgroup per vector, 6.8 with a wave;
-  // 2048^3 12.9 and 11.6, 3000^3 23.7 and 21.5.
-  const bool few = a.nvec + b.nvec <= 2048;
-  if (Kc <= 256) SRQ_COMPACT(64, 1);
-  else if (Kc <= 1024) {
-    if (few) SRQ_COMPACT(256, 1);
-    else SRQ_COMPACT(64, 4);
-  } else if (Kc <= 2048) {
-    if (few) SRQ_COMPACT(256, 2);
-    else SRQ_COMPACT(64, 8);
-  } else if (Kc <= 4096) {
-    if (few) SRQ_COMPACT(256, 4);
-    else SRQ_COMPACT(64, 16);
-  } else SRQ_COMPACT(256, 8);
+  if (Kc <= 1024) SRQ_COMPACT(1);
+  else if (Kc <= 2048) SRQ_COMPACT(2);
+  else if (Kc <= 4096) SRQ_COMPACT(4);
+  else SRQ_COMPACT(8);
 #undef SRQ_COMPACT
   return hipGetLastError();
 }
