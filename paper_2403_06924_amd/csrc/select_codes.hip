@@ -21,37 +21,49 @@ typedef unsigned u4a __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ s2 both(int x) { return s2{(short)x, (short)x}; }
 
-// the bits 15 and 31 of word j of eight as bits j and j + 8
+// One bit of each of sixteen elements out of the signs of eight pairs: pushed in from the top two places at a time, the even
+// elements end in the odd bits of the low half, the odd ones in those of the high half.
 struct Bits16 {
   unsigned acc = 0;
-  __device__ __forceinline__ void take(unsigned w, int j) { acc |= (w & 0x80008000u) >> (7 - j); }
-  __device__ __forceinline__ unsigned get() const { return (acc >> 8 & 0xffu) | (acc >> 16 & 0xff00u); }
+  __device__ __forceinline__ void take(unsigned w) { acc = (w & 0x80008000u) | (acc >> 2); }
+  __device__ __forceinline__ unsigned get() const { return (acc >> 1 & 0x5555u) | (acc >> 16 & 0xaaaau); }
 };
 
-// sixteen elements: bits of those above the threshold's key, and of those that have to be looked at
+// |256 code + residual code| - key of elements 2 j and 2 j + 1 of the sixteen in q and r (residual codes plus 128); the
+// differences are at least -32767
+__device__ __forceinline__ s2 above_key(const unsigned (&q)[4], const unsigned (&r)[4], int j, s2 hi, s2 lo) {
+  const s2 w = __builtin_bit_cast(s2, __builtin_amdgcn_perm(q[j >> 1], r[j >> 1], j & 1 ? 0x07030602u : 0x05010400u));
+  return __builtin_elementwise_max(__builtin_elementwise_sub_sat(w, hi), __builtin_elementwise_sub_sat(lo, w));
+}
+
+// sixteen elements: bits of those above the threshold's key, and of those that have to be looked at (that key's own and the
+// topmost one's).  Bound by vector instructions as much as by memory: eleven for two elements (with other pairs, whose bits
+// took two more and the topmost key eight, 62 us instead of 54 for two operands of 8192 x 8192, calls of 2048^3 67.6 instead of 65.8).
 __device__ __forceinline__ void compare16(u4a q, u4a r, int tk, int top, unsigned& above, unsigned& open) {
   const unsigned qw[4] = {q.x, q.y, q.z, q.w};
   const unsigned rw[4] = {r.x ^ 0x80808080u, r.y ^ 0x80808080u, r.z ^ 0x80808080u, r.w ^ 0x80808080u};
-  const s2 hi = both(tk + 128), lo = both(128 - tk), last = both(top - tk), none = both(0), one = both(1);
-  Bits16 gt, ge, tp;
+  const s2 hi = both(tk + 128), lo = both(128 - tk), none = both(0);
+  Bits16 gt, lt;
+  s2 most = both(-32767);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    // elements j and j + 8 as 256 code + residual code + 128
-    const unsigned b = j & 3;
-    const unsigned lo8 = __builtin_amdgcn_perm(qw[j >> 2], rw[j >> 2], 0x0c0c0400u + 0x0101u * b);
-    const unsigned hi8 = __builtin_amdgcn_perm(qw[2 + (j >> 2)], rw[2 + (j >> 2)], 0x04000c0cu + 0x01010000u * b);
-    const s2 w = __builtin_bit_cast(s2, lo8 | hi8);
-    // |256 code + residual code| - tk
-    const s2 d = __builtin_elementwise_max(__builtin_elementwise_sub_sat(w, hi), __builtin_elementwise_sub_sat(lo, w));
-    gt.take(__builtin_bit_cast(unsigned, (s2)(none - d)), j);
-    ge.take(~__builtin_bit_cast(unsigned, d), j);
-    // d == last: (e - 1) & ~e has the sign bit of e == 0 (and of e = 0x8000 never: d - last >= -32767)
-    const s2 e = d ^ last;
-    tp.take(__builtin_bit_cast(unsigned, (s2)(e - one)) & ~__builtin_bit_cast(unsigned, e), j);
+    const s2 d = above_key(qw, rw, j, hi, lo);
+    gt.take(__builtin_bit_cast(unsigned, (s2)(none - d)));
+    lt.take(__builtin_bit_cast(unsigned, d));
+    most = __builtin_elementwise_max(most, d);
   }
-  const unsigned g = gt.get();
-  above = g;
-  open = (ge.get() & ~g) | tp.get();
+  above = gt.get();
+  open = ~lt.get() & ~above & 0xffffu;
+  if (most.x == top - tk || most.y == top - tk) {      // (none is above the topmost key)
+    const s2 last = both(top - tk), one = both(1);
+    Bits16 at;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const s2 e = above_key(qw, rw, j, hi, lo) ^ last;
+      at.take(__builtin_bit_cast(unsigned, (s2)(e - one)) & ~__builtin_bit_cast(unsigned, e));   // (the sign of e == 0)
+    }
+    open |= at.get();
+  }
 }
 
 __device__ __forceinline__ bool ordinary(float x) { return x > 0.f && x < INFINITY; }
