@@ -1010,6 +1010,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // (term 2 is formed transposed: its sparse vectors are columns of C)
     const Sparse24Operand op24a = {p.a24v1, p.a24v2, p.a24n1, p.a24n2, p.a24f, p.RB_int, Kc, p.s_a, p.s_rb};
     const Sparse24Operand op24b = {p.b24v1, p.b24v2, p.b24n1, p.b24n2, p.b24f, p.RA_int, Kc, p.s_ra, p.s_b};
+    bool pack_late = false;
+    CompactTail tail;
     {
     StageTimer tm(h, st, SRQ_STAGE_SELECT);
     // line 7: GetAvgVec, and the thresholds of Eq. avgQuan
@@ -1031,13 +1033,27 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // 2048^3 74.8 / 71.1, 4096^2 x 2048 195 / 192, 3000^3 239 / 229)
     const bool in_strips = strips && (K <= 1024 || (term_a && !codes_a) || (term_b && !codes_b));
     const bool mask_in_strips_a = in_strips && term_a && !count_a, mask_in_strips_b = in_strips && term_b && !count_b;
+    // (few vectors, both executions known: the compaction adds the counts up itself)
+    const bool compact_pair = K <= kStripsMaxK && strategy == SRQ_STRATEGY_CSR_MFMA && !sync_mode && !always_dense && strips_compact_ok(M, N);
+    const StripCompact pack_a = {term_a ? (int)M : 0, p.mask_a, p.tot_a, p.A_int, p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.Ad, p.nnz + 0};
+    const StripCompact pack_b = {term_b ? (int)N : 0, p.mask_b, p.tot_b, p.B_int, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.Bd, p.nnz + 1};
+    // Compaction behind the tiles of the corrections, in their launch: the selection writes what these read (from the codes, or
+    // in FP32 up to K = 1024).  The compressed arrays have to hold any selection: nothing has counted the kept entries by then.
+    if (strips && (K <= 1024 || !in_strips) && compact_pair && term_a && term_b && !dbg && !every_stage && p.cap_a >= M * K && p.cap_b >= N * K &&
+        gemm_tile64_tail_ok(M, N, Kc)) {
+      GemmEpilogue et = ep;
+      et.mode = kGemmAccum; et.row_part = et.col_part = nullptr; et.D_F_copy = nullptr;
+      et.s_row = p.s_a; et.s_col = p.s_rb;
+      et.final_scale = scale_needed;
+      pack_late = gemm_tile64_ok(M, N, Kc, p.Ad, Kc, p.RB_int, Kc, et) && gemm_tile64_ok(M, N, Kc, p.RA_int, Kc, p.Bd, Kc, et);
+    }
     if (in_strips || (strips_ok(M, N, K) && !strips)) {
       // (the means alone where the passes of the strips are not taken: the order of the additions depends on the shape,
       // not on what is expected of the executions)
       const StripSelect sa = {A, lda, p.row_part, parts_n, (double)N, theta_a, p.drow, p.t_a, mask_in_strips_a ? p.mask_a : nullptr,
-                             mask_in_strips_a || count_a ? p.tot_a : nullptr};
+                             mask_in_strips_a || count_a ? p.tot_a : nullptr, p.A_int, pack_late ? p.Ad : nullptr, (int)Kc};
       const StripSelect sb = {B, ldb, p.col_part, parts_m, (double)M, theta_b, p.dcol, p.t_b, mask_in_strips_b ? p.mask_b : nullptr,
-                             mask_in_strips_b || count_b ? p.tot_b : nullptr};
+                             mask_in_strips_b || count_b ? p.tot_b : nullptr, p.B_int, pack_late ? p.Bd : nullptr, (int)Kc};
       SRQ_HIP(h, launch_select_pair(sa, sb, M, N, K, st));
     } else if (!strips) {
       SRQ_HIP(h, launch_reduce_means_pair(p.row_part, parts_n, M, N, theta_a, p.drow, p.t_a, p.col_part, parts_m, N, M,
@@ -1045,9 +1061,9 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     }
     if (!in_strips && (strips || codes_a || codes_b)) {
       const CodesSelect ca = {strips ? p.row_part : nullptr, parts_n, (double)N, theta_a, p.drow, p.t_a, A, lda, 1, p.A_int, p.RA_int,
-                              p.s_a, p.lam_a, p.lam_ra, codes_a ? p.mask_a : nullptr, p.tot_a, strips || codes_a ? M : 0};
+                              p.s_a, p.lam_a, p.lam_ra, codes_a ? p.mask_a : nullptr, p.tot_a, strips || codes_a ? M : 0, pack_late ? p.Ad : nullptr};
       const CodesSelect cb = {strips ? p.col_part : nullptr, parts_m, (double)M, theta_b, p.dcol, p.t_b, B, 1, ldb, p.B_int, p.RB_int,
-                              p.s_b, p.lam_b, p.lam_rb, codes_b ? p.mask_b : nullptr, p.tot_b, strips || codes_b ? N : 0};
+                              p.s_b, p.lam_b, p.lam_rb, codes_b ? p.mask_b : nullptr, p.tot_b, strips || codes_b ? N : 0, pack_late ? p.Bd : nullptr};
       SRQ_HIP(h, launch_select_codes(ca, cb, K, Kc, qmax, trunc, st));
     }
     im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
@@ -1077,12 +1093,11 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         (int64_t)ceil((K > 8192 ? kAutoMfmaDensityBLongK : kAutoMfmaDensityB) * (double)N * (double)K);
     const ScanDecision dec = {p.paths, const_cast<int32_t*>(seen_paths(h)), min_mfma_a, min_mfma_b, stats_dev,
                               term_a ? p.cap_a : kNoCap, term_b ? p.cap_b : kNoCap};
-    // (few vectors, both executions known: the compaction adds the counts up itself)
-    const bool compact_pair = K <= kStripsMaxK && strategy == SRQ_STRATEGY_CSR_MFMA && !sync_mode && !always_dense && strips_compact_ok(M, N);
-    if (compact_pair) {
-      const StripCompact ca = {term_a ? (int)M : 0, p.mask_a, p.tot_a, p.A_int, p.a_ptr, p.a_idx, p.a_val, p.cap_a, p.Ad, p.nnz + 0};
-      const StripCompact cb = {term_b ? (int)N : 0, p.mask_b, p.tot_b, p.B_int, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.Bd, p.nnz + 1};
-      SRQ_HIP(h, launch_compact_pair(ca, cb, K, Kc, st));
+    if (pack_late) {
+      tail = {pack_a, pack_b, 0, (int)K, 0};
+      tail.a.dense = tail.b.dense = nullptr;
+    } else if (compact_pair) {
+      SRQ_HIP(h, launch_compact_pair(pack_a, pack_b, K, Kc, st));
     } else {
       SRQ_HIP(h, launch_scan_pair(term_a ? p.tot_a : nullptr, M, p.a_ptr, p.nnz + 0,
                                   term_b ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st, auto_dev ? &dec : nullptr));
@@ -1294,7 +1309,14 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                       !dbg && gemm_pair_ok(M, N, Kc, t1a, Kc, p.RB_int, Kc, sec12, e1);
     // both terms in 2:4 form: one launch as well, on the sparse matrix cores
     const bool pair24 = path_a == kPath24 && path_b == kPath24;
-    if (pair) {
+    if (pack_late) {
+      StageTimer tm(h, st, SRQ_STAGE_TERM1);
+      GemmEpilogue e12 = e1;
+      e12.final_scale = scale_needed;
+      e12.guard_nnz = nullptr;
+      const DirectProducts pr = {{{p.Ad, p.RB_int, p.s_a, p.s_rb}, {p.RA_int, p.Bd, p.s_ra, p.s_b}}, 2};
+      SRQ_HIP(h, launch_gemm_i8_tile64_tail(M, N, Kc, Kc, pr, e12, tail, st));
+    } else if (pair) {
       StageTimer tm(h, st, SRQ_STAGE_TERM1);
       GemmEpilogue e12 = e1;
       e12.final_scale = scale_needed;
@@ -1339,7 +1361,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     e2.s_row = p.s_ra; e2.s_col = p.s_b;
     e2.D_int = dbg ? dbg->DR2_int : nullptr;
     e2.final_scale = scale_needed;
-    if (pair || pair24) {
+    if (pack_late || pair || pair24) {
       // (term 2 went with term 1)
     } else if (path_b == 1) {
       StageTimer tm(h, st, SRQ_STAGE_TERM2);

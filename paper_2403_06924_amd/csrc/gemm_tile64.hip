@@ -12,7 +12,8 @@
 //  * few tiles (at most one per compute unit): eight stages, so that the round trips of a long K
 //    overlap seven deep;
 //  * more: four or three stages, two or three workgroups per compute unit, whose loads, products and
-//    accesses to C overlap each other's.
+//    accesses to C overlap each other's;
+//  * corrections whose launch also compacts the operands (CompactTail): four or three, so that compacting workgroups fit beside.
 //
 // Both corrections go through one launch (DirectProducts) as one stream of K-tiles, each product with
 // accumulators of its own: they are added to C in registers, in the order of Algorithm 1, and C is read and
@@ -22,6 +23,7 @@
 // touch sixteen rows and the vector-memory path takes 64 clocks for it instead of 16.  8192 x 8192 x
 // 256: 262 us.)
 #include "srq_internal.h"
+#include "compact.h"
 #include "gemm_tiles.h"
 #include "gemm_tile64.h"
 
@@ -33,14 +35,26 @@ constexpr int kOperand = BT * BK;                    // 8 KiB
 constexpr int kStage = 2 * kOperand;                 // A tile then B tile
 constexpr int kLoads = 4;                            // per wave and K-tile: 2 for A, 2 for B
 
-template <int NP, int NST, bool SUMS>
+struct NoTail {};
+
+template <int NP, int NST, bool SUMS, class Tail, int NV>   // NV: pieces of 1024 elements that the tail compacts
 __global__ __launch_bounds__(256, NST >= 8 ? 1 : 12 / NST) void gemm_i8_tile64_kernel(int64_t M, int64_t N, int K, int64_t lda,
                                                                                     int64_t ldb, int tiles_m, int tiles_n,
-                                                                                    DirectProducts pr, GemmEpilogue ep) {
+                                                                                    DirectProducts pr, GemmEpilogue ep, Tail more) {
   static_assert(!SUMS || NP == 1, "");
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   __shared__ double rowx[SUMS ? 2 * BT : 1], colx[SUMS ? 2 * BT : 1];
   if (guard_tripped(ep)) return;                     // the whole grid leaves together
+  if constexpr (std::is_same_v<Tail, CompactTail>) {
+    if ((int)blockIdx.x >= more.tiles) {
+      __shared__ int64_t before[4];
+      __shared__ int count[4];
+      const int group = (int)blockIdx.x - more.tiles;
+      const bool second = group >= more.groups_a;
+      compact_four<NV>(second ? more.b : more.a, second ? group - more.groups_a : group, more.K, K, before, count);
+      return;
+    }
+  }
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) int8_t*)lds);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
   const int quad = lane >> 4, rl = lane & 15;
@@ -173,21 +187,52 @@ hipError_t launch(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, con
   // stages: as many as the stream has K-tiles, at most 8 where a compute unit has one tile, 4 where it has
   // two, else 3
   const int cap = tm * tn <= 256 ? 8 : tm * tn <= 512 ? 4 : 3;
-  void (*kern)(int64_t, int64_t, int, int64_t, int64_t, int, int, DirectProducts, GemmEpilogue);
+  void (*kern)(int64_t, int64_t, int, int64_t, int64_t, int, int, DirectProducts, GemmEpilogue, NoTail);
   int nst;
-  if (cap == 8 && ktiles > 4) { kern = gemm_i8_tile64_kernel<NP, 8, SUMS>; nst = 8; }
-  else if (cap >= 4 && ktiles > 3) { kern = gemm_i8_tile64_kernel<NP, 4, SUMS>; nst = 4; }
-  else { kern = gemm_i8_tile64_kernel<NP, 3, SUMS>; nst = 3; }
+  if (cap == 8 && ktiles > 4) { kern = gemm_i8_tile64_kernel<NP, 8, SUMS, NoTail, 0>; nst = 8; }
+  else if (cap >= 4 && ktiles > 3) { kern = gemm_i8_tile64_kernel<NP, 4, SUMS, NoTail, 0>; nst = 4; }
+  else { kern = gemm_i8_tile64_kernel<NP, 3, SUMS, NoTail, 0>; nst = 3; }
   const int bytes = nst * kStage;
   if (bytes > 48 * 1024) {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), bytes);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(256), bytes, st, M, N, (int)K, lda, ldb, (int)tm, (int)tn, pr, ep);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(256), bytes, st, M, N, (int)K, lda, ldb, (int)tm, (int)tn, pr, ep, NoTail{});
   return hipGetLastError();
 }
 
 }  // namespace
+
+// A compute unit holds a tile of C (or two) and compacting workgroups beside it, which take the place of a launch of their own
+// between the selection and the corrections: 64 KiB of LDS for each (with 80 KiB and 48 bytes two do not fit, and the compaction
+// begins where the tiles end: 1024^3 35 us a call, as with 128 KiB), 48 KiB where there is more than one tile for a compute unit.
+// Calls at 5 % kept, us, separate launches / this: 300 x 400 x 1000 31.4 / 27.9, 512^3 26.0 / 22.4, 700 x 900 x 800 35.2 / 31.4, 1024^3
+// 34.8 / 30.8, 2000 x 400 x 300 28.3 / 25.5, 1400^2 x 1000 41.9 / 38.2, 1500^2 x 1200 51.3 / 46.9, 1000^2 x 3000 59.0 / 53.4, 500 x 600 x
+// 4000 62.4 / 57.0, 640^2 x 5000 76.3 / 69.2, 300^2 x 8000 92.8 / 85.1.  Compacted by the workgroups of the tiles after their stores 1024^3 takes 34.7, 512^3 28.7.  Larger
+// tiles leave no LDS for a second workgroup.
+bool gemm_tile64_tail_ok(int64_t M, int64_t N, int64_t K) { return K <= kStripsMaxK && ((M + BT - 1) / BT) * ((N + BT - 1) / BT) <= 640; }
+
+hipError_t launch_gemm_i8_tile64_tail(int64_t M, int64_t N, int64_t K, int64_t ld, const DirectProducts& pr, const GemmEpilogue& ep,
+                                      const CompactTail& with, hipStream_t st) {
+  const int64_t tm = (M + BT - 1) / BT, tn = (N + BT - 1) / BT;
+  CompactTail tail = with;
+  tail.tiles = (int)(tm * tn);
+  tail.groups_a = (tail.a.nvec + 3) / 4;
+  const int nst = tail.tiles <= 256 ? 4 : 3;
+  void (*kern)(int64_t, int64_t, int, int64_t, int64_t, int, int, DirectProducts, GemmEpilogue, CompactTail);
+#define SRQ_TAIL(NV) kern = nst == 4 ? gemm_i8_tile64_kernel<2, 4, false, CompactTail, NV> : gemm_i8_tile64_kernel<2, 3, false, CompactTail, NV>
+  if (K <= 1024) SRQ_TAIL(1);
+  else if (K <= 2048) SRQ_TAIL(2);
+  else if (K <= 4096) SRQ_TAIL(4);
+  else SRQ_TAIL(8);
+#undef SRQ_TAIL
+  const int bytes = nst * kStage;
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tail.tiles + tail.groups_a + (tail.b.nvec + 3) / 4)), dim3(256), bytes, st, M, N, (int)K, ld, ld,
+                     (int)tm, (int)tn, pr, ep, tail);
+  return hipGetLastError();
+}
 
 hipError_t launch_gemm_i8_tile64(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
                                  const GemmEpilogue& ep, hipStream_t st) {

@@ -11,6 +11,7 @@
 // What bounds it: 2 bytes per element (4.8 TB/s on two operands of 8192 x 8192).  Both operands, us, from FP32 / from codes:
 // 8192 x 8192 each 46 + (68 with the residual codes of B) / 55; 4096 x 4096 and 4096 x 14336 12 + 50 / 35 with a wave per
 // vector (55 with a workgroup for each, which has too few bytes on their way).
+#include "compact.h"
 #include "stream.h"
 
 namespace srq {
@@ -130,16 +131,24 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
     return m;
   };
   int total = 0;
-  auto put = [&](int64_t e, unsigned m) {
-    if (exists && e < words * 64) out[e >> 4] = (uint16_t)m;
+  auto put = [&](int64_t e, unsigned m, u4a code) {
+    if (exists && e < words * 64) {
+      out[e >> 4] = (uint16_t)m;
+      if (o.D) {
+        u4a d;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = code[j] & bytes_of(m >> (4 * j) & 15u);
+        *reinterpret_cast<u4a*>(o.D + v * ld + e) = d;
+      }
+    }
     total += __popc(m);
   };
   const bool none = !(t < INFINITY) || (s == 0.f && lam == 0.f && t >= 0.f);   // (nothing is above NaN, infinity or the maximum of a zero vector)
   if (none) {
-    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, 0u);
+    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, 0u, u4a{0, 0, 0, 0});
   } else if (!(ordinary(lam) && ordinary(s) && rlam < INFINITY && t >= 0.f)) {
 #pragma unroll 1
-    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, look_all(e) & present(e));
+    for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, look_all(e) & present(e), *reinterpret_cast<const u4a*>(q + e));
   } else {
     const float zc = biased_code(t, lam, qmax, TRUNC), tc = code_value(zc);
     const int tk = (int)tc * 256 + (int)code_value(biased_code(t - tc * s, rlam, qmax, TRUNC));
@@ -162,7 +171,7 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
         open &= t1;
       }
       if (open) m |= look(e, open);
-      put(e, m);
+      put(e, m, qv[i]);
     }
   }
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);

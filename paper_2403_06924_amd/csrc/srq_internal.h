@@ -238,6 +238,7 @@ struct CodesSelect {
   uint64_t* mask;              // null: the mean and the threshold only
   int32_t* counts;
   int64_t nvec;                // 0: no such operand
+  int8_t* D;                   // the kept codes, zeros elsewhere, laid out as Q (zeros past the end are there); null: not wanted
 };
 // (veclen at most 32768)
 bool select_codes_ok(int qmax, float theta);
@@ -315,6 +316,9 @@ struct StripSelect {
   float *mean, *thresh;
   uint64_t* mask;              // null: the mean and the threshold only, and with counts a zero there if no entry is above
   int32_t* counts;             // the threshold (of zero, unless it is no number)
+  const int8_t* Q;             // with D (K <= 1024): codes, rows of ldq bytes (a multiple of 128) with zeros past K
+  int8_t* D;                   // zero-filled codes, the same layout; null: not wanted
+  int ldq;
 };
 struct StripCompact {
   int nvec;
@@ -426,6 +430,15 @@ bool gemm_tile64_ok(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t l
                     const GemmEpilogue& ep);
 hipError_t launch_gemm_i8_tile64(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, const DirectProducts& pr,
                                  const GemmEpilogue& ep, hipStream_t st);
+// The pair of corrections with the compaction of both operands in the same launch, behind the tiles (its operands are
+// the zero-filled codes, which the selection has written).  True where that is the better way, for a pair that goes to this kernel.
+struct CompactTail {
+  StripCompact a, b;
+  int groups_a, K, tiles;      // groups of four vectors of a; elements of a vector; tiles of C (the first and the last: set by the launch)
+};
+bool gemm_tile64_tail_ok(int64_t M, int64_t N, int64_t K);
+hipError_t launch_gemm_i8_tile64_tail(int64_t M, int64_t N, int64_t K, int64_t ld, const DirectProducts& pr, const GemmEpilogue& ep,
+                                      const CompactTail& tail, hipStream_t st);
 // at most 32 rows, 64 of a narrower product, and no sums (gemm_skinny.hip)
 hipError_t launch_gemm_i8_skinny(int64_t M, int64_t N, int64_t K, const int8_t* Qa, int64_t lda, const int8_t* Qb,
                                  int64_t ldb, const GemmEpilogue& ep, hipStream_t st);

@@ -23,6 +23,7 @@
 // 10000 x 1024 x 2048 234 / 215, 4000 x 100 x 2000 70.6 / 62.0, 2048^2 x 512 46.6 / 42.9, 1024^3 35.3 / 35.1.
 // Kernel times in a call, us, as ten launches and as these three: 1024^3 8.8 + 4.6 + 6.0 now; 2048^3 quantize 21.7 and
 // 13.3, select 20.4 and 9.8, scan and compaction 20.2 and 11.6.
+#include "compact.h"
 #include "stream.h"
 
 namespace srq {
@@ -346,6 +347,15 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
   float4 x[NV4];
   int n[NV4];
   if (s.mask) load_row<RT, NV4>(x, n, s.X + row * s.ldx, K, tid);   // (on their way while the threshold is formed)
+  constexpr bool kDense = RT == 64 && NV4 <= 4;        // K <= 1024
+  unsigned code[kDense ? NV4 : 1];
+  if (kDense && s.D) {
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) {
+      const int e = 4 * (tid + i * RT);
+      code[kDense ? i : 0] = *reinterpret_cast<const unsigned*>(s.Q + row * s.ldq + (e < s.ldq ? e : 0));
+    }
+  }
   const double sum = sum_of(s, row, rows);
   float t;
   mean_of(s, row, sum, tid == 0, t);
@@ -359,6 +369,7 @@ __device__ __forceinline__ void select_row(const StripSelect& s, int64_t row, in
     nib &= (1u << n[i]) - 1u;
     total += __popc(nib);
     store_nibble(s.mask + row * words, words, c4, nib);
+    if (kDense && s.D && 4 * c4 < s.ldq) *reinterpret_cast<unsigned*>(s.D + row * s.ldq + 4 * c4) = code[kDense ? i : 0] & bytes_of(nib);
   }
   for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
   if constexpr (RT > 64) {
@@ -417,6 +428,16 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
   const int ncol = col0 + 4 <= cols ? 4 : col0 < cols ? (int)(cols - col0) : 0;
   float4 v[RPT];
   if (s.mask) load_patch<TH, CG, RPT>(v, s.X, s.ldx, strip, row0, col0, cols, K);
+  constexpr int kDense = !kWaveSums && RPT <= 8 ? RPT / 4 : 0;   // words of codes per column, K <= 1024
+  unsigned code[4][kDense ? kDense : 1];
+  if (kDense && s.D) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const unsigned* src = reinterpret_cast<const unsigned*>(s.Q + (col0 + c < cols ? col0 + c : cols - 1) * s.ldq + (row0 < s.ldq ? row0 : 0));
+#pragma unroll
+      for (int i = 0; i < kDense; ++i) code[c][i] = src[i];
+    }
+  }
   if constexpr (kWaveSums) {
     for (int c = w; c < BC; c += TH / 64) {
       const int64_t pc = (int64_t)strip * BC + c;
@@ -454,6 +475,15 @@ __device__ __forceinline__ void select_strip(const StripSelect& s, int strip, in
     bits[1] |= ok && a.y > t[1] ? 1u << i : 0u;
     bits[2] |= ok && a.z > t[2] ? 1u << i : 0u;
     bits[3] |= ok && a.w > t[3] ? 1u << i : 0u;
+  }
+  if (kDense && s.D && row0 < s.ldq) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (c >= ncol) break;
+      unsigned* dst = reinterpret_cast<unsigned*>(s.D + (col0 + c) * s.ldq + row0);
+#pragma unroll
+      for (int i = 0; i < kDense; ++i) dst[i] = code[c][i] & bytes_of(bits[c] >> (4 * i) & 15u);
+    }
   }
   store_bits<TH, CG, RPT>(s.mask, s.counts, strip, cols, K, col0, ncol, bits, ism);
 }
@@ -566,89 +596,12 @@ __global__ __launch_bounds__(TH) void reduce_cols_kernel(StripReduce s, int64_t 
 }
 
 // ---- compaction ------------------------------------------------------------------------------------
-// A vector by a wave, sixteen elements per lane and piece: the place of a lane's first kept entry is the number of entries of
-// earlier vectors, pieces and lanes (the last from five ballots of its own count, 0..16).  Codes and zero-filled copy have rows
-// of Kc bytes (a multiple of 16) with zeros past K.  One 16-byte load and store per 1024 elements, and as many stores of entries
-// as the lane with most of them has: with four elements per lane, us, 2999 x 4097 x 3001 26 / 16, calls 226 / 216, 2048^3 70.6 / 67.5,
-// 2000 x 1500 x 6000 161 / 154, reduction of 2000 x 15000 124 / 112.
-template <int NV>                                      // pieces of 1024 elements
+template <int NV>                                      // see compact.h
 __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int groups_a, int K, int Kc) {
   __shared__ int64_t before[4];
   __shared__ int count[4];
-  typedef unsigned u4a __attribute__((ext_vector_type(4)));
-  typedef int i4a __attribute__((ext_vector_type(4)));
   const bool second = (int)blockIdx.x >= groups_a;
-  const StripCompact& s = second ? b : a;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int v0 = ((int)blockIdx.x - (second ? groups_a : 0)) * 4, v = v0 + w;
-  const bool ok = v < s.nvec;
-  const int words = (K + 63) / 64, last = 4 * words - 1;
-  const uint16_t* mv = reinterpret_cast<const uint16_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
-  const int8_t* qv = s.Q + (int64_t)(ok ? v : 0) * Kc;
-  u4a code[NV];
-  unsigned m[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {                       // (without branches: what is not wanted is read where something is)
-    const int e = 1024 * i + 16 * lane;
-    m[i] = mv[e >> 4 < last ? e >> 4 : last];
-    code[i] = *reinterpret_cast<const u4a*>(qv + (e < Kc ? e : 0));
-  }
-  // kept entries of the vectors before the workgroup's (v0 is a multiple of four)
-  int64_t sum = 0;
-  for (int i = 4 * tid; i < v0; i += 1024) {
-    const i4a c = *reinterpret_cast<const i4a*>(s.counts + i);
-    sum += (int64_t)c.x + c.y + c.z + c.w;
-  }
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) before[w] = sum;
-  const uint64_t lower = (1ull << lane) - 1ull;
-  int at[NV], mine = 0;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int e = 1024 * i + 16 * lane;
-    if (!ok || e >= K) m[i] = 0;                       // (bits past K are zero)
-    if (s.dense && ok && e < Kc) {
-      u4a o;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const unsigned nib = m[i] >> (4 * j);
-        o[j] = code[i][j] & (((nib & 1u) ? 0xffu : 0u) | ((nib & 2u) ? 0xff00u : 0u) | ((nib & 4u) ? 0xff0000u : 0u) |
-                             ((nib & 8u) ? 0xff000000u : 0u));
-      }
-      *reinterpret_cast<u4a*>(s.dense + (int64_t)v * Kc + e) = o;
-    }
-    const int cnt = __popc(m[i]);
-    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4), b3 = __ballot(cnt & 8), b4 = __ballot(cnt & 16);
-    at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower) + 8 * __popcll(b3 & lower) +
-            16 * __popcll(b4 & lower);
-    mine += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2) + 8 * __popcll(b3) + 16 * __popcll(b4);
-  }
-  if (lane == 0) count[w] = mine;
-  __syncthreads();
-  int64_t first = before[0] + before[1] + before[2] + before[3];
-  for (int j = 0; j < w; ++j) first += count[j];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    int64_t p = first + at[i];
-    unsigned left = m[i];
-    while (left) {
-      const int j = __ffs((int)left) - 1;
-      left &= left - 1u;
-      if (p < s.capacity) {
-        const unsigned word = (j & 8) ? ((j & 4) ? code[i][3] : code[i][2]) : ((j & 4) ? code[i][1] : code[i][0]);
-        s.idx[p] = 1024 * i + 16 * lane + j;
-        s.val[p] = (int8_t)(word >> (8 * (j & 3)));
-      }
-      ++p;
-    }
-  }
-  if (lane == 0 && ok) {
-    s.ptr[v] = (int32_t)first;
-    if (v == s.nvec - 1) {
-      s.ptr[s.nvec] = (int32_t)(first + mine);
-      if (s.nnz) *s.nnz = first + mine;
-    }
-  }
+  compact_four<NV>(second ? b : a, (int)blockIdx.x - (second ? groups_a : 0), K, Kc, before, count);
 }
 
 // a strip of B is 4 * CG columns wide

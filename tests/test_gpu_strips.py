@@ -343,3 +343,33 @@ def test_product_in_place_of_an_operand(srq, b, n):
             srq.compensated_gemm(A, B, inf, out=out)
             torch.cuda.synchronize()
             assert torch.equal(out, ref), (M, N, place)
+
+
+# (M, N, K): one tile and one over 256 of them, more than 512; one, two, four and eight pieces of a vector; vectors that are no
+# whole group of four, K no multiple of 16; both selections (FP32 up to 1024)
+@pytest.mark.parametrize("shape", [(65, 70, 260), (300, 401, 1000), (1024, 1024, 1024), (1029, 1020, 515), (1500, 1501, 700), (2100, 63, 257),
+                                   (333, 270, 1025), (513, 515, 2049), (90, 1111, 4100)])
+@pytest.mark.parametrize("alpha,beta", [(1.0, 0.0), (-0.5, 0.25)])
+def test_compaction_behind_the_tiles(srq, b, shape, alpha, beta):
+    """The corrections that compact their operands in the same launch against separate launches (a call with debug
+    outputs): the same bits in C, CSR / CSC and statistics, also where a vector keeps nothing or everything."""
+    M, N, K = shape
+    rng = np.random.default_rng(sum(shape))
+    A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
+    A[2] = 0
+    A[5] *= 10
+    A[6, 3] = np.nan
+    B[:, -1] *= 10
+    B[::2, 1] = 2.0 ** -140
+    C_in = dev(rng.standard_normal((M, N)).astype(F32)) if beta else None
+    theta, got = 2.0 / K ** 0.5, []
+    for debug in (False, True):
+        stats = b.stats_tensor()
+        C, _, _ = srq.compensated_gemm(dev(A), dev(B), theta, theta, strategy=b.STRATEGY_CSR_MFMA, alpha=alpha, beta=beta, C_in=C_in,
+                                       stats=stats, debug=debug)
+        torch.cuda.synchronize()
+        im = srq.intermediates(M, N, K)
+        got.append([host(C)] + [host(im[s + n]).copy() for s in "ab" for n in ("_ptr", "_idx", "_val")] + [b.read_stats(stats)])
+    for x, y in zip(got[0][:-1], got[1][:-1]):
+        assert np.array_equal(x, y, equal_nan=x.dtype.kind == "f")
+    assert got[0][-1] == got[1][-1] and got[0][-1]["nnz_a"] == len(got[0][2]) > 0 and got[0][-1]["nnz_b"] == len(got[0][5]) > 0
