@@ -868,6 +868,13 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   const bool count_a = comp && always_dense && term_a && theta_a == 0.f && (strips || fastA);
   const bool count_b = comp && always_dense && term_b && theta_b == 0.f && (strips || once_b);
   const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b);
+  // Decision, compaction and copies of a large call in one launch, from the sums of counts that a selection from the codes leaves
+  // (they lie where the 2:4 form of A' goes in other calls)
+  const int64_t sums_a = term_a ? (M + 255) / 256 : 0, sums_b = term_b ? (N + 255) / 256 : 0;
+  const bool one_compaction = once_b && fastA && comp && strategy == SRQ_STRATEGY_AUTO && dense_fallback_density > 1.f &&
+                              (!term_a || select_codes_ok(qmax, theta_a)) && (!term_b || codes_b) && K <= kCompactDecideMaxK &&
+                              M < (1 << 24) && N < (1 << 24) && (sums_a + sums_b) * kSumStride <= 32 * Kc;
+  int32_t* const sums = one_compaction ? reinterpret_cast<int32_t*>(p.a24v1) : nullptr;
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
   {
   StageTimer tm(h, st, SRQ_STAGE_QUANTIZE);
@@ -890,7 +897,8 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   // accumulate into start at zero
   const bool tot_b_clear = comp && term_b && !codes_b;
   const ClearList b_clear =
-      once_b && comp ? ClearList{once_words ? once_lines : nullptr, 2 * once_words, nullptr, 0,
+      once_b && comp ? ClearList{once_words ? once_lines : nullptr, 2 * once_words, reinterpret_cast<uint32_t*>(sums),
+                                 sums ? (sums_a + sums_b) * kSumStride : 0,
                                  tot_b_clear ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N}
       : once_b ? ClearList{reinterpret_cast<uint32_t*>(p.s_b), N, reinterpret_cast<uint32_t*>(p.lam_b), N, nullptr, 0}
                : ClearList{p.amax_b, N, comp ? p.ramax_b : nullptr, N, tot_b_clear ? reinterpret_cast<uint32_t*>(p.tot_b) : nullptr, N};
@@ -1061,9 +1069,11 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     }
     if (!in_strips && (strips || codes_a || codes_b)) {
       const CodesSelect ca = {strips ? p.row_part : nullptr, parts_n, (double)N, theta_a, p.drow, p.t_a, A, lda, 1, p.A_int, p.RA_int,
-                              p.s_a, p.lam_a, p.lam_ra, codes_a ? p.mask_a : nullptr, p.tot_a, strips || codes_a ? M : 0, pack_late ? p.Ad : nullptr};
+                              p.s_a, p.lam_a, p.lam_ra, codes_a ? p.mask_a : nullptr, p.tot_a, strips || codes_a ? M : 0,
+                              pack_late ? p.Ad : nullptr, sums};
       const CodesSelect cb = {strips ? p.col_part : nullptr, parts_m, (double)M, theta_b, p.dcol, p.t_b, B, 1, ldb, p.B_int, p.RB_int,
-                              p.s_b, p.lam_b, p.lam_rb, codes_b ? p.mask_b : nullptr, p.tot_b, strips || codes_b ? N : 0, pack_late ? p.Bd : nullptr};
+                              p.s_b, p.lam_b, p.lam_rb, codes_b ? p.mask_b : nullptr, p.tot_b, strips || codes_b ? N : 0,
+                              pack_late ? p.Bd : nullptr, sums ? sums + sums_a * kSumStride : nullptr};
       SRQ_HIP(h, launch_select_codes(ca, cb, K, Kc, qmax, trunc, st));
     }
     im.drow = p.drow; im.dcol = p.dcol; im.t_a = p.t_a; im.t_b = p.t_b;
@@ -1098,6 +1108,15 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       tail.a.dense = tail.b.dense = nullptr;
     } else if (compact_pair) {
       SRQ_HIP(h, launch_compact_pair(pack_a, pack_b, K, Kc, st));
+    } else if (one_compaction) {
+      // (k-major copies of the residual codes for terms on the vector ALUs, and of those the hint asks for in any case)
+      CompactDecide g;
+      memset(&g, 0, sizeof(g));
+      g.a = pack_a; g.b = pack_b; g.sums = sums; g.dec = dec;
+      g.em_a = {p.RA_int, p.RA_em, term_b ? M : 0, kAlways};
+      g.em_b = {p.RB_int, p.RB_em, term_a ? N : 0, kAlways};
+      g.always_a = h->last_path_b == kPathValu; g.always_b = h->last_path_a == kPathValu;
+      SRQ_HIP(h, launch_compact_decide(g, K, Kc, st));
     } else {
       SRQ_HIP(h, launch_scan_pair(term_a ? p.tot_a : nullptr, M, p.a_ptr, p.nnz + 0,
                                   term_b ? p.tot_b : nullptr, N, p.b_ptr, p.nnz + 1, st, auto_dev ? &dec : nullptr));
@@ -1164,7 +1183,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
                                     p.a24n1, p.a24v2, p.a24n2, p.a24f, st));
         im.a_idx = p.a_idx; im.a_val = p.a_val;
       } else if (path_a != 3) {
-        if (!compact_pair)
+        if (!compact_pair && !one_compaction)
           SRQ_HIP(h, launch_scatter_mask(p.mask_a, M, K, p.A_int, Kc, p.a_ptr, p.a_idx, p.a_val, p.cap_a,
                                          (path_a == kPathMfma || auto_dev) ? p.Ad : nullptr, Kc, known_a, st,
                                          auto_dev ? a_on_mfma : kAlways));
@@ -1177,7 +1196,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       if (path_b == kPath24) {
         SRQ_HIP(h, launch_scatter24(p.mask_b, N, K, Kc, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b, p.b24v1,
                                     p.b24n1, p.b24v2, p.b24n2, p.b24f, st));
-      } else if (!compact_pair) {
+      } else if (!compact_pair && !one_compaction) {
         SRQ_HIP(h, launch_scatter_mask(p.mask_b, N, K, p.B_int, Kc, p.b_ptr, p.b_idx, p.b_val, p.cap_b,
                                        (path_b == kPathMfma || auto_dev) ? p.Bd : nullptr, Kc, known_b, st,
                                        auto_dev ? b_on_mfma : kAlways));
@@ -1197,7 +1216,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       // (k-major copies of K-contiguous codes that are there; of those the hint asks for in any case)
       const bool copy_a = term_b && ra_vm_done && !ra_em_done, copy_b = term_a && rb_vm_done && !rb_em_done;
       const bool hint_a = copy_a && h->last_path_b == kPathValu, hint_b = copy_b && h->last_path_a == kPathValu;
-      if (copy_a || copy_b)
+      if ((copy_a || copy_b) && !one_compaction)
         SRQ_HIP(h, launch_codes_em({p.RA_int, p.RA_em, copy_a ? M : 0, hint_a ? kAlways : b_on_valu},
                                    {p.RB_int, p.RB_em, copy_b ? N : 0, hint_b ? kAlways : a_on_valu}, K, Kc, st));
       auto resid_a = [&](bool vm, RunIf run) -> hipError_t {

@@ -13,79 +13,94 @@ static __device__ __forceinline__ unsigned bytes_of(unsigned nib) { return ((nib
 // as the lane with most of them has: with four elements per lane, us, 2999 x 4097 x 3001 26 / 16, calls 226 / 216, 2048^3 70.6 / 67.5,
 // 2000 x 1500 x 6000 161 / 154, reduction of 2000 x 15000 124 / 112.
 template <int NV>                                      // pieces of 1024 elements
-static __device__ __forceinline__ void compact_four(const StripCompact& s, int group, int K, int Kc, int64_t (&before)[4], int (&count)[4]) {
+struct CompactFour {
   typedef unsigned u4a __attribute__((ext_vector_type(4)));
   typedef int i4a __attribute__((ext_vector_type(4)));
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int v0 = 4 * group, v = v0 + w;
-  const bool ok = v < s.nvec;
-  const int words = (K + 63) / 64, last = 4 * words - 1;
-  const uint16_t* mv = reinterpret_cast<const uint16_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
-  const int8_t* qv = s.Q + (int64_t)(ok ? v : 0) * Kc;
   u4a code[NV];
   unsigned m[NV];
+  int v;
+  bool ok;
+
+  // vectors 4 group .. + 3, one for a wave
+  __device__ __forceinline__ void load(const StripCompact& s, int group, int K, int Kc) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    v = 4 * group + w;
+    ok = v < s.nvec;
+    const int words = (K + 63) / 64, last = 4 * words - 1;
+    const uint16_t* mv = reinterpret_cast<const uint16_t*>(s.mask + (int64_t)(ok ? v : 0) * words);
+    const int8_t* qv = s.Q + (int64_t)(ok ? v : 0) * Kc;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {                       // (without branches: what is not wanted is read where something is)
-    const int e = 1024 * i + 16 * lane;
-    m[i] = mv[e >> 4 < last ? e >> 4 : last];
-    code[i] = *reinterpret_cast<const u4a*>(qv + (e < Kc ? e : 0));
+    for (int i = 0; i < NV; ++i) {                     // (without branches: what is not wanted is read where something is)
+      const int e = 1024 * i + 16 * lane;
+      m[i] = mv[e >> 4 < last ? e >> 4 : last];
+      code[i] = *reinterpret_cast<const u4a*>(qv + (e < Kc ? e : 0));
+    }
   }
-  // kept entries of the vectors before the workgroup's (v0 is a multiple of four)
+  // before: kept entries of the vectors before the workgroup's, in four parts, behind no barrier yet
+  __device__ __forceinline__ void store(const StripCompact& s, int8_t* dense, int K, int Kc, const int64_t (&before)[4], int (&count)[4],
+                                        bool around = false) {   // (zero-filled codes around the caches)
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t lower = (1ull << lane) - 1ull;
+    int at[NV], mine = 0;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = 1024 * i + 16 * lane;
+      if (!ok || e >= K) m[i] = 0;                     // (bits past K are zero)
+      if (dense && ok && e < Kc) {
+        u4a o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = code[i][j] & bytes_of(m[i] >> (4 * j) & 15u);
+        if (around) __builtin_nontemporal_store(o, reinterpret_cast<u4a*>(dense + (int64_t)v * Kc + e));
+        else *reinterpret_cast<u4a*>(dense + (int64_t)v * Kc + e) = o;
+      }
+      const int cnt = __popc(m[i]);
+      const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4), b3 = __ballot(cnt & 8), b4 = __ballot(cnt & 16);
+      at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower) + 8 * __popcll(b3 & lower) +
+              16 * __popcll(b4 & lower);
+      mine += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2) + 8 * __popcll(b3) + 16 * __popcll(b4);
+    }
+    if (lane == 0) count[w] = mine;
+    __syncthreads();
+    int64_t first = before[0] + before[1] + before[2] + before[3];
+    for (int j = 0; j < w; ++j) first += count[j];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      int64_t p = first + at[i];
+      unsigned left = m[i];
+      while (left) {
+        const int j = __ffs((int)left) - 1;
+        left &= left - 1u;
+        if (p < s.capacity) {
+          const unsigned word = (j & 8) ? ((j & 4) ? code[i][3] : code[i][2]) : ((j & 4) ? code[i][1] : code[i][0]);
+          s.idx[p] = 1024 * i + 16 * lane + j;
+          s.val[p] = (int8_t)(word >> (8 * (j & 3)));
+        }
+        ++p;
+      }
+    }
+    if (lane == 0 && ok) {
+      s.ptr[v] = (int32_t)first;
+      if (v == s.nvec - 1) {
+        s.ptr[s.nvec] = (int32_t)(first + mine);
+        if (s.nnz) *s.nnz = first + mine;
+      }
+    }
+  }
+};
+
+template <int NV>
+static __device__ __forceinline__ void compact_four(const StripCompact& s, int group, int K, int Kc, int64_t (&before)[4], int (&count)[4]) {
+  CompactFour<NV> f;
+  f.load(s, group, K, Kc);
+  // kept entries of the vectors before the workgroup's
   int64_t sum = 0;
-  for (int i = 4 * tid; i < v0; i += 1024) {
-    const i4a c = *reinterpret_cast<const i4a*>(s.counts + i);
+  for (int i = 4 * (int)threadIdx.x; i < 4 * group; i += 1024) {
+    const auto c = *reinterpret_cast<const typename CompactFour<NV>::i4a*>(s.counts + i);
     sum += (int64_t)c.x + c.y + c.z + c.w;
   }
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) before[w] = sum;
-  const uint64_t lower = (1ull << lane) - 1ull;
-  int at[NV], mine = 0;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int e = 1024 * i + 16 * lane;
-    if (!ok || e >= K) m[i] = 0;                       // (bits past K are zero)
-    if (s.dense && ok && e < Kc) {
-      u4a o;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const unsigned nib = m[i] >> (4 * j);
-        o[j] = code[i][j] & (((nib & 1u) ? 0xffu : 0u) | ((nib & 2u) ? 0xff00u : 0u) | ((nib & 4u) ? 0xff0000u : 0u) |
-                             ((nib & 8u) ? 0xff000000u : 0u));
-      }
-      *reinterpret_cast<u4a*>(s.dense + (int64_t)v * Kc + e) = o;
-    }
-    const int cnt = __popc(m[i]);
-    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4), b3 = __ballot(cnt & 8), b4 = __ballot(cnt & 16);
-    at[i] = mine + __popcll(b0 & lower) + 2 * __popcll(b1 & lower) + 4 * __popcll(b2 & lower) + 8 * __popcll(b3 & lower) +
-            16 * __popcll(b4 & lower);
-    mine += __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2) + 8 * __popcll(b3) + 16 * __popcll(b4);
-  }
-  if (lane == 0) count[w] = mine;
-  __syncthreads();
-  int64_t first = before[0] + before[1] + before[2] + before[3];
-  for (int j = 0; j < w; ++j) first += count[j];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    int64_t p = first + at[i];
-    unsigned left = m[i];
-    while (left) {
-      const int j = __ffs((int)left) - 1;
-      left &= left - 1u;
-      if (p < s.capacity) {
-        const unsigned word = (j & 8) ? ((j & 4) ? code[i][3] : code[i][2]) : ((j & 4) ? code[i][1] : code[i][0]);
-        s.idx[p] = 1024 * i + 16 * lane + j;
-        s.val[p] = (int8_t)(word >> (8 * (j & 3)));
-      }
-      ++p;
-    }
-  }
-  if (lane == 0 && ok) {
-    s.ptr[v] = (int32_t)first;
-    if (v == s.nvec - 1) {
-      s.ptr[s.nvec] = (int32_t)(first + mine);
-      if (s.nnz) *s.nnz = first + mine;
-    }
-  }
+  if ((threadIdx.x & 63) == 0) before[threadIdx.x >> 6] = sum;
+  f.store(s, s.dense, K, Kc, before, count);
 }
 
 }  // namespace srq

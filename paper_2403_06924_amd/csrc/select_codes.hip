@@ -182,7 +182,10 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
 #pragma unroll
     for (int i = 0; i < TH / 64; ++i) total += sm[sub * (TH / 64) + i];
   }
-  if (tid == 0 && exists) o.counts[v] = total;
+  if (tid == 0 && exists) {
+    o.counts[v] = total;
+    if (o.sums && total) atomicAdd(o.sums + (v >> 8) * kSumStride, total);
+  }
 }
 
 }  // namespace

@@ -223,6 +223,9 @@ inline int64_t cols_once_words(int64_t rows, int64_t cols) {
   return pieces > 1 ? pieces * strips * kColsOnceCols : 0;
 }
 hipError_t launch_cols_once(const ColsOnce& g, int64_t rows, int64_t cols, int qmax, int trunc, bool given, hipStream_t st);
+// Sums of counts (of 256 vectors each) that a selection leaves lie this many words apart: atomics on one line are served one
+// after the other, 5 ns each (next to each other: selection of two operands of 8192 x 8192 129 us, 54 to 56 like this and without sums)
+constexpr int kSumStride = 64;
 // Keep-masks and counts of one or two operands from codes and residual codes (select_codes.hip), with the means of |D_F| and
 // the thresholds or after them
 struct CodesSelect {
@@ -239,6 +242,7 @@ struct CodesSelect {
   int32_t* counts;
   int64_t nvec;                // 0: no such operand
   int8_t* D;                   // the kept codes, zeros elsewhere, laid out as Q (zeros past the end are there); null: not wanted
+  int32_t* sums;               // the counts of every 256 vectors are added up here (kSumStride), on top of what is there; null: not wanted
 };
 // (veclen at most 32768)
 bool select_codes_ok(int qmax, float theta);
@@ -331,6 +335,17 @@ struct StripCompact {
   int8_t* dense;               // null: not wanted
   int64_t* nnz;                // null: not wanted
 };
+// Both operands of a call whose executions are decided on the device (codes_em.hip): K <= 16384, fewer than 2^24 vectors
+constexpr int64_t kCompactDecideMaxK = 16384;
+struct CompactDecide {
+  StripCompact a, b;           // nvec 0: no such term; dense: written where the term goes to the matrix cores
+  const int32_t* sums;         // counts of every 256 vectors of a, then of b (kSumStride)
+  ScanDecision dec;
+  CodesEm em_a, em_b;          // copies for a term on the vector ALUs (em_a: term 2), or in any case; nvec 0: none.  `run` is not read
+  int always_a, always_b;
+  int groups_a, groups_b, around;   // set by the launch
+};
+hipError_t launch_compact_decide(const CompactDecide& g, int64_t K, int64_t Kc, hipStream_t st);
 struct StripReduce {
   const float* X;
   int64_t ldx;

@@ -127,3 +127,45 @@ def test_counts_of_operands_that_are_not_compacted(srq, b, shape):
     assert (host(im["a_ptr"]) == np.concatenate([[0], np.cumsum(counts[0])])).all()
     assert (host(im["b_ptr"]) == np.concatenate([[0], np.cumsum(counts[1])])).all()
     assert st["nnz_a"] == counts[0].sum() and st["nnz_b"] == counts[1].sum() and counts[0][0] > 0
+
+
+# (M, N, K): vectors that are no whole group of four, one and one over a sum's 256; two to sixteen pieces of a vector.  Kept shares on
+# either side of where a term changes its execution.
+@pytest.mark.parametrize("shape", [(2301, 1030, 1700), (257, 2100, 4099), (100, 2001, 4300), (256, 255, 8200), (1030, 70, 16384)])
+@pytest.mark.parametrize("kept", [(0.0005, 0.0003), (0.05, 0.0003), (0.0005, 0.05), (0.05, 0.05), (0.05, None), (None, 0.0003)])
+def test_decision_and_compaction_in_one_launch(srq, b, shape, kept):
+    """SRQ_STRATEGY_AUTO decided on the device (debug outputs keep it from taking the matrix cores outright): compressed operands,
+    statistics and both terms against the definitions and a call with the execution given, bit for bit."""
+    if srq.late:
+        pytest.skip("the default wait is enough")
+    M, N, K = shape
+    rng = np.random.default_rng(sum(shape))
+    A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
+    A[1], B[:, 2], A[3, 5] = 0, 0, np.nan
+    def theta(share):                                         # |x| over the mean of |D_F|, about 0.8 sqrt(K)
+        if share is None:
+            return float("inf")
+        return float(np.quantile(np.abs(B[:, -1 - min(N, 64):-1]), 1 - share)) / (0.8 * K ** 0.5)
+    ta, tb = theta(kept[0]), theta(kept[1])
+    out = []
+    for hint in (1, 2):
+        srq.set_auto_hint(hint, hint)
+        stats = b.stats_tensor()
+        C, _, dbg = srq.compensated_gemm(dev(A), dev(B), ta, tb, stats=stats, debug=True)
+        torch.cuda.synchronize()
+        im, st = srq.intermediates(M, N, K), b.read_stats(stats)
+        for term, V, s, codes in ((0, A, "a", im["A_int"]), (1, B.T, "b", im["B_int"])):
+            if kept[term] is None:
+                assert st["path_" + s] == 0 and st["nnz_" + s] == 0
+                continue
+            with np.errstate(invalid="ignore"):
+                vec, k = np.nonzero(np.abs(V) > host(im["t_" + s])[:, None])
+            assert (host(im[s + "_ptr"]) == np.searchsorted(vec, np.arange(len(V) + 1))).all()
+            assert (host(im[s + "_idx"]) == k).all() and (host(im[s + "_val"]) == host(codes)[vec, k]).all()
+            assert st["nnz_" + s] == len(k) > 0 and st["path_" + s] == (2 if kept[term] > 0.01 else 1)
+        out.append([host(C)] + [host(dbg[x]) for x in ("DR1_int", "DR2_int")])
+    C, _, dbg = srq.compensated_gemm(dev(A), dev(B), ta, tb, strategy=b.STRATEGY_CSR_MFMA, debug=True)
+    torch.cuda.synchronize()
+    ref = [host(C)] + [host(dbg[x]) for x in ("DR1_int", "DR2_int")]
+    for got in out:
+        assert all(np.array_equal(x, y, equal_nan=x.dtype.kind == "f") for x, y in zip(got, ref))
