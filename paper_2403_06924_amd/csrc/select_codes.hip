@@ -77,7 +77,14 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
   const CodesSelect& o = first ? a : b;
   const int tid = threadIdx.x & (TH - 1);
   const int sub = TH >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / TH) : 0;
-  int64_t v = (first ? blockIdx.x : blockIdx.x - groups_a) * VECS + sub;
+  int64_t group = first ? blockIdx.x : blockIdx.x - groups_a;
+  if (o.elem_step != 1) {
+    // 32 neighbouring columns, which share lines of X, on one XCD: what has to be looked at is found in its L2
+    constexpr int64_t kNear = 32 / VECS;
+    const int64_t groups = (o.nvec + VECS - 1) / VECS, q = group >> 3;
+    if (group < groups / (8 * kNear) * (8 * kNear)) group = ((q / kNear) * 8 + (group & 7)) * kNear + q % kNear;
+  }
+  int64_t v = group * VECS + sub;
   const bool exists = v < o.nvec;
   if (!exists) v = o.nvec - 1;                         // (does the last vector's work again and writes nothing)
   const int8_t *const q = o.Q + v * ld, *const r = o.R + v * ld;
@@ -190,8 +197,11 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
 
 }  // namespace
 
-// (With few codes the threshold's bin is wide: 3 bits have 49 keys.  A threshold of zero leaves every zero to be looked at.)
-bool select_codes_ok(int qmax, float theta) { return qmax >= 7 && theta > 0.f; }
+// (With few codes the threshold's bin is wide, and most of it is looked at in FP32 where outliers set the scale: calls, us, the passes
+// over FP32 / from the codes, 4 bits 384 x 5952 x 8576 329 / 422, 5000 x 4000 x 3000 341 / 432, without outliers 336 / 310; 7 bits 315 /
+// 271, 8 bits 320 / 277.  A threshold of zero leaves every zero to be looked at.  What stays slower, 4096^3 with 80 % kept of
+// numbers over twenty binades 425 / 495, is where the threshold is in the lowest of 65000 bins.)
+bool select_codes_ok(int qmax, float theta) { return qmax >= 63 && theta > 0.f; }
 
 hipError_t launch_select_codes(const CodesSelect& a, const CodesSelect& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st) {
   if (a.nvec + b.nvec <= 0 || veclen <= 0) return hipSuccess;

@@ -79,7 +79,7 @@ def operand(rng, kind, nvec, K):
 # put exactly on an entry of some vectors
 @pytest.mark.parametrize("shape", [(300, 1800, 4099), (40, 2100, 8192), (1030, 1029, 8205), (20, 2040, 16384)])
 @pytest.mark.parametrize("kind", ["normal", "outliers", "ties"])
-@pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (4, 0)])
+@pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (7, 0), (4, 0)])
 def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
     if srq.late:
         pytest.skip("nothing is exchanged in the selection")
