@@ -2,6 +2,8 @@
 // corrections gather from, out of the K-contiguous ones: 2 bytes moved per element, where a pass of fused.hip that writes
 // them from the FP32 operand moves 5.
 //
+// Behind them the launch that decides, compacts and copies for large calls.
+//
 // A thread transposes 16 x 16 bytes in registers.  A wave has 8 x 8 of these, so that its loads are 128 contiguous bytes of eight
 // vectors and its stores 128 contiguous bytes of eight k.  Nothing is shared; bound by the 2 bytes per element.
 #include <cstring>

@@ -5,12 +5,13 @@
 //   rows_fused_kernel   operand A (one scale per row): the row is read ONCE into registers;
 //                       amax, lambda, codes, residual, residual amax and residual codes all
 //                       come out of that one read.
-//   cols_pass_kernel    operand B (one scale per column, row-major K x N): three streaming
+//   cols_pass_kernel    operand B (one scale per column, row-major K x N) where cols_once.hip does not take it (a
+//                       matrix-wide scale, more than 32768 rows): three streaming
 //                       passes (amax | codes + max|residual| | residual codes), each thread
 //                       holding a 16-row x 4-column patch so that the transposed (K-contiguous)
 //                       INT8 output is written 16 bytes at a time without going through LDS.
-//   *_mask_kernel       threshold compare of Eq. avgQuan -> one keep-bit per element (the only
-//                       pass that has to re-read FP32 after the first product) + per-vector
+//   *_mask_kernel       threshold compare of Eq. avgQuan in FP32 (what select_codes.hip does not take) -> one
+//                       keep-bit per element + per-vector
 //                       counts.  Inside the whole-path call the residual codes whose layout is
 //                       only needed after the selection come out of this read as well: B's
 //                       third pass is the selection pass (cols_pass_kernel<kColsMaskResid>),

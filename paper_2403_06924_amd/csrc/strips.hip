@@ -6,23 +6,20 @@
 //                        scales and residual codes.  A workgroup has either rows of A in registers or a
 //                        strip of 4 * CG columns of B over all of K (TH / CG pieces of RPT rows).
 //   select_pair_kernel   means of |D_F| from the partial sums, thresholds, keep-masks and counts of both
-//                        operands, cut in the same way (no atomics, nothing to clear).
+//                        operands, cut in the same way (no atomics, nothing to clear); beyond K = 1024 for thresholds and
+//                        codes that select_codes.hip does not take.
 //   quant_cols_kernel, reduce_rows_kernel, reduce_cols_kernel   the staged entry points on one operand
 //   compact_pair_kernel  compaction to CSR / CSC and to zero-filled codes of both operands; every workgroup
-//                        adds up the counts before its vector itself, so that no scan runs in between.
+//                        adds up the counts before its vector itself, so that no scan runs in between (behind the
+//                        tiles of the corrections where they are 64 x 64, gemm_tile64.hip).
 //
 // What bounds them: at these sizes the latency of a launch and of one trip through a workgroup, not
 // bandwidth; hence few elements per thread for short K (RPT 4 or 8) and as many workgroups as there are.
 // A strip reads 64, 32 or 16 bytes of each row of B; strips that share 128-byte lines are given to the same
 // XCD (strip_of), where the line is found in L2 the second time.
-// Up to K = 2048 a wave has a row of A to itself, or a vector of the compaction where there are many: nothing in a row
-// then waits at a barrier, and the workgroups are a quarter to an eighth as many.  So it is up to K = 4096 with 16
-// pieces per lane (a workgroup per row has a compute unit to itself there, because the kernel needs 188 registers, its strips 162:
-// 2048^2 x 2112 quantize 30 / 22, select 25 / 16, calls 105 / 89; 3000^3 229 / 206).  With a workgroup per row and
-// vector / a wave: 2048^3 quantize 17.6 / 13.3 us, select 11.6 / 9.8, compact 12.9 / 11.6, calls 83.4 / 77.2;
-// 10000 x 1024 x 2048 234 / 215, 4000 x 100 x 2000 70.6 / 62.0, 2048^2 x 512 46.6 / 42.9, 1024^3 35.3 / 35.1.
-// Kernel times in a call, us, as ten launches and as these three: 1024^3 8.8 + 4.6 + 6.0 now; 2048^3 quantize 21.7 and
-// 13.3, select 20.4 and 9.8, scan and compaction 20.2 and 11.6.
+// Up to K = 4096 a wave has a row of A to itself: nothing in a row then waits at a barrier, and the workgroups are a quarter to an
+// eighth as many.  With a workgroup per row / a wave: 2048^3 quantize 17.6 / 13.3 us, 2048^2 x 2112 30 / 22.
+// (the kernel for K beyond 2048 needs 188 registers, its strips 162).
 #include "compact.h"
 #include "stream.h"
 
