@@ -867,12 +867,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   const bool always_dense = dense_fallback_density <= 0.f;
   const bool count_a = comp && always_dense && term_a && theta_a == 0.f && (strips || fastA);
   const bool count_b = comp && always_dense && term_b && theta_b == 0.f && (strips || once_b);
-  const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b);
+  const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b, strips);
   // Decision, compaction and copies of a large call in one launch, from the sums of counts that a selection from the codes leaves
   // (they lie where the 2:4 form of A' goes in other calls)
   const int64_t sums_a = term_a ? (M + 255) / 256 : 0, sums_b = term_b ? (N + 255) / 256 : 0;
   const bool one_compaction = once_b && fastA && comp && strategy == SRQ_STRATEGY_AUTO && dense_fallback_density > 1.f &&
-                              (!term_a || select_codes_ok(qmax, theta_a)) && (!term_b || codes_b) && K <= kCompactDecideMaxK &&
+                              (!term_a || select_codes_ok(qmax, theta_a, strips)) && (!term_b || codes_b) && K <= kCompactDecideMaxK &&
                               M < (1 << 24) && N < (1 << 24) && (sums_a + sums_b) * kSumStride <= 32 * Kc;
   int32_t* const sums = one_compaction ? reinterpret_cast<int32_t*>(p.a24v1) : nullptr;
   // lines 1: Quant.  amax per vector -> scale, lambda -> codes (and max |residual| per vector)
@@ -1036,7 +1036,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
       return term_b && dense_fallback_density > 1.f && path_reads_em(expect_b) &&
              rows_mask_resid_em_ok(A, M, K, lda, p.s_a, p.lam_a, p.lam_ra, p.RA_em, M, p.t_a);
     }();
-    const bool codes_a = term_a && ra_vm_done && K <= 32768 && select_codes_ok(qmax, theta_a);
+    const bool codes_a = term_a && ra_vm_done && K <= 32768 && select_codes_ok(qmax, theta_a, strips);
     // (calls, us, in FP32 / from the codes: 1024^3 36.4 / 37.4, 2048^2 x 512 40.6 / 42.2, 4096^2 x 512 115 / 118, but 1500^3 61.6 / 58.8,
     // 2048^3 74.8 / 71.1, 4096^2 x 2048 195 / 192, 3000^3 239 / 229)
     const bool in_strips = strips && (K <= 1024 || (term_a && !codes_a) || (term_b && !codes_b));

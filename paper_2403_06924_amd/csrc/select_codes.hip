@@ -201,9 +201,12 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
 
 // (With few codes the threshold's bin is wide, and most of it is looked at in FP32 where outliers set the scale: calls, us, the passes
 // over FP32 / from the codes, 4 bits 384 x 5952 x 8576 329 / 422, 5000 x 4000 x 3000 341 / 432, without outliers 336 / 310; 7 bits 315 /
-// 271, 8 bits 320 / 277.  A threshold of zero leaves every zero to be looked at.  What stays slower, 4096^3 with 80 % kept of
-// numbers over twenty binades 425 / 495, is where the threshold is in the lowest of 65000 bins.)
-bool select_codes_ok(int qmax, float theta) { return qmax >= 63 && theta > 0.f; }
+// 271, 8 bits 320 / 277.  On the path of strips.hip most of what is looked at is found in the caches, and the compaction may go
+// behind the tiles: with outliers / normal, 4 bits, 96 x 128 x 3371 57.4 / 51.5 and 52.3 / 46.0, 640^2 x 4000 74.2 / 68.8 and 69.1 / 58.4,
+// 2000^3 70.9 / 66.6 and 73.1 / 69.6, 100 x 1900 x 7000 170 / 176 and 126 / 103.  3 bits have 49 keys.  A threshold of zero leaves every
+// zero to be looked at.  What stays slower, 4096^3 with 80 % kept of numbers over twenty binades 425 / 495, is where the threshold
+// is in the lowest of 65000 bins.)
+bool select_codes_ok(int qmax, float theta, bool strips) { return qmax >= (strips ? 7 : 63) && theta > 0.f; }
 
 hipError_t launch_select_codes(const CodesSelect& a, const CodesSelect& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st) {
   if (a.nvec + b.nvec <= 0 || veclen <= 0) return hipSuccess;

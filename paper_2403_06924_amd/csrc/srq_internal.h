@@ -245,7 +245,7 @@ struct CodesSelect {
   int32_t* sums;               // the counts of every 256 vectors are added up here (kSumStride), on top of what is there; null: not wanted
 };
 // (veclen at most 32768)
-bool select_codes_ok(int qmax, float theta);
+bool select_codes_ok(int qmax, float theta, bool strips);   // strips: the call is on the path of strips.hip
 hipError_t launch_select_codes(const CodesSelect& a, const CodesSelect& b, int64_t veclen, int64_t ld, int qmax, int trunc, hipStream_t st);
 // k-major copies of one or two residual code matrices (codes_em.hip): nvec rows of ld bytes (16-byte aligned, ld a multiple of
 // 16) to veclen rows of nvec bytes
