@@ -155,7 +155,9 @@ __global__ __launch_bounds__(256) void select_codes_kernel(CodesSelect a, CodesS
   const bool none = !(t < INFINITY) || (s == 0.f && lam == 0.f && t >= 0.f);   // (nothing is above NaN, infinity or the maximum of a zero vector)
   if (none) {
     for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, 0u, u4a{0, 0, 0, 0});
-  } else if (!(ordinary(lam) && ordinary(s) && rlam < INFINITY && t >= 0.f)) {
+  } else if (!(ordinary(lam) && ordinary(s) && qmax * s < INFINITY && rlam < INFINITY && t >= 0.f)) {
+    // (qmax * s overflows where the scale of a maximum next to FLT_MAX is rounded up: that element's residual is infinite, and
+    // rlam zero as where every residual is)
 #pragma unroll 1
     for (int64_t e = 16 * tid; e < words * 64; e += STEP) put(e, look_all(e) & present(e), *reinterpret_cast<const u4a*>(q + e));
   } else {

@@ -75,6 +75,17 @@ def operand(rng, kind, nvec, K):
     return V
 
 
+def assert_selection(srq, A, B):
+    """The compressed operands of the last call are the entries above its thresholds and their codes."""
+    im = srq.intermediates(A.shape[0], B.shape[1], A.shape[1])
+    for V, t, ptr, idx, val, codes in ((A, im["t_a"], im["a_ptr"], im["a_idx"], im["a_val"], im["A_int"]),
+                                       (B.T, im["t_b"], im["b_ptr"], im["b_idx"], im["b_val"], im["B_int"])):
+        with np.errstate(invalid="ignore"):
+            vec, k = np.nonzero(np.abs(V) > host(t)[:, None])
+        assert (host(ptr) == np.searchsorted(vec, np.arange(len(V) + 1))).all()
+        assert (host(idx)[:len(k)] == k).all() and (host(val)[:len(k)] == host(codes)[vec, k]).all()
+
+
 # (M, N, K): one wave, two and four of them per vector, a last piece that is no whole sixteen; the operands' thresholds
 # put exactly on an entry of some vectors
 @pytest.mark.parametrize("shape", [(300, 1800, 4099), (40, 2100, 8192), (1030, 1029, 8205), (20, 2040, 16384)])
@@ -91,15 +102,35 @@ def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
         srq.compensated_gemm(dev(A), dev(B), theta, theta, bits=bits, rounding=b.ROUND_TRUNC if trunc else b.ROUND_NEAREST_EVEN,
                              strategy=b.STRATEGY_CSR_MFMA, max_density=1.0)
         torch.cuda.synchronize()
-        im = srq.intermediates(M, N, K)
-        for V, t, ptr, idx, val, codes in ((A, im["t_a"], im["a_ptr"], im["a_idx"], im["a_val"], im["A_int"]),
-                                           (B.T, im["t_b"], im["b_ptr"], im["b_idx"], im["b_val"], im["B_int"])):
-            with np.errstate(invalid="ignore"):
-                vec, k = np.nonzero(np.abs(V) > host(t)[:, None])
-            assert (host(ptr) == np.searchsorted(vec, np.arange(len(V) + 1))).all()
-            assert (host(idx)[:len(k)] == k).all() and (host(val)[:len(k)] == host(codes)[vec, k]).all()
+        assert_selection(srq, A, B)
         # once more with the threshold of row 7 on (or next to) an entry
-        theta = float(np.sort(np.abs(A[7]))[-K // 10] / host(im["drow"])[7])
+        theta = float(np.sort(np.abs(A[7]))[-K // 10] / host(srq.intermediates(M, N, K)["drow"])[7])
+
+
+# at 8 bits the code of FLT_MAX times its scale is infinite, and with it the largest residual of the vector, whose lambda becomes
+# zero as if there were none
+@pytest.mark.parametrize("shape", [(300, 400, 1100), (300, 1800, 4099)])
+@pytest.mark.parametrize("side", ["a", "b"])
+@pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (7, 0)])
+def test_selection_with_an_infinite_residual(srq, b, shape, side, bits, trunc):
+    if srq.late:
+        pytest.skip("nothing is exchanged in the selection")
+    M, N, K = shape
+    rng = np.random.default_rng(K + bits)
+    A, B = rng.standard_normal((M, K)), rng.standard_normal((K, N))
+    V, W = (A, B) if side == "a" else (B.T, A)
+    W /= K ** 0.5                                             # (means of |D_F| as large as the entries of V)
+    for row, sigma, top in ((4, 2e37, 1.0), (5, 1e37, -1.0), (6, 5e36, 1.0)):
+        V[row] *= sigma
+        V[row, 7] = top * np.finfo(F32).max
+    A, B = A.astype(F32), B.astype(F32)
+    srq.compensated_gemm(dev(A), dev(B), 1.0, 1.0, bits=bits, rounding=b.ROUND_TRUNC if trunc else b.ROUND_NEAREST_EVEN,
+                         strategy=b.STRATEGY_CSR_MFMA, max_density=1.0)
+    torch.cuda.synchronize()
+    im = srq.intermediates(M, N, K)
+    kept = np.diff(host(im[side + "_ptr"]))[4:7]
+    assert np.isfinite(host(im["t_" + side])[4:7]).all() and (kept > 0).all() and (kept < K).all()
+    assert_selection(srq, A, B)
 
 
 # (the last three: columns in one read; a wave and a workgroup per row)
