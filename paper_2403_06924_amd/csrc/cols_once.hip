@@ -13,10 +13,11 @@
 // Measured (rocprofv3, us), the passes of fused.hip / this: 8192 x 8192 maxima + codes + (residual codes and mask) 61 + 63 + 68 /
 // 93 (4.3 TB/s), 4096 x 14336 41 + 50 + 50 / 79, scales given and mask 48 + 50 / 73, codes alone 41 + 50 / 57; 4096 x 4096 27.
 //
-// Every wait ends: a workgroup waits for a bounded time, and what has not been published by then (others may be kept
+// Every wait ends: a workgroup waits for a bounded time in each exchange (exchange_wait.h), and what has not been published by then (others may be kept
 // from starting by whatever else runs) it works out from memory by itself, which is slower and gives the same
 // bits: maxima do not depend on an order.
 #include <type_traits>
+#include "exchange_wait.h"
 #include "gemm_lanes.h"
 #include "stream.h"
 
@@ -31,17 +32,10 @@ constexpr uint32_t kPublished = 0x80000000u;          // (maxima are not negativ
 __device__ __forceinline__ void put_word(uint32_t* p, uint32_t w) {
   __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// the word at p once it is `there`, or what it is when the time is over
 template <class There>
-__device__ __forceinline__ uint32_t wait_until(const uint32_t* p, uint32_t ticks, There there) {
-  uint32_t w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (there(w)) return w;
-  const uint64_t until = wall_clock64() + ticks;
-  do {
-    __builtin_amdgcn_s_sleep(4);
-    w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } while (!there(w) && wall_clock64() < until);
-  return w;
+__device__ __forceinline__ uint32_t wait_for(ExchangeWait& wait, const uint32_t* p, There there) {
+  return wait.word([p]() { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, there,
+                   []() { return (uint64_t)wall_clock64(); }, []() { __builtin_amdgcn_s_sleep(4); });
 }
 
 // max |x|, or max |x - fl(code * s)|, of the four columns of a column group over all rows
@@ -109,8 +103,9 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
       // (what other pieces have added to red in the meantime belongs to the same column)
       if (tid < BC) put_word(mine + piece * BC + tid, red[tid] | kPublished);
       bool late = false;
+      ExchangeWait wait{g.wait_ticks};
       for (int i = tid; i < pieces * BC; i += 256) {
-        const uint32_t w = wait_until(mine + i, g.wait_ticks, [](uint32_t x) { return x != 0; });
+        const uint32_t w = wait_for(wait, mine + i, [](uint32_t x) { return x != 0; });
         if (w) atomicMax(&red[i & (BC - 1)], w & ~kPublished);
         else late = true;
       }
@@ -139,7 +134,8 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
         if (tid == 0) {
           __hip_atomic_fetch_add(state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           const uint32_t all = (uint32_t)pieces;
-          const uint32_t w = wait_until(state, g.wait_ticks, [all](uint32_t x) { return (x & 0xffffu) == all; });
+          ExchangeWait wait{g.wait_ticks};
+          const uint32_t w = wait_for(wait, state, [all](uint32_t x) { return (x & 0xffffu) == all; });
           late = (w & 0xffffu) != all;
         }
         if (has) {

@@ -36,6 +36,46 @@ def test_columns_in_one_read(srq, b, shape, bits):
     reduction(srq, b, shape, 1, bits)
 
 
+def test_columns_in_one_read_on_several_streams(b):
+    """Calls on four streams at once, a handle each, with more workgroups than the chip holds: those that exchange maxima may be
+    kept from starting by the others' for as long as they wait.  Every call's outputs are those of the same call by itself."""
+    gen = torch.Generator(device="cuda").manual_seed(43)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda")
+
+    def quantize(h, X):
+        return h.quantize(X, b.AXIS_COL)
+
+    def reduction(h, X):
+        Q, s, lam = h.quantize(X, b.AXIS_COL)
+        r = h.build_sparse_residual(X, b.AXIS_COL, s, lam, 50 * s)
+        n = X.numel() // 20                                   # (some 12 % are kept)
+        return [r["Rq"], r["rscale"], r["ptr"], r["nnz"], r["idx"][:n], r["val"][:n]]
+
+    def whole(h, X):
+        return [h.compensated_gemm(X[:1500], X[1500:6500, :2000], 0.03)[0]] if X.shape == (6500, 5000) else \
+               [h.compensated_gemm(X[:, :9000], X[:, 9000:].reshape(9000, -1), 0.03)[0]]
+
+    calls = [(quantize, normal(16385, 3000)), (reduction, normal(8192, 4096)), (whole, normal(6500, 5000)), (whole, normal(1800, 18000))]
+    calls = [(b.Srq(device=0), torch.cuda.Stream(), run, X) for run, X in calls]
+    try:
+        refs = [[t.clone() for t in run(h, X)] for h, _, run, X in calls]
+        torch.cuda.synchronize()
+        outs = [[] for _ in calls]
+        for _ in range(6):
+            for (h, stream, run, X), out in zip(calls, outs):
+                with torch.cuda.stream(stream):
+                    out.append(run(h, X))
+        torch.cuda.synchronize()
+        for ref, out in zip(refs, outs):
+            for got in out:
+                assert all(torch.equal(x, y) for x, y in zip(got, ref))
+    finally:
+        for h, _, _, _ in calls:
+            h.close()
+
+
 @pytest.mark.parametrize("shape", [(4099, 37), (4608, 32)])
 def test_other_layouts_and_parts_of_the_reduction(srq, b, shape):
     X = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(shape[1]), device="cuda")
