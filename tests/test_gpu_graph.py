@@ -24,6 +24,16 @@ def srq():
 @pytest.mark.parametrize("strategy_name", ["mfma", "valu", "smfmac", "auto", "dense"])
 @pytest.mark.parametrize("shape", [(256, 256, 256), (1024, 768, 512)])
 def test_fixed_strategy_call_replays_from_a_graph(srq, strategy_name, shape):
+    replays(srq, strategy_name, shape, 2.0)
+
+
+# B in one read, the execution of both terms decided on the device in the launch that compacts: many entries and few
+@pytest.mark.parametrize("sigmas", [2.0, 3.5])
+def test_large_call_decided_on_the_device_replays_from_a_graph(srq, sigmas):
+    replays(srq, "auto", (4400, 4300, 2100), sigmas)
+
+
+def replays(srq, strategy_name, shape, sigmas):
     from paper_2403_06924_amd import binding as b
     strategy = {"mfma": b.STRATEGY_CSR_MFMA, "valu": b.STRATEGY_CSR_VALU, "smfmac": b.STRATEGY_CSR_SMFMAC,
                 "auto": b.STRATEGY_AUTO, "dense": b.STRATEGY_AUTO}[strategy_name]
@@ -35,7 +45,7 @@ def test_fixed_strategy_call_replays_from_a_graph(srq, strategy_name, shape):
         A = rng.standard_normal((M, K)).astype(np.float32)
         B = rng.standard_normal((K, N)).astype(np.float32)
         return torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
-    theta = 2.0 / (0.8 * K ** 0.5)                       # a few percent of each operand
+    theta = sigmas / (0.8 * K ** 0.5)                    # 2: a few percent of each operand
     Ad, Bd = draw()
     Cg = torch.empty((M, N), dtype=torch.float32, device="cuda")
     stats = b.stats_tensor()
