@@ -130,7 +130,11 @@ typedef struct srq_intermediates_t {
 
 /* Creates a handle bound to HIP device `device` (host call).  device = -1 creates a handle
  * without a device: every entry point still validates its arguments and then returns
- * SRQ_STATUS_NO_DEVICE instead of launching (used to test validation on a CPU-only host). */
+ * SRQ_STATUS_NO_DEVICE instead of launching (used to test validation on a CPU-only host).
+ * The environment variable SRQ_EXCHANGE_WAIT_TICKS, read here, says how long workgroups that
+ * exchange the maxima of columns wait for each other before they work them out alone, in ticks of
+ * 10 ns: a decimal number of at most 1000000.  Anything else, or nothing, is 20000 (200 us).  Results
+ * do not depend on it. */
 srq_status_t srq_create(srq_handle_t* handle, int device);
 srq_status_t srq_destroy(srq_handle_t handle);
 

@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include "exchange_wait.h"
 #include "srq_internal.h"
 
 using namespace srq;
@@ -281,10 +282,7 @@ srq_status_t srq_create(srq_handle_t* handle, int device) {
   if (!c) return SRQ_STATUS_INVALID_ARG;
   memset(c, 0, sizeof(*c));
   c->device = device;
-  // (200 us; whoever runs out of it works the maxima out alone, which zero has every workgroup do that does not find
-  // them at once)
-  const char* ticks = getenv("SRQ_EXCHANGE_WAIT_TICKS");
-  c->wait_ticks = ticks ? (uint32_t)strtoul(ticks, nullptr, 10) : 20000u;
+  c->wait_ticks = exchange_ticks(getenv("SRQ_EXCHANGE_WAIT_TICKS"));
   if (device >= 0) {
     int n = 0;
     hipError_t e = hipGetDeviceCount(&n);

@@ -35,6 +35,20 @@ struct ExchangeWait {
   }
 };
 
+// How long that is, in ticks of 10 ns: 200 us, or what a text asks for, a decimal number of at most 10 ms.  With zero everybody
+// works out alone what is not there at the first look.
+constexpr uint32_t kExchangeTicks = 20000, kMostExchangeTicks = 1000000;
+inline uint32_t exchange_ticks(const char* text) {
+  if (!text || !*text) return kExchangeTicks;
+  uint32_t n = 0;
+  for (; *text; ++text) {
+    if (*text < '0' || *text > '9') return kExchangeTicks;
+    n = 10 * n + (uint32_t)(*text - '0');
+    if (n > kMostExchangeTicks) return kExchangeTicks;
+  }
+  return n;
+}
+
 }  // namespace srq
 
 #endif  // SRQ_EXCHANGE_WAIT_H_
