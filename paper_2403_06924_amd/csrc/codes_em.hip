@@ -96,9 +96,10 @@ __device__ __forceinline__ int part_of(const int32_t* sums, int n) {
 }
 
 template <int NV>
-__global__ __launch_bounds__(256) void compact_decide_kernel(CompactDecide g, int K, int Kc) {
+__global__ __launch_bounds__(256, NV <= 8 ? 5 : 3) void compact_decide_kernel(CompactDecide g, int K, int Kc) {
   __shared__ int64_t before[4];
   __shared__ int count[4], total[2][4];
+  __shared__ __attribute__((aligned(16))) uint8_t gather[4 * kGatherWave];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, id = blockIdx.x;
   const int compact = g.groups_a + g.groups_b;
   const int sums_a = (g.a.nvec + 255) / 256, sums_b = (g.b.nvec + 255) / 256;
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(256) void compact_decide_kernel(CompactDecide g, in
     sum = wave_sum(sum);
     if (lane == 0) before[w] = sum;
     totals(!second || id == 0, second || id == 0);
-    f.store(s, kept(second) >= (second ? g.dec.min_mfma_b : g.dec.min_mfma_a) ? s.dense : nullptr, K, Kc, before, count, g.around);
+    f.store(s, kept(second) >= (second ? g.dec.min_mfma_b : g.dec.min_mfma_a) ? s.dense : nullptr, K, Kc, before, count, gather, g.around);
     if (id == 0 && threadIdx.x == 0) {
       const int64_t na = kept(0), nb = kept(1);
       const int pa = g.a.nvec ? (na >= g.dec.min_mfma_a ? 2 : 1) : 0, pb = g.b.nvec ? (nb >= g.dec.min_mfma_b ? 2 : 1) : 0;

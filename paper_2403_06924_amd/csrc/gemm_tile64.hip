@@ -51,7 +51,8 @@ __global__ __launch_bounds__(256, NST >= 8 ? 1 : 12 / NST) void gemm_i8_tile64_k
       __shared__ int count[4];
       const int group = (int)blockIdx.x - more.tiles;
       const bool second = group >= more.groups_a;
-      compact_four<NV>(second ? more.b : more.a, second ? group - more.groups_a : group, more.K, K, before, count);
+      compact_four<NV>(second ? more.b : more.a, second ? group - more.groups_a : group, more.K, K, before, count,
+                       reinterpret_cast<uint8_t*>(lds));
       return;
     }
   }

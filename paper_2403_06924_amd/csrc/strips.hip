@@ -597,8 +597,9 @@ template <int NV>                                      // see compact.h
 __global__ __launch_bounds__(256) void compact_pair_kernel(StripCompact a, StripCompact b, int groups_a, int K, int Kc) {
   __shared__ int64_t before[4];
   __shared__ int count[4];
+  __shared__ __attribute__((aligned(16))) uint8_t gather[4 * kGatherWave];
   const bool second = (int)blockIdx.x >= groups_a;
-  compact_four<NV>(second ? b : a, (int)blockIdx.x - (second ? groups_a : 0), K, Kc, before, count);
+  compact_four<NV>(second ? b : a, (int)blockIdx.x - (second ? groups_a : 0), K, Kc, before, count, gather);
 }
 
 // a strip of B is 4 * CG columns wide

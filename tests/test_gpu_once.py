@@ -203,7 +203,8 @@ def test_counts_of_operands_that_are_not_compacted(srq, b, shape):
 # (M, N, K): vectors that are no whole group of four, one and one over a sum's 256; two to sixteen pieces of a vector.  Kept shares on
 # either side of where a term changes its execution.
 @pytest.mark.parametrize("shape", [(2301, 1030, 1700), (257, 2100, 4099), (100, 2001, 4300), (256, 255, 8200), (1030, 70, 16384)])
-@pytest.mark.parametrize("kept", [(0.0005, 0.0003), (0.05, 0.0003), (0.0005, 0.05), (0.05, 0.05), (0.05, None), (None, 0.0003)])
+@pytest.mark.parametrize("kept", [(0.0005, 0.0003), (0.05, 0.0003), (0.0005, 0.05), (0.05, 0.05), (0.05, None), (None, 0.0003),
+                                  (0.9, 0.2)])
 def test_decision_and_compaction_in_one_launch(srq, b, shape, kept):
     """SRQ_STRATEGY_AUTO decided on the device (debug outputs keep it from taking the matrix cores outright): compressed operands,
     statistics and both terms against the definitions and a call with the execution given, bit for bit."""
@@ -240,3 +241,29 @@ def test_decision_and_compaction_in_one_launch(srq, b, shape, kept):
     ref = [host(C)] + [host(dbg[x]) for x in ("DR1_int", "DR2_int")]
     for got in out:
         assert all(np.array_equal(x, y, equal_nan=x.dtype.kind == "f") for x, y in zip(got, ref))
+
+
+# one, two, four and eight pieces of a vector, a last one that is partly there; vectors that are no whole group of four
+@pytest.mark.parametrize("shape", [(701, 1024), (203, 1500), (150, 4096), (61, 8190)])
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("room", [1.0, 0.37])
+def test_compaction_of_crowded_vectors(b, shape, axis, room):
+    """Vectors that keep nothing to everything, pieces on either side of the number of entries from which on they go through
+    LDS; room for all entries, or for some that end within a vector."""
+    nvec, K = shape
+    rng = np.random.default_rng(K)
+    V = np.argsort(rng.random((nvec, K)), axis=1).astype(F32) + 1             # 1 .. K in any order
+    count = (np.arange(nvec) * 7919 % (K + 1)).astype(np.int64)
+    count[:24] = np.minimum(K, np.r_[0, 1, 3, 157:167, 255:258, 511:514, K - 3:K + 1, 160 * (-(-K // 1024))])
+    V *= rng.choice([-1.0, 1.0], V.shape).astype(F32)
+    X, t = dev(V if axis == 0 else V.T.copy()), dev((K - count + 0.5).astype(F32))
+    capacity = int(room * count.sum())
+    h = b.Srq(device=0)
+    try:
+        Q, scale, lam = h.quantize(X, axis)
+        r = h.build_sparse_residual(X, axis, scale, lam, t, capacity=capacity)
+        vec, k = np.nonzero(np.abs(V) > host(t)[:, None])
+        assert int(r["nnz"].item()) == count.sum() and (host(r["ptr"]) == np.r_[0, np.cumsum(count)]).all()
+        assert (host(r["idx"]) == k[:capacity]).all() and (host(r["val"]) == host(Q)[vec, k][:capacity]).all()
+    finally:
+        h.close()

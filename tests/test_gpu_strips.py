@@ -350,7 +350,8 @@ def test_product_in_place_of_an_operand(srq, b, n):
 @pytest.mark.parametrize("shape", [(65, 70, 260), (300, 401, 1000), (1024, 1024, 1024), (1029, 1020, 515), (1500, 1501, 700), (2100, 63, 257),
                                    (333, 270, 1025), (513, 515, 2049), (90, 1111, 4100)])
 @pytest.mark.parametrize("alpha,beta", [(1.0, 0.0), (-0.5, 0.25)])
-def test_compaction_behind_the_tiles(srq, b, shape, alpha, beta):
+@pytest.mark.parametrize("bits,share", [(8, 2.0), (8, 0.2), (4, 2.0)])   # (share: a few percent, most of the entries)
+def test_compaction_behind_the_tiles(srq, b, shape, alpha, beta, bits, share):
     """The corrections that compact their operands in the same launch against separate launches (a call with debug
     outputs): the same bits in C, CSR / CSC and statistics, also where a vector keeps nothing or everything."""
     M, N, K = shape
@@ -362,10 +363,10 @@ def test_compaction_behind_the_tiles(srq, b, shape, alpha, beta):
     B[:, -1] *= 10
     B[::2, 1] = 2.0 ** -140
     C_in = dev(rng.standard_normal((M, N)).astype(F32)) if beta else None
-    theta, got = 2.0 / K ** 0.5, []
+    theta, got = share / K ** 0.5, []
     for debug in (False, True):
         stats = b.stats_tensor()
-        C, _, _ = srq.compensated_gemm(dev(A), dev(B), theta, theta, strategy=b.STRATEGY_CSR_MFMA, alpha=alpha, beta=beta, C_in=C_in,
+        C, _, _ = srq.compensated_gemm(dev(A), dev(B), theta, theta, bits=bits, strategy=b.STRATEGY_CSR_MFMA, alpha=alpha, beta=beta, C_in=C_in,
                                        stats=stats, debug=debug)
         torch.cuda.synchronize()
         im = srq.intermediates(M, N, K)
