@@ -147,6 +147,45 @@ def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
         theta = float(np.sort(np.abs(A[7]))[-K // 10] / host(srq.intermediates(M, N, K)["drow"])[7])
 
 
+# (M, N, K): both operands' vectors by one to four waves, columns by workgroups of their own (from 1280 on) or not, their last sixteen,
+# four and eight rows not whole; with means formed in the same launch and after them; kept codes written on the side (the first two) or
+# not.  Thresholds within the lowest bins of most vectors, and beyond them.
+@pytest.mark.parametrize("shape", [(300, 400, 1100), (90, 1290, 4100), (1283, 1301, 1503), (40, 1450, 2052), (700, 60, 3001), (100, 1900, 7001),
+                                   (530, 2050, 4501), (20, 2030, 16385)])
+@pytest.mark.parametrize("kind,sigmas", [("wide", 0.0002), ("wide", 0.5), ("far", 0.2), ("far", 3.0)])
+@pytest.mark.parametrize("bits,trunc", [(8, 0), (7, 1), (4, 0)])
+def test_selection_with_thresholds_in_the_lowest_bins(srq, b, shape, kind, sigmas, bits, trunc):
+    if srq.late:
+        pytest.skip("nothing is exchanged in the selection")
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K + bits)
+
+    def vectors(nvec):
+        if kind == "wide":
+            V = np.ldexp(rng.choice([-1.0, 1.0], (nvec, K)) * (1 + rng.random((nvec, K))), rng.integers(-10, 11, (nvec, K)))
+        else:                                                 # a few outliers that set the scales
+            V = rng.standard_normal((nvec, K))
+            V[::2, rng.integers(0, K, 3)] *= 1000.0
+        V = V.astype(F32)
+        V[0] = 0
+        V[1] = F32(2.0 ** -140) * np.sign(V[1])
+        V[3, 5], V[3, K - 1], V[8, 6] = np.nan, np.nan, np.nan
+        return V
+
+    A, B = vectors(M), vectors(N).T.copy()
+    # the means of |D_F| go with the vectors' own size: thresholds about `sigmas` times what most entries are
+    theta = sigmas / (K ** 0.5 * (40.0 if kind == "far" else 150.0))
+    stats = b.stats_tensor()
+    for strategy in (b.STRATEGY_CSR_MFMA, b.STRATEGY_AUTO):
+        srq.compensated_gemm(dev(A), dev(B), theta, theta, bits=bits, rounding=b.ROUND_TRUNC if trunc else b.ROUND_NEAREST_EVEN,
+                             strategy=strategy, stats=stats, max_density=1.0, debug=strategy == b.STRATEGY_AUTO)
+        torch.cuda.synchronize()
+        assert_selection(srq, A, B)
+        st = b.read_stats(stats)
+        im = srq.intermediates(M, N, K)
+        assert st["nnz_a"] == int(im["a_ptr"][-1]) > 0 and st["nnz_b"] == int(im["b_ptr"][-1]) > 0
+
+
 # at 8 bits the code of FLT_MAX times its scale is infinite, and with it the largest residual of the vector, whose lambda becomes
 # zero as if there were none
 @pytest.mark.parametrize("shape", [(300, 400, 1100), (300, 1800, 4099)])
