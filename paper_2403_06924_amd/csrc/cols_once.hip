@@ -52,7 +52,7 @@ __device__ __forceinline__ void strip_maxima(const float* X, int64_t rows, int64
   }
 }
 
-template <bool TRUNC, bool GIVEN, bool RESID, bool MASK, bool EM>   // EM: residual codes element-major too (or alone)
+template <bool TRUNC, bool GIVEN, bool RESID, bool MASK, bool EM>   // EM: residual codes element-major
 __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, int64_t rows, int64_t cols, float qmax, int pieces) {
   __shared__ uint32_t red[BC], kept[BC];
   const int tid = threadIdx.x, cg = tid & (CG - 1), rb = tid / CG;
@@ -331,14 +331,16 @@ __global__ __launch_bounds__(256, EM ? 3 : 4) void cols_once_kernel(ColsOnce g, 
         }
       }
     }
+    if (!EM) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      packed[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], 4);
-      asm volatile("" : "+v"(packed[c][i / 4]));
+      for (int c = 0; c < 4; ++c) {
+        packed[c][i / 4] = pack_codes(z[0][c], z[1][c], z[2][c], z[3][c], 4);
+        asm volatile("" : "+v"(packed[c][i / 4]));
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (!EM || g.Rvm) put(g.Rvm, g.ldr, packed);
+  if (!EM) put(g.Rvm, g.ldr, packed);
 }
 
 }  // namespace
@@ -352,16 +354,18 @@ hipError_t launch_cols_once(const ColsOnce& g, int64_t rows, int64_t cols, int q
   const int64_t pieces = (rows + BR - 1) / BR, strips = (cols + BC - 1) / BC;
   const dim3 grid((unsigned)(strips * pieces));
   const bool resid = g.rscale != nullptr, mask = g.mask != nullptr;
+  // (what no call asks for: a mask with scales yet to be formed, codes alone with scales given, both layouts, k-major codes of a
+  // whole call, which are copied)
+  if ((mask && !given) || (!resid && given) || (resid && (!g.Rvm == !g.Rem)) || (g.Rem && !given)) return hipErrorInvalidValue;
 #define SRQ_ONCE(GIVEN, RESID, MASK, EM)                                                                                       \
   hipLaunchKernelGGL((trunc ? cols_once_kernel<true, GIVEN, RESID, MASK, EM> : cols_once_kernel<false, GIVEN, RESID, MASK, EM>), \
                      grid, dim3(256), 0, st, g, rows, cols, (float)qmax, (int)pieces)
   if (!resid) SRQ_ONCE(false, false, false, false);
   else if (g.Rem) {
-    if (given && mask) SRQ_ONCE(true, true, true, true);
-    else if (given) SRQ_ONCE(true, true, false, true);
-    else SRQ_ONCE(false, true, false, true);
+    if (mask) SRQ_ONCE(true, true, true, true);
+    else SRQ_ONCE(true, true, false, true);
   } else {
-    if (given && mask) SRQ_ONCE(true, true, true, false);
+    if (mask) SRQ_ONCE(true, true, true, false);
     else if (given) SRQ_ONCE(true, true, false, false);
     else SRQ_ONCE(false, true, false, false);
   }

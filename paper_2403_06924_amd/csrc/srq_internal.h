@@ -204,7 +204,7 @@ struct ColsOnce {
   int8_t* Q;                   // codes, vector-major
   int64_t ldq;
   float *rscale, *rlambda;     // null: no residual; rlambda may be null by itself
-  int8_t* Rvm;                 // residual codes in either layout or both
+  int8_t* Rvm;                 // residual codes in one layout or the other (k-major: with scales given)
   int64_t ldr;
   int8_t* Rem;
   int64_t ldem;
