@@ -17,14 +17,20 @@ def b():
     return binding
 
 
+@pytest.fixture(scope="module")
+def srq(b):
+    h = b.Srq(device=0)
+    yield h
+    h.close()
+
+
 @pytest.fixture(scope="module", params=["20000", "0"])
-def srq(b, request):
+def exchanging(b, request):
     """A handle whose workgroups wait for each other, and one where whoever does not find a maximum at once works it out
     alone."""
     with pytest.MonkeyPatch.context() as m:
         m.setenv("SRQ_EXCHANGE_WAIT_TICKS", request.param)
         h = b.Srq(device=0)
-    h.late = request.param == "0"
     yield h
     h.close()
 
@@ -32,8 +38,28 @@ def srq(b, request):
 # (rows, columns): pieces of 512 rows, patches of 16, strips of 32 columns, the last columns no whole patch
 @pytest.mark.parametrize("shape", [(4097, 4), (4100, 5), (4111, 31), (4607, 33), (4608, 34), (4609, 67), (8704, 98), (16385, 6), (32768, 9)])
 @pytest.mark.parametrize("bits", [8, 3])
-def test_columns_in_one_read(srq, b, shape, bits):
-    reduction(srq, b, shape, 1, bits)
+def test_columns_in_one_read(exchanging, b, shape, bits):
+    reduction(exchanging, b, shape, 1, bits)
+
+
+@pytest.mark.parametrize("shape", [(1100, 1030, 4099), (40, 2050, 8192), (2100, 37, 16385)])
+@pytest.mark.parametrize("bits,trunc", [(8, 0), (5, 1)])
+def test_columns_in_one_read_of_a_whole_call(exchanging, b, shape, bits, trunc):
+    """Codes, scales, residual codes and residual scales of B against those of the rows of its transpose, which nothing is
+    exchanged for."""
+    M, N, K = shape
+    rng = np.random.default_rng(K + bits)
+    A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
+    B[:, 3], B[:, 4], B[7, 5], B[-1, 6] = 0, F32(1e-39), np.nan, 1e38
+    rounding = b.ROUND_TRUNC if trunc else b.ROUND_NEAREST_EVEN
+    exchanging.compensated_gemm(dev(A), dev(B), 0.03, bits=bits, rounding=rounding)
+    torch.cuda.synchronize()
+    im = {key: t.clone() for key, t in exchanging.intermediates(M, N, K).items() if key in ("B_int", "s_b", "lam_b", "RB_int", "s_rb")}
+    V = dev(B.T.copy())
+    Q, s, lam = exchanging.quantize(V, b.AXIS_ROW, bits=bits, rounding=rounding)
+    r = exchanging.build_sparse_residual(V, b.AXIS_ROW, s, lam, None, bits=bits, rounding=rounding, want_selection=False)
+    for key, ref in (("B_int", Q), ("s_b", s), ("lam_b", lam), ("RB_int", r["Rq"]), ("s_rb", r["rscale"])):
+        assert torch.equal(im[key], ref), key
 
 
 def test_columns_in_one_read_on_several_streams(b):
@@ -77,18 +103,18 @@ def test_columns_in_one_read_on_several_streams(b):
 
 
 @pytest.mark.parametrize("shape", [(4099, 37), (4608, 32)])
-def test_other_layouts_and_parts_of_the_reduction(srq, b, shape):
+def test_other_layouts_and_parts_of_the_reduction(exchanging, b, shape):
     X = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(shape[1]), device="cuda")
     X[:, 3] = 0
     X[:, 4] = 1e-39                                           # (qmax / amax overflows)
     t = X.abs().mean(dim=0).contiguous()
     for rounding in (b.ROUND_NEAREST_EVEN, b.ROUND_TRUNC):
-        Q, s, lam = srq.quantize(X, b.AXIS_COL, rounding=rounding)
-        Qt, st, lamt = srq.quantize(X.t().contiguous(), b.AXIS_ROW, rounding=rounding)
+        Q, s, lam = exchanging.quantize(X, b.AXIS_COL, rounding=rounding)
+        Qt, st, lamt = exchanging.quantize(X.t().contiguous(), b.AXIS_ROW, rounding=rounding)
         assert torch.equal(Q, Qt) and torch.equal(s, st) and torch.equal(lam, lamt)
-        r = srq.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding)
-        rt = srq.build_sparse_residual(X.t().contiguous(), b.AXIS_ROW, s, lam, t, rounding=rounding)
-        em = srq.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding, r_layout=b.LAYOUT_ELEMENT_MAJOR)
+        r = exchanging.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding)
+        rt = exchanging.build_sparse_residual(X.t().contiguous(), b.AXIS_ROW, s, lam, t, rounding=rounding)
+        em = exchanging.build_sparse_residual(X, b.AXIS_COL, s, lam, t, rounding=rounding, r_layout=b.LAYOUT_ELEMENT_MAJOR)
         n = int(r["nnz"].item())
         for key in ("Rq", "rscale", "ptr", "nnz"):
             assert torch.equal(r[key], rt[key]), key
@@ -132,8 +158,6 @@ def assert_selection(srq, A, B):
 @pytest.mark.parametrize("kind", ["normal", "outliers", "ties"])
 @pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (7, 0), (4, 0)])
 def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
-    if srq.late:
-        pytest.skip("nothing is exchanged in the selection")
     M, N, K = shape
     rng = np.random.default_rng(M + N + K + bits)
     A, B = operand(rng, kind, M, K), operand(rng, kind, N, K).T.copy()
@@ -155,8 +179,6 @@ def test_selection_from_codes(srq, b, shape, kind, bits, trunc):
 @pytest.mark.parametrize("kind,sigmas", [("wide", 0.0002), ("wide", 0.5), ("far", 0.2), ("far", 3.0)])
 @pytest.mark.parametrize("bits,trunc", [(8, 0), (7, 1), (4, 0)])
 def test_selection_with_thresholds_in_the_lowest_bins(srq, b, shape, kind, sigmas, bits, trunc):
-    if srq.late:
-        pytest.skip("nothing is exchanged in the selection")
     M, N, K = shape
     rng = np.random.default_rng(M + N + K + bits)
 
@@ -192,8 +214,6 @@ def test_selection_with_thresholds_in_the_lowest_bins(srq, b, shape, kind, sigma
 @pytest.mark.parametrize("side", ["a", "b"])
 @pytest.mark.parametrize("bits,trunc", [(8, 0), (8, 1), (7, 0)])
 def test_selection_with_an_infinite_residual(srq, b, shape, side, bits, trunc):
-    if srq.late:
-        pytest.skip("nothing is exchanged in the selection")
     M, N, K = shape
     rng = np.random.default_rng(K + bits)
     A, B = rng.standard_normal((M, K)), rng.standard_normal((K, N))
@@ -218,8 +238,6 @@ def test_selection_with_an_infinite_residual(srq, b, shape, side, bits, trunc):
 def test_counts_of_operands_that_are_not_compacted(srq, b, shape):
     """The dense branch whatever the counts, thresholds of zero: every entry that is not zero counts, and none where the
     threshold is no number (0 times a mean that has overflowed)."""
-    if srq.late:
-        pytest.skip("the default wait is enough")
     M, N, K = shape
     rng = np.random.default_rng(K)
     A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
@@ -247,8 +265,6 @@ def test_counts_of_operands_that_are_not_compacted(srq, b, shape):
 def test_decision_and_compaction_in_one_launch(srq, b, shape, kept):
     """SRQ_STRATEGY_AUTO decided on the device (debug outputs keep it from taking the matrix cores outright): compressed operands,
     statistics and both terms against the definitions and a call with the execution given, bit for bit."""
-    if srq.late:
-        pytest.skip("the default wait is enough")
     M, N, K = shape
     rng = np.random.default_rng(sum(shape))
     A, B = rng.standard_normal((M, K)).astype(F32), rng.standard_normal((K, N)).astype(F32)
