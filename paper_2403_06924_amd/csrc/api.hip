@@ -53,9 +53,11 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // (the paper's switch between SPMM and GEMM, Algorithm 1 lines 11-15, with the ratio of the
 // two kernels' throughputs on MI355X in place of the paper's eta).  Set where whole calls with both terms
 // on one or the other kernel broke even with the 32x32x32 products: 0.65 % (8192^3), 0.6 % (4096^3), 0.95 %
-// (6144^3, whose 576 tiles load the 256 compute units unevenly), 0.62 % (16384^3).  With today's products
-// 8192^3 breaks even at 0.5 % (vector ALUs / matrix cores, ms: 0.1 % 1.21 / 1.60, 0.5 % 1.60 / 1.60, 0.7 % 1.78 /
-// 1.60); the lines have not been moved.
+// (6144^3, whose 576 tiles load the 256 compute units unevenly), 0.62 % (16384^3).  With today's kernels they
+// lie too high: calls break even at 0.27 % (4096^3), 0.52 % (6144^3), 0.6 % (8192^3), 0.4 % (4096 x 14336 x 4096) and
+// 0.55 % (16384^3), the terms by themselves at 0.48, 0.6, 0.65, 0.53, 0.55 % (term 1) and 0.28, 0.57, 0.47, 0.48, 0.52 % (term
+// 2).  Both terms, ms, vector ALUs / matrix cores at 0.3, 0.5, 0.6 and 0.7 %: 4096^3 0.256 / 0.250, 0.283 / 0.251, 0.296 / 0.251, 0.311 /
+// 0.252; 8192^3 1.17 / 1.41, 1.33 / 1.41, 1.42 / 1.42, 1.56 / 1.42; 16384^3 7.77 / 9.77, 9.83 / 9.79, 10.5 / 9.8, 11.0 / 9.8.
 // execution of a correction term as reported in srq_stats_t (0: term skipped)
 constexpr int kPathValu = 1, kPathMfma = 2, kPathDense = 3, kPath24 = 4, kPathColblock = 5;
 constexpr int kPathOnDevice = 6;          // host-side marker: vector ALUs or matrix cores, decided on the device
@@ -859,12 +861,12 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
   const bool once_b = !strips && !global_scale && cols_once_ok(K, N, ldb);
   const int64_t once_words = once_b && comp ? cols_once_words(K, N) : 0;
   uint32_t* const once_lines = reinterpret_cast<uint32_t*>(p.b24v1);
-  // selection from the codes, of an operand whose two code matrices are there by then
   // Both terms on the unreduced codes whatever the counts: those of a threshold of zero are of the entries that are not zero, which
   // the passes that quantize count on the side, and no mask is read by anybody (8192^2: 17 us per operand for one more pass)
   const bool always_dense = dense_fallback_density <= 0.f;
   const bool count_a = comp && always_dense && term_a && theta_a == 0.f && (strips || fastA);
   const bool count_b = comp && always_dense && term_b && theta_b == 0.f && (strips || once_b);
+  // selection from the codes, of an operand whose two code matrices are there by then (of A: below)
   const bool codes_b = (once_b || strips) && comp && term_b && select_codes_ok(qmax, theta_b, strips);
   // Decision, compaction and copies of a large call in one launch, from the sums of counts that a selection from the codes leaves
   // (they lie where the 2:4 form of A' goes in other calls)
@@ -1094,7 +1096,7 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
     // line 9 and the branch of line 11: which execution each term takes.  SRQ_STRATEGY_AUTO: decided
     // on the device, by the scan kernel itself, which then also writes the statistics.
     // (for K > 8192 the K x 512-byte slab of codes an XCD gathers from outgrows its L2 and the
-    // vector-ALU kernel loses earlier: measured crossover 0.62 % at 16384^3)
+    // vector-ALU kernel loses earlier)
     const int64_t min_mfma_a =
         (int64_t)ceil((K > 8192 ? kAutoMfmaDensityALongK : kAutoMfmaDensityA) * (double)M * (double)K);
     const int64_t min_mfma_b =
@@ -1135,8 +1137,6 @@ srq_status_t srq_compensated_gemm(srq_handle_t h, int64_t M, int64_t N, int64_t 
         if (strategy == SRQ_STRATEGY_AUTO) return d >= crossover ? 2 : 1;
         return strategy_path(strategy);
       };
-      // (for K > 8192 the K x 512-byte slab of codes an XCD gathers from outgrows its L2 and the
-      // vector-ALU kernel loses earlier: measured crossover 0.62 % at 16384^3)
       if (term_a) path_a = pick(da, K > 8192 ? kAutoMfmaDensityALongK : kAutoMfmaDensityA);
       if (term_b) path_b = pick(db, K > 8192 ? kAutoMfmaDensityBLongK : kAutoMfmaDensityB);
       if (term_a && strategy == SRQ_STRATEGY_AUTO) h->last_path_a = path_a;

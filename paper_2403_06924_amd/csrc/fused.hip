@@ -6,7 +6,9 @@
 //                       amax, lambda, codes, residual, residual amax and residual codes all
 //                       come out of that one read.
 //   cols_pass_kernel    operand B (one scale per column, row-major K x N) where cols_once.hip does not take it (a
-//                       matrix-wide scale, more than 32768 rows): three streaming
+//                       matrix-wide scale, more than 32768 rows, fewer than four or more than 2^24 columns, a leading
+//                       dimension from 2^20 on, a staged call for k-major codes or whose workspace does not hold the
+//                       exchanged lines): three streaming
 //                       passes (amax | codes + max|residual| | residual codes), each thread
 //                       holding a 16-row x 4-column patch so that the transposed (K-contiguous)
 //                       INT8 output is written 16 bytes at a time without going through LDS.

@@ -9,9 +9,9 @@
 // those of the topmost key, which NaN shares, and whole vectors whose scales are not ordinary numbers or whose threshold
 // lies in one of the lowest bins.
 //
-// What bounds it: 2 bytes per element (4.8 TB/s on two operands of 8192 x 8192).  Both operands, us, from FP32 / from codes:
-// 8192 x 8192 each 46 + (68 with the residual codes of B) / 54 to 56; 4096 x 4096 and 4096 x 14336 12 + 50 / 36 with a wave per
-// vector (55 with a workgroup for each, which has too few bytes on their way).
+// What bounds it: 2 bytes per element (5.7 TB/s on two operands of 8192 x 8192).  Both operands, us, from FP32 / from codes:
+// 8192 x 8192 each 46 + (68 with the residual codes of B) / 47 to 51; 4096 x 4096 and 4096 x 14336 12 + 50 / 32 with a wave per
+// vector (with a workgroup for each, which has too few bytes on their way, 55 against 36 at the time).
 // On the side: the zero-filled codes (16 bytes per lane, what is in registers already) where the corrections follow at once, and the
 // counts of every 256 vectors where the compaction wants them.
 #include "compact.h"
