@@ -49,6 +49,7 @@ __global__ __launch_bounds__(256, NST >= 8 ? 1 : 12 / NST) void gemm_i8_tile64_k
     if ((int)blockIdx.x >= more.tiles) {
       __shared__ int64_t before[4];
       __shared__ int count[4];
+      static_assert(NST * kStage >= 4 * kGatherWave, "the stages' LDS gathers the entries of crowded vectors");
       const int group = (int)blockIdx.x - more.tiles;
       const bool second = group >= more.groups_a;
       compact_four<NV>(second ? more.b : more.a, second ? group - more.groups_a : group, more.K, K, before, count,
